@@ -1,0 +1,1299 @@
+// Small and medium batches (up to kBucketMaxBatch updates).  What bounds them is not the memory but the number of
+// dependent steps: the general path -- a radix sort, the split chains, the apply kernel -- is 13 to 20 launches of 2-5 us,
+// and it walks runs of up to 1024 updates with one wavefront.  Here the batch goes through three kernels instead:
+//
+//   bucket_partition  every tile of the batch is ordered, in arrival order, by bucket -- a hash of the stripe -- and
+//                     written out together with the table of where each bucket begins in it; the range check and the
+//                     load counts of the tile are done on the way.  No scan over tiles: a bucket is the list of its
+//                     pieces in the tiles.  The entries of hot stripes, found in a sample, get buckets of their own.
+//   bucket_apply      one workgroup per bucket collects the pieces in LDS, sorts them by (row, position) there and
+//                     applies the bucket's stripes.
+//   heavy_stripes     stripes with long runs: split over the columns, which are independent chains, so that each is read
+//                     once and no workgroup waits for another.
+//
+// The results are those of the general path: fp64 chains in arrival order, every touched element rounded once.
+// Measured against the general path (us a call, D = 128): 2048 updates 54 -> 21; 26 624 half Zipf 173 -> 58; 65 536
+// uniform on 2^14 rows 60 -> 50; 300 007 Zipf, combined rule 325 -> 220.  The kernels of the 26 624: partition 7.6,
+// apply 40 (97 MB, 21 us at the rate of the large batches), heavy stripes 11.
+#include "rows.h"
+
+namespace ecrm {
+
+typedef unsigned long long u64;
+
+constexpr int kBucketWaves = kBucketThreads / kWave;
+constexpr int kPartWaves = kPartThreads / kWave;
+constexpr uint32_t kHotRun = 256;       // stripes with about this many updates or more are looked for in a sample
+constexpr uint32_t kHeavyMin = 512;     // a stripe of an oversized bucket with more updates goes to heavy_stripes
+static_assert(kHeavyMin >= kHeavyRunMin, "the list of heavy stripes has room for one per kHeavyRunMin updates");
+
+// Bijective mix of a stripe number: the high part selects the bucket, the low bits split a bucket further.
+__device__ __forceinline__ uint32_t mix32(uint32_t g)
+{
+    g ^= g >> 16;
+    g *= 0x9E3779B1u;
+    g ^= g >> 15;
+    g *= 0xD1B54A33u;
+    return g ^ (g >> 16);
+}
+__device__ __forceinline__ uint32_t bucket_of(uint32_t g, uint32_t buckets) { return __umulhi(mix32(g), buckets); }
+
+__device__ __forceinline__ uint32_t item_row(u64 it) { return (uint32_t)(it >> 32); }
+
+// exclusive scan of one value per thread over a workgroup of WAVES waves
+template <int WAVES = kBucketWaves>
+__device__ __forceinline__ uint32_t bucket_excl_scan(uint32_t v, uint32_t *s_wave, uint32_t &total)
+{
+    const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
+    uint32_t incl = v;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t t = __shfl_up(incl, d, kWave);
+        if (lane >= (uint32_t)d) incl += t;
+    }
+    if (lane == kWave - 1) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t off = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const uint32_t t = s_wave[w];
+        if ((uint32_t)w < wave) off += t;
+        tot += t;
+    }
+    __syncthreads();
+    total = tot;
+    return off + incl - v;
+}
+
+struct RowArgs {
+    float *E, *A, *PE, *PA;
+    const float *grads;
+    Geometry geo;
+};
+
+// ================================================================================================
+// the walk over a window of sorted (row, gradient row) pairs
+// ================================================================================================
+
+// One step of the walk takes up to U consecutive updates of one entry.  What it needs from memory: their gradients; the
+// rows of E and A if the first of them is its entry's first; the parity rows if the entry opens a stripe.  Rows that are
+// not needed are asked for through a buffer resource of size zero, which returns zeros without touching memory: every
+// step issues the same loads, so the compiler knows how many are younger than the ones it waits for, and the loads of
+// Q steps really are in flight.  (With the loads under branches, as in the apply kernel of large batches, it waits for
+// everything before each entry; there the 24 waves of a compute unit hide that, here there are too few of them.  A load
+// of size zero still takes its 17 cycles of the compute unit's memory pipe, which a batch of this size can afford and
+// the large ones cannot: 2^22 updates in 963 us with branches, 1300 us with steps of one update.)
+template <int NC, int U>
+struct StepLoads {
+    float2 a[NC], e[NC], g[U][NC], pe[NC], pa[NC];
+};
+
+// The chain of the entry in work and the parity rows of its stripe; carried from window to window where a stripe or a
+// run does not end inside one.  All zero between entries (and the parities between stripes): rows are added to it as
+// they arrive, zeros for steps that bring none, so that taking a set of loads in needs no branch.
+template <int NC>
+struct Walk {
+    D2 G[NC], acc[NC], pe[NC], pa[NC];
+    float2 e[NC], a[NC];
+    __device__ __forceinline__ void clear_entry()
+    {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            G[i] = acc[i] = D2{0, 0};
+            e[i] = a[i] = float2{0, 0};
+        }
+    }
+    __device__ __forceinline__ void clear_stripe()
+    {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) pe[i] = pa[i] = D2{0, 0};
+    }
+};
+
+__device__ __forceinline__ rsrc_t row_if(const float *table, uint32_t row, uint32_t D, uint32_t col0, bool wanted)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(table + (size_t)row * D + col0), 0,
+                                             wanted ? (int)((D - col0) * 4u) : 0, kRsrcFlags);
+}
+
+// Issues the loads of the step that starts in lane t; returns how many updates it takes (0: nothing is left).
+template <int NC, int U, bool PARITY>
+__device__ __forceinline__ uint32_t issue_step(StepLoads<NC, U> &l, const RowArgs &a, uint32_t col0, uint32_t wkey,
+                                               uint32_t widx, u64 rowheads, u64 stripeheads, uint32_t t, uint32_t end)
+{
+    const uint32_t D = a.geo.D, lane = min(t, (uint32_t)kWave - 1u);
+    const bool in = t < end, head = in && ((rowheads >> lane) & 1ull), opens = in && ((stripeheads >> lane) & 1ull);
+    const u64 next = rowheads & ~bits_below(lane + 1u);
+    const uint32_t run_end = next ? min(lowest_bit(next), end) : end;
+    const uint32_t cnt = in ? min((uint32_t)U, run_end - t) : 0u;
+    const uint32_t x = from_lane(wkey, lane);
+    const rsrc_t arow = row_if(a.A, x, D, col0, head), erow = row_if(a.E, x, D, col0, head);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        l.a[i] = ld2(arow, i);
+        l.e[i] = ld2(erow, i);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const rsrc_t grow = row_if(a.grads, from_lane(widx, min(t + u, (uint32_t)kWave - 1u)), D, col0, (uint32_t)u < cnt);
+#pragma unroll
+        for (int i = 0; i < NC; ++i) l.g[u][i] = ldg2(grow, i);
+    }
+    if (PARITY) {
+        const uint32_t g = a.geo.dk.div(x);
+        const rsrc_t perow = row_if(a.PE, g, D, col0, opens), parow = row_if(a.PA, g, D, col0, opens);
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            l.pe[i] = ld2(perow, i);
+            l.pa[i] = ld2(parow, i);
+        }
+    }
+    return cnt;
+}
+
+// The updates in lanes [first, end) of a window, in order.  A run or a stripe may begin before the window (its state is
+// in w) and end behind it (`run_goes_on`, `stripe_goes_on`: its state stays there).
+template <int NC, int MODE, bool PARITY, int Q, int U>
+__device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uint32_t widx, u64 rowheads, u64 stripeheads,
+                                            uint32_t first, uint32_t end, uint32_t cb, Walk<NC> &w, bool run_goes_on,
+                                            bool stripe_goes_on)
+{
+    const uint32_t D = a.geo.D;
+    const RuleParams rp = rule_params(a.geo);
+    const uint32_t col0 = cb * NC * 128u;
+    StepLoads<NC, U> l[Q];
+    uint32_t at[Q], cnt[Q], next = first;          // lane a step in flight starts in, and how many updates it takes
+#pragma unroll
+    for (int s = 0; s < Q; ++s) {
+        at[s] = next;
+        cnt[s] = issue_step<NC, U, PARITY>(l[s], a, col0, wkey, widx, rowheads, stripeheads, next, end);
+        next += cnt[s];
+        asm volatile("" ::: "memory");             // in this order: the first set is waited for first
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // No way out of the loop but its end: an exit in the middle would let the compiler see a path into the next round
+    // with fewer loads behind the first set's.  Steps past the end take zeros in and compute nothing.
+    while (cnt[0]) {
+#pragma unroll
+        for (int s = 0; s < Q; ++s) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+                w.a[i].x += l[s].a[i].x;
+                w.a[i].y += l[s].a[i].y;
+                w.e[i].x += l[s].e[i].x;
+                w.e[i].y += l[s].e[i].y;
+                if (!Rule<MODE>::combine) {
+                    w.G[i].x += (double)l[s].a[i].x;
+                    w.G[i].y += (double)l[s].a[i].y;
+                }
+            }
+            // One branch for the step, none for its updates, whose square roots then overlap: a missing one is a zero
+            // gradient, which leaves sums alone; momentum takes it with a decay of one and a rate of zero.
+            if (cnt[s]) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    RuleParams ru = rp;
+                    if (MODE == kMomentumSeq && (uint32_t)u >= cnt[s]) {
+                        ru.mu = 1.0;
+                        ru.lr = 0.0;
+                    }
+#pragma unroll
+                    for (int i = 0; i < NC; ++i) item2<MODE>(w.G[i], w.acc[i], l[s].g[u][i], ru);
+                }
+            }
+            if (PARITY) {
+#pragma unroll
+                for (int i = 0; i < NC; ++i) {
+                    w.pe[i].x += (double)l[s].pe[i].x;
+                    w.pe[i].y += (double)l[s].pe[i].y;
+                    w.pa[i].x += (double)l[s].pa[i].x;
+                    w.pa[i].y += (double)l[s].pa[i].y;
+                }
+            }
+            // The set is taken in before its registers' next loads are asked for (moved up, those would go to other
+            // registers and be copied at the end of the loop, which waits for them).
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+                asm volatile("" : "+v"(w.G[i].x), "+v"(w.G[i].y), "+v"(w.acc[i].x), "+v"(w.acc[i].y), "+v"(w.e[i].x),
+                             "+v"(w.e[i].y), "+v"(w.a[i].x), "+v"(w.a[i].y) : : "memory");
+                if (PARITY) asm volatile("" : "+v"(w.pe[i].x), "+v"(w.pe[i].y), "+v"(w.pa[i].x), "+v"(w.pa[i].y) : : "memory");
+            }
+            const uint32_t t = at[s], t1 = t + cnt[s];
+            const bool took = cnt[s] != 0;
+            at[s] = next;
+            cnt[s] = issue_step<NC, U, PARITY>(l[s], a, col0, wkey, widx, rowheads, stripeheads, next, end);
+            next += cnt[s];
+            const bool last = t1 >= end;
+            if (took && (last ? !run_goes_on : (bool)((rowheads >> t1) & 1ull))) {          // the entry is complete
+                const uint32_t x = from_lane(wkey, t);
+                const rsrc_t erow = row_f32(a.E, x, D, col0), arow = row_f32(a.A, x, D, col0);
+#pragma unroll
+                for (int i = 0; i < NC; ++i) {
+                    const D2 e64 = widen2(w.e[i]), a64 = widen2(w.a[i]);
+                    finish2<MODE>(w.G[i], w.acc[i], a64, rp);
+                    st2(erow, i, narrow2(D2{e64.x - w.acc[i].x, e64.y - w.acc[i].y}));
+                    st2(arow, i, narrow2(w.G[i]));
+                    if (PARITY) {
+                        w.pe[i].x -= w.acc[i].x;
+                        w.pe[i].y -= w.acc[i].y;
+                        w.pa[i].x += w.G[i].x - a64.x;
+                        w.pa[i].y += w.G[i].y - a64.y;
+                    }
+                }
+                if (PARITY && (last ? !stripe_goes_on : (bool)((stripeheads >> t1) & 1ull))) {
+                    const uint32_t g = a.geo.dk.div(x);
+                    const rsrc_t perow = row_f32(a.PE, g, D, col0), parow = row_f32(a.PA, g, D, col0);
+#pragma unroll
+                    for (int i = 0; i < NC; ++i) {
+                        st2(perow, i, narrow2(w.pe[i]));
+                        st2(parow, i, narrow2(w.pa[i]));
+                    }
+                    w.clear_stripe();
+                }
+                w.clear_entry();
+            }
+        }
+    }
+}
+
+// ================================================================================================
+// partition
+// ================================================================================================
+
+struct PartitionArgs {
+    const uint64_t *keys;
+    u64 *items;                // [n]: tile by tile, row << 32 | position in the batch
+    uint16_t *table;           // [tiles][buckets + kHotBuckets + 1]: where each bucket begins in the tile
+    uint32_t *tile_cnt;        // [tiles][2S]: load counts of the tile (not for the combined rules)
+    uint32_t *tile_bad;        // [tiles]
+    Header *hdr;
+    uint32_t n, buckets, rows, count;
+    uint32_t clear_sticky, packed;
+    Divider dk, dS;
+    RecoveryView rv;
+};
+
+// sort key of one key of the batch: its row, its stripe; false if it takes no part (out of range, or held back)
+__device__ __forceinline__ bool takes_part(const PartitionArgs &a, uint64_t k64, uint32_t &x, uint32_t &g, bool &bad)
+{
+    x = (uint32_t)k64;
+    g = 0;
+    bad = !a.packed && k64 >= (uint64_t)a.rows;
+    if (bad || held_back(a.rv, x, a.dk, a.dS)) return false;
+    g = a.dk.div(x);
+    return true;
+}
+
+// Stripes that a sample of the batch -- kSample keys at fixed distances, the same for every workgroup -- holds so often
+// that they have about kHotRun updates or more.  Their entries get buckets of their own behind the others, so that
+// neither the sorting of a bucket nor the walk of a workgroup ever sees a hot run; what the sample misses (less than
+// 0.4 % of the batch each) is found in its bucket.  The choice depends on nothing but the sample: every workgroup
+// makes the same one.
+// A batch of up to kSmallSampled updates gets along with half the sample: what it misses is at most a bucket's length.
+constexpr uint32_t kSample = 1024, kSampleSlots = 2048, kHotCand = 256, kHotMax = 64, kHotSlots = 256;
+constexpr uint32_t kSmallSampled = kBucketCap * (kSample / 2) / 4;
+
+struct SampleShared {
+    uint32_t g[kSampleSlots], c[kSampleSlots];
+    uint32_t cand_g[kHotCand], cand_c[kHotCand];
+};
+struct HotShared {
+    uint32_t g[kHotSlots], h[kHotSlots];       // open addressing: stripe, its number among the hot ones
+    uint32_t n_cand;
+};
+
+__device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n, SampleShared &t, HotShared &hot)
+{
+    const uint32_t tid = threadIdx.x;
+    const uint32_t sample = n <= kSmallSampled ? kSample / 2 : kSample;
+    const uint32_t least = max(4u, (sample * kHotRun + n - 1u) / n), cap = min(kHotMax, kHotBuckets / a.dk.d);
+    for (uint32_t i = tid; i < kSampleSlots; i += kPartThreads) {
+        t.g[i] = kNoKey;
+        t.c[i] = 0;
+    }
+    for (uint32_t i = tid; i < kHotSlots; i += kPartThreads) hot.g[i] = kNoKey;
+    if (tid == 0) hot.n_cand = 0;
+    __syncthreads();
+    uint64_t key[kSample / kPartThreads];
+#pragma unroll
+    for (uint32_t r = 0; r < kSample / kPartThreads; ++r)
+        key[r] = r * kPartThreads < sample ? a.keys[((uint64_t)(r * kPartThreads + tid) * n) / sample] : 0u;
+#pragma unroll
+    for (uint32_t r = 0; r < kSample / kPartThreads; ++r) {
+        uint32_t x, g;
+        bool bad;
+        if (r * kPartThreads >= sample || !takes_part(a, key[r], x, g, bad)) continue;
+        for (uint32_t s = mix32(g) & (kSampleSlots - 1u);; s = (s + 1u) & (kSampleSlots - 1u)) {   // at most kSample slots fill
+            const uint32_t was = atomicCAS(&t.g[s], kNoKey, g);
+            if (was == kNoKey || was == g) {
+                atomicAdd(&t.c[s], 1u);
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < kSampleSlots; i += kPartThreads) {
+        if (t.c[i] >= least) {                                      // at most kSample / 4 = kHotCand of them
+            const uint32_t at = atomicAdd(&hot.n_cand, 1u);
+            t.cand_g[at] = t.g[i];
+            t.cand_c[at] = t.c[i];
+        }
+    }
+    __syncthreads();
+    const uint32_t nc = hot.n_cand;
+    if (tid < nc) {                                                 // the cap most frequent, smaller numbers first
+        const uint32_t g = t.cand_g[tid], c = t.cand_c[tid];
+        uint32_t rank = 0;
+        for (uint32_t i = 0; i < nc; ++i)
+            rank += t.cand_c[i] > c || (t.cand_c[i] == c && t.cand_g[i] < g) ? 1u : 0u;
+        if (rank < cap) {
+            uint32_t s = mix32(g) & (kHotSlots - 1u);
+            while (atomicCAS(&hot.g[s], kNoKey, g) != kNoKey) s = (s + 1u) & (kHotSlots - 1u);     // kHotMax < kHotSlots
+            hot.h[s] = rank;
+        }
+    }
+    __syncthreads();
+    return min(nc, cap);
+}
+
+// Bound by its chain of dependent steps (keys, ranks, scan, write), not by its 16 bytes per update; the ranks are
+// those of the sort's scatter kernel -- equal buckets of a wave are matched with ballots -- with one 16-bit counter per
+// wave and bucket, the eight of a bucket side by side in LDS.
+template <int IPT>
+__global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(PartitionArgs a)
+{
+    constexpr uint32_t kTile = kPartThreads * IPT;
+    __shared__ __align__(16) uint16_t s_cnt[kMaxBuckets + kHotBuckets][kPartWaves];
+    __shared__ HotShared s_hot;
+    __shared__ uint32_t s_srv[2 * kBucketMaxServers];
+    __shared__ uint32_t s_wave[kPartWaves];
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave, tile = blockIdx.x;
+    const uint32_t n = a.packed ? min(a.n, a.hdr->buf_count) : a.n;       // a replay: everything that is waiting now
+    const uint32_t S = a.dS.d, tile0 = tile * kTile;
+    static_assert(sizeof(SampleShared) <= sizeof(s_cnt), "the sample is counted where the buckets are, before them");
+    const uint32_t n_hot = n >= kSample * 4u ? find_hot(a, n, *(SampleShared *)&s_cnt[0][0], s_hot) : 0u;
+    const uint32_t B = a.buckets + kHotBuckets;                           // buckets in the table; the last are the hot entries'
+    for (uint32_t i = tid; i < B; i += kPartThreads) *(ulonglong2 *)s_cnt[i] = ulonglong2{0, 0};
+    for (uint32_t i = tid; i < 2 * S; i += kPartThreads) s_srv[i] = 0;
+    __syncthreads();
+
+    uint32_t row[IPT], dig[IPT], rank[IPT];
+    bool in[IPT], bad = false;
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const uint32_t i = tile0 + wave * (kWave * IPT) + r * kWave + lane;
+        row[r] = dig[r] = 0;
+        in[r] = false;
+        if (i < n) {
+            uint32_t x, g;
+            bool out;
+            in[r] = takes_part(a, a.keys[i], x, g, out);
+            bad |= out;
+            if (in[r]) {
+                const uint32_t j = x - g * a.dk.d;
+                row[r] = x;
+                dig[r] = bucket_of(g, a.buckets);
+                if (n_hot) {
+                    for (uint32_t s = mix32(g) & (kHotSlots - 1u); s_hot.g[s] != kNoKey; s = (s + 1u) & (kHotSlots - 1u)) {
+                        if (s_hot.g[s] == g) {
+                            dig[r] = a.buckets + s_hot.h[s] * a.dk.d + j;
+                            break;
+                        }
+                    }
+                }
+                if (a.count) {
+                    atomicAdd(&s_srv[a.dS.mod(g + 1 + j)], 1u);
+                    atomicAdd(&s_srv[S + a.dS.mod(g)], 1u);
+                }
+            }
+        }
+    }
+    const int bits = 32 - __builtin_clz(n_hot ? B - 1u : max(a.buckets - 1u, 1u));
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        u64 peers = __ballot(in[r]);
+        for (int b = 0; b < bits; ++b) {
+            const bool bit = (dig[r] >> b) & 1u;
+            const u64 bal = __ballot(bit);
+            peers &= bit ? bal : ~bal;
+        }
+        const uint32_t below = (uint32_t)__popcll(peers & bits_below(lane));
+        const uint32_t old = s_cnt[dig[r]][wave];
+        __builtin_amdgcn_wave_barrier();
+        if (in[r] && below == 0) s_cnt[dig[r]][wave] = (uint16_t)(old + (uint32_t)__popcll(peers));
+        __builtin_amdgcn_wave_barrier();
+        rank[r] = old + below;
+    }
+    bad = __syncthreads_or(bad);
+
+    uint16_t *out = a.table + (size_t)tile * (B + 1);
+    uint32_t carry = 0;
+    for (uint32_t d0 = 0; d0 < B; d0 += kPartThreads) {
+        const uint32_t d = d0 + tid;
+        uint32_t c[kPartWaves], tot = 0;
+#pragma unroll
+        for (int w = 0; w < kPartWaves; ++w) {
+            c[w] = d < B ? s_cnt[d][w] : 0u;
+            tot += c[w];
+        }
+        uint32_t all;
+        uint32_t at = carry + bucket_excl_scan<kPartWaves>(tot, s_wave, all);
+        carry += all;
+        if (d < B) {
+            out[d] = (uint16_t)at;
+#pragma unroll
+            for (int w = 0; w < kPartWaves; ++w) {
+                s_cnt[d][w] = (uint16_t)at;
+                at += c[w];
+            }
+        }
+    }
+    if (tid == 0) {
+        out[B] = (uint16_t)carry;
+        a.tile_bad[tile] = bad ? 1u : 0u;
+    }
+    if (a.count)
+        for (uint32_t i = tid; i < 2 * S; i += kPartThreads) a.tile_cnt[(size_t)tile * 2 * S + i] = s_srv[i];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const uint32_t i = tile0 + wave * (kWave * IPT) + r * kWave + lane;
+        if (in[r]) a.items[tile0 + s_cnt[dig[r]][wave] + rank[r]] = ((u64)row[r] << 32) | i;
+    }
+    // the header of the call: no other workgroup of this launch touches it (a replay reads buf_count only)
+    if (tile == 0 && tid == 0) {
+        Header *h = a.hdr;
+        if (a.clear_sticky) {
+            h->err_sticky = 0;
+            h->buf_count = 0;
+            h->free_count = 0;
+            h->bump = 0;
+        }
+        h->batch_bad = 0;
+        h->n_long = 0;
+        h->n_pieces = 0;
+        h->n_long_items = 0;
+        h->n_batch = n;
+        h->n_valid = n;
+        h->n_held = 0;
+        h->n_heavy = 0;
+        h->heavy_ticket = 0;
+        for (uint32_t c = 0; c < kMidClasses; ++c) h->n_mid[c] = 0;
+    }
+}
+
+// ================================================================================================
+// a bucket's stripes, from its items in LDS
+// ================================================================================================
+
+// Sorts m distinct items (m <= kBucketCap), with room for as many in tmp.  Every wave first orders pieces of 64: each item
+// counts the smaller ones of its piece -- reads that all lanes share --, then it looks up its place in the other pieces
+// by binary search.  One short loop for lists of all lengths: code that only a few long lists ran through cost more in
+// instruction fetches than it saved (a bitonic network: 11 us for 600 items; unrolled cases by length: 20 us).
+__device__ __forceinline__ void sort_items(u64 *s_item, u64 *s_tmp, uint32_t m)
+{
+    const uint32_t tid = threadIdx.x, lane = lane_id(), pieces = (m + kWave - 1) / kWave;
+    if (tid < pieces * kWave - m) s_item[m + tid] = ~0ull;       // fewer than 64: what is read behind the list counts as larger
+    __syncthreads();
+    for (uint32_t i = tid; i - lane < m; i += kBucketThreads) {
+        const u64 it = s_item[i], *piece = s_item + (i - lane);
+        uint32_t rank = 0;
+#pragma unroll 8
+        for (uint32_t j = 0; j < (uint32_t)kWave; j += 2) {
+            const ulonglong2 v = *(const ulonglong2 *)(piece + j);
+            rank += (v.x < it ? 1u : 0u) + (v.y < it ? 1u : 0u);
+        }
+        if (i < m) s_tmp[i - lane + rank] = it;
+        else s_tmp[i] = ~0ull;                                   // the padding stays behind the list
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < m; i += kBucketThreads) {
+        const u64 it = s_tmp[i];
+        uint32_t rank = lane;                                    // its place in its own piece
+        for (uint32_t o = 0; o < pieces; o += 2) {               // two other pieces at a time
+            const u64 *pa = s_tmp + o * kWave, *pb = pa + (o + 1 < pieces ? kWave : 0);
+            uint32_t la = 0, lb = 0;
+#pragma unroll
+            for (uint32_t step = kWave; step > 0; step /= 2) {
+                const uint32_t ta = la + step, tb = lb + step;
+                const u64 va = pa[min(ta, (uint32_t)kWave) - 1u], vb = pb[min(tb, (uint32_t)kWave) - 1u];
+                la = ta <= (uint32_t)kWave && va < it ? ta : la;
+                lb = tb <= (uint32_t)kWave && vb < it ? tb : lb;
+            }
+            rank += (o != i / kWave ? la : 0u) + (o + 1 < pieces && o + 1 != i / kWave ? lb : 0u);
+        }
+        s_item[rank] = it;
+    }
+    __syncthreads();
+}
+
+struct ListShared {
+    uint32_t heavy[kBucketCap / kHeavyRunMin];               // stripes for heavy_stripes: start | end << 16
+    uint32_t n_heavy, chunk;
+    uint32_t srv[2 * kBucketMaxServers];
+};
+
+// Applies every stripe of a sorted list of m items (m <= kBucketCap).  Chunks of CH positions are handed to the waves as
+// they come free; a wave owns the stripes that open in its chunk.  A stripe that does not end inside the wave's
+// 64-position window is walked window by window with its state in registers; one with a run of heavy_run updates or more
+// is only listed in sh.heavy.
+// A barrier has to lie between the last write of the list and this call; the call ends with one.
+template <int NC, int MODE, bool PARITY, uint32_t CH>
+__device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, uint32_t m, uint32_t heavy_run,
+                                           ListShared &sh)
+{
+    constexpr int kQ = 2, kU = NC == 1 ? 4 : 2;
+    const uint32_t lane = lane_id();
+    const Divider dk = a.geo.dk;
+    if (threadIdx.x == 0) {
+        sh.n_heavy = 0;
+        sh.chunk = kBucketWaves;
+    }
+    __syncthreads();
+    for (uint32_t c = uniform(threadIdx.x / kWave); c * CH < m;) {
+        const uint32_t p0 = c * CH;
+        if (lane == 0) c = atomicAdd(&sh.chunk, 1u);         // the chunk after this one
+        c = uniform(c);
+        const u64 it = p0 + lane < m ? items[p0 + lane] : ~0ull;
+        const uint32_t wkey = item_row(it), widx = (uint32_t)it;
+        uint32_t leftk = __shfl_up(wkey, 1, kWave);
+        if (lane == 0) leftk = p0 ? item_row(items[p0 - 1]) : kNoKey;
+        const bool valid = wkey != kNoKey;
+        const u64 rowheads = __ballot(!valid || leftk == kNoKey || leftk != wkey);
+        const u64 stripeheads = __ballot(valid && (leftk == kNoKey || dk.div(leftk) != dk.div(wkey)));
+        const u64 owned = stripeheads & bits_below(CH);
+        if (!owned) continue;
+        const uint32_t first = lowest_bit(owned), last = 63u - (uint32_t)__builtin_clzll(owned);
+        const u64 after = stripeheads & ~bits_below(last + 1);
+        const bool inside = after != 0ull || p0 + kWave >= m;
+        const uint32_t end = inside ? (after ? lowest_bit(after) : min((uint32_t)kWave, m - p0)) : last;
+        // the stripe that goes on behind the window: where it ends, and how long its runs are
+        const uint32_t big_start = p0 + last;
+        uint32_t big_end = big_start;
+        bool heavy = false;
+        if (!inside) {
+            const uint32_t g = dk.div(from_lane(wkey, last));
+            for (;;) {
+                const uint32_t p = big_end + lane;
+                const uint32_t key = p < m ? item_row(items[p]) : kNoKey;
+                const bool same = key != kNoKey && dk.div(key) == g;
+                if (__ballot(same && p + heavy_run - 1 < m && item_row(items[min(p + heavy_run - 1, m - 1)]) == key)) heavy = true;
+                const u64 other = __ballot(!same);
+                if (other) {
+                    big_end += lowest_bit(other);
+                    break;
+                }
+                big_end += kWave;
+            }
+            if (heavy && lane == 0) sh.heavy[atomicAdd(&sh.n_heavy, 1u)] = big_start | (big_end << 16);
+        }
+        for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
+            Walk<NC> walk;
+            walk.clear_entry();
+            walk.clear_stripe();
+            // the window, then the windows of the stripe that goes on behind it
+            uint32_t wk = wkey, wi = widx, from = first, to = end, p = p0;
+            u64 rh = rowheads, sth = stripeheads;
+            bool run_on = false, stripe_on = false;
+            for (bool more = !inside && !heavy;;) {
+                walk_window<NC, MODE, PARITY, kQ, kU>(a, wk, wi, rh, sth, from, to, cb, walk, run_on, stripe_on);
+                if (!more) break;
+                p = stripe_on ? p + kWave : big_start;
+                const u64 nx = p + lane < big_end ? items[p + lane] : ~0ull;
+                wk = item_row(nx);
+                wi = (uint32_t)nx;
+                uint32_t lk = __shfl_up(wk, 1, kWave);
+                if (lane == 0) lk = p > big_start ? item_row(items[p - 1]) : kNoKey;
+                rh = __ballot(lk != wk);
+                sth = p == big_start ? 1ull : 0ull;
+                from = 0;
+                stripe_on = p + kWave < big_end;
+                to = stripe_on ? (uint32_t)kWave : big_end - p;
+                run_on = stripe_on && uniform(item_row(items[stripe_on ? p + kWave : p])) == from_lane(wk, kWave - 1);
+                more = stripe_on;
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Combined rules: one entry update and one parity update per modified entry (Sec. 3.6, Sec. 4.4).  The list is sorted.
+__device__ __forceinline__ void count_list(const Geometry &geo, const u64 *items, uint32_t m, uint32_t *s_srv,
+                                           u64 *load_data, u64 *load_parity)
+{
+    const uint32_t S = geo.S;
+    for (uint32_t i = threadIdx.x; i < 2 * S; i += kBucketThreads) s_srv[i] = 0;
+    __syncthreads();
+    for (uint32_t p = threadIdx.x; p < m; p += kBucketThreads) {
+        const uint32_t x = item_row(items[p]);
+        if (p && item_row(items[p - 1]) == x) continue;
+        const uint32_t g = geo.dk.div(x), j = x - g * geo.k;
+        atomicAdd(&s_srv[geo.dS.mod(g + 1 + j)], 1u);
+        atomicAdd(&s_srv[S + geo.dS.mod(g)], 1u);
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < 2 * S; i += kBucketThreads) {
+        u64 *to = i < S ? load_data : load_parity;
+        if (s_srv[i] && to) atomicAdd(&to[i < S ? i : i - S], (u64)s_srv[i]);
+    }
+    __syncthreads();
+}
+
+// ================================================================================================
+// one workgroup per bucket
+// ================================================================================================
+
+struct BucketArgs : RowArgs {
+    const uint64_t *keys;        // the batch: the caller's keys, or the list entries of a replay (packed)
+    const u64 *items;
+    u64 *tmp, *dense;            // [n] each: an oversized bucket's items in arrival order; its heavy stripes', sorted
+    const uint16_t *table;
+    const uint32_t *tile_cnt, *tile_bad;
+    uint32_t *heavy;             // [2 * (n / kHeavyRunMin + 64)]: start in `dense`, number of updates
+    Header *hdr;
+    u64 *load_data, *load_parity;
+    uint32_t n, tile, tiles, buckets, packed;
+    uint32_t heavy_run;          // a run of at least this many updates goes to heavy_stripes with its stripe
+};
+
+// gradient row of an item, from its position in the batch
+__device__ __forceinline__ u64 resolved(const BucketArgs &a, u64 it)
+{
+    return a.packed ? (it & 0xFFFFFFFF00000000ull) | (a.keys[(uint32_t)it] >> 32) : it;
+}
+
+// One more stripe for heavy_stripes, at base + at0 in `dense` (one thread).  Every such stripe has at least kHeavyRunMin
+// updates, or is one of the at most kHotMax that the sample found: there is room in the list.
+constexpr uint32_t kCounted = 0x80000000u;  // flag beside the number: the combined rules' load is counted already
+__device__ __forceinline__ void list_heavy(const BucketArgs &a, uint32_t &dense_used, uint32_t base, uint32_t at0, uint32_t count,
+                                           bool counted)
+{
+    const uint32_t i = atomicAdd(&a.hdr->n_heavy, 1u);
+    a.heavy[2 * i] = base + at0;
+    a.heavy[2 * i + 1] = count | (counted ? kCounted : 0u);
+    dense_used = at0 + count;
+}
+
+constexpr uint32_t kStripeSlots = 1024;     // LDS table of an oversized bucket's stripes
+constexpr uint32_t kStripeFill = 640;       // ... and how many it may hold
+constexpr uint32_t kHeavySlots = 16;
+
+struct BucketShared {
+    __align__(16) u64 item[kBucketCap];
+    union {
+        u64 tmp[kBucketCap];                                   // of the sort
+        struct { uint32_t tab_g[kStripeSlots], tab_c[kStripeSlots]; };     // of an oversized bucket, before it
+    };
+    ListShared list;
+    uint32_t pref[kMaxTiles + 1], start[kMaxTiles], wave[kBucketWaves];
+    uint32_t hv[kHeavySlots], hv_n, fill, light, n_light, over;
+    uint32_t member[kBucketWaves][64];
+    uint32_t dense_used;
+};
+
+__device__ __forceinline__ uint32_t stripe_slot(const uint32_t *tab_g, uint32_t g)      // g is in the table
+{
+    uint32_t s = (g * 0x85EBCA77u) >> 22;
+    while (tab_g[s] != g) s = (s + 1u) & (kStripeSlots - 1u);
+    return s;
+}
+
+// where the bucket's q-th item, in arrival order, lies in a.items
+__device__ __forceinline__ uint32_t place_of(const BucketShared &sh, uint32_t tiles, uint32_t q)
+{
+    uint32_t lo = 0, hi = tiles;                                    // pref[lo] <= q < pref[hi]
+    while (hi - lo > 1u) {
+        const uint32_t mid = (lo + hi) / 2u;
+        if (sh.pref[mid] <= q) lo = mid; else hi = mid;
+    }
+    return sh.start[lo] + (q - sh.pref[lo]);
+}
+
+// A bucket with more items than LDS takes: hot stripes.  Its items are first laid out in arrival order in tmp; then,
+// for one part of the stripes after the other (by the low bits of the mix, split until a part fits), the stripes are
+// counted in an LDS table, the light ones are collected, sorted and applied like any bucket, and the heavy ones -- more
+// than kHeavyMin updates -- are written to `dense`, entry by entry in arrival order, for heavy_stripes.  A part of a
+// single stripe always fits, so the splitting ends.  Uniform over the workgroup.  Every pass over the items keeps
+// kAhead loads of a thread in flight (one at a time, a bucket of 14 000 items took 130 us).
+constexpr int kAhead = 4;
+
+// the bucket's items in arrival order; RESOLVE: with their gradient rows in place of their positions.  A wave takes whole
+// pieces, kCopyAhead of them at a time: each step is a trip to memory.
+template <bool RESOLVE>
+__device__ __forceinline__ void copy_bucket(const BucketArgs &a, const BucketShared &sh, u64 *to)
+{
+    constexpr uint32_t kCopyAhead = 8;
+    const uint32_t lane = lane_id();
+    for (uint32_t t0 = uniform(threadIdx.x / kWave) * kCopyAhead; t0 < a.tiles; t0 += kBucketWaves * kCopyAhead) {
+        uint32_t longest = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < kCopyAhead; ++u) {
+            const uint32_t t = min(t0 + u, a.tiles - 1u);
+            longest = max(longest, sh.pref[t + 1] - sh.pref[t]);
+        }
+        for (uint32_t c = lane; c - lane < longest; c += kWave) {
+            u64 it[kCopyAhead];
+#pragma unroll
+            for (uint32_t u = 0; u < kCopyAhead; ++u) {
+                const uint32_t t = min(t0 + u, a.tiles - 1u);
+                it[u] = c < sh.pref[t + 1] - sh.pref[t] ? a.items[sh.start[t] + c] : 0ull;
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < kCopyAhead; ++u) {
+                const uint32_t t = t0 + u;
+                if (t < a.tiles && c < sh.pref[t + 1] - sh.pref[t]) to[sh.pref[t] + c] = RESOLVE ? resolved(a, it[u]) : it[u];
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ void oversized_begin(const BucketArgs &a, BucketShared &sh, uint32_t base)
+{
+    copy_bucket<false>(a, sh, a.tmp + base);
+    if (threadIdx.x == 0) sh.dense_used = 0;
+    __threadfence_block();
+    __syncthreads();
+}
+
+// f(item) for the items [lo, hi) of tmp, `lane` of `width` taking every width-th; positions past hi: f(~0)
+template <typename F>
+__device__ __forceinline__ void stream_items(const u64 *tmp, uint32_t lo, uint32_t hi, uint32_t lane, uint32_t width, F f)
+{
+    for (uint32_t q0 = lo; q0 < hi; q0 += kAhead * width) {
+        u64 it[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t q = q0 + u * width + lane;
+            it[u] = q < hi ? tmp[q] : ~0ull;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) f(it[u]);
+    }
+}
+
+// The parts still to come: `part` are the low `depth` bits of the next one; depth < 0: none is left.
+struct PartWalk {
+    uint32_t part;
+    int depth;
+};
+
+// One part: its heavy stripes go to `dense`, its light ones' items to LDS, not sorted yet; returns how many they are.
+__device__ __forceinline__ uint32_t oversized_part(const BucketArgs &a, BucketShared &sh, uint32_t m, uint32_t base,
+                                                   PartWalk &walk)
+{
+    const uint32_t tid = threadIdx.x, lane = lane_id(), w = uniform(tid / kWave), k = a.geo.k;
+    const Divider dk = a.geo.dk;
+    const u64 *tmp = a.tmp + base;
+    u64 *dense = a.dense + base;
+    uint32_t part = walk.part, mask;
+    int depth = walk.depth;
+    for (;;) {
+        mask = depth >= 32 ? ~0u : (1u << depth) - 1u;
+        // ---- count the part's stripes
+        for (uint32_t i = tid; i < kStripeSlots; i += kBucketThreads) {
+            sh.tab_g[i] = kNoKey;
+            sh.tab_c[i] = 0;
+        }
+        if (tid == 0) sh.fill = sh.light = sh.n_light = sh.over = sh.hv_n = 0;
+        __syncthreads();
+        volatile uint32_t *over = &sh.over;
+        stream_items(tmp, 0, m, tid, kBucketThreads, [&](u64 it) {
+            const uint32_t g = dk.div(item_row(it));
+            // one lane for all of the wave's items of its stripe: a hot stripe's counter, updated by every lane, is
+            // what this pass would wait for
+            bool in = it != ~0ull && (mix32(g) & mask) == part;
+            uint32_t c = 0;
+            for (u64 todo = __ballot(in); todo;) {
+                const u64 same = __ballot(in && g == from_lane(g, lowest_bit(todo)));
+                if (lane == lowest_bit(todo)) c = (uint32_t)__popcll(same);
+                todo &= ~same;
+            }
+            if (c == 0 || *over) return;
+            uint32_t s = (g * 0x85EBCA77u) >> 22, tries = 0;
+            for (; tries < kStripeSlots; ++tries) {                 // bounded: a full table means the part is split
+                const uint32_t was = atomicCAS(&sh.tab_g[s], kNoKey, g);
+                if (was == kNoKey && atomicAdd(&sh.fill, 1u) >= kStripeFill) *over = 1;
+                if (was == kNoKey || was == g) break;
+                s = (s + 1u) & (kStripeSlots - 1u);
+            }
+            if (tries < kStripeSlots) atomicAdd(&sh.tab_c[s], c);
+            else *over = 1;
+        });
+        __syncthreads();
+        if (!sh.over) {
+            for (uint32_t s = tid; s < kStripeSlots; s += kBucketThreads) {
+                const uint32_t c = sh.tab_c[s];
+                if (c > kHeavyMin) {
+                    const uint32_t i = atomicAdd(&sh.hv_n, 1u);
+                    if (i < kHeavySlots) sh.hv[i] = s;
+                } else if (c) {
+                    atomicAdd(&sh.light, c);
+                }
+            }
+        }
+        __syncthreads();
+        const bool split = sh.over || sh.hv_n > kHeavySlots || sh.light > kBucketCap;
+        __syncthreads();
+        if (!split) break;                                          // ends: a part of one stripe fits
+        ++depth;
+    }
+    // ---- the light stripes
+    const uint32_t light = uniform(sh.light), nh = uniform(sh.hv_n);
+    if (light)
+        stream_items(tmp, 0, m, tid, kBucketThreads, [&](u64 it) {
+            const uint32_t g = dk.div(item_row(it));
+            if (it == ~0ull || (mix32(g) & mask) != part) return;
+            if (sh.tab_c[stripe_slot(sh.tab_g, g)] <= kHeavyMin) sh.item[atomicAdd(&sh.n_light, 1u)] = it;
+        });
+    // ---- the heavy ones: a stable partition by member, every wave a contiguous quarter of the items
+    const uint32_t quarter = (m + kBucketWaves - 1) / kBucketWaves, q_lo = min(w * quarter, m), q_hi = min(q_lo + quarter, m);
+    for (uint32_t h = 0; h < nh; ++h) {
+        const uint32_t slot = uniform(sh.hv[h]), g = uniform(sh.tab_g[slot]), c = uniform(sh.tab_c[slot]);
+        for (uint32_t j = tid; j < kBucketWaves * 64u; j += kBucketThreads) (&sh.member[0][0])[j] = 0;
+        __syncthreads();
+        stream_items(tmp, q_lo, q_hi, lane, kWave, [&](u64 it) {
+            const uint32_t x = item_row(it);
+            const bool in = it != ~0ull && dk.div(x) == g;
+            for (u64 todo = __ballot(in); todo;) {                  // at most k rounds
+                const uint32_t who = lowest_bit(todo);
+                const u64 same = __ballot(in && x == from_lane(x, who));
+                if (lane == who) sh.member[w][x - g * k] += (uint32_t)__popcll(same);      // the wave's own counter
+                todo &= ~same;
+            }
+        });
+        __syncthreads();
+        const uint32_t at0 = uniform(sh.dense_used);
+        if (w == 0) {                                               // lane j: where member j's updates begin, wave by wave
+            uint32_t cnt[kBucketWaves], all = 0;
+#pragma unroll
+            for (int v = 0; v < kBucketWaves; ++v) {
+                cnt[v] = sh.member[v][lane];
+                all += cnt[v];
+            }
+            uint32_t incl = all;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const uint32_t t = __shfl_up(incl, d, kWave);
+                if (lane >= (uint32_t)d) incl += t;
+            }
+            uint32_t at = at0 + incl - all;
+#pragma unroll
+            for (int v = 0; v < kBucketWaves; ++v) {
+                sh.member[v][lane] = at;
+                at += cnt[v];
+            }
+        }
+        __syncthreads();
+        stream_items(tmp, q_lo, q_hi, lane, kWave, [&](u64 it) {
+            const uint32_t x = item_row(it);
+            const bool mine = it != ~0ull && dk.div(x) == g;
+            const uint32_t j = mine ? x - g * k : 0u;
+            u64 peers = __ballot(mine);
+#pragma unroll
+            for (int b = 0; b < 6; ++b) {
+                const bool bit = (j >> b) & 1u;
+                const u64 bal = __ballot(bit);
+                peers &= bit ? bal : ~bal;
+            }
+            const uint32_t at = sh.member[w][j], below = (uint32_t)__popcll(peers & bits_below(lane));
+            __builtin_amdgcn_wave_barrier();
+            if (mine) {
+                dense[at + below] = resolved(a, it);
+                if (below == 0) sh.member[w][j] = at + (uint32_t)__popcll(peers);
+            }
+            __builtin_amdgcn_wave_barrier();
+        });
+        __syncthreads();                                            // every wave has taken at0
+        if (tid == 0) list_heavy(a, sh.dense_used, base, at0, c, false);
+        __syncthreads();
+    }
+    // ---- next part: the parts are the leaves of a binary tree over the low bits, left to right
+    while (depth > 0 && ((part >> (depth - 1)) & 1u)) {
+        part &= ~(1u << (depth - 1));
+        --depth;
+    }
+    if (depth > 0) part |= 1u << (depth - 1);
+    walk.part = part;
+    walk.depth = depth > 0 ? depth : -1;
+    __syncthreads();
+    return light;
+}
+
+template <int NC, int MODE, bool PARITY>
+__global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_kernel(BucketArgs a)
+{
+    __shared__ BucketShared sh;
+    const uint32_t tid = threadIdx.x, b = blockIdx.x, B = a.buckets + kHotBuckets, S = a.geo.S, k = a.geo.k;
+    const bool hot = b >= a.buckets, hot_head = hot && (b - a.buckets) % k == 0 && b + k <= B;   // an entry of a hot stripe, its first
+    bool key_bad = false;
+    uint32_t from = 0, len = 0, stripe_len = 0;
+    if (tid < a.tiles) {
+        const uint16_t *row = a.table + (size_t)tid * (B + 1) + b;
+        key_bad = a.tile_bad[tid] != 0;
+        from = tid * a.tile + row[0];
+        len = (uint32_t)row[1] - row[0];
+        if (hot_head) stripe_len = (uint32_t)row[k] - row[0];
+    }
+    const bool full = a.hdr->batch_bad != 0;                        // the recovery buffer could not take its part
+    key_bad = __syncthreads_or(key_bad);
+    if (key_bad || full) {
+        if (b == 0 && tid == 0 && key_bad) {
+            a.hdr->batch_bad = 1;
+            atomicOr(&a.hdr->err_sticky, 1u);
+        }
+        return;
+    }
+    uint32_t m;
+    const uint32_t at = bucket_excl_scan(len, sh.wave, m);
+    if (!Rule<MODE>::combine && b == 0) {                           // the batch is valid: publish its per-server counts
+        for (uint32_t i = tid; i < 2 * S; i += kBucketThreads) sh.list.srv[i] = 0;
+        __syncthreads();
+        for (uint32_t i = tid; i < a.tiles * 2 * S; i += kBucketThreads) {
+            const uint32_t c = a.tile_cnt[i];
+            if (c) atomicAdd(&sh.list.srv[i % (2 * S)], c);
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i < 2 * S; i += kBucketThreads) {
+            u64 *to = i < S ? a.load_data : a.load_parity;
+            if (to) to[i < S ? i : i - S] += sh.list.srv[i];
+        }
+    }
+    if (hot_head) {
+        uint32_t count;
+        bucket_excl_scan(stripe_len, sh.wave, count);
+        if (count) {
+            uint32_t start;
+            bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, start);
+            if (tid == 0) list_heavy(a, sh.dense_used, start, 0, count, false);
+        }
+    }
+    if (m == 0) return;
+    if (tid <= a.tiles && tid < kMaxTiles) sh.pref[tid] = at;       // [tiles] = m as well (len is 0 there)
+    if (tid == 0) sh.pref[a.tiles] = m;
+    if (tid < a.tiles) sh.start[tid] = from;
+    __syncthreads();
+    if (hot) {                                                      // one entry's updates, in arrival order as they are
+        uint32_t start;
+        bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, start);
+        copy_bucket<true>(a, sh, a.dense + start);
+        return;
+    }
+    // An ordinary bucket is one list; an oversized one comes in parts, one list after the other.
+    const bool oversized = m > kBucketCap;
+    uint32_t base = 0;                                              // items of the batch in earlier buckets
+    bool have_base = oversized;
+    PartWalk walk{0u, 0};
+    if (oversized) {
+        bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, base);
+        oversized_begin(a, sh, base);
+    } else if (tid == 0) {
+        sh.dense_used = 0;
+    }
+    for (;;) {
+        uint32_t list = m;
+        if (oversized) {
+            list = oversized_part(a, sh, m, base, walk);
+        } else {
+            constexpr int P = kBucketCap / kBucketThreads;
+            u64 it[P];
+#pragma unroll
+            for (int c = 0; c < P; ++c) {
+                const uint32_t q = c * kBucketThreads + tid;
+                if (q < m) it[c] = a.items[place_of(sh, a.tiles, q)];
+            }
+#pragma unroll
+            for (int c = 0; c < P; ++c) {
+                const uint32_t q = c * kBucketThreads + tid;
+                if (q < m) sh.item[q] = it[c];
+            }
+            __syncthreads();
+        }
+        if (list) {
+            sort_items(sh.item, sh.tmp, list);
+            if (a.packed) {
+                for (uint32_t i = tid; i < list; i += kBucketThreads) sh.item[i] = resolved(a, sh.item[i]);
+                __syncthreads();
+            }
+            if (Rule<MODE>::combine) count_list(a.geo, sh.item, list, sh.list.srv, a.load_data, a.load_parity);
+            apply_list<NC, MODE, PARITY, kBucketChunk>(a, sh.item, list, a.heavy_run, sh.list);
+            const uint32_t nh = uniform(sh.list.n_heavy);
+            if (nh && !have_base) {
+                bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, base);
+                have_base = true;
+            }
+            for (uint32_t h = 0; h < nh; ++h) {                     // the long runs' stripes, sorted as they are
+                const uint32_t at0 = uniform(sh.dense_used), hs = uniform(sh.list.heavy[h]);
+                const uint32_t start = hs & 0xFFFFu, count = (hs >> 16) - start;
+                for (uint32_t i = tid; i < count; i += kBucketThreads) a.dense[base + at0 + i] = sh.item[start + i];
+                __syncthreads();                                    // every wave has taken at0
+                if (tid == 0) list_heavy(a, sh.dense_used, base, at0, count, true);
+                __syncthreads();
+            }
+        }
+        if (!oversized || walk.depth < 0) break;
+    }
+}
+
+// ================================================================================================
+// heavy stripes
+// ================================================================================================
+
+// (stripe, 16 columns) per workgroup: the columns of a row are independent chains, so a hot entry spreads over D / 16
+// workgroups that never wait for each other and read every gradient once (64-byte pieces).  A lane holds two columns
+// of T consecutive updates; the 64 groups of eight lanes exchange their summaries by shuffles and, across waves,
+// through LDS, and take their steps from registers: 1024 updates per round.
+constexpr int kHeavyThreads = 512;
+constexpr int kHeavyWaves = kHeavyThreads / kWave;
+constexpr uint32_t kHeavyCols = 16;
+
+// gradient rows of a run's updates at, at + 1 (past its end: its last update's)
+__device__ __forceinline__ void heavy_indices(const u64 *run, uint32_t L, uint32_t at, uint32_t &i0, uint32_t &i1)
+{
+    i0 = (uint32_t)run[min(at, L - 1u)];
+    i1 = (uint32_t)run[min(at + 1u, L - 1u)];
+}
+
+// two columns of the run's updates at .. at + T - 1, zeros past its end
+template <int T>
+__device__ __forceinline__ void heavy_rows(float2 (&r)[T], const float *grads, uint32_t D, uint32_t col, bool live, uint32_t i0,
+                                           uint32_t i1, uint32_t lane, uint32_t at, uint32_t L)
+{
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+        const uint32_t idx = __shfl(u & 1 ? i1 : i0, (int)((lane & 56u) + u / 2), kWave);
+        r[u] = float2{0, 0};
+        if (live && at + u < L) r[u] = *(const float2 *)(grads + (size_t)idx * D + col);
+    }
+}
+
+template <int MODE, bool PARITY>
+__global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs a)
+{
+    constexpr bool kMomentum = MODE == kMomentumSeq;
+    constexpr int T = 16;
+    __shared__ double s_sum[2][kHeavyWaves][8][2];
+    __shared__ double s_dec[2][kHeavyWaves];
+    __shared__ uint32_t s_job;
+    if (a.hdr->batch_bad) return;
+    const uint32_t nh = a.hdr->n_heavy, D = a.geo.D, k = a.geo.k, lane = lane_id();
+    const uint32_t w = uniform(threadIdx.x / kWave), col_lane = lane & 7u, sub = w * 8u + lane / 8u;
+    const uint32_t ncg = (D + kHeavyCols - 1) / kHeavyCols;
+    const RuleParams rp = rule_params(a.geo);
+    // jobs are handed out as workgroups come free: their lengths differ by orders of magnitude
+    for (;;) {
+        if (threadIdx.x == 0) s_job = atomicAdd(&a.hdr->heavy_ticket, 1u);
+        __syncthreads();
+        const uint32_t job = uniform(s_job);
+        if (job >= nh * ncg) break;
+        const uint32_t h = job / ncg, cg = job - h * ncg;
+        const uint32_t start = a.heavy[2 * h], what = a.heavy[2 * h + 1], end = start + (what & ~kCounted);
+        const u64 *items = a.dense;
+        const uint32_t col = cg * kHeavyCols + 2u * col_lane;
+        const bool live = col < D;                                  // D is a multiple of 4: both columns or none
+        const uint32_t g = a.geo.dk.div(uniform(item_row(items[start])));
+        D2 pe = D2{0, 0}, pa = D2{0, 0};
+        if (PARITY && live) {
+            pe = widen2(*(const float2 *)(a.PE + (size_t)g * D + col));
+            pa = widen2(*(const float2 *)(a.PA + (size_t)g * D + col));
+        }
+        uint32_t buf = 0;
+        for (uint32_t p = start; p < end;) {
+            const uint32_t x = uniform(item_row(items[p]));
+            uint32_t lo = p, hi = end;                              // items[lo] has row x; hi: the first that has not
+            while (hi - lo > 1) {
+                const uint32_t step = (hi - lo + kWave - 1) / kWave, probe = lo + (lane + 1u) * step;
+                const uint32_t in = (uint32_t)__popcll(__ballot(probe < hi && item_row(items[min(probe, end - 1)]) == x));
+                const uint32_t out = lo + (in + 1u) * step;
+                lo += in * step;
+                if (in < (uint32_t)kWave && out < hi) hi = out;
+            }
+            const uint32_t L = hi - p;
+            float *erow = a.E + (size_t)x * D + col, *arow = a.A + (size_t)x * D + col;
+            float2 e = float2{0, 0}, a0 = float2{0, 0};
+            if (live) {
+                e = *(const float2 *)erow;
+                a0 = *(const float2 *)arow;
+            }
+            D2 state = start2<MODE>(widen2(a0)), acc = D2{0, 0};
+            // The rows of a round are asked for while the round before is computed, its indices a round earlier.  The
+            // eight lanes of a group fetch two of its T indices each.
+            float2 gr[T], nx[T];
+            uint32_t i0, i1;
+            heavy_indices(items + p, L, sub * T + 2u * col_lane, i0, i1);
+            heavy_rows<T>(nx, a.grads, D, col, live, i0, i1, lane, sub * T, L);
+            heavy_indices(items + p, L, 64u * T + sub * T + 2u * col_lane, i0, i1);
+            for (uint32_t r0 = 0; r0 < L; r0 += 64u * T, buf ^= 1u) {
+                const uint32_t off = r0 + sub * T;
+                const uint32_t cnt = off < L ? min((uint32_t)T, L - off) : 0u;
+#pragma unroll
+                for (int u = 0; u < T; ++u) gr[u] = nx[u];
+                if (r0 + 64u * T < L) {
+                    heavy_rows<T>(nx, a.grads, D, col, live, i0, i1, lane, off + 64u * T, L);
+                    heavy_indices(items + p, L, off + 128u * T + 2u * col_lane, i0, i1);
+                }
+                if (Rule<MODE>::combine) {                          // a sum: nothing to exchange before the run's end
+#pragma unroll
+                    for (int u = 0; u < T; ++u) {                   // zeros past the end of the run
+                        acc.x += (double)gr[u].x;
+                        acc.y += (double)gr[u].y;
+                    }
+                    continue;
+                }
+                D2 s = D2{0, 0};
+                double d = 1.0;
+#pragma unroll
+                for (int u = 0; u < T; ++u) {
+                    if ((uint32_t)u < cnt) {
+                        summary2<MODE>(s, gr[u], rp);
+                        if (kMomentum) d *= rp.mu;
+                    }
+                }
+                // inclusive scan over the wave's eight groups of the maps v -> d * v + s
+#pragma unroll
+                for (int by = 8; by < kWave; by <<= 1) {
+                    const double ox = __shfl_up(s.x, by, kWave), oy = __shfl_up(s.y, by, kWave);
+                    const double od = kMomentum ? __shfl_up(d, by, kWave) : 1.0;
+                    if (lane >= (uint32_t)by) {
+                        s.x = kMomentum ? fma(d, ox, s.x) : s.x + ox;
+                        s.y = kMomentum ? fma(d, oy, s.y) : s.y + oy;
+                        if (kMomentum) d *= od;
+                    }
+                }
+                if (lane >= 56u) {
+                    s_sum[buf][w][col_lane][0] = s.x;
+                    s_sum[buf][w][col_lane][1] = s.y;
+                    if (col_lane == 0) s_dec[buf][w] = d;
+                }
+                // what lies before this group inside the wave
+                D2 ex = D2{__shfl_up(s.x, 8, kWave), __shfl_up(s.y, 8, kWave)};
+                double ed = kMomentum ? __shfl_up(d, 8, kWave) : 1.0;
+                if (lane < 8u) {
+                    ex = D2{0, 0};
+                    ed = 1.0;
+                }
+                __syncthreads();
+                D2 mine = state;
+#pragma unroll
+                for (int v = 0; v < kHeavyWaves; ++v) {
+                    if ((uint32_t)v == w) mine = state;
+                    const double fx = s_sum[buf][v][col_lane][0], fy = s_sum[buf][v][col_lane][1];
+                    const double dv = kMomentum ? s_dec[buf][v] : 1.0;
+                    state.x = kMomentum ? fma(dv, state.x, fx) : state.x + fx;
+                    state.y = kMomentum ? fma(dv, state.y, fy) : state.y + fy;
+                }
+                mine.x = kMomentum ? fma(ed, mine.x, ex.x) : mine.x + ex.x;
+                mine.y = kMomentum ? fma(ed, mine.y, ex.y) : mine.y + ex.y;
+#pragma unroll
+                for (int u = 0; u < T; ++u) {
+                    if ((uint32_t)u < cnt) item2<MODE>(mine, acc, gr[u], rp);
+                }
+            }
+            {                                                       // sum of the steps over groups, then over waves
+#pragma unroll
+                for (int by = 8; by < kWave; by <<= 1) {
+                    acc.x += __shfl_xor(acc.x, by, kWave);
+                    acc.y += __shfl_xor(acc.y, by, kWave);
+                }
+                if (lane < 8u) {
+                    s_sum[buf][w][col_lane][0] = acc.x;
+                    s_sum[buf][w][col_lane][1] = acc.y;
+                }
+                __syncthreads();
+                acc = D2{0, 0};
+#pragma unroll
+                for (int v = 0; v < kHeavyWaves; ++v) {
+                    acc.x += s_sum[buf][v][col_lane][0];
+                    acc.y += s_sum[buf][v][col_lane][1];
+                }
+                buf ^= 1u;
+                if (Rule<MODE>::combine) {
+                    state = acc;
+                    acc = D2{0, 0};
+                }
+            }
+            const D2 e64 = widen2(e), a64 = widen2(a0);
+            finish2<MODE>(state, acc, a64, rp);
+            if (live && sub == 0) {
+                *(float2 *)erow = narrow2(D2{e64.x - acc.x, e64.y - acc.y});
+                *(float2 *)arow = narrow2(state);
+            }
+            pe.x -= acc.x;
+            pe.y -= acc.y;
+            pa.x += state.x - a64.x;
+            pa.y += state.y - a64.y;
+            if (cg == 0 && threadIdx.x == 0) {
+                if (L > kLongRun) {                                 // reported by ecrm_batch_stats
+                    atomicAdd(&a.hdr->n_long, 1u);
+                    atomicAdd(&a.hdr->n_long_items, (u64)L);
+                }
+                if (Rule<MODE>::combine && !(what & kCounted)) {
+                    atomicAdd(&a.load_data[a.geo.dS.mod(g + 1 + (x - g * k))], 1ull);
+                    if (a.load_parity) atomicAdd(&a.load_parity[a.geo.dS.mod(g)], 1ull);
+                }
+            }
+            p = hi;
+        }
+        if (PARITY && live && sub == 0) {
+            *(float2 *)(a.PE + (size_t)g * D + col) = narrow2(pe);
+            *(float2 *)(a.PA + (size_t)g * D + col) = narrow2(pa);
+        }
+        __syncthreads();                                            // s_sum and s_job are free for the next job
+    }
+}
+
+// ================================================================================================
+// host side
+// ================================================================================================
+
+template <int NC, int MODE>
+static void bucket_apply_for(const BucketArgs &a, bool parity, bool heavy, int cus, hipStream_t st)
+{
+    const dim3 grid(a.buckets + kHotBuckets), block(kBucketThreads);
+    const uint32_t most = a.n / kHeavyRunMin * ((a.geo.D + kHeavyCols - 1) / kHeavyCols);
+    const dim3 hgrid(most < (uint32_t)cus ? most : (uint32_t)cus), hblock(kHeavyThreads);
+    if (parity) {
+        hipLaunchKernelGGL((bucket_apply_kernel<NC, MODE, true>), grid, block, 0, st, a);
+        if (heavy) hipLaunchKernelGGL((heavy_stripes_kernel<MODE, true>), hgrid, hblock, 0, st, a);
+    } else {
+        hipLaunchKernelGGL((bucket_apply_kernel<NC, MODE, false>), grid, block, 0, st, a);
+        if (heavy) hipLaunchKernelGGL((heavy_stripes_kernel<MODE, false>), hgrid, hblock, 0, st, a);
+    }
+}
+
+void launch_bucket_partition(const BucketScratch &bs, Header *hdr, const Geometry &g, const RecoveryView &rv,
+                             const uint64_t *keys, uint32_t n, BatchSource src, bool clear_sticky, hipStream_t st)
+{
+    const BucketPlan p = bucket_plan(n);
+    PartitionArgs a;
+    a.keys = keys; a.items = bs.items; a.table = bs.table; a.tile_cnt = bs.tile_cnt; a.tile_bad = bs.tile_bad;
+    a.hdr = hdr; a.n = n; a.buckets = p.buckets; a.rows = g.rows;
+    a.count = (g.mode & 2u) ? 0u : 1u;               // the combined rules count per modified entry, later
+    a.clear_sticky = clear_sticky ? 1u : 0u;
+    a.packed = src == kWaitingUpdates ? 1u : 0u;
+    a.dk = g.dk; a.dS = g.dS; a.rv = rv;
+    const dim3 grid(p.tiles), block(kPartThreads);
+    switch (p.ipt) {
+        case 1: hipLaunchKernelGGL(bucket_partition_kernel<1>, grid, block, 0, st, a); break;
+        case 2: hipLaunchKernelGGL(bucket_partition_kernel<2>, grid, block, 0, st, a); break;
+        default: hipLaunchKernelGGL(bucket_partition_kernel<4>, grid, block, 0, st, a); break;
+    }
+}
+
+void launch_bucket_apply(const BucketScratch &bs, Header *hdr, const Geometry &g, float *E, float *A, float *PE, float *PA,
+                         unsigned long long *load_data, unsigned long long *load_parity, const uint64_t *keys,
+                         const float *grads, uint32_t n, BatchSource src, int cus, hipStream_t st)
+{
+    const BucketPlan p = bucket_plan(n);
+    BucketArgs a;
+    a.E = E; a.A = A; a.PE = PE; a.PA = PA; a.grads = grads; a.geo = g;
+    a.keys = keys; a.items = bs.items; a.tmp = bs.tmp; a.dense = bs.dense; a.table = bs.table;
+    a.tile_cnt = bs.tile_cnt; a.tile_bad = bs.tile_bad; a.heavy = bs.heavy; a.hdr = hdr;
+    a.load_data = load_data; a.load_parity = load_parity;
+    a.n = n; a.tile = p.ipt * kPartThreads; a.tiles = p.tiles; a.buckets = p.buckets;
+    a.packed = src == kWaitingUpdates ? 1u : 0u;
+    a.heavy_run = heavy_run(n);
+    const bool heavy = n >= kHeavyRunMin;
+    ECRM_DISPATCH(bucket_apply_for, a, PE != nullptr, heavy, cus, st);
+}
+
+}  // namespace ecrm

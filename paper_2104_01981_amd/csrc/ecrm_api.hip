@@ -15,6 +15,7 @@ struct Layout {
     size_t bytes;
     size_t off_cnt, off_keys[2], off_vals[2], off_hist, off_bintotal, off_long_slot, off_long_meta,
         off_piece_slot, off_partial, off_partial2, off_long_res, off_active;
+    size_t off_table, off_tile_cnt, off_tile_bad, off_tmp, off_heavy, off_hold_tiles;   // the bucket path's, over the others
 };
 
 // The caller's device arrays one update works on.
@@ -97,8 +98,43 @@ static Layout make_layout(uint32_t max_batch, uint32_t D, uint32_t S, bool has_p
     l.off_partial = take((size_t)l.max_pieces * D * sizeof(double));
     l.off_partial2 = take(has_partial2 ? (size_t)l.max_pieces * D * sizeof(double) : 0);
     l.off_long_res = take((size_t)l.max_slots * 2 * D * sizeof(double));
-    l.bytes = off;
+    // The bucket path's arrays over the general path's from the block histograms on (its items and its dense list take
+    // the two pairs of sort buffers): a call takes one path or the other.
+    const size_t general_end = off;
+    off = l.off_hist;
+    const uint32_t nb = max_batch < kBucketMaxBatch ? max_batch : kBucketMaxBatch;
+    size_t table = 0, tiles = 0;
+    for (uint32_t ipt = 1; ipt <= 4; ipt *= 2) {        // the largest batch of each tile size
+        const uint32_t most = ipt * kPartThreads * kMaxTiles, n_ipt = most < nb ? most : nb;
+        const BucketPlan p = bucket_plan(n_ipt);
+        const size_t entries = (size_t)p.tiles * (p.buckets + kHotBuckets + 1);
+        if (entries > table) table = entries;
+        if (p.tiles > tiles) tiles = p.tiles;
+    }
+    const uint32_t servers = S < kBucketMaxServers ? S : kBucketMaxServers;
+    l.off_table = take(table * 2);
+    l.off_tile_cnt = take(tiles * 2 * servers * 4);
+    l.off_tile_bad = take(tiles * 4);
+    l.off_tmp = take((size_t)nb * 8);
+    l.off_heavy = take(((size_t)nb / kHeavyRunMin + 64) * 2 * 4);
+    l.off_hold_tiles = take(((size_t)nb / kHoldTile + 1) * 4);
+    l.bytes = off > general_end ? off : general_end;
     return l;
+}
+
+static BucketScratch carve_buckets(const Layout &l, const Scratch &s)
+{
+    char *b = (char *)s.hdr;
+    BucketScratch r;
+    r.items = (unsigned long long *)s.keys[0];       // spans keys[0] and keys[1]
+    r.dense = (unsigned long long *)s.vals[0];
+    r.table = (uint16_t *)(b + l.off_table);
+    r.tile_cnt = (uint32_t *)(b + l.off_tile_cnt);
+    r.tile_bad = (uint32_t *)(b + l.off_tile_bad);
+    r.tmp = (unsigned long long *)(b + l.off_tmp);
+    r.heavy = (uint32_t *)(b + l.off_heavy);
+    r.hold_tiles = (uint32_t *)(b + l.off_hold_tiles);
+    return r;
 }
 
 static Scratch carve(const Layout &l, void *base, bool has_partial2)
@@ -278,6 +314,15 @@ int ecrm_route(ecrm_ctx *c, const uint64_t *keys, uint64_t n, uint64_t *stripe, 
     return check_launch();
 }
 
+// Which way a batch goes.  Up to kBucketMaxBatch updates the buckets' three launches beat the sort's and the chains'
+// thirteen to twenty; gradient propagation groups the batch twice, and a caller that has set the chain tiers' knob wants
+// those tiers: both take the general path, as do more servers than the per-tile counts are kept for.
+static bool takes_buckets(const ecrm_ctx *c, uint32_t n)
+{
+    return n <= kBucketMaxBatch && c->cfg.propagation != ECRM_PROP_GRADIENT && c->cfg.servers <= kBucketMaxServers &&
+           !c->tune_mid_min_rows;
+}
+
 // One batch through the whole pipeline, on tables t with scratch s (laid out by l).  During a recovery,
 // held-back items are appended to buf[target] (and the key space gets one more value, `rows`, for them
 // to sort behind the rest).
@@ -290,6 +335,21 @@ static int run_update(ecrm_ctx *c, const Tables &t, const Scratch &s, const Layo
     hipEvent_t *ev = nullptr;
     if (c->profiling && c->ev_calls < ECRM_PROFILE_MAX_CALLS) ev = c->ev[c->ev_calls++];
 
+    if (takes_buckets(c, n32)) {
+        const BucketScratch bs = carve_buckets(l, s);
+        const bool diff = c->cfg.propagation == ECRM_PROP_DIFFERENCE;
+        if (ev) (void)hipEventRecord(ev[0], st);
+        launch_bucket_partition(bs, s.hdr, c->geo, rv, keys, n32, src, clear_sticky, st);
+        if (rv.active || src == kWaitingUpdates)
+            launch_hold_back(s.hdr, bs.hold_tiles, bs.tile_bad, bucket_plan(n32).tiles, c->geo, rv, keys, grads, n32, src,
+                             c->hb, c->buf_cur, st);
+        if (ev) (void)hipEventRecord(ev[1], st);
+        if (ev) (void)hipEventRecord(ev[2], st);
+        launch_bucket_apply(bs, s.hdr, c->geo, t.E, t.A, diff ? t.PE : nullptr, diff ? t.PA : nullptr, t.load_data,
+                            diff ? t.load_parity : nullptr, keys, grads, n32, src, c->cus, st);
+        if (ev) (void)hipEventRecord(ev[3], st);
+        return check_launch();
+    }
     launch_reset(s, c->geo.S, n32, clear_sticky, src, st);
     if (ev) (void)hipEventRecord(ev[0], st);
     int key_bits = c->key_bits;
@@ -301,7 +361,7 @@ static int run_update(ecrm_ctx *c, const Tables &t, const Scratch &s, const Layo
     uint32_t *sk = nullptr, *si = nullptr;
     launch_sort(s, c->geo, rv, keys, n32, n_dev, src, key_bits, false, true, &sk, &si, st);
     if (rv.active || src == kWaitingUpdates)
-        launch_hold_back(s, c->geo, rv, keys, grads, n32, src, c->hb, c->buf_cur, st);
+        launch_hold_back(s.hdr, s.long_slot, nullptr, 0, c->geo, rv, keys, grads, n32, src, c->hb, c->buf_cur, st);
     if (ev) (void)hipEventRecord(ev[1], st);
     launch_chains(s, c->geo, lg, t.A, grads, sk, si, n32, l.max_slots, l.max_pieces, c->cus, st);
     launch_active_groups(s, c->geo, sk, n32, st);
@@ -316,6 +376,7 @@ static int run_update(ecrm_ctx *c, const Tables &t, const Scratch &s, const Layo
         // arrival order.
         Geometry gp = c->geo;
         gp.k = 1;
+        gp.dk = make_divider(1);
         int bits = 1;
         while (bits < 32 && (1ull << bits) < c->cfg.rows / c->cfg.k) ++bits;
         if (ev) (void)hipEventRecord(ev[3], st);

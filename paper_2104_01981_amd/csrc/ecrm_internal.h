@@ -50,6 +50,36 @@ constexpr uint32_t kMidClasses = 7;  // the runs are listed by length (x2 per cl
 constexpr uint32_t kChunk = ECRM_CHUNK;   // sorted positions whose stripes one wave owns per grid-stride step (<= 63)
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
+// ---- batches that go through buckets instead of the sort (buckets.hip) ---------------------------
+constexpr uint32_t kBucketMaxBatch = 1u << 19;
+constexpr int kBucketThreads = 256;
+constexpr int kPartThreads = 512;            // of the partition: 8 waves, 1, 2 or 4 updates per thread
+constexpr uint32_t kMaxBuckets = 4096;
+constexpr uint32_t kHotBuckets = 256;        // more, for the entries of hot stripes
+constexpr uint32_t kMaxTiles = 256;          // one thread per tile when a bucket is collected
+constexpr uint32_t kBucketCap = 1024;        // items of a bucket that are sorted in LDS
+constexpr uint32_t kBucketMaxServers = 64;   // per-tile load counts are kept for at most this many servers
+constexpr uint32_t kBucketChunk = 8;         // sorted positions whose stripes a wave owns at a time
+// A stripe with a run this long leaves its bucket and is split over the columns (heavy_stripes): one wave walks ~10 updates
+// per us, the split takes ~5 us per 1024 but a workgroup for every 16 columns, so that there must not be many of them:
+// at most 2048 runs of n / 2048.
+constexpr uint32_t kHeavyRunMin = 128;
+inline uint32_t heavy_run(uint32_t n) { return n / 2048u > kHeavyRunMin ? n / 2048u : kHeavyRunMin; }
+struct BucketPlan { uint32_t ipt, tiles, buckets; };
+// Tiles as small as kMaxTiles of them allow.  Buckets of 16 updates while that gives no more than the 1024 workgroups that
+// are resident at once -- the fewer updates a wave walks one after the other the better --, of 64 from then on, of more
+// when the largest number of buckets is reached.
+inline BucketPlan bucket_plan(uint32_t n)
+{
+    BucketPlan p;
+    p.ipt = n <= 1u * kPartThreads * kMaxTiles ? 1u : n <= 2u * kPartThreads * kMaxTiles ? 2u : 4u;
+    p.tiles = (n + p.ipt * kPartThreads - 1) / (p.ipt * kPartThreads);
+    const uint32_t fine = n / 16u < 1024u ? n / 16u : 1024u, most = n / 64u > fine ? n / 64u : fine;
+    p.buckets = most < 1u ? 1u : most > kMaxBuckets ? kMaxBuckets : most;
+    return p;
+}
+static_assert(kBucketMaxBatch <= 4u * kPartThreads * kMaxTiles, "the plan's largest tile covers the largest batch");
+
 // ---- device-side header at the start of the scratch buffer --------------------------------------
 struct Header {
     uint32_t err_sticky;   // set once any batch carried a key >= rows
@@ -69,7 +99,9 @@ struct Header {
     uint32_t n_mid[kMidClasses];   // long rows of this batch that one workgroup walks, by length class
     uint32_t mid_ticket;   // next of them to be handed out (cleared by reset)
     uint32_t n_active;     // groups of sorted positions the apply kernel has work for (cleared by reset)
-    uint32_t pad[42];
+    uint32_t n_heavy;      // stripes the bucket kernel left to heavy_stripes (cleared by the partition)
+    uint32_t heavy_ticket; // next of its jobs to be handed out (cleared by the partition)
+    uint32_t pad[40];
 };
 static_assert(sizeof(Header) == 256, "header is one 256-byte block");
 
@@ -88,6 +120,16 @@ struct Scratch {           // device pointers carved out of the caller's scratch
     double *partial;               // [max_pieces][D]
     double *partial2;              // [max_pieces][D], momentum SGD only (else null)
     double *long_res;              // [max_slots][2][D]: sum of steps, final accumulator
+};
+
+// The bucket path's arrays: they lie where the general path keeps its own (a call takes one path or the other).
+struct BucketScratch {
+    unsigned long long *items, *dense, *tmp;   // [n] each
+    uint16_t *table;               // [tiles][buckets + kHotBuckets + 1]
+    uint32_t *tile_cnt;            // [tiles][2 * S]
+    uint32_t *tile_bad;            // [tiles]
+    uint32_t *heavy;               // [2 * (n / kHeavyRunMin + 64)]
+    uint32_t *hold_tiles;          // tile counts of the hold-back kernels
 };
 
 // Division of 32-bit numbers by a divisor fixed for the life of a context (k, S, stripes per chunk):
@@ -197,9 +239,16 @@ void launch_reset(const Scratch &s, uint32_t S, uint32_t n, bool clear_sticky, B
 void launch_sort(const Scratch &s, const Geometry &g, const RecoveryView &rv, const uint64_t *keys, uint32_t n,
                  const uint32_t *n_dev, BatchSource src, int key_bits, bool by_stripe, bool count_servers,
                  uint32_t **sorted_keys, uint32_t **sorted_vals, hipStream_t st);
-void launch_hold_back(const Scratch &s, const Geometry &g, const RecoveryView &rv, const uint64_t *keys,
-                      const float *grads, uint32_t n, BatchSource src, const HoldBuffer &hb, uint32_t cur,
-                      hipStream_t st);
+// tile_count: scratch for the tiles' counts; tile_bad (may be null): per partition tile, whether it carried a bad key
+void launch_hold_back(Header *hdr, uint32_t *tile_count, const uint32_t *tile_bad, uint32_t bad_tiles, const Geometry &g,
+                      const RecoveryView &rv, const uint64_t *keys, const float *grads, uint32_t n, BatchSource src,
+                      const HoldBuffer &hb, uint32_t cur, hipStream_t st);
+constexpr uint32_t kHoldTile = 2048;
+void launch_bucket_partition(const BucketScratch &bs, Header *hdr, const Geometry &g, const RecoveryView &rv,
+                             const uint64_t *keys, uint32_t n, BatchSource src, bool clear_sticky, hipStream_t st);
+void launch_bucket_apply(const BucketScratch &bs, Header *hdr, const Geometry &g, float *E, float *A, float *PE, float *PA,
+                         unsigned long long *load_data, unsigned long long *load_parity, const uint64_t *keys,
+                         const float *grads, uint32_t n, BatchSource src, int cus, hipStream_t st);
 void launch_recover_range(const Geometry &g, float *E, float *A, float *PE, float *PA, uint32_t server,
                           uint32_t g_lo, uint32_t g_hi, int grid_blocks, hipStream_t st);
 void launch_clear_buffer(const Scratch &s, hipStream_t st);

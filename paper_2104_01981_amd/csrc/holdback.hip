@@ -12,7 +12,7 @@ namespace ecrm {
 
 constexpr int kHoldThreads = 256;
 constexpr int kHoldIpt = 8;                        // items per thread
-constexpr int kHoldTile = kHoldThreads * kHoldIpt;
+static_assert(kHoldTile == kHoldThreads * kHoldIpt, "a tile is what a workgroup looks at");
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -59,10 +59,14 @@ __global__ __launch_bounds__(kHoldThreads) void hold_count_kernel(const uint64_t
 
 // pass 2 (one block): exclusive scan of the tile counts; totals and the capacity check
 __global__ __launch_bounds__(1024) void hold_scan_kernel(uint32_t *tile_count, uint32_t ntiles, Header *hdr, uint32_t n,
-                                                         const uint32_t *n_dev, uint32_t packed, uint32_t buf_cap)
+                                                         const uint32_t *n_dev, uint32_t packed, uint32_t buf_cap,
+                                                         const uint32_t *tile_bad, uint32_t bad_tiles)
 {
     __shared__ uint32_t s_w[16];
     __shared__ uint32_t s_carry;
+    bool bad = false;                              // a key out of range anywhere: nothing of the batch may be appended
+    for (uint32_t t = threadIdx.x; t < bad_tiles; t += 1024) bad |= tile_bad[t] != 0;
+    bad = __syncthreads_or(bad);
     if (n_dev) n = min(n, *n_dev);
     if (threadIdx.x == 0) s_carry = 0;
     __syncthreads();
@@ -91,6 +95,10 @@ __global__ __launch_bounds__(1024) void hold_scan_kernel(uint32_t *tile_count, u
         const uint32_t held = s_carry;
         hdr->n_held = held;
         hdr->n_valid = n - held;
+        if (bad) {
+            hdr->batch_bad = 1;
+            hdr->err_sticky |= 1u;
+        }
         // no room: the batch is rejected as a whole (a replay only ever shrinks the list)
         if (!packed && (unsigned long long)hdr->buf_count + held > buf_cap) {
             hdr->batch_bad = 1;
@@ -201,22 +209,22 @@ __global__ void hold_commit_kernel(Header *hdr, uint32_t packed)
     }
 }
 
-void launch_hold_back(const Scratch &s, const Geometry &g, const RecoveryView &rv, const uint64_t *keys,
-                      const float *grads, uint32_t n, BatchSource src, const HoldBuffer &hb, uint32_t cur,
-                      hipStream_t st)
+void launch_hold_back(Header *hdr, uint32_t *tile_count, const uint32_t *tile_bad, uint32_t bad_tiles, const Geometry &g,
+                      const RecoveryView &rv, const uint64_t *keys, const float *grads, uint32_t n, BatchSource src,
+                      const HoldBuffer &hb, uint32_t cur, hipStream_t st)
 {
     const uint32_t packed = src == kWaitingUpdates ? 1u : 0u;
-    const uint32_t *n_dev = packed ? &s.hdr->n_batch : nullptr;
+    const uint32_t *n_dev = packed ? &hdr->n_batch : nullptr;
     const uint32_t ntiles = (n + kHoldTile - 1) / kHoldTile;
-    uint32_t *tile_count = s.long_slot;            // free until the chain kernels run
     // a caller's batch appends to the list in use; a replay reads it and builds the other one
     unsigned long long *list_out = packed ? hb.list[cur ^ 1u] : hb.list[cur];
     hipLaunchKernelGGL(hold_count_kernel, dim3(ntiles), dim3(kHoldThreads), 0, st, keys, n, n_dev, g.rows, g.dk, g.dS, rv,
                        packed, tile_count);
-    hipLaunchKernelGGL(hold_scan_kernel, dim3(1), dim3(1024), 0, st, tile_count, ntiles, s.hdr, n, n_dev, packed, hb.cap);
+    hipLaunchKernelGGL(hold_scan_kernel, dim3(1), dim3(1024), 0, st, tile_count, ntiles, hdr, n, n_dev, packed, hb.cap,
+                       tile_bad, bad_tiles);
     hipLaunchKernelGGL(hold_scatter_kernel, dim3(ntiles), dim3(kHoldThreads), 0, st, keys, grads, n, n_dev, g.rows, g.D, g.dk,
-                       g.dS, rv, packed, tile_count, s.hdr, list_out, hb.rows, hb.free_list);
-    hipLaunchKernelGGL(hold_commit_kernel, dim3(1), dim3(64), 0, st, s.hdr, packed);
+                       g.dS, rv, packed, tile_count, hdr, list_out, hb.rows, hb.free_list);
+    hipLaunchKernelGGL(hold_commit_kernel, dim3(1), dim3(64), 0, st, hdr, packed);
 }
 
 }  // namespace ecrm

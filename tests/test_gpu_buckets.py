@@ -1,0 +1,121 @@
+"""The bucket path (batches of up to 2^19 updates) against the oracle where it can go wrong: runs around the 64 updates
+above which a workgroup's waves share a stripe, stripes around the 512 updates above which one of an oversized bucket is
+split over the columns, buckets around the 1024 items LDS takes, tiles and bucket counts at their edges, every rule,
+row widths with and without a remainder, with and without parities.  Tolerance: that of Case.compare (fp64 chains
+rounded once on both sides; a re-association moves a value across a rounding boundary with probability ~1e-6)."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+from ecrm_case import Case, grads_for, log
+
+pytestmark = pytest.mark.gpu
+
+
+def _mix32(g):
+    m = 0xFFFFFFFF
+    g = g.astype(np.uint64)
+    g ^= g >> np.uint64(16)
+    g = (g * np.uint64(0x9E3779B1)) & np.uint64(m)
+    g ^= g >> np.uint64(15)
+    g = (g * np.uint64(0xD1B54A33)) & np.uint64(m)
+    return g ^ (g >> np.uint64(16))
+
+
+def _check(c, keys, seed, what):
+    for call in range(2):
+        c.update(keys if call == 0 else keys[::-1].copy(), grads_for(seed, call * len(keys), len(keys), c.D))
+    counts = np.bincount(keys.astype(np.int64))
+    stats = c.ctx.batch_stats()
+    assert stats["long_rows"] == int((counts > 1024).sum())
+    assert stats["long_items"] == int(counts[counts > 1024].sum())
+    log(what, len(keys), c.compare(what))
+    if c.propagation == 0:
+        c.check_invariant()
+
+
+RULES = [(0, 0), (1, 0), (0, 1), (1, 1)]
+
+
+@pytest.mark.parametrize("opt,comb", RULES)
+@pytest.mark.parametrize("D,k,S", [(128, 4, 5), (36, 10, 11), (200, 2, 64), (16, 1, 2), (512, 3, 7)])
+def test_runs_and_stripes_around_the_thresholds(D, k, S, opt, comb):
+    rng = np.random.default_rng(11)
+    R = k * 3000
+    lens = [1, 2, 15, 16, 17, 47, 48, 49, 56, 57, 63, 64, 65, 127, 128, 129, 255, 511, 512, 513, 1023, 1024, 1025, 1500, 3000]
+    stripes = rng.permutation(R // k)[:2 * len(lens)]
+    keys = []
+    for i, m in enumerate(lens):
+        keys.append(np.full(m, stripes[2 * i] * k + i % k))                 # one entry has all of a stripe's updates
+        keys.append(stripes[2 * i + 1] * k + rng.integers(0, k, m))         # ... or its entries share them
+    keys.append(rng.integers(0, R, 6000))
+    keys = rng.permutation(np.concatenate(keys)).astype(np.uint64)
+    c = Case(R, D, k, S, max_batch=len(keys), seed=43, optimizer=opt, momentum=0.9, combine=comb)
+    _check(c, keys, 43, f"thresholds {(D, k, S, opt, comb)}")
+
+
+@pytest.mark.parametrize("prop", [0, 2])
+@pytest.mark.parametrize("R,D,k,S,n", [
+    (4 * 5000, 128, 4, 5, 2049), (4 * 5000, 128, 4, 5, 32 * 512 + 1), (4 * 100000, 8, 4, 5, (1 << 17) + 1),
+    (4 * 60000, 8, 4, 5, 1 << 18), (4 * 60000, 4, 4, 5, (1 << 18) + 1), (2 * 60000, 12, 2, 3, (1 << 19) - 1),
+    (63 * 30, 1024, 63, 64, 5000), (7, 64, 7, 8, 4000), (1 << 20, 128, 4, 5, 33)])
+def test_sizes_at_the_edges_of_the_plan(R, D, k, S, n, prop):
+    c = Case(R, D, k, S, max_batch=n, seed=47, propagation=prop)
+    _check(c, si.uniform_keys(47, 0, n, R), 47, f"plan {(R, D, k, S, n, prop)}")
+
+
+@pytest.mark.parametrize("opt,comb", RULES)
+def test_one_bucket_gets_everything(opt, comb):
+    """Keys chosen so that their stripes fall into one bucket of the plan: more stripes than the LDS table of an
+    oversized bucket holds, so the bucket is worked off in parts, light and heavy stripes in each."""
+    D, k, S, R = 20, 4, 5, 4 * (1 << 20)
+    n = 40000
+    buckets = n // 32
+    g = np.arange(R // k, dtype=np.uint64)
+    mine = g[(_mix32(g) * np.uint64(buckets)) >> np.uint64(32) == 7]
+    assert len(mine) > 800
+    rng = np.random.default_rng(3)
+    stripes = np.concatenate([rng.permutation(mine)[:800].repeat(40), np.full(n - 32000 - 2000, mine[0]), np.full(2000, mine[-1])])
+    keys = rng.permutation(stripes * np.uint64(k) + rng.integers(0, k, n).astype(np.uint64))
+    c = Case(R, D, k, S, max_batch=n, seed=53, optimizer=opt, momentum=0.9, combine=comb)
+    _check(c, keys, 53, f"one bucket {(opt, comb)}")
+
+
+def test_two_runs_are_bit_identical():
+    n, R = 60000, 4 * 20000
+    keys = si.zipf_keys(5, 0, n, 1 << 16, 1 << 16)
+    outs = []
+    for _ in range(2):
+        c = Case(R, 128, 4, 5, n, seed=3)
+        c.ctx.update(torch.from_numpy(keys.view(np.int64)).cuda(), grads_for(3, 0, n, 128))
+        assert c.ctx.status() == 0
+        outs.append([t.clone() for t in (c.E, c.A, c.PE, c.PA, c.ld, c.lp)])
+    for x, y in zip(*outs):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("prop", [0, 2])
+@pytest.mark.parametrize("opt,comb", RULES)
+@pytest.mark.parametrize("R,D,k,S,n", [(4 * 900, 128, 4, 5, 30000), (10 * 3000, 68, 10, 13, 9001), (2 * 77, 256, 2, 64, 2000),
+                                       (3 * 50, 300, 3, 5, 1 << 16)])
+def test_same_as_the_general_path(R, D, k, S, n, opt, comb, prop):
+    """The bucket path against the sort and the chain tiers (the knob sends a batch there): two fp64 chains in arrival
+    order, each rounded once, so the tables agree but for re-association across a rounding boundary (~1e-6 of the
+    elements, one ulp); the counters are equal."""
+    keys = si.zipf_keys(59, 0, n, 1 << 14, 1 << 14) % np.uint64(R)
+    kt, g = torch.from_numpy(keys.view(np.int64)).cuda(), grads_for(59, 0, n, D)
+    out = []
+    for general in (False, True):
+        c = Case(R, D, k, S, max_batch=n, seed=59, optimizer=opt, momentum=0.9, combine=comb, propagation=prop)
+        if general:
+            c.ctx.tune(1, 0xFFFFFFFF)              # ECRM_TUNE_MID_MIN_ROWS: the chain tiers, no one-workgroup walk
+        c.ctx.update(kt, g)
+        assert c.ctx.status() == 0
+        out.append((c.E, c.A, c.PE, c.PA, c.ld, c.lp))
+    for a, b in zip(*out):
+        if a.dtype == torch.float32:
+            assert int((a != b).sum()) <= 1e-4 * a.numel() + 2
+            assert torch.allclose(a, b, rtol=1e-5, atol=1e-9)
+        else:
+            assert torch.equal(a, b)
