@@ -26,6 +26,10 @@ namespace ecrm {
 constexpr uint32_t kGroupsPerTicket = 8;
 constexpr int kListThreads = 256;
 constexpr uint32_t kListMaxTiles = 4;
+// A stripe of more updates than this goes to the end of the list, which the apply kernel takes first.  64 costs the list
+// kernel time and gains the apply kernel nothing; 1024 leaves half of the gain (skewed batch of 2^24:
+// 2363, 2266 and 2264 us with 1024, 256 and 64).
+constexpr uint32_t kSlowStripe = 256;
 
 // Lists the groups of kChunk sorted positions in which a stripe begins: the groups the apply kernel has work
 // for.  All others lie inside runs -- every group of a long row's positions but its first -- and while
@@ -34,19 +38,22 @@ constexpr uint32_t kListMaxTiles = 4;
 // tiles of kListThreads groups: a tile's positions are read coalesced, all loads of a thread in flight
 // together, and their stripe numbers staged in LDS; a position whose stripe differs from its left neighbour's
 // marks its group; the marked groups are appended to the list with one counter update per block (the list
-// ascends inside a block's part; the order of the parts does not matter).
+// ascends inside a block's part; the order of the parts does not matter).  Groups with a long stripe are listed from
+// the array's end (hdr->n_heavy of them).
 __global__ __launch_bounds__(kListThreads) void active_groups_kernel(const uint32_t *sk, uint32_t n, Header *hdr,
-                                                                     Divider dk, uint32_t tiles, uint32_t *active)
+                                                                     Divider dk, uint32_t tiles, uint32_t *active, uint32_t cap)
 {
     constexpr uint32_t kTilePos = kListThreads * kChunk;                   // positions of a tile
     constexpr uint32_t kNone = 0xFFFFFFFFu, kEdge = 0xFFFFFFFEu;           // no stripe has these numbers
     __shared__ uint32_t s_q[1 + kTilePos];                                 // [0]: the position left of the tile
     __shared__ uint32_t s_mark[kListMaxTiles][kListThreads];
     __shared__ uint32_t s_cnt[kListMaxTiles][kListThreads / kWave];
-    __shared__ uint32_t s_base;
+    __shared__ uint32_t s_base, s_nslow, s_slow_base;
     if (hdr->batch_bad) return;
     n = min(n, hdr->n_valid);
     const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
+    uint32_t slow_mask = 0;                                                // bit t: group (t, tid) has a long stripe
+    if (tid == 0) s_nslow = 0;
     const uint32_t g0 = blockIdx.x * tiles * (uint32_t)kListThreads;       // the block's first group
     for (uint32_t t = 0; t < tiles; ++t) {
         const uint32_t p_lo = (g0 + t * (uint32_t)kListThreads) * kChunk;  // < n + 2^16: no overflow, n <= 2^31
@@ -56,6 +63,10 @@ __global__ __launch_bounds__(kListThreads) void active_groups_kernel(const uint3
             const uint32_t p = p_lo + i * (uint32_t)kListThreads + tid;
             key[i] = p < n ? sk[p] : kNone;
         }
+        // the stripe at the group's last position is the last that begins in it, if one does; the others end inside it
+        const uint32_t rel_last = tid * kChunk + kChunk - 1u, far = rel_last + kSlowStripe;
+        uint32_t far_key = kNone;
+        if (far >= kTilePos && p_lo + far < n) far_key = sk[p_lo + far];
         if (tid == 0) s_q[0] = (p_lo > 0 && p_lo <= n) ? dk.div(sk[p_lo - 1]) : kEdge;
 #pragma unroll
         for (uint32_t i = 0; i < kChunk; ++i)
@@ -68,16 +79,20 @@ __global__ __launch_bounds__(kListThreads) void active_groups_kernel(const uint3
             const uint32_t q = s_q[1 + rel];
             if (q != kNone && q != s_q[rel]) s_mark[t][rel / kChunk] = 1u;  // every writer writes 1
         }
+        const uint32_t q_far = far < kTilePos ? s_q[1 + far] : far_key == kNone ? kNone : dk.div(far_key);
+        if (q_far != kNone && q_far == s_q[1 + rel_last]) slow_mask |= 1u << t;
         __syncthreads();                                                   // s_q is free for the next tile
     }
     // compaction of the block's marks: per wave and tile a count, then one place in the list for the block
     uint32_t mine_mask = 0;                                                // bit t: group (t, tid) is marked
     for (uint32_t t = 0; t < tiles; ++t) {
-        const bool mine = s_mark[t][tid] != 0;
+        const bool marked = s_mark[t][tid] != 0, mine = marked && !((slow_mask >> t) & 1u);
+        if (!marked) slow_mask &= ~(1u << t);
         const unsigned long long bal = __ballot(mine);
         if (mine) mine_mask |= 1u << t;
         if (lane == 0) s_cnt[t][w] = (uint32_t)__popcll(bal);
     }
+    const uint32_t slow_at = slow_mask ? atomicAdd(&s_nslow, (uint32_t)__popc(slow_mask)) : 0u;
     __syncthreads();
     uint32_t total = 0, before[kListMaxTiles];
 #pragma unroll
@@ -93,7 +108,10 @@ __global__ __launch_bounds__(kListThreads) void active_groups_kernel(const uint3
         }
     }
     if (tid == 0) s_base = total ? atomicAdd(&hdr->n_active, total) : 0u;
+    if (tid == kWave) s_slow_base = s_nslow ? atomicAdd(&hdr->n_heavy, s_nslow) : 0u;
     __syncthreads();
+    for (uint32_t at = s_slow_base + slow_at; slow_mask; slow_mask &= slow_mask - 1u, ++at)
+        active[cap - 1u - at] = g0 + (uint32_t)__builtin_ctz(slow_mask) * (uint32_t)kListThreads + tid;
 #pragma unroll
     for (uint32_t t = 0; t < kListMaxTiles; ++t) {
         const bool mine = (mine_mask >> t) & 1u;                           // never set for t >= tiles
@@ -106,8 +124,10 @@ struct ApplyArgs {
     float *E, *A, *PE, *PA;
     const float *grads;
     const uint32_t *sk, *si;
-    const uint32_t *active;      // groups of kChunk sorted positions in which a stripe begins (hdr->n_active of them);
-                                 // null: no list was made, every group is looked at
+    const uint32_t *active;      // groups of sorted positions in which a stripe begins, hdr->n_active from the front and
+                                 // hdr->n_heavy, with a long stripe, from the end; null: no list was made, every group
+                                 // is looked at
+    uint32_t groups;             // room in the list
     const uint32_t *long_slot, *long_len;
     const double *long_res;
     Header *hdr;
@@ -383,45 +403,103 @@ __device__ __forceinline__ void apply_window(const ApplyArgs &a, uint32_t wkey, 
     }
 }
 
+// The groups of kChunk sorted positions in which a stripe begins (active_groups_kernel lists them) are handed out through a
+// counter instead of by a fixed stride: the work per group varies (runs, long stripes), and with a fixed stride the
+// slowest wave set the kernel's time (6.50 -> 6.22 ms).  One ticket covers kGroupsPerTicket listed groups: one group per
+// ticket made the counter itself the bottleneck (12.5 ms), 64 per ticket is too coarse again.  A wave's first ticket is
+// its own number (no counter traffic at start-up, which is all a small batch consists of); later ones come from the
+// counter.  Small batches get smaller tickets, so that every wave has work.  Groups with a long stripe come first, one to
+// a ticket: one wave walks such a stripe for up to 150 us, and where it came late the others were idle meanwhile (apply
+// kernels of Zipf and half-Zipf batches: 617 -> 535, 2226 -> 2110, 2390 -> 2263, 7770 -> 7672 us).
+struct GroupTickets {
+    uint32_t nslow, nact, per, ticket;
+    bool first;
+    __device__ __forceinline__ void init(const ApplyArgs &a, uint32_t n)
+    {
+        const uint32_t ngroups = (n + kChunk - 1) / kChunk;
+        nslow = a.active ? min(a.hdr->n_heavy, ngroups) : 0u;
+        nact = a.active ? min(a.hdr->n_active, ngroups) : ngroups;   // no list (a small batch): every group
+        per = min(kGroupsPerTicket, max(1u, nact / (4u * wave_count())));
+        ticket = wave_id();
+        first = true;
+    }
+    // the next ticket's groups: lane i < left holds the i-th
+    __device__ __forceinline__ bool next(const ApplyArgs &a, uint32_t &listed, uint32_t &left)
+    {
+        const uint32_t lane = lane_id(), all = nslow + (nact + per - 1u) / per;
+        if (!first) {
+            if (all <= wave_count()) return false;
+            uint32_t t = 0;
+            if (lane == 0) t = atomicAdd(&a.hdr->apply_ticket, 1u);
+            ticket = wave_count() + uniform(t);
+        }
+        first = false;
+        if (ticket >= all) return false;
+        if (ticket < nslow) {
+            left = 1u;
+            listed = a.active[a.groups - 1u - ticket];
+        } else {
+            const uint32_t at = (ticket - nslow) * per;
+            left = min(per, nact - at);
+            listed = lane < left ? (a.active ? a.active[at + lane] : at + lane) : 0u;
+        }
+        return true;
+    }
+};
+
+// the batch is valid: publish its per-server counts
+__device__ __forceinline__ void publish_counts(const ApplyArgs &a)
+{
+    if (blockIdx.x != 0) return;
+    const uint32_t S = a.geo.S;
+    for (uint32_t i = threadIdx.x; i < S; i += blockDim.x) {
+        if (a.load_data) a.load_data[i] += a.cnt[i];
+        if (a.load_parity) a.load_parity[i] += a.cnt[S + i];
+    }
+}
+
+// What a wave finds in the 64 positions from a group's first: heads of rows and of stripes, and the range of the stripes
+// that begin in the group and end in the window.
+struct Window {
+    unsigned long long rowheads, stripeheads;
+    uint32_t first, end, last;
+    bool any, last_inside;       // any: a stripe begins in the group; else nothing below holds.  The last one may go on.
+};
+__device__ __forceinline__ Window look_at(uint32_t wkey, uint32_t prevk, uint32_t p0, uint32_t n, uint32_t k)
+{
+    const uint32_t lane = lane_id();
+    Window w;
+    uint32_t leftk = __shfl_up(wkey, 1, kWave);
+    if (lane == 0) leftk = prevk;
+    const bool valid = wkey != kNoKey;
+    const bool rh = !valid || leftk == kNoKey || leftk != wkey;    // lanes past n end the last run
+    const bool sh = valid && (leftk == kNoKey || leftk / k != wkey / k);
+    w.rowheads = __ballot(rh);
+    w.stripeheads = __ballot(sh);
+    const uint32_t vend = min((uint32_t)kWave, n - p0);
+    const unsigned long long owned = w.stripeheads & bits_below(kChunk);
+    w.any = owned != 0;
+    w.first = w.any ? lowest_bit(owned) : 0u;
+    w.last = w.any ? 63u - (uint32_t)__builtin_clzll(owned) : 0u;
+    const unsigned long long after = w.stripeheads & ~bits_below(w.last + 1);
+    w.last_inside = after != 0ull || p0 + kWave >= n;
+    w.end = w.last_inside ? (after ? lowest_bit(after) : vend) : w.last;
+    return w;
+}
+
 template <int NC, int MODE, bool PARITY>
 __device__ __forceinline__ void apply_stripes_body(const ApplyArgs &a)
 {
     if (a.hdr->batch_bad) return;
-    // the batch is valid: publish its per-server counts
-    if (blockIdx.x == 0) {
-        const uint32_t S = a.geo.S;
-        for (uint32_t i = threadIdx.x; i < S; i += blockDim.x) {
-            if (a.load_data) a.load_data[i] += a.cnt[i];
-            if (a.load_parity) a.load_parity[i] += a.cnt[S + i];
-        }
-    }
+    publish_counts(a);
     const uint32_t n = min(a.n, a.hdr->n_valid), k = a.geo.k, lane = lane_id();
-    // The groups of kChunk sorted positions in which a stripe begins (active_groups_kernel lists them) are handed
-    // out through a counter instead of by a fixed stride: the work per group varies (runs, long stripes), and
-    // with a fixed stride the slowest wave set the kernel's time (6.50 -> 6.22 ms).  One ticket covers
-    // kGroupsPerTicket listed groups: one group per ticket made the counter itself the bottleneck (12.5 ms), 64
-    // per ticket is too coarse again.  A wave's first ticket is its own number (no counter traffic at start-up,
-    // which is all a small batch consists of); later ones come from the counter.  Small batches get smaller
-    // tickets, so that every wave has work.
-    const uint32_t ngroups = (n + kChunk - 1) / kChunk;
-    const uint32_t nact = a.active ? min(a.hdr->n_active, ngroups) : ngroups;   // no list (a small batch): every group
-    const uint32_t per_ticket = min(kGroupsPerTicket, max(1u, nact / (4u * wave_count())));
-    const bool one_ticket_each = (nact + per_ticket - 1) / per_ticket <= wave_count();
-    uint32_t at = wave_id() * per_ticket;              // the ticket's place in the list
+    GroupTickets tickets;
+    tickets.init(a, n);
     uint32_t left = 0, taken = 0, listed = 0;          // groups left in the ticket, taken from it; lane i: its group i
     uint32_t pf_ch = 0xFFFFFFFFu, pf_key = 0, pf_idx = 0, pf_prev = 0;
-    for (bool first_ticket = true;;) {
+    for (;;) {
         if (left == 0) {
-            if (!first_ticket) {
-                if (one_ticket_each) break;
-                uint32_t t = 0;
-                if (lane == 0) t = atomicAdd(&a.hdr->apply_ticket, 1u);
-                at = (wave_count() + uniform(t)) * per_ticket;
-            }
-            first_ticket = false;
-            if (at >= nact) break;
-            left = min(per_ticket, nact - at);
-            listed = lane < left ? (a.active ? a.active[at + lane] : at + lane) : 0u;
+            if (!tickets.next(a, listed, left)) break;
             taken = 0;
         }
         const uint32_t ch = from_lane(listed, taken);
@@ -447,24 +525,11 @@ __device__ __forceinline__ void apply_stripes_body(const ApplyArgs &a)
             pf_idx = q0 + lane < n ? a.si[q0 + lane] : 0u;
             pf_prev = q0 ? a.sk[q0 - 1] : kNoKey;
         }
-        uint32_t leftk = __shfl_up(wkey, 1, kWave);
-        if (lane == 0) leftk = prevk;
-        const bool valid = wkey != kNoKey;
-        const bool rh = !valid || leftk == kNoKey || leftk != wkey;    // lanes past n end the last run
-        const bool sh = valid && (leftk == kNoKey || leftk / k != wkey / k);
-        const unsigned long long rowheads = __ballot(rh);
-        const unsigned long long stripeheads = __ballot(sh);
-        const uint32_t vend = min((uint32_t)kWave, n - p0);
-        const unsigned long long owned = stripeheads & bits_below(kChunk);
-        if (!owned) continue;
-        const uint32_t first = lowest_bit(owned);
-        const uint32_t last = 63u - (uint32_t)__builtin_clzll(owned);
-        const unsigned long long after = stripeheads & ~bits_below(last + 1);
-        const bool last_inside = after != 0ull || p0 + kWave >= n;
-        const uint32_t end = last_inside ? (after ? lowest_bit(after) : vend) : last;
+        const Window w = look_at(wkey, prevk, p0, n, k);
+        if (!w.any) continue;
         for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
-            apply_window<NC, MODE, PARITY>(a, wkey, widx, rowheads, stripeheads, first, end, cb);
-            if (!last_inside) apply_stripe_general<NC, MODE, PARITY>(a, n, p0 + last, cb);
+            apply_window<NC, MODE, PARITY>(a, wkey, widx, w.rowheads, w.stripeheads, w.first, w.end, cb);
+            if (!w.last_inside) apply_stripe_general<NC, MODE, PARITY>(a, n, p0 + w.last, cb);
         }
     }
 }
@@ -682,8 +747,8 @@ void launch_active_groups(const Scratch &s, const Geometry &g, const uint32_t *s
     // a large batch: several tiles per block, so that the list's counter is not updated at its own pace
     const uint32_t tiles = groups > 64u * kListThreads ? kListMaxTiles : 1u;
     const uint32_t per_block = tiles * kListThreads;
-    hipLaunchKernelGGL(active_groups_kernel, dim3((groups + per_block - 1) / per_block), dim3(kListThreads), 0, st, sk, n,
-                       s.hdr, make_divider(g.k), tiles, s.active);
+    const dim3 grid((groups + per_block - 1) / per_block), block(kListThreads);
+    hipLaunchKernelGGL(active_groups_kernel, grid, block, 0, st, sk, n, s.hdr, make_divider(g.k), tiles, s.active, groups);
 }
 
 void launch_apply(const Scratch &s, const Geometry &g, const LaunchGrids &lg, float *E, float *A, float *PE, float *PA,
@@ -696,6 +761,7 @@ void launch_apply(const Scratch &s, const Geometry &g, const LaunchGrids &lg, fl
     a.grads = grads; a.sk = sk; a.si = si;
     a.long_slot = s.long_slot; a.long_len = s.long_len; a.long_res = s.long_res;
     a.active = lists_groups(n) ? s.active : nullptr;
+    a.groups = (n + kChunk - 1) / kChunk;
     a.hdr = s.hdr; a.cnt = s.cnt;
     a.load_data = load_data; a.load_parity = load_parity;
     a.n = n; a.geo = g;
