@@ -1096,6 +1096,8 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
             pe = widen2(*(const float2 *)(a.PE + (size_t)g * D + col));
             pa = widen2(*(const float2 *)(a.PA + (size_t)g * D + col));
         }
+        // Half of s_sum for the next exchange.  It changes with every exchange and with nothing else: a half is written again
+        // only behind the barrier of the exchange in between, which every wave passes after it has read the half.
         uint32_t buf = 0;
         for (uint32_t p = start; p < end;) {
             const uint32_t x = uniform(item_row(items[p]));
@@ -1122,7 +1124,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
             heavy_indices(items + p, L, sub * T + 2u * col_lane, i0, i1);
             heavy_rows<T>(nx, a.grads, D, col, live, i0, i1, lane, sub * T, L);
             heavy_indices(items + p, L, 64u * T + sub * T + 2u * col_lane, i0, i1);
-            for (uint32_t r0 = 0; r0 < L; r0 += 64u * T, buf ^= 1u) {
+            for (uint32_t r0 = 0; r0 < L; r0 += 64u * T) {
                 const uint32_t off = r0 + sub * T;
                 const uint32_t cnt = off < L ? min((uint32_t)T, L - off) : 0u;
 #pragma unroll
@@ -1187,6 +1189,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
                 for (int u = 0; u < T; ++u) {
                     if ((uint32_t)u < cnt) item2<MODE>(mine, acc, gr[u], rp);
                 }
+                buf ^= 1u;
             }
             {                                                       // sum of the steps over groups, then over waves
 #pragma unroll

@@ -119,3 +119,29 @@ def test_same_as_the_general_path(R, D, k, S, n, opt, comb, prop):
             assert torch.allclose(a, b, rtol=1e-5, atol=1e-9)
         else:
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("opt,comb", RULES)
+@pytest.mark.parametrize("R,D,n_stripes", [(10 * 64, 16, 40), (10 * 64, 132, 12)])
+def test_heavy_stripes_of_many_entries(R, D, n_stripes, opt, comb):
+    """Heavy stripes all of whose ten entries were hit, so that a workgroup exchanges sums for one entry right after the
+    other: entries of one, two and three rounds of 1024 updates in changing order.  Against the oracle, and twice from
+    the same start, which has to give the same bits."""
+    k, S = 10, 11
+    rng = np.random.default_rng(71)
+    lens = [130, 1024, 200, 1025, 150, 2049, 131, 257, 2048, 300]
+    keys = [np.full(lens[(j + 3 * s) % k], s * k + j) for s in range(n_stripes) for j in range(k)]
+    keys = rng.permutation(np.concatenate(keys + [rng.integers(0, R, 999)])).astype(np.uint64)
+    c = Case(R, D, k, S, max_batch=len(keys), seed=67, optimizer=opt, momentum=0.9, combine=comb)
+    kt, g = torch.from_numpy(keys.view(np.int64)).cuda(), grads_for(67, 0, len(keys), D)
+    tables = (c.E, c.A, c.PE, c.PA, c.ld, c.lp)
+    start, runs = [t.clone() for t in tables], []
+    for _ in range(2):
+        for t, s in zip(tables, start):
+            t.copy_(s)
+        c.ctx.update(kt, g)
+        runs.append([t.clone() for t in tables])
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
+    c.oracle_update(keys, g)
+    log("heavy stripes of many entries", (R, D, opt, comb), c.compare("heavy stripes of many entries"))
