@@ -188,17 +188,21 @@ __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uin
                 }
             }
             // One branch for the step, none for its updates, whose square roots then overlap: a missing one is a zero
-            // gradient, which leaves sums alone; momentum takes it with a decay of one and a rate of zero.
+            // gradient, which leaves sums and steps alone.  Momentum takes no such step: its chain is kept as it was (a
+            // rate of zero would make NaN of an infinite velocity).
             if (cnt[s]) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    RuleParams ru = rp;
-                    if (MODE == kMomentumSeq && (uint32_t)u >= cnt[s]) {
-                        ru.mu = 1.0;
-                        ru.lr = 0.0;
-                    }
+                    const bool there = MODE != kMomentumSeq || (uint32_t)u < cnt[s];
 #pragma unroll
-                    for (int i = 0; i < NC; ++i) item2<MODE>(w.G[i], w.acc[i], l[s].g[u][i], ru);
+                    for (int i = 0; i < NC; ++i) {
+                        D2 G = w.G[i], acc = w.acc[i];
+                        item2<MODE>(G, acc, l[s].g[u][i], rp);
+                        w.G[i].x = there ? G.x : w.G[i].x;
+                        w.G[i].y = there ? G.y : w.G[i].y;
+                        w.acc[i].x = there ? acc.x : w.acc[i].x;
+                        w.acc[i].y = there ? acc.y : w.acc[i].y;
+                    }
                 }
             }
             if (PARITY) {
