@@ -89,24 +89,25 @@ struct StepLoads {
 };
 
 // The chain of the entry in work and the parity rows of its stripe; carried from window to window where a stripe or a
-// run does not end inside one.  All zero between entries (and the parities between stripes): rows are added to it as
-// they arrive, zeros for steps that bring none, so that taking a set of loads in needs no branch.
+// run does not end inside one.  A step that brings no rows leaves those of the entry and the stripe in work as they are:
+// taking a set of loads in is a select and needs no branch (added to zeros instead, a stored -0.0 became +0.0).
 template <int NC>
 struct Walk {
     D2 G[NC], acc[NC], pe[NC], pa[NC];
     float2 e[NC], a[NC];
-    __device__ __forceinline__ void clear_entry()
+    __device__ __forceinline__ void begin()
     {
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            G[i] = acc[i] = D2{0, 0};
+            pe[i] = pa[i] = D2{0, 0};
             e[i] = a[i] = float2{0, 0};
         }
+        clear_chain();
     }
-    __device__ __forceinline__ void clear_stripe()
+    __device__ __forceinline__ void clear_chain()
     {
 #pragma unroll
-        for (int i = 0; i < NC; ++i) pe[i] = pa[i] = D2{0, 0};
+        for (int i = 0; i < NC; ++i) G[i] = acc[i] = D2{0, 0};
     }
 };
 
@@ -176,15 +177,16 @@ __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uin
     while (cnt[0]) {
 #pragma unroll
         for (int s = 0; s < Q; ++s) {
+            const bool head = cnt[s] && ((rowheads >> at[s]) & 1ull), opens = cnt[s] && ((stripeheads >> at[s]) & 1ull);
 #pragma unroll
             for (int i = 0; i < NC; ++i) {
-                w.a[i].x += l[s].a[i].x;
-                w.a[i].y += l[s].a[i].y;
-                w.e[i].x += l[s].e[i].x;
-                w.e[i].y += l[s].e[i].y;
+                w.a[i].x = head ? l[s].a[i].x : w.a[i].x;
+                w.a[i].y = head ? l[s].a[i].y : w.a[i].y;
+                w.e[i].x = head ? l[s].e[i].x : w.e[i].x;
+                w.e[i].y = head ? l[s].e[i].y : w.e[i].y;
                 if (!Rule<MODE>::combine) {
-                    w.G[i].x += (double)l[s].a[i].x;
-                    w.G[i].y += (double)l[s].a[i].y;
+                    w.G[i].x = head ? (double)l[s].a[i].x : w.G[i].x;
+                    w.G[i].y = head ? (double)l[s].a[i].y : w.G[i].y;
                 }
             }
             // One branch for the step, none for its updates, whose square roots then overlap: a missing one is a zero
@@ -208,10 +210,10 @@ __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uin
             if (PARITY) {
 #pragma unroll
                 for (int i = 0; i < NC; ++i) {
-                    w.pe[i].x += (double)l[s].pe[i].x;
-                    w.pe[i].y += (double)l[s].pe[i].y;
-                    w.pa[i].x += (double)l[s].pa[i].x;
-                    w.pa[i].y += (double)l[s].pa[i].y;
+                    w.pe[i].x = opens ? (double)l[s].pe[i].x : w.pe[i].x;
+                    w.pe[i].y = opens ? (double)l[s].pe[i].y : w.pe[i].y;
+                    w.pa[i].x = opens ? (double)l[s].pa[i].x : w.pa[i].x;
+                    w.pa[i].y = opens ? (double)l[s].pa[i].y : w.pa[i].y;
                 }
             }
             // The set is taken in before its registers' next loads are asked for (moved up, those would go to other
@@ -252,9 +254,8 @@ __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uin
                         st2(perow, i, narrow2(w.pe[i]));
                         st2(parow, i, narrow2(w.pa[i]));
                     }
-                    w.clear_stripe();
                 }
-                w.clear_entry();
+                w.clear_chain();
             }
         }
     }
@@ -593,8 +594,7 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
         }
         for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
             Walk<NC> walk;
-            walk.clear_entry();
-            walk.clear_stripe();
+            walk.begin();
             // the window, then the windows of the stripe that goes on behind it
             uint32_t wk = wkey, wi = widx, from = first, to = end, p = p0;
             u64 rh = rowheads, sth = stripeheads;
@@ -1145,7 +1145,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
                     }
                     continue;
                 }
-                D2 s = D2{0, 0};
+                D2 s = D2{-0.0, -0.0};                              // the neutral summand: +0.0 would take a -0.0's sign
                 double d = 1.0;
 #pragma unroll
                 for (int u = 0; u < T; ++u) {
@@ -1174,7 +1174,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
                 D2 ex = D2{__shfl_up(s.x, 8, kWave), __shfl_up(s.y, 8, kWave)};
                 double ed = kMomentum ? __shfl_up(d, 8, kWave) : 1.0;
                 if (lane < 8u) {
-                    ex = D2{0, 0};
+                    ex = D2{-0.0, -0.0};
                     ed = 1.0;
                 }
                 __syncthreads();

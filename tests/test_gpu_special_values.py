@@ -87,3 +87,23 @@ def test_infinities(opt, comb, mu, D, general):
             A[:, 5] = -np.inf                       # an Adagrad accumulator is a sum of squares: never infinite before NaN
     for name, got, w in run(D, opt, comb, mu, general, spoil):
         assert np.isinf(w).any()
+
+
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("D", [8, 260])
+@pytest.mark.parametrize("opt,comb,mu", RULES)
+def test_signed_zeros(opt, comb, mu, D, general):
+    def spoil(tables, keys, grads):
+        E, A, PE, PA = tables
+        E[:, :4] = -0.0
+        PE[:, :3] = -0.0
+        PA[:, :2] = -0.0
+        grads[:, 0] = 0.0
+        grads[:, 1:3] = -0.0
+        if opt == 1:
+            A[:, :3] = -0.0
+    for name, got, w in run(D, opt, comb, mu, general, spoil):
+        zero = w == 0
+        assert zero.any() or (name == "A" and opt == 0)       # Adagrad's accumulators start above zero
+        np.testing.assert_array_equal(got[zero], 0.0, err_msg=name)
+        np.testing.assert_array_equal(np.signbit(got[zero]), np.signbit(w[zero]), err_msg=name)
