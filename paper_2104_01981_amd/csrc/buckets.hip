@@ -1050,6 +1050,11 @@ constexpr int kHeavyThreads = 512;
 constexpr int kHeavyWaves = kHeavyThreads / kWave;
 constexpr uint32_t kHeavyCols = 16;
 
+// The decay over a number of updates, a power of mu.  One that underflows is kept at the smallest normal number unless mu
+// itself is zero: a decay of zero would make NaN of an infinite velocity, which the rule keeps infinite.  What it adds to
+// a finite one is below 1e-269, nothing in 32 bits.
+__device__ __forceinline__ double decay(double power, double mu) { return mu > 0.0 ? fmax(power, 2.2250738585072014e-308) : power; }
+
 // gradient rows of a run's updates at, at + 1 (past its end: its last update's)
 __device__ __forceinline__ void heavy_indices(const u64 *run, uint32_t L, uint32_t at, uint32_t &i0, uint32_t &i1)
 {
@@ -1151,7 +1156,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
                 for (int u = 0; u < T; ++u) {
                     if ((uint32_t)u < cnt) {
                         summary2<MODE>(s, gr[u], rp);
-                        if (kMomentum) d *= rp.mu;
+                        if (kMomentum) d = decay(d * rp.mu, rp.mu);
                     }
                 }
                 // inclusive scan over the wave's eight groups of the maps v -> d * v + s
@@ -1162,7 +1167,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
                     if (lane >= (uint32_t)by) {
                         s.x = kMomentum ? fma(d, ox, s.x) : s.x + ox;
                         s.y = kMomentum ? fma(d, oy, s.y) : s.y + oy;
-                        if (kMomentum) d *= od;
+                        if (kMomentum) d = decay(d * od, rp.mu);
                     }
                 }
                 if (lane >= 56u) {

@@ -107,3 +107,14 @@ def test_signed_zeros(opt, comb, mu, D, general):
         assert zero.any() or (name == "A" and opt == 0)       # Adagrad's accumulators start above zero
         np.testing.assert_array_equal(got[zero], 0.0, err_msg=name)
         np.testing.assert_array_equal(np.signbit(got[zero]), np.signbit(w[zero]), err_msg=name)
+
+
+@pytest.mark.parametrize("mu", [0.001, 1e-20, 0.0])
+def test_infinite_velocity_under_a_strong_decay(mu):
+    """Heavy stripes: the decay over 128 updates underflows in 64 bits, but the rule keeps an infinite velocity infinite
+    (with mu = 0 it makes NaN of it at the next update)."""
+    def spoil(tables, keys, grads):
+        tables[1][:, 0] = -np.inf
+        grads[middle(keys), 1] = np.inf
+    for name, got, w in run(16, 1, 0, mu, False, spoil):
+        assert np.isinf(w).any() or mu == 0
