@@ -23,20 +23,8 @@ typedef unsigned long long u64;
 
 constexpr int kBucketWaves = kBucketThreads / kWave;
 constexpr int kPartWaves = kPartThreads / kWave;
-constexpr uint32_t kHotRun = 256;       // stripes with about this many updates or more are looked for in a sample
 constexpr uint32_t kHeavyMin = 512;     // a stripe of an oversized bucket with more updates goes to heavy_stripes
 static_assert(kHeavyMin >= kHeavyRunMin, "the list of heavy stripes has room for one per kHeavyRunMin updates");
-
-// Bijective mix of a stripe number: the high part selects the bucket, the low bits split a bucket further.
-__device__ __forceinline__ uint32_t mix32(uint32_t g)
-{
-    g ^= g >> 16;
-    g *= 0x9E3779B1u;
-    g ^= g >> 15;
-    g *= 0xD1B54A33u;
-    return g ^ (g >> 16);
-}
-__device__ __forceinline__ uint32_t bucket_of(uint32_t g, uint32_t buckets) { return __umulhi(mix32(g), buckets); }
 
 __device__ __forceinline__ uint32_t item_row(u64 it) { return (uint32_t)(it >> 32); }
 
@@ -289,14 +277,11 @@ __device__ __forceinline__ bool takes_part(const PartitionArgs &a, uint64_t k64,
     return true;
 }
 
-// Stripes that a sample of the batch -- kSample keys at fixed distances, the same for every workgroup -- holds so often
-// that they have about kHotRun updates or more.  Their entries get buckets of their own behind the others, so that
-// neither the sorting of a bucket nor the walk of a workgroup ever sees a hot run; what the sample misses (less than
-// 0.4 % of the batch each) is found in its bucket.  The choice depends on nothing but the sample: every workgroup
-// makes the same one.
-// A batch of up to kSmallSampled updates gets along with half the sample: what it misses is at most a bucket's length.
-constexpr uint32_t kSample = 1024, kSampleSlots = 2048, kHotCand = 256, kHotMax = 64, kHotSlots = 256;
-constexpr uint32_t kSmallSampled = kBucketCap * (kSample / 2) / 4;
+// Stripes that the sample of the batch (bucket_plan.h), the same for every workgroup, holds so often that they are likely
+// to have kHotRun updates or more.  Their entries get buckets of their own behind the others, so that neither the sorting
+// of a bucket nor the walk of a workgroup sees a hot run; a stripe that the sample misses is found in its bucket.  The
+// choice depends on nothing but the sample: every workgroup makes the same one.
+constexpr uint32_t kSampleSlots = 2048, kHotCand = 256, kHotMax = 64, kHotSlots = 256;
 
 struct SampleShared {
     uint32_t g[kSampleSlots], c[kSampleSlots];
@@ -310,8 +295,7 @@ struct HotShared {
 __device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n, SampleShared &t, HotShared &hot)
 {
     const uint32_t tid = threadIdx.x;
-    const uint32_t sample = n <= kSmallSampled ? kSample / 2 : kSample;
-    const uint32_t least = max(4u, (sample * kHotRun + n - 1u) / n), cap = min(kHotMax, kHotBuckets / a.dk.d);
+    const uint32_t sample = 1u << sample_bits(n), least = hot_hits(n), cap = min(kHotMax, kHotBuckets / a.dk.d);
     for (uint32_t i = tid; i < kSampleSlots; i += kPartThreads) {
         t.g[i] = kNoKey;
         t.c[i] = 0;
@@ -322,7 +306,7 @@ __device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n,
     uint64_t key[kSample / kPartThreads];
 #pragma unroll
     for (uint32_t r = 0; r < kSample / kPartThreads; ++r)
-        key[r] = r * kPartThreads < sample ? a.keys[((uint64_t)(r * kPartThreads + tid) * n) / sample] : 0u;
+        key[r] = r * kPartThreads < sample ? a.keys[sample_position(r * kPartThreads + tid, n)] : 0u;
 #pragma unroll
     for (uint32_t r = 0; r < kSample / kPartThreads; ++r) {
         uint32_t x, g;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bucket_plan.h"
 #include "ecrm.h"
 
 namespace ecrm {
@@ -49,36 +50,6 @@ constexpr uint32_t kMidClasses = 7;  // the runs are listed by length (x2 per cl
 #endif
 constexpr uint32_t kChunk = ECRM_CHUNK;   // sorted positions whose stripes one wave owns per grid-stride step (<= 63)
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
-
-// ---- batches that go through buckets instead of the sort (buckets.hip) ---------------------------
-constexpr uint32_t kBucketMaxBatch = 1u << 19;
-constexpr int kBucketThreads = 256;
-constexpr int kPartThreads = 512;            // of the partition: 8 waves, 1, 2 or 4 updates per thread
-constexpr uint32_t kMaxBuckets = 4096;
-constexpr uint32_t kHotBuckets = 256;        // more, for the entries of hot stripes
-constexpr uint32_t kMaxTiles = 256;          // one thread per tile when a bucket is collected
-constexpr uint32_t kBucketCap = 1024;        // items of a bucket that are sorted in LDS
-constexpr uint32_t kBucketMaxServers = 64;   // per-tile load counts are kept for at most this many servers
-constexpr uint32_t kBucketChunk = 8;         // sorted positions whose stripes a wave owns at a time
-// A stripe with a run this long leaves its bucket and is split over the columns (heavy_stripes): one wave walks ~10 updates
-// per us, the split takes ~5 us per 1024 but a workgroup for every 16 columns, so that there must not be many of them:
-// at most 2048 runs of n / 2048.
-constexpr uint32_t kHeavyRunMin = 128;
-inline uint32_t heavy_run(uint32_t n) { return n / 2048u > kHeavyRunMin ? n / 2048u : kHeavyRunMin; }
-struct BucketPlan { uint32_t ipt, tiles, buckets; };
-// Tiles as small as kMaxTiles of them allow.  Buckets of 16 updates while that gives no more than the 1024 workgroups that
-// are resident at once -- the fewer updates a wave walks one after the other the better --, of 64 from then on, of more
-// when the largest number of buckets is reached.
-inline BucketPlan bucket_plan(uint32_t n)
-{
-    BucketPlan p;
-    p.ipt = n <= 1u * kPartThreads * kMaxTiles ? 1u : n <= 2u * kPartThreads * kMaxTiles ? 2u : 4u;
-    p.tiles = (n + p.ipt * kPartThreads - 1) / (p.ipt * kPartThreads);
-    const uint32_t fine = n / 16u < 1024u ? n / 16u : 1024u, most = n / 64u > fine ? n / 64u : fine;
-    p.buckets = most < 1u ? 1u : most > kMaxBuckets ? kMaxBuckets : most;
-    return p;
-}
-static_assert(kBucketMaxBatch <= 4u * kPartThreads * kMaxTiles, "the plan's largest tile covers the largest batch");
 
 // ---- device-side header at the start of the scratch buffer --------------------------------------
 struct Header {

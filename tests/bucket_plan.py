@@ -1,0 +1,79 @@
+"""The library's own plan of a batch that goes through buckets, and its sample for hot stripes: csrc/bucket_plan.h compiled
+for the host, so that no test has to repeat its formulas."""
+from __future__ import annotations
+
+import ctypes as C
+import os
+import subprocess
+import tempfile
+
+import numpy as np
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2104_01981_amd", "csrc")
+SOURCE = """
+#include "bucket_plan.h"
+using namespace ecrm;
+extern "C" {
+uint32_t plan_buckets(uint32_t n) { return bucket_plan(n).buckets; }
+uint32_t plan_heavy_run(uint32_t n) { return heavy_run(n); }
+uint32_t plan_bucket_cap() { return kBucketCap; }
+uint32_t plan_hot_run() { return kHotRun; }
+uint32_t plan_hot_hits(uint32_t n) { return hot_hits(n); }
+uint32_t plan_sample(uint32_t n, uint32_t *at)
+{
+    for (uint32_t i = 0; i < 1u << sample_bits(n); ++i) at[i] = sample_position(i, n);
+    return 1u << sample_bits(n);
+}
+void plan_mix(uint32_t *g, uint32_t m) { for (uint32_t i = 0; i < m; ++i) g[i] = mix32(g[i]); }
+}
+"""
+_lib = None
+
+
+def lib():
+    global _lib
+    if _lib is None:
+        with tempfile.TemporaryDirectory() as tmp:
+            src, out = os.path.join(tmp, "plan.cpp"), os.path.join(tmp, "plan.so")
+            with open(src, "w") as f:
+                f.write(SOURCE)
+            subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-I", CSRC, src, "-o", out])
+            _lib = C.CDLL(out)
+    return _lib
+
+
+def buckets(n):
+    return int(lib().plan_buckets(C.c_uint32(n)))
+
+
+def heavy_run(n):
+    return int(lib().plan_heavy_run(C.c_uint32(n)))
+
+
+def bucket_cap():
+    return int(lib().plan_bucket_cap())
+
+
+def hot_run():
+    return int(lib().plan_hot_run())
+
+
+def mix(stripes):
+    g = np.ascontiguousarray(stripes, np.uint32).copy()
+    lib().plan_mix(g.ctypes.data_as(C.POINTER(C.c_uint32)), C.c_uint32(len(g)))
+    return g
+
+
+def bucket_of(stripes, n):
+    return (mix(stripes).astype(np.uint64) * np.uint64(buckets(n))) >> np.uint64(32)
+
+
+def sample_positions(n):
+    at = np.empty(1024, np.uint32)
+    return at[:lib().plan_sample(C.c_uint32(n), at.ctypes.data_as(C.POINTER(C.c_uint32)))].astype(np.int64)
+
+
+def hot_stripes(keys, k):
+    """The stripes that the partition takes for hot (before it keeps the most frequent ones of too many)."""
+    g, hits = np.unique(np.asarray(keys, np.int64)[sample_positions(len(keys))] // k, return_counts=True)
+    return g[hits >= int(lib().plan_hot_hits(C.c_uint32(len(keys))))]
