@@ -912,15 +912,15 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
 {
     __shared__ BucketShared sh;
     const uint32_t tid = threadIdx.x, b = blockIdx.x, B = a.buckets + kHotBuckets, S = a.geo.S, k = a.geo.k;
-    const bool hot = b >= a.buckets, hot_head = hot && (b - a.buckets) % k == 0 && b + k <= B;   // an entry of a hot stripe, its first
-    bool key_bad = false;
+    bool hot = b >= a.buckets, key_bad = false;                     // hot: an entry of a hot stripe, the member-th
+    const uint32_t member = hot ? (b - a.buckets) % k : 0u;
     uint32_t from = 0, len = 0, stripe_len = 0;
     if (tid < a.tiles) {
         const uint16_t *row = a.table + (size_t)tid * (B + 1) + b;
         key_bad = a.tile_bad[tid] != 0;
         from = tid * a.tile + row[0];
         len = (uint32_t)row[1] - row[0];
-        if (hot_head) stripe_len = (uint32_t)row[k] - row[0];
+        if (hot && b - member + k <= B) stripe_len = (uint32_t)row[k - member] - row[-(int)member];
     }
     const bool full = a.hdr->batch_bad != 0;                        // the recovery buffer could not take its part
     key_bad = __syncthreads_or(key_bad);
@@ -932,6 +932,20 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
         return;
     }
     uint32_t m;
+    if (hot) {
+        bucket_excl_scan(stripe_len, sh.wave, m);
+        if (m < kHotRun) {
+            // no stripe, or one that the sample took for hot by chance (a few hits out of a segment each): its entries'
+            // buckets lie side by side in every tile, so the first workgroup takes them as one ordinary bucket
+            if (member != 0 || m == 0) return;
+            hot = false;
+            len = stripe_len;
+        } else if (member == 0) {
+            uint32_t start;
+            bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, start);
+            if (tid == 0) list_heavy(a, sh.dense_used, start, 0, m, false);
+        }
+    }
     const uint32_t at = bucket_excl_scan(len, sh.wave, m);
     if (!Rule<MODE>::combine && b == 0) {                           // the batch is valid: publish its per-server counts
         for (uint32_t i = tid; i < 2 * S; i += kBucketThreads) sh.list.srv[i] = 0;
@@ -944,15 +958,6 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
         for (uint32_t i = tid; i < 2 * S; i += kBucketThreads) {
             u64 *to = i < S ? a.load_data : a.load_parity;
             if (to) to[i < S ? i : i - S] += sh.list.srv[i];
-        }
-    }
-    if (hot_head) {
-        uint32_t count;
-        bucket_excl_scan(stripe_len, sh.wave, count);
-        if (count) {
-            uint32_t start;
-            bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, start);
-            if (tid == 0) list_heavy(a, sh.dense_used, start, 0, count, false);
         }
     }
     if (m == 0) return;

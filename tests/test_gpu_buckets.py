@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+import bucket_plan as bp
 import synth_inputs as si
 from ecrm_case import Case, grads_for, log
 
@@ -145,3 +146,24 @@ def test_heavy_stripes_of_many_entries(R, D, n_stripes, opt, comb):
         assert torch.equal(a, b)
     c.oracle_update(keys, g)
     log("heavy stripes of many entries", (R, D, opt, comb), c.compare("heavy stripes of many entries"))
+
+
+@pytest.mark.parametrize("opt,comb", RULES)
+@pytest.mark.parametrize("n,D,k,S", [(8192, 36, 4, 5), (70001, 128, 10, 11), (200000, 12, 1, 2)])
+def test_stripes_taken_for_hot_by_chance(n, D, k, S, opt, comb):
+    """Stripes that fill just as many sampled positions as make them hot, and hold fewer, as many and more updates in all than
+    the 256 below which they are given back to the ordinary buckets; one whose updates are all of one member."""
+    rng = np.random.default_rng(n)
+    R = k * (n // 8)
+    at, hits = bp.sample_positions(n), int(bp.lib().plan_hot_hits(n))
+    keys = rng.integers(k * 16, R, n)
+    off = rng.permutation(np.setdiff1d(np.arange(n), at))
+    at = rng.permutation(at)
+    totals = [hits, hits + 1, 100, 128, 200, bp.hot_run() - 1, bp.hot_run(), bp.hot_run() + 1, 300]
+    for g, total in enumerate(totals):
+        mine, at, off = np.concatenate([at[:hits], off[:total - hits]]), at[hits:], off[total - hits:]
+        keys[mine] = g * k + (k - 1 if g % 3 == 2 else rng.integers(0, k, total))
+    assert set(range(len(totals))) <= set(bp.hot_stripes(keys, k).tolist())
+    assert (np.bincount(keys // k)[:len(totals)] == totals).all()
+    c = Case(R, D, k, S, max_batch=n, seed=73, optimizer=opt, momentum=0.9, combine=comb)
+    _check(c, keys.astype(np.uint64), 73, f"hot by chance {(n, opt, comb)}")
