@@ -1074,6 +1074,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
     __shared__ uint32_t s_job;
     if (a.hdr->batch_bad) return;
     const uint32_t nh = a.hdr->n_heavy, D = a.geo.D, k = a.geo.k, lane = lane_id();
+    if (nh == 0) return;
     const uint32_t w = uniform(threadIdx.x / kWave), col_lane = lane & 7u, sub = w * 8u + lane / 8u;
     const uint32_t ncg = (D + kHeavyCols - 1) / kHeavyCols;
     const RuleParams rp = rule_params(a.geo);
