@@ -23,8 +23,8 @@ typedef unsigned long long u64;
 
 constexpr int kBucketWaves = kBucketThreads / kWave;
 constexpr int kPartWaves = kPartThreads / kWave;
-constexpr uint32_t kHeavyMin = 512;     // a stripe of an oversized bucket with more updates goes to heavy_stripes
-static_assert(kHeavyMin >= kHeavyRunMin, "the list of heavy stripes has room for one per kHeavyRunMin updates");
+constexpr uint32_t kLongRuns = 4;       // updates per entry from which on a stripe behind a window is walked run by run
+constexpr uint32_t kLongList = kBucketCap / (kWave - kBucketChunk);      // such stripes that a list can hold
 
 __device__ __forceinline__ uint32_t item_row(u64 it) { return (uint32_t)(it >> 32); }
 
@@ -245,6 +245,122 @@ __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uin
                 }
                 w.clear_chain();
             }
+        }
+    }
+}
+
+// The runs of one long stripe, [start, end) of a sorted list: a wave takes every kBucketWaves-th of them, from the w-th on,
+// and leaves the sums of their differences in dpe and dpa.  Per run, the rows of the entry are asked for together with the
+// first gradients, and the gradients of U updates are in flight while the U before them are applied: 8 updates per us, twice
+// as many as the steps of the window walk, which carry the loads of rows that most of them do not need.
+template <int NC, int MODE>
+__device__ __forceinline__ void walk_runs(const RowArgs &a, const u64 *items, uint32_t start, uint32_t end, uint32_t cb,
+                                          uint32_t w, D2 (&dpe)[NC], D2 (&dpa)[NC])
+{
+    constexpr uint32_t U = NC == 1 ? 8 : 4;
+    const uint32_t D = a.geo.D, lane = lane_id(), col0 = cb * NC * 128u;
+    const RuleParams rp = rule_params(a.geo);
+    for (uint32_t pos = start, r = 0, run_end; pos < end; pos = run_end, ++r) {
+        const uint32_t x = uniform(item_row(items[pos]));
+        for (run_end = pos;; run_end += kWave) {
+            const uint32_t p = run_end + lane;
+            const u64 other = __ballot(p >= end || item_row(items[min(p, end - 1u)]) != x);
+            if (!other) continue;
+            run_end += lowest_bit(other);
+            break;
+        }
+        if (r % kBucketWaves != w) continue;
+        const rsrc_t erow = row_f32(a.E, x, D, col0), arow = row_f32(a.A, x, D, col0);
+        float2 e[NC], a0[NC], now[U][NC], next[U][NC];
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            e[i] = ld2(erow, i);
+            a0[i] = ld2(arow, i);
+        }
+        // the gradients of updates t .. t + U - 1 (past the run's end: the last one's)
+        auto load = [&](float2 (&g)[U][NC], uint32_t t) {
+            const uint32_t idx = (uint32_t)items[min(t + (lane & (U - 1u)), run_end - 1u)];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const rsrc_t grow = row_f32(a.grads, from_lane(idx, u), D, col0);
+#pragma unroll
+                for (int i = 0; i < NC; ++i) g[u][i] = ldg2(grow, i);
+            }
+        };
+        load(now, pos);
+        D2 G[NC], acc[NC];
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            G[i] = start2<MODE>(widen2(a0[i]));
+            acc[i] = D2{0, 0};
+        }
+        for (uint32_t t = pos;; t += U) {
+            const bool more = t + U < run_end;
+            if (more) load(next, t + U);
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u)
+                if (t + u < run_end) {
+#pragma unroll
+                    for (int i = 0; i < NC; ++i) item2<MODE>(G[i], acc[i], now[u][i], rp);
+                }
+            if (!more) break;
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u)
+#pragma unroll
+                for (int i = 0; i < NC; ++i) now[u][i] = next[u][i];
+        }
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const D2 e64 = widen2(e[i]), a64 = widen2(a0[i]);
+            finish2<MODE>(G[i], acc[i], a64, rp);
+            st2(erow, i, narrow2(D2{e64.x - acc[i].x, e64.y - acc[i].y}));
+            st2(arow, i, narrow2(G[i]));
+            dpe[i].x -= acc[i].x;
+            dpe[i].y -= acc[i].y;
+            dpa[i].x += G[i].x - a64.x;
+            dpa[i].y += G[i].y - a64.y;
+        }
+    }
+}
+
+// A long stripe by the whole workgroup: its entries are independent, only their differences meet in the parity rows, so the
+// waves share the runs and add their sums up through LDS (s_part: kBucketWaves * NC * 128 doubles).  Every wave calls this.
+// 16 384 updates on 256 rows, 256 to a stripe: 100 us a call when the owner walked it alone, 79 run by run, 58 shared.
+template <int NC, int MODE, bool PARITY>
+__device__ __forceinline__ void walk_long_stripe(const RowArgs &a, const u64 *items, uint32_t start, uint32_t end, double *s_part)
+{
+    const uint32_t w = uniform(threadIdx.x / kWave), lane = lane_id(), D = a.geo.D;
+    const uint32_t g = a.geo.dk.div(uniform(item_row(items[start])));
+    for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
+        D2 d[2][NC];                                    // the neutral summand
+#pragma unroll
+        for (int i = 0; i < NC; ++i) d[0][i] = d[1][i] = D2{-0.0, -0.0};
+        walk_runs<NC, MODE>(a, items, start, end, cb, w, d[0], d[1]);
+        if (!PARITY) continue;
+#pragma unroll
+        for (uint32_t q = 0; q < 2; ++q) {              // the parity entry, by wave 0; its state, by wave 1
+            const rsrc_t row = row_f32(q ? a.PA : a.PE, g, D, cb * NC * 128u);
+            float2 old[NC];
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+                if (w == q) old[i] = ld2(row, i);
+                *(double2 *)(s_part + (w * NC + i) * 128u + 2u * lane) = double2{d[q][i].x, d[q][i].y};
+            }
+            __syncthreads();
+            if (w == q) {
+#pragma unroll
+                for (int i = 0; i < NC; ++i) {
+                    D2 sum = widen2(old[i]);
+#pragma unroll
+                    for (int v = 0; v < kBucketWaves; ++v) {
+                        const double2 part = *(const double2 *)(s_part + (v * NC + i) * 128u + 2u * lane);
+                        sum.x += part.x;
+                        sum.y += part.y;
+                    }
+                    st2(row, i, narrow2(sum));
+                }
+            }
+            __syncthreads();
         }
     }
 }
@@ -518,24 +634,29 @@ __device__ __forceinline__ void sort_items(u64 *s_item, u64 *s_tmp, uint32_t m)
 
 struct ListShared {
     uint32_t heavy[kBucketCap / kHeavyRunMin];               // stripes for heavy_stripes: start | end << 16
-    uint32_t n_heavy, chunk;
+    uint32_t longs[kLongList];                               // stripes that the whole workgroup walks, the same way
+    uint32_t n_heavy, n_long, chunk;
     uint32_t srv[2 * kBucketMaxServers];
 };
 
 // Applies every stripe of a sorted list of m items (m <= kBucketCap).  Chunks of CH positions are handed to the waves as
 // they come free; a wave owns the stripes that open in its chunk.  A stripe that does not end inside the wave's
-// 64-position window is walked window by window with its state in registers; one with a run of heavy_run updates or more
-// is only listed in sh.heavy.
+// 64-position window
+//   - is only listed in sh.heavy if it has a run of heavy_run updates and that makes up more than half of it, or if it has
+//     shared_stripe updates;
+//   - is walked by the whole workgroup afterwards if its updates are spread over entries with several each (s_part: room
+//     for walk_long_stripe);
+//   - is walked by its owner otherwise, window by window with its state in registers: there is nothing to share.
 // A barrier has to lie between the last write of the list and this call; the call ends with one.
 template <int NC, int MODE, bool PARITY, uint32_t CH>
 __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, uint32_t m, uint32_t heavy_run,
-                                           ListShared &sh)
+                                           uint32_t shared_stripe, ListShared &sh, double *s_part)
 {
     constexpr int kQ = 2, kU = NC == 1 ? 4 : 2;
     const uint32_t lane = lane_id();
     const Divider dk = a.geo.dk;
     if (threadIdx.x == 0) {
-        sh.n_heavy = 0;
+        sh.n_heavy = sh.n_long = 0;
         sh.chunk = kBucketWaves;
     }
     __syncthreads();
@@ -559,14 +680,15 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
         // the stripe that goes on behind the window: where it ends, and how long its runs are
         const uint32_t big_start = p0 + last;
         uint32_t big_end = big_start;
-        bool heavy = false;
+        bool heavy = false, shared = false;
         if (!inside) {
             const uint32_t g = dk.div(from_lane(wkey, last));
+            bool long_run = false, one_run = false;                 // of heavy_run updates; of more than half of the stripe
             for (;;) {
                 const uint32_t p = big_end + lane;
                 const uint32_t key = p < m ? item_row(items[p]) : kNoKey;
                 const bool same = key != kNoKey && dk.div(key) == g;
-                if (__ballot(same && p + heavy_run - 1 < m && item_row(items[min(p + heavy_run - 1, m - 1)]) == key)) heavy = true;
+                if (__ballot(same && p + heavy_run - 1 < m && item_row(items[min(p + heavy_run - 1, m - 1)]) == key)) long_run = true;
                 const u64 other = __ballot(!same);
                 if (other) {
                     big_end += lowest_bit(other);
@@ -574,7 +696,15 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
                 }
                 big_end += kWave;
             }
-            if (heavy && lane == 0) sh.heavy[atomicAdd(&sh.n_heavy, 1u)] = big_start | (big_end << 16);
+            const uint32_t size = big_end - big_start, half = size / 2u;
+            for (uint32_t q = big_start; q + half < big_end; q += kWave) {
+                const uint32_t p = min(q + lane, big_end - half - 1u);
+                if (__ballot(item_row(items[p + half]) == item_row(items[p]))) one_run = true;
+            }
+            heavy = long_run && (one_run || size >= shared_stripe);
+            shared = !heavy && !one_run && size >= kLongRuns * dk.d;
+            if (lane == 0 && heavy) sh.heavy[atomicAdd(&sh.n_heavy, 1u)] = big_start | (big_end << 16);
+            if (lane == 0 && shared) sh.longs[atomicAdd(&sh.n_long, 1u)] = big_start | (big_end << 16);
         }
         for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
             Walk<NC> walk;
@@ -583,7 +713,7 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
             uint32_t wk = wkey, wi = widx, from = first, to = end, p = p0;
             u64 rh = rowheads, sth = stripeheads;
             bool run_on = false, stripe_on = false;
-            for (bool more = !inside && !heavy;;) {
+            for (bool more = !inside && !heavy && !shared;;) {
                 walk_window<NC, MODE, PARITY, kQ, kU>(a, wk, wi, rh, sth, from, to, cb, walk, run_on, stripe_on);
                 if (!more) break;
                 p = stripe_on ? p + kWave : big_start;
@@ -603,6 +733,12 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
         }
     }
     __syncthreads();
+    const uint32_t n_long = uniform(sh.n_long);
+    for (uint32_t i = 0; i < n_long; ++i) {                  // their order in the list may vary; they share nothing
+        const uint32_t what = uniform(sh.longs[i]);
+        walk_long_stripe<NC, MODE, PARITY>(a, items, what & 0xFFFFu, what >> 16, s_part);
+    }
+    if (n_long) __syncthreads();
 }
 
 // Combined rules: one entry update and one parity update per modified entry (Sec. 3.6, Sec. 4.4).  The list is sorted.
@@ -641,7 +777,7 @@ struct BucketArgs : RowArgs {
     Header *hdr;
     u64 *load_data, *load_parity;
     uint32_t n, tile, tiles, buckets, packed;
-    uint32_t heavy_run;          // a run of at least this many updates goes to heavy_stripes with its stripe
+    uint32_t heavy_run, shared_stripe;       // bucket_plan.h
 };
 
 // gradient row of an item, from its position in the batch
@@ -669,7 +805,7 @@ constexpr uint32_t kHeavySlots = 16;
 struct BucketShared {
     __align__(16) u64 item[kBucketCap];
     union {
-        u64 tmp[kBucketCap];                                   // of the sort
+        __align__(16) u64 tmp[kBucketCap];                     // of the sort, and sums of walk_long_stripe
         struct { uint32_t tab_g[kStripeSlots], tab_c[kStripeSlots]; };     // of an oversized bucket, before it
     };
     ListShared list;
@@ -699,8 +835,8 @@ __device__ __forceinline__ uint32_t place_of(const BucketShared &sh, uint32_t ti
 
 // A bucket with more items than LDS takes: hot stripes.  Its items are first laid out in arrival order in tmp; then,
 // for one part of the stripes after the other (by the low bits of the mix, split until a part fits), the stripes are
-// counted in an LDS table, the light ones are collected, sorted and applied like any bucket, and the heavy ones -- more
-// than kHeavyMin updates -- are written to `dense`, entry by entry in arrival order, for heavy_stripes.  A part of a
+// counted in an LDS table, the light ones are collected, sorted and applied like any bucket, and the heavy ones --
+// heavy_stripe(k) updates or more -- are written to `dense`, entry by entry in arrival order, for heavy_stripes.  A part of a
 // single stripe always fits, so the splitting ends.  Uniform over the workgroup.  Every pass over the items keeps
 // kAhead loads of a thread in flight (one at a time, a bucket of 14 000 items took 130 us).
 constexpr int kAhead = 4;
@@ -773,6 +909,7 @@ __device__ __forceinline__ uint32_t oversized_part(const BucketArgs &a, BucketSh
     const Divider dk = a.geo.dk;
     const u64 *tmp = a.tmp + base;
     u64 *dense = a.dense + base;
+    const uint32_t heavy = heavy_stripe(k);
     uint32_t part = walk.part, mask;
     int depth = walk.depth;
     for (;;) {
@@ -811,7 +948,7 @@ __device__ __forceinline__ uint32_t oversized_part(const BucketArgs &a, BucketSh
         if (!sh.over) {
             for (uint32_t s = tid; s < kStripeSlots; s += kBucketThreads) {
                 const uint32_t c = sh.tab_c[s];
-                if (c > kHeavyMin) {
+                if (c >= heavy) {
                     const uint32_t i = atomicAdd(&sh.hv_n, 1u);
                     if (i < kHeavySlots) sh.hv[i] = s;
                 } else if (c) {
@@ -831,7 +968,7 @@ __device__ __forceinline__ uint32_t oversized_part(const BucketArgs &a, BucketSh
         stream_items(tmp, 0, m, tid, kBucketThreads, [&](u64 it) {
             const uint32_t g = dk.div(item_row(it));
             if (it == ~0ull || (mix32(g) & mask) != part) return;
-            if (sh.tab_c[stripe_slot(sh.tab_g, g)] <= kHeavyMin) sh.item[atomicAdd(&sh.n_light, 1u)] = it;
+            if (sh.tab_c[stripe_slot(sh.tab_g, g)] < heavy) sh.item[atomicAdd(&sh.n_light, 1u)] = it;
         });
     // ---- the heavy ones: a stable partition by member, every wave a contiguous quarter of the items
     const uint32_t quarter = (m + kBucketWaves - 1) / kBucketWaves, q_lo = min(w * quarter, m), q_hi = min(q_lo + quarter, m);
@@ -907,11 +1044,15 @@ __device__ __forceinline__ uint32_t oversized_part(const BucketArgs &a, BucketSh
     return light;
 }
 
+static_assert(sizeof(BucketShared::tmp) >= kBucketWaves * 2 * 128 * sizeof(double), "walk_long_stripe's sums for NC = 2");
+
 template <int NC, int MODE, bool PARITY>
 __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_kernel(BucketArgs a)
 {
     __shared__ BucketShared sh;
-    const uint32_t tid = threadIdx.x, b = blockIdx.x, B = a.buckets + kHotBuckets, S = a.geo.S, k = a.geo.k;
+    const uint32_t tid = threadIdx.x, B = a.buckets + kHotBuckets, S = a.geo.S, k = a.geo.k;
+    // the hot stripes' buckets first: what takes longest must not begin last
+    const uint32_t b = blockIdx.x < kHotBuckets ? a.buckets + blockIdx.x : blockIdx.x - kHotBuckets;
     bool hot = b >= a.buckets, key_bad = false;                     // hot: an entry of a hot stripe, the member-th
     const uint32_t member = hot ? (b - a.buckets) % k : 0u;
     uint32_t from = 0, len = 0, stripe_len = 0;
@@ -934,9 +1075,9 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
     uint32_t m;
     if (hot) {
         bucket_excl_scan(stripe_len, sh.wave, m);
-        if (m < kHotRun) {
-            // no stripe, or one that the sample took for hot by chance (a few hits out of a segment each): its entries'
-            // buckets lie side by side in every tile, so the first workgroup takes them as one ordinary bucket
+        if (m < a.shared_stripe) {
+            // no stripe, or one that is not as long as the sample made it look: its entries' buckets lie side by side in
+            // every tile, so the first workgroup takes them as one ordinary bucket
             if (member != 0 || m == 0) return;
             hot = false;
             len = stripe_len;
@@ -1008,7 +1149,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
                 __syncthreads();
             }
             if (Rule<MODE>::combine) count_list(a.geo, sh.item, list, sh.list.srv, a.load_data, a.load_parity);
-            apply_list<NC, MODE, PARITY, kBucketChunk>(a, sh.item, list, a.heavy_run, sh.list);
+            apply_list<NC, MODE, PARITY, kBucketChunk>(a, sh.item, list, a.heavy_run, a.shared_stripe, sh.list, (double *)sh.tmp);
             const uint32_t nh = uniform(sh.list.n_heavy);
             if (nh && !have_base) {
                 bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, base);
@@ -1294,6 +1435,7 @@ void launch_bucket_apply(const BucketScratch &bs, Header *hdr, const Geometry &g
     a.n = n; a.tile = p.ipt * kPartThreads; a.tiles = p.tiles; a.buckets = p.buckets;
     a.packed = src == kWaitingUpdates ? 1u : 0u;
     a.heavy_run = heavy_run(n);
+    a.shared_stripe = shared_stripe(n, g.k);
     const bool heavy = n >= kHeavyRunMin;
     ECRM_DISPATCH(bucket_apply_for, a, PE != nullptr, heavy, cus, st);
 }

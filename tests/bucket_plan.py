@@ -17,7 +17,8 @@ extern "C" {
 uint32_t plan_buckets(uint32_t n) { return bucket_plan(n).buckets; }
 uint32_t plan_heavy_run(uint32_t n) { return heavy_run(n); }
 uint32_t plan_bucket_cap() { return kBucketCap; }
-uint32_t plan_hot_run() { return kHotRun; }
+uint32_t plan_heavy_stripe(uint32_t k) { return heavy_stripe(k); }
+uint32_t plan_shared_stripe(uint32_t n, uint32_t k) { return shared_stripe(n, k); }
 uint32_t plan_hot_hits(uint32_t n) { return hot_hits(n); }
 uint32_t plan_sample(uint32_t n, uint32_t *at)
 {
@@ -54,8 +55,12 @@ def bucket_cap():
     return int(lib().plan_bucket_cap())
 
 
-def hot_run():
-    return int(lib().plan_hot_run())
+def heavy_stripe(k):
+    return int(lib().plan_heavy_stripe(C.c_uint32(k)))
+
+
+def shared_stripe(n, k):
+    return int(lib().plan_shared_stripe(C.c_uint32(n), C.c_uint32(k)))
 
 
 def mix(stripes):

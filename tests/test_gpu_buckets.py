@@ -152,14 +152,15 @@ def test_heavy_stripes_of_many_entries(R, D, n_stripes, opt, comb):
 @pytest.mark.parametrize("n,D,k,S", [(8192, 36, 4, 5), (70001, 128, 10, 11), (200000, 12, 1, 2)])
 def test_stripes_taken_for_hot_by_chance(n, D, k, S, opt, comb):
     """Stripes that fill just as many sampled positions as make them hot, and hold fewer, as many and more updates in all than
-    the 256 below which they are given back to the ordinary buckets; one whose updates are all of one member."""
+    the number below which they are given back to the ordinary buckets; one whose updates are all of one member."""
     rng = np.random.default_rng(n)
     R = k * (n // 8)
     at, hits = bp.sample_positions(n), int(bp.lib().plan_hot_hits(n))
     keys = rng.integers(k * 16, R, n)
     off = rng.permutation(np.setdiff1d(np.arange(n), at))
     at = rng.permutation(at)
-    totals = [hits, hits + 1, 100, 128, 200, bp.hot_run() - 1, bp.hot_run(), bp.hot_run() + 1, 300]
+    limit = bp.shared_stripe(n, k)
+    totals = [hits, hits + 1, 100, 128, 200, limit - 1, limit, limit + 1, limit + 50]
     for g, total in enumerate(totals):
         mine, at, off = np.concatenate([at[:hits], off[:total - hits]]), at[hits:], off[total - hits:]
         keys[mine] = g * k + (k - 1 if g % 3 == 2 else rng.integers(0, k, total))
@@ -167,3 +168,30 @@ def test_stripes_taken_for_hot_by_chance(n, D, k, S, opt, comb):
     assert (np.bincount(keys // k)[:len(totals)] == totals).all()
     c = Case(R, D, k, S, max_batch=n, seed=73, optimizer=opt, momentum=0.9, combine=comb)
     _check(c, keys.astype(np.uint64), 73, f"hot by chance {(n, opt, comb)}")
+
+
+@pytest.mark.parametrize("opt,comb", RULES)
+@pytest.mark.parametrize("D,k,S,n", [(128, 4, 5, 30000), (300, 2, 3, 60000), (36, 10, 11, 20000), (1024, 3, 5, 20000),
+                                     (8, 63, 64, 40000), (64, 1, 2, 20000)])
+@pytest.mark.parametrize("parity", [True, False])
+def test_stripes_shared_by_a_workgroup(D, k, S, n, parity, opt, comb):
+    """Stripes that do not end inside a window of 64 positions: around the window, around four updates to an entry from which
+    they are shared, around the length from which they are not any more; spread evenly, with one run of half and of more
+    than half of them, with an untouched entry, and with a run long enough to be heavy in a stripe that it dominates or not."""
+    rng = np.random.default_rng(D + k)
+    limit, run = bp.shared_stripe(n, k), bp.heavy_run(n)
+    sizes = [57, 58, 63, 64, 65, 71, 4 * k - 1, 4 * k, 4 * k + 1, 128, run, 2 * run - 1, 2 * run, 2 * run + 1, limit - 1, limit, limit + 1]
+    stripes = rng.permutation(n // 8)[:4 * len(sizes)]
+    keys = []
+    for i, size in enumerate(sizes):
+        even, half, more, most = (stripes[4 * i + j] * k for j in range(4))
+        keys.append(even + np.arange(size) % k)
+        keys.append(half + np.concatenate([np.full(size // 2, k - 1), rng.integers(0, k, size - size // 2)]))
+        keys.append(more + np.concatenate([np.full(size // 2 + 1, 0), np.arange(size - size // 2 - 1) % k]))
+        keys.append(most + np.concatenate([np.full(size - size // 8, k // 2), rng.integers(k // 2, k, size // 8)]))
+    keys = np.concatenate(keys)
+    assert len(keys) < n
+    R = k * (n // 8)
+    keys = rng.permutation(np.concatenate([keys, rng.integers(0, R, n - len(keys))])).astype(np.uint64)
+    c = Case(R, D, k, S, max_batch=n, seed=79, optimizer=opt, momentum=0.9, combine=comb, propagation=0 if parity else 2)
+    _check(c, keys, 79, f"shared {(D, k, n, parity, opt, comb)}")
