@@ -244,8 +244,9 @@ int ecrm_clear_status(ecrm_ctx *ctx, void *hip_stream);
  * ECRM_MID_RUN updates in a call is walked by one workgroup -- one read of its gradients instead of two --
  * but only in calls with at least this many such long entries, since one workgroup is slow and pays only
  * when all of them are busy.  Default (value 0): four per workgroup the device holds at once.  Any other value
- * also sends batches of every size through the sort and the chain tiers; by default those of up to 2^19 updates are
- * grouped in buckets instead (same results; out[1] and out[4] of ecrm_batch_stats are 0 then).  EINVAL for
+ * also sends batches of every size through the sort and the chain tiers; by default those of up to 2^19 updates (2^18 on a
+ * table of fewer than 128 rows) are grouped in buckets instead (same results; out[1] and out[4] of ecrm_batch_stats are 0
+ * then).  EINVAL for
  * an unknown knob or a value above 2^32-1.
  * ecrm_host_placement runs on the HOST only (no GPU needed): it evaluates, with the very 32-bit
  * arithmetic the kernels use, where `key` lies -- out[0] = stripe, out[1] = member, out[2] = data

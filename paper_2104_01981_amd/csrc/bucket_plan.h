@@ -13,7 +13,14 @@
 
 namespace ecrm {
 
+// Batches up to here go through buckets.  us a call with the sort and the chain tiers / with buckets, D = 128, k = 4, at 2^18 and at
+// 2^19 updates: uniform on 4 n rows 306 / 233 and 537 / 438, on n / 8 rows 240 / 119 and 278 / 158; Zipf on n rows 448 / 195
+// and 499 / 319; D = 512 on 4 n rows 672 / 691 (2 n rows) and 1584 / 1592; k = 10 on n / 16 rows 152 / 178 at 2^19.  Beyond, the sort's fixed cost is
+// small; and a batch whose updates share few rows is slower in buckets from 300 000 updates on (2^19 on n / 32 rows 130 / 150).
 constexpr uint32_t kBucketMaxBatch = 1u << 19;
+// ... but for the larger half of them on the smallest tables, which the chain tiers spread better: 2^19 updates on 16, 32, 64,
+// 128 rows take 179, 177, 175, 176 us there, in buckets 317, 449, 217, 154.
+constexpr uint32_t kFewRows = 128, kFewRowsBatch = 1u << 18;
 constexpr int kBucketThreads = 256;
 constexpr int kPartThreads = 512;            // of the partition: 8 waves, 1, 2 or 4 updates per thread
 constexpr uint32_t kMaxBuckets = 4096;
@@ -44,6 +51,22 @@ ECRM_HD uint32_t shared_stripe(uint32_t n, uint32_t k)
     return root > heavy_stripe(k) ? root : heavy_stripe(k);
 }
 static_assert(kHeavyEntryMin * 64u <= kBucketCap, "a stripe that is not heavy fits a list");
+// A stripe of the sample with split_stripe(n, D) updates has its runs cut into segments, which go to as many workgroups as
+// there are; a shorter one is walked by D / 16 workgroups, in rounds of kSplitSegment updates.  A round takes 3.5 us and a
+// segment 17, so that a batch of nothing but such stripes breaks even where a stripe's rounds take as long as all the
+// segments together.
+constexpr uint32_t kSplitStripeMin = 8192, kSplitSegment = 1024;
+ECRM_HD uint32_t split_stripe(uint32_t n, uint32_t D)
+{
+    const uint32_t even = n / 64u * ((D + 15u) / 16u);       // < 2^20 updates, 64 groups of columns: below 2^20
+    return even > kSplitStripeMin ? even : kSplitStripeMin;
+}
+// segments of a batch of n updates: one per kSplitSegment, and a partly filled one for every run of such a stripe
+ECRM_HD uint32_t split_segments(uint32_t n, uint32_t k)
+{
+    const uint32_t runs = n / kSplitStripeMin * k;
+    return runs ? n / kSplitSegment + (runs < kHotBuckets ? runs : kHotBuckets) : 0u;
+}
 struct BucketPlan { uint32_t ipt, tiles, buckets; };
 // Tiles as small as kMaxTiles of them allow.  Buckets of 16 updates while that gives no more than the 1024 workgroups that
 // are resident at once -- the fewer updates a wave walks one after the other the better --, of 64 from then on, of more

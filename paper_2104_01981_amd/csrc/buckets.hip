@@ -23,6 +23,7 @@ typedef unsigned long long u64;
 
 constexpr int kBucketWaves = kBucketThreads / kWave;
 constexpr int kPartWaves = kPartThreads / kWave;
+constexpr uint32_t kHeavyCols = 16;      // columns of a job of heavy_stripes
 constexpr uint32_t kLongRuns = 4;       // updates per entry from which on a stripe behind a window is walked run by run
 constexpr uint32_t kLongList = kBucketCap / (kWave - kBucketChunk);      // such stripes that a list can hold
 
@@ -582,6 +583,7 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
         h->n_valid = n;
         h->n_held = 0;
         h->n_heavy = 0;
+        h->n_segments = 0;
         h->heavy_ticket = 0;
         for (uint32_t c = 0; c < kMidClasses; ++c) h->n_mid[c] = 0;
     }
@@ -774,10 +776,11 @@ struct BucketArgs : RowArgs {
     const uint16_t *table;
     const uint32_t *tile_cnt, *tile_bad;
     uint32_t *heavy;             // [2 * (n / kHeavyRunMin + 64)]: start in `dense`, number of updates
+    SplitScratch split;          // of stripes whose runs are cut up
     Header *hdr;
     u64 *load_data, *load_parity;
     uint32_t n, tile, tiles, buckets, packed;
-    uint32_t heavy_run, shared_stripe;       // bucket_plan.h
+    uint32_t heavy_run, shared_stripe, split_stripe;         // bucket_plan.h
 };
 
 // gradient row of an item, from its position in the batch
@@ -822,15 +825,15 @@ __device__ __forceinline__ uint32_t stripe_slot(const uint32_t *tab_g, uint32_t 
     return s;
 }
 
-// where the bucket's q-th item, in arrival order, lies in a.items
-__device__ __forceinline__ uint32_t place_of(const BucketShared &sh, uint32_t tiles, uint32_t q)
+// where the q-th item, in arrival order, of a bucket lies in a.items: pref are its items in earlier tiles, start its places
+__device__ __forceinline__ uint32_t place_of(const uint32_t *pref, const uint32_t *start, uint32_t tiles, uint32_t q)
 {
     uint32_t lo = 0, hi = tiles;                                    // pref[lo] <= q < pref[hi]
     while (hi - lo > 1u) {
         const uint32_t mid = (lo + hi) / 2u;
-        if (sh.pref[mid] <= q) lo = mid; else hi = mid;
+        if (pref[mid] <= q) lo = mid; else hi = mid;
     }
-    return sh.start[lo] + (q - sh.pref[lo]);
+    return start[lo] + (q - pref[lo]);
 }
 
 // A bucket with more items than LDS takes: hot stripes.  Its items are first laid out in arrival order in tmp; then,
@@ -1044,6 +1047,32 @@ __device__ __forceinline__ uint32_t oversized_part(const BucketArgs &a, BucketSh
     return light;
 }
 
+// One entry, the r-th hot bucket, of a stripe of split_stripe updates or more: its updates are left where the partition put
+// them, and described -- how many, where each tile's lie -- and cut into segments for heavy_stripes.
+__device__ __forceinline__ void split_run(const BucketArgs &a, BucketShared &sh, uint32_t r, uint32_t from, uint32_t len)
+{
+    const uint32_t tid = threadIdx.x, ncg = (a.geo.D + kHeavyCols - 1) / kHeavyCols;
+    uint32_t m;
+    const uint32_t at = bucket_excl_scan(len, sh.wave, m);
+    const uint32_t segs = (m + kSplitSegment - 1) / kSplitSegment;
+    if (tid == 0) {
+        sh.fill = segs ? atomicAdd(&a.hdr->n_segments, segs) : 0u;
+        a.split.run[r] = SplitRun{sh.fill, m};
+    }
+    uint32_t *pref = a.split.tiles + (size_t)r * kSplitTileWords, *start = pref + kMaxTiles + 1;
+    if (tid < a.tiles) {
+        pref[tid] = at;
+        start[tid] = from;
+    }
+    if (tid == 0) pref[a.tiles] = m;
+    __syncthreads();
+    const uint32_t first = sh.fill;
+    for (uint32_t i = tid; i < segs; i += kBucketThreads) a.split.segment_run[first + i] = r;
+    for (uint32_t i = tid; i < segs * ncg; i += kBucketThreads) a.split.summed[(size_t)first * ncg + i] = 0;
+    if (r % a.geo.k == 0)
+        for (uint32_t i = tid; i < ncg; i += kBucketThreads) a.split.arrived[r / a.geo.k * ncg + i] = 0;
+}
+
 static_assert(sizeof(BucketShared::tmp) >= kBucketWaves * 2 * 128 * sizeof(double), "walk_long_stripe's sums for NC = 2");
 
 template <int NC, int MODE, bool PARITY>
@@ -1081,6 +1110,9 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
             if (member != 0 || m == 0) return;
             hot = false;
             len = stripe_len;
+        } else if (m >= a.split_stripe) {
+            split_run(a, sh, b - a.buckets, from, len);
+            return;
         } else if (member == 0) {
             uint32_t start;
             bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, start);
@@ -1133,7 +1165,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
 #pragma unroll
             for (int c = 0; c < P; ++c) {
                 const uint32_t q = c * kBucketThreads + tid;
-                if (q < m) it[c] = a.items[place_of(sh, a.tiles, q)];
+                if (q < m) it[c] = a.items[place_of(sh.pref, sh.start, a.tiles, q)];
             }
 #pragma unroll
             for (int c = 0; c < P; ++c) {
@@ -1178,7 +1210,6 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
 // through LDS, and take their steps from registers: 1024 updates per round.
 constexpr int kHeavyThreads = 512;
 constexpr int kHeavyWaves = kHeavyThreads / kWave;
-constexpr uint32_t kHeavyCols = 16;
 
 // The decay over a number of updates, a power of mu.  One that underflows is kept at the smallest normal number unless mu
 // itself is zero: a decay of zero would make NaN of an infinite velocity, which the rule keeps infinite.  What it adds to
@@ -1205,26 +1236,333 @@ __device__ __forceinline__ void heavy_rows(float2 (&r)[T], const float *grads, u
     }
 }
 
+constexpr int kHeavyT = 16;                  // updates that a group of eight lanes takes at a time
+static_assert(kSplitSegment == kHeavyThreads / 8 * kHeavyT, "a segment is one round of a workgroup");
+
+// what the waves exchange: sums (or, at the end of a run, steps) of two columns a lane, and the decay over a wave's updates
+struct HeavyExchange {
+    double sum[kHeavyWaves][8][2], dec[kHeavyWaves];
+};
+constexpr uint32_t kFoldParts = kHeavyThreads / kHeavyCols, kFoldLength = 16;       // of heavy_segment
+static_assert(kFoldParts * kFoldLength * kSplitSegment >= kBucketMaxBatch && kHeavyThreads * kSplitSegment >= kBucketMaxBatch,
+              "a run's segments are folded in one go, and waited for by a thread each");
+struct HeavyShared {
+    HeavyExchange ex[2];
+    double part[2][kFoldParts][kHeavyCols], dec[kFoldParts];
+    uint32_t pref[kMaxTiles + 1], start[kMaxTiles];
+    uint32_t job, last;
+};
+
+// Sums of a round: every wave leaves that of its updates in ex; returned is what lies before the lane's group inside its
+// wave, with its decay.
+template <int MODE>
+__device__ __forceinline__ D2 heavy_sums(const float2 (&gr)[kHeavyT], uint32_t cnt, const RuleParams &rp, HeavyExchange &ex,
+                                         uint32_t w, double &before_decay)
+{
+    constexpr bool kMomentum = MODE == kMomentumSeq;
+    const uint32_t lane = lane_id(), col_lane = lane & 7u;
+    D2 s = D2{-0.0, -0.0};                              // the neutral summand: +0.0 would take a -0.0's sign
+    double d = 1.0;
+#pragma unroll
+    for (int u = 0; u < kHeavyT; ++u) {
+        if ((uint32_t)u < cnt) {
+            summary2<MODE>(s, gr[u], rp);
+            if (kMomentum) d = decay(d * rp.mu, rp.mu);
+        }
+    }
+    // inclusive scan over the wave's eight groups of the maps v -> d * v + s
+#pragma unroll
+    for (int by = 8; by < kWave; by <<= 1) {
+        const double ox = __shfl_up(s.x, by, kWave), oy = __shfl_up(s.y, by, kWave);
+        const double od = kMomentum ? __shfl_up(d, by, kWave) : 1.0;
+        if (lane >= (uint32_t)by) {
+            s.x = kMomentum ? fma(d, ox, s.x) : s.x + ox;
+            s.y = kMomentum ? fma(d, oy, s.y) : s.y + oy;
+            if (kMomentum) d = decay(d * od, rp.mu);
+        }
+    }
+    if (lane >= 56u) {
+        ex.sum[w][col_lane][0] = s.x;
+        ex.sum[w][col_lane][1] = s.y;
+        if (col_lane == 0) ex.dec[w] = d;
+    }
+    D2 before = D2{__shfl_up(s.x, 8, kWave), __shfl_up(s.y, 8, kWave)};
+    before_decay = kMomentum ? __shfl_up(d, 8, kWave) : 1.0;
+    if (lane < 8u) {
+        before = D2{-0.0, -0.0};
+        before_decay = 1.0;
+    }
+    return before;
+}
+
+// behind a barrier after heavy_sums: takes `state` from the round's start to its end, returns it as the lane's group finds it
+template <int MODE>
+__device__ __forceinline__ D2 heavy_fold(D2 &state, const HeavyExchange &ex, uint32_t w, const D2 &before, double before_decay)
+{
+    constexpr bool kMomentum = MODE == kMomentumSeq;
+    const uint32_t col_lane = lane_id() & 7u;
+    D2 mine = state;
+#pragma unroll
+    for (int v = 0; v < kHeavyWaves; ++v) {
+        if ((uint32_t)v == w) mine = state;
+        const double fx = ex.sum[v][col_lane][0], fy = ex.sum[v][col_lane][1];
+        const double dv = kMomentum ? ex.dec[v] : 1.0;
+        state.x = kMomentum ? fma(dv, state.x, fx) : state.x + fx;
+        state.y = kMomentum ? fma(dv, state.y, fy) : state.y + fy;
+    }
+    mine.x = kMomentum ? fma(before_decay, mine.x, before.x) : mine.x + before.x;
+    mine.y = kMomentum ? fma(before_decay, mine.y, before.y) : mine.y + before.y;
+    return mine;
+}
+
+// sum of the groups' steps over the workgroup, for every lane; one barrier, after ex was written
+__device__ __forceinline__ D2 heavy_total(D2 acc, HeavyExchange &ex, uint32_t w)
+{
+    const uint32_t lane = lane_id(), col_lane = lane & 7u;
+#pragma unroll
+    for (int by = 8; by < kWave; by <<= 1) {
+        acc.x += __shfl_xor(acc.x, by, kWave);
+        acc.y += __shfl_xor(acc.y, by, kWave);
+    }
+    if (lane < 8u) {
+        ex.sum[w][col_lane][0] = acc.x;
+        ex.sum[w][col_lane][1] = acc.y;
+    }
+    __syncthreads();
+    acc = D2{0, 0};
+#pragma unroll
+    for (int v = 0; v < kHeavyWaves; ++v) {
+        acc.x += ex.sum[v][col_lane][0];
+        acc.y += ex.sum[v][col_lane][1];
+    }
+    return acc;
+}
+
+// ---- runs that are cut into segments -------------------------------------------------------------
+// With a batch on a handful of entries -- the smallest tables of a model, one very hot row -- a run has tens of thousands of
+// updates, and D / 16 workgroups walking it at 3.5 us per 1024 are what everything waits for.  Such a stripe's runs are
+// cut into segments of one round each.  A workgroup sums up its segment, publishes the sum, takes the sums of the segments
+// before it for its starting state, computes its steps from the gradients it still has in registers, and leaves
+// their sum; the last workgroup of the stripe (and 16 columns) to arrive applies the totals, entry by entry, segment by segment in order.
+// The wait for earlier segments ends: jobs are handed out in ascending order by one counter, so whoever waits knows the
+// earlier ones to be in the hands of workgroups that are already running, and those publish before they wait themselves.
+// us a call, D = 128, one workgroup to a run and 16 columns / cut up: all of 2^14, 2^16, 2^18 updates on one row 92 / 35, 304 / 54,
+// 1169 / 170; half of 2^18 706 / 222; 2^16 on 16 rows 104 / 65.
+
+// What workgroups of one launch leave each other is written and read by relaxed atomics of device scope: they pass by the
+// caches that the XCDs do not share.  published() waits until a wave's are done, so that a flag or a count written next is
+// seen after them.  (Fences of device scope would write back and invalidate those caches as a whole, for every segment:
+// 2^19 updates on 2^7 rows took 800 us with them.)
+__device__ __forceinline__ double shared_load(const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void shared_store(double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void published() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Folds the sums (ROWS = 1) or the sums and steps (2) of segments first .. first + count - 1, columns cg * 16 ..: kFoldParts
+// threads per column take kFoldLength segments each and leave theirs in sh.part, with the decay in sh.dec.  The last
+// segment's decay is last_dec, that of the others dec.  Ends with a barrier.
+template <int MODE, int ROWS>
+__device__ __forceinline__ void fold_segments(const BucketArgs &a, HeavyShared &sh, uint32_t first, uint32_t count, uint32_t cg,
+                                              double dec, double last_dec)
+{
+    constexpr bool kMomentum = MODE == kMomentumSeq;
+    const uint32_t c = threadIdx.x % kHeavyCols, part = threadIdx.x / kHeavyCols, col = cg * kHeavyCols + c, D = a.geo.D;
+    constexpr uint32_t kAtOnce = 8;
+    const uint32_t begin = part * kFoldLength, end = min(begin + kFoldLength, count);
+    double s = -0.0, steps = 0.0, d = 1.0;
+    for (uint32_t j0 = begin; j0 < end; j0 += kAtOnce) {
+        double v[ROWS][kAtOnce];
+#pragma unroll
+        for (uint32_t i = 0; i < kAtOnce; ++i) {
+            const bool in = j0 + i < end && col < D;
+#pragma unroll
+            for (int q = 0; q < ROWS; ++q)
+                v[q][i] = in ? shared_load((q ? a.split.steps : a.split.sums) + (size_t)(first + j0 + i) * D + col) : 0.0;
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kAtOnce; ++i) {
+            if (j0 + i >= end) break;
+            const double di = j0 + i + 1u == count ? last_dec : dec;
+            s = kMomentum ? fma(di, s, v[0][i]) : s + v[0][i];
+            if (kMomentum) d = decay(d * di, (double)a.geo.mu);
+            if (ROWS == 2) steps += v[ROWS - 1][i];
+        }
+    }
+    sh.part[0][part][c] = s;
+    if (ROWS == 2) sh.part[1][part][c] = steps;
+    if (c == 0) sh.dec[part] = d;
+    __syncthreads();
+}
+
+// the decay over m updates
+__device__ __forceinline__ double decay_over(uint32_t m, double mu)
+{
+    double r = 1.0, p = mu;
+    for (; m; m >>= 1) {
+        if (m & 1u) r = decay(r * p, mu);
+        p = decay(p * p, mu);
+    }
+    return r;
+}
+
+// The last workgroup of a stripe applies what its segments have left: 16 columns, a thread each.
+template <int MODE, bool PARITY>
+__device__ __forceinline__ void finish_stripe(const BucketArgs &a, HeavyShared &sh, uint32_t h, uint32_t g, uint32_t cg)
+{
+    constexpr bool kMomentum = MODE == kMomentumSeq;
+    const uint32_t D = a.geo.D, k = a.geo.k, tid = threadIdx.x, col = cg * kHeavyCols + tid;
+    const RuleParams rp = rule_params(a.geo);
+    const double dec = kMomentum ? decay_over(kSplitSegment, rp.mu) : 1.0;
+    const bool mine = tid < kHeavyCols && col < D;
+    double pe = 0, pa = 0;
+    if (PARITY && mine) {
+        pe = (double)a.PE[(size_t)g * D + col];
+        pa = (double)a.PA[(size_t)g * D + col];
+    }
+    for (uint32_t j = 0; j < k; ++j) {
+        const SplitRun run = a.split.run[h * k + j];
+        if (run.updates == 0) continue;
+        const uint32_t segs = (run.updates + kSplitSegment - 1) / kSplitSegment, x = g * k + j;
+        const double last_dec = kMomentum ? decay_over(run.updates - (segs - 1) * kSplitSegment, rp.mu) : 1.0;
+        fold_segments<MODE, 2>(a, sh, run.first, segs, cg, dec, last_dec);
+        if (mine) {
+            float *e = a.E + (size_t)x * D + col, *state0 = a.A + (size_t)x * D + col;
+            const double e64 = (double)*e, a64 = (double)*state0;
+            double state = Rule<MODE>::start(a64), acc = 0.0;
+            for (uint32_t p = 0; p * kFoldLength < segs; ++p) {
+                state = kMomentum ? fma(sh.dec[p], state, sh.part[0][p][tid]) : state + sh.part[0][p][tid];
+                if (!Rule<MODE>::combine) acc += sh.part[1][p][tid];
+            }
+            Rule<MODE>::finish(state, acc, a64, rp);
+            *e = (float)(e64 - acc);
+            *state0 = (float)state;
+            pe -= acc;
+            pa += state - a64;
+        }
+        if (cg == 0 && tid == 0) {
+            if (run.updates > kLongRun) {
+                atomicAdd(&a.hdr->n_long, 1u);
+                atomicAdd(&a.hdr->n_long_items, (u64)run.updates);
+            }
+            if (Rule<MODE>::combine) {
+                atomicAdd(&a.load_data[a.geo.dS.mod(g + 1 + j)], 1ull);
+                if (a.load_parity) atomicAdd(&a.load_parity[a.geo.dS.mod(g)], 1ull);
+            }
+        }
+        __syncthreads();                                            // sh.part is free for the next entry
+    }
+    if (PARITY && mine) {
+        a.PE[(size_t)g * D + col] = (float)pe;
+        a.PA[(size_t)g * D + col] = (float)pa;
+    }
+}
+
+// One segment, 16 columns.
+template <int MODE, bool PARITY>
+__device__ __forceinline__ void heavy_segment(const BucketArgs &a, HeavyShared &sh, uint32_t segment, uint32_t cg)
+{
+    constexpr bool kMomentum = MODE == kMomentumSeq;
+    constexpr int T = kHeavyT;
+    const uint32_t D = a.geo.D, k = a.geo.k, tid = threadIdx.x, lane = lane_id(), w = uniform(tid / kWave);
+    const uint32_t col_lane = lane & 7u, sub = w * 8u + lane / 8u, ncg = (D + kHeavyCols - 1) / kHeavyCols;
+    const RuleParams rp = rule_params(a.geo);
+    const uint32_t r = a.split.segment_run[segment], h = r / k;
+    const SplitRun run = a.split.run[r];
+    const uint32_t nth = segment - run.first, L = run.updates, col = cg * kHeavyCols + 2u * col_lane;
+    const bool live = col < D;                                      // D is a multiple of 4: both columns or none
+    const uint32_t *tiles = a.split.tiles + (size_t)r * kSplitTileWords;
+    for (uint32_t t = tid; t <= a.tiles; t += kHeavyThreads) {
+        sh.pref[t] = tiles[t];
+        if (t < a.tiles) sh.start[t] = tiles[kMaxTiles + 1 + t];
+    }
+    __syncthreads();
+    // the eight lanes of a group look up two of its T updates each (past the run's end: the last one)
+    const uint32_t off = nth * kSplitSegment + sub * T, q = off + 2u * col_lane;
+    const u64 it0 = resolved(a, a.items[place_of(sh.pref, sh.start, a.tiles, min(q, L - 1u))]);
+    const u64 it1 = resolved(a, a.items[place_of(sh.pref, sh.start, a.tiles, min(q + 1u, L - 1u))]);
+    const uint32_t x = uniform(item_row(it0)), g = a.geo.dk.div(x);
+    float2 gr[T];
+    heavy_rows<T>(gr, a.grads, D, col, live, (uint32_t)it0, (uint32_t)it1, lane, off, L);
+    const uint32_t cnt = off < L ? min((uint32_t)T, L - off) : 0u;
+    D2 state = D2{0, 0};
+    if (!Rule<MODE>::combine && live) state = widen2(*(const float2 *)(a.A + (size_t)x * D + col));
+    double ed;
+    const D2 ex = heavy_sums<MODE>(gr, cnt, rp, sh.ex[0], w, ed);
+    __syncthreads();
+    // ---- its sum, for the segments behind it (and for the run's end)
+    if (w == 0 && lane < 8u && live) {
+        D2 sum = D2{-0.0, -0.0};
+        heavy_fold<MODE>(sum, sh.ex[0], w, ex, ed);
+        double *to = a.split.sums + (size_t)segment * D + col;
+        shared_store(to, sum.x);
+        shared_store(to + 1, sum.y);
+    }
+    uint32_t *summed = a.split.summed + (size_t)run.first * ncg + cg;
+    if (w == 0) {
+        published();
+        if (lane == 0) __hip_atomic_store(summed + (size_t)nth * ncg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!Rule<MODE>::combine) {
+        // ---- the state it starts from
+        if (tid < nth)                                              // nth < 512
+            while (!__hip_atomic_load(summed + (size_t)tid * ncg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) __builtin_amdgcn_s_sleep(2);
+        __syncthreads();
+        const double dec = kMomentum ? decay_over(kSplitSegment, rp.mu) : 1.0;
+        fold_segments<MODE, 1>(a, sh, run.first, nth, cg, dec, dec);
+        for (uint32_t p = 0; p * kFoldLength < nth; ++p) {
+            const double px = sh.part[0][p][2u * col_lane], py = sh.part[0][p][2u * col_lane + 1u], dp = kMomentum ? sh.dec[p] : 1.0;
+            state.x = kMomentum ? fma(dp, state.x, px) : state.x + px;
+            state.y = kMomentum ? fma(dp, state.y, py) : state.y + py;
+        }
+        // ---- its steps
+        D2 mine = heavy_fold<MODE>(state, sh.ex[0], w, ex, ed), acc = D2{0, 0};
+#pragma unroll
+        for (int u = 0; u < T; ++u) {
+            if ((uint32_t)u < cnt) item2<MODE>(mine, acc, gr[u], rp);
+        }
+        acc = heavy_total(acc, sh.ex[1], w);
+        if (w == 0 && lane < 8u && live) {
+            double *to = a.split.steps + (size_t)segment * D + col;
+            shared_store(to, acc.x);
+            shared_store(to + 1, acc.y);
+        }
+    }
+    // ---- the last to arrive of the stripe's segments
+    if (w == 0) {
+        const uint32_t m = lane < k ? a.split.run[h * k + lane].updates : 0u;
+        uint32_t all = (m + kSplitSegment - 1) / kSplitSegment;
+#pragma unroll
+        for (int by = 1; by < kWave; by <<= 1) all += __shfl_xor(all, by, kWave);
+        published();
+        if (lane == 0)
+            sh.last = __hip_atomic_fetch_add(a.split.arrived + h * ncg + cg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == all;
+    }
+    __syncthreads();
+    if (uniform(sh.last)) finish_stripe<MODE, PARITY>(a, sh, h, g, cg);
+}
+
 template <int MODE, bool PARITY>
 __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs a)
 {
-    constexpr bool kMomentum = MODE == kMomentumSeq;
-    constexpr int T = 16;
-    __shared__ double s_sum[2][kHeavyWaves][8][2];
-    __shared__ double s_dec[2][kHeavyWaves];
-    __shared__ uint32_t s_job;
+    constexpr int T = kHeavyT;
+    __shared__ HeavyShared sh;
     if (a.hdr->batch_bad) return;
-    const uint32_t nh = a.hdr->n_heavy, D = a.geo.D, k = a.geo.k, lane = lane_id();
-    if (nh == 0) return;
+    const uint32_t nh = a.hdr->n_heavy, ns = a.hdr->n_segments, D = a.geo.D, k = a.geo.k, lane = lane_id();
+    if (nh + ns == 0) return;
     const uint32_t w = uniform(threadIdx.x / kWave), col_lane = lane & 7u, sub = w * 8u + lane / 8u;
     const uint32_t ncg = (D + kHeavyCols - 1) / kHeavyCols;
     const RuleParams rp = rule_params(a.geo);
     // jobs are handed out as workgroups come free: their lengths differ by orders of magnitude
     for (;;) {
-        if (threadIdx.x == 0) s_job = atomicAdd(&a.hdr->heavy_ticket, 1u);
+        if (threadIdx.x == 0) sh.job = atomicAdd(&a.hdr->heavy_ticket, 1u);
         __syncthreads();
-        const uint32_t job = uniform(s_job);
-        if (job >= nh * ncg) break;
+        uint32_t job = uniform(sh.job);
+        if (job >= (ns + nh) * ncg) break;
+        if (job < ns * ncg) {                                       // the segments first, in order: heavy_segment relies on it
+            heavy_segment<MODE, PARITY>(a, sh, job / ncg, job % ncg);
+            __syncthreads();
+            continue;
+        }
+        job -= ns * ncg;
         const uint32_t h = job / ncg, cg = job - h * ncg;
         const uint32_t start = a.heavy[2 * h], what = a.heavy[2 * h + 1], end = start + (what & ~kCounted);
         const u64 *items = a.dense;
@@ -1236,7 +1574,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
             pe = widen2(*(const float2 *)(a.PE + (size_t)g * D + col));
             pa = widen2(*(const float2 *)(a.PA + (size_t)g * D + col));
         }
-        // Half of s_sum for the next exchange.  It changes with every exchange and with nothing else: a half is written again
+        // Half of sh.ex for the next exchange.  It changes with every exchange and with nothing else: a half is written again
         // only behind the barrier of the exchange in between, which every wave passes after it has read the half.
         uint32_t buf = 0;
         for (uint32_t p = start; p < end;) {
@@ -1281,50 +1619,10 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
                     }
                     continue;
                 }
-                D2 s = D2{-0.0, -0.0};                              // the neutral summand: +0.0 would take a -0.0's sign
-                double d = 1.0;
-#pragma unroll
-                for (int u = 0; u < T; ++u) {
-                    if ((uint32_t)u < cnt) {
-                        summary2<MODE>(s, gr[u], rp);
-                        if (kMomentum) d = decay(d * rp.mu, rp.mu);
-                    }
-                }
-                // inclusive scan over the wave's eight groups of the maps v -> d * v + s
-#pragma unroll
-                for (int by = 8; by < kWave; by <<= 1) {
-                    const double ox = __shfl_up(s.x, by, kWave), oy = __shfl_up(s.y, by, kWave);
-                    const double od = kMomentum ? __shfl_up(d, by, kWave) : 1.0;
-                    if (lane >= (uint32_t)by) {
-                        s.x = kMomentum ? fma(d, ox, s.x) : s.x + ox;
-                        s.y = kMomentum ? fma(d, oy, s.y) : s.y + oy;
-                        if (kMomentum) d = decay(d * od, rp.mu);
-                    }
-                }
-                if (lane >= 56u) {
-                    s_sum[buf][w][col_lane][0] = s.x;
-                    s_sum[buf][w][col_lane][1] = s.y;
-                    if (col_lane == 0) s_dec[buf][w] = d;
-                }
-                // what lies before this group inside the wave
-                D2 ex = D2{__shfl_up(s.x, 8, kWave), __shfl_up(s.y, 8, kWave)};
-                double ed = kMomentum ? __shfl_up(d, 8, kWave) : 1.0;
-                if (lane < 8u) {
-                    ex = D2{-0.0, -0.0};
-                    ed = 1.0;
-                }
+                double ed;
+                const D2 ex = heavy_sums<MODE>(gr, cnt, rp, sh.ex[buf], w, ed);
                 __syncthreads();
-                D2 mine = state;
-#pragma unroll
-                for (int v = 0; v < kHeavyWaves; ++v) {
-                    if ((uint32_t)v == w) mine = state;
-                    const double fx = s_sum[buf][v][col_lane][0], fy = s_sum[buf][v][col_lane][1];
-                    const double dv = kMomentum ? s_dec[buf][v] : 1.0;
-                    state.x = kMomentum ? fma(dv, state.x, fx) : state.x + fx;
-                    state.y = kMomentum ? fma(dv, state.y, fy) : state.y + fy;
-                }
-                mine.x = kMomentum ? fma(ed, mine.x, ex.x) : mine.x + ex.x;
-                mine.y = kMomentum ? fma(ed, mine.y, ex.y) : mine.y + ex.y;
+                D2 mine = heavy_fold<MODE>(state, sh.ex[buf], w, ex, ed);
 #pragma unroll
                 for (int u = 0; u < T; ++u) {
                     if ((uint32_t)u < cnt) item2<MODE>(mine, acc, gr[u], rp);
@@ -1332,22 +1630,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
                 buf ^= 1u;
             }
             {                                                       // sum of the steps over groups, then over waves
-#pragma unroll
-                for (int by = 8; by < kWave; by <<= 1) {
-                    acc.x += __shfl_xor(acc.x, by, kWave);
-                    acc.y += __shfl_xor(acc.y, by, kWave);
-                }
-                if (lane < 8u) {
-                    s_sum[buf][w][col_lane][0] = acc.x;
-                    s_sum[buf][w][col_lane][1] = acc.y;
-                }
-                __syncthreads();
-                acc = D2{0, 0};
-#pragma unroll
-                for (int v = 0; v < kHeavyWaves; ++v) {
-                    acc.x += s_sum[buf][v][col_lane][0];
-                    acc.y += s_sum[buf][v][col_lane][1];
-                }
+                acc = heavy_total(acc, sh.ex[buf], w);
                 buf ^= 1u;
                 if (Rule<MODE>::combine) {
                     state = acc;
@@ -1380,7 +1663,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
             *(float2 *)(a.PE + (size_t)g * D + col) = narrow2(pe);
             *(float2 *)(a.PA + (size_t)g * D + col) = narrow2(pa);
         }
-        __syncthreads();                                            // s_sum and s_job are free for the next job
+        __syncthreads();                                            // what is in LDS is free for the next job
     }
 }
 
@@ -1430,12 +1713,13 @@ void launch_bucket_apply(const BucketScratch &bs, Header *hdr, const Geometry &g
     BucketArgs a;
     a.E = E; a.A = A; a.PE = PE; a.PA = PA; a.grads = grads; a.geo = g;
     a.keys = keys; a.items = bs.items; a.tmp = bs.tmp; a.dense = bs.dense; a.table = bs.table;
-    a.tile_cnt = bs.tile_cnt; a.tile_bad = bs.tile_bad; a.heavy = bs.heavy; a.hdr = hdr;
+    a.tile_cnt = bs.tile_cnt; a.tile_bad = bs.tile_bad; a.heavy = bs.heavy; a.split = bs.split; a.hdr = hdr;
     a.load_data = load_data; a.load_parity = load_parity;
     a.n = n; a.tile = p.ipt * kPartThreads; a.tiles = p.tiles; a.buckets = p.buckets;
     a.packed = src == kWaitingUpdates ? 1u : 0u;
     a.heavy_run = heavy_run(n);
     a.shared_stripe = shared_stripe(n, g.k);
+    a.split_stripe = split_stripe(n, g.D);
     const bool heavy = n >= kHeavyRunMin;
     ECRM_DISPATCH(bucket_apply_for, a, PE != nullptr, heavy, cus, st);
 }

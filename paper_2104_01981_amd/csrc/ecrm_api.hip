@@ -15,7 +15,8 @@ struct Layout {
     size_t bytes;
     size_t off_cnt, off_keys[2], off_vals[2], off_hist, off_bintotal, off_long_slot, off_long_meta,
         off_piece_slot, off_partial, off_partial2, off_long_res, off_active;
-    size_t off_table, off_tile_cnt, off_tile_bad, off_tmp, off_heavy, off_hold_tiles;   // the bucket path's, over the others
+    size_t off_table, off_tile_cnt, off_tile_bad, off_tmp, off_heavy, off_hold_tiles, off_split_run, off_split_tiles,
+        off_segment_run, off_summed, off_arrived, off_sums, off_steps;    // the bucket path's, over the others
 };
 
 // The caller's device arrays one update works on.
@@ -72,7 +73,7 @@ static bool divider_ok(const Divider &v)
     return true;
 }
 
-static Layout make_layout(uint32_t max_batch, uint32_t D, uint32_t S, bool has_partial2)
+static Layout make_layout(uint32_t max_batch, uint32_t D, uint32_t k, uint32_t S, bool has_partial2)
 {
     Layout l;
     l.max_batch = max_batch;
@@ -118,6 +119,14 @@ static Layout make_layout(uint32_t max_batch, uint32_t D, uint32_t S, bool has_p
     l.off_tmp = take((size_t)nb * 8);
     l.off_heavy = take(((size_t)nb / kHeavyRunMin + 64) * 2 * 4);
     l.off_hold_tiles = take(((size_t)nb / kHoldTile + 1) * 4);
+    const size_t segments = split_segments(nb, k), groups = (D + 15) / 16, split_runs = segments ? kHotBuckets : 0;
+    l.off_split_run = take(split_runs * sizeof(SplitRun));
+    l.off_split_tiles = take(split_runs * kSplitTileWords * 4);
+    l.off_segment_run = take(segments * 4);
+    l.off_summed = take(segments * groups * 4);
+    l.off_arrived = take((split_runs / k) * groups * 4);
+    l.off_sums = take(segments * D * sizeof(double));
+    l.off_steps = take(segments * D * sizeof(double));
     l.bytes = off > general_end ? off : general_end;
     return l;
 }
@@ -134,6 +143,13 @@ static BucketScratch carve_buckets(const Layout &l, const Scratch &s)
     r.tmp = (unsigned long long *)(b + l.off_tmp);
     r.heavy = (uint32_t *)(b + l.off_heavy);
     r.hold_tiles = (uint32_t *)(b + l.off_hold_tiles);
+    r.split.run = (SplitRun *)(b + l.off_split_run);
+    r.split.tiles = (uint32_t *)(b + l.off_split_tiles);
+    r.split.segment_run = (uint32_t *)(b + l.off_segment_run);
+    r.split.summed = (uint32_t *)(b + l.off_summed);
+    r.split.arrived = (uint32_t *)(b + l.off_arrived);
+    r.split.sums = (double *)(b + l.off_sums);
+    r.split.steps = (double *)(b + l.off_steps);
     return r;
 }
 
@@ -222,8 +238,8 @@ int ecrm_create(const ecrm_config *cfg, ecrm_ctx **out)
     c->key_bits = 1;
     while (c->key_bits < 32 && (1ull << c->key_bits) < cfg->rows) ++c->key_bits;
     c->has_partial2 = cfg->optimizer == ECRM_OPT_MOMENTUM && !cfg->combine;
-    c->lay = make_layout((uint32_t)cfg->max_batch, cfg->dim, cfg->servers, c->has_partial2);
-    c->slay = make_layout(ECRM_STATIC_MAX_BATCH, cfg->dim, cfg->servers, c->has_partial2);
+    c->lay = make_layout((uint32_t)cfg->max_batch, cfg->dim, cfg->k, cfg->servers, c->has_partial2);
+    c->slay = make_layout(ECRM_STATIC_MAX_BATCH, cfg->dim, cfg->k, cfg->servers, c->has_partial2);
     *out = c;
     return ECRM_OK;
 }
@@ -315,12 +331,13 @@ int ecrm_route(ecrm_ctx *c, const uint64_t *keys, uint64_t n, uint64_t *stripe, 
 }
 
 // Which way a batch goes.  Up to kBucketMaxBatch updates the buckets' three launches beat the sort's and the chains'
-// thirteen to twenty; gradient propagation groups the batch twice, and a caller that has set the chain tiers' knob wants
-// those tiers: both take the general path, as do more servers than the per-tile counts are kept for.
+// thirteen to twenty, but for large batches on a handful of rows (bucket_plan.h); gradient propagation groups the batch
+// twice, and a caller that has set the chain tiers' knob wants those tiers: both take the general path, as do more servers
+// than the per-tile counts are kept for.
 static bool takes_buckets(const ecrm_ctx *c, uint32_t n)
 {
-    return n <= kBucketMaxBatch && c->cfg.propagation != ECRM_PROP_GRADIENT && c->cfg.servers <= kBucketMaxServers &&
-           !c->tune_mid_min_rows;
+    return n <= kBucketMaxBatch && (n <= kFewRowsBatch || c->cfg.rows >= kFewRows) && c->cfg.propagation != ECRM_PROP_GRADIENT &&
+           c->cfg.servers <= kBucketMaxServers && !c->tune_mid_min_rows;
 }
 
 // One batch through the whole pipeline, on tables t with scratch s (laid out by l).  During a recovery,

@@ -72,7 +72,8 @@ struct Header {
     uint32_t n_active;     // groups of sorted positions the apply kernel has work for (cleared by reset)
     uint32_t n_heavy;      // stripes the bucket kernel left to heavy_stripes (cleared by the partition)
     uint32_t heavy_ticket; // next of its jobs to be handed out (cleared by the partition)
-    uint32_t pad[40];
+    uint32_t n_segments;   // segments of runs that heavy_stripes cuts up (cleared by the partition)
+    uint32_t pad[39];
 };
 static_assert(sizeof(Header) == 256, "header is one 256-byte block");
 
@@ -93,6 +94,17 @@ struct Scratch {           // device pointers carved out of the caller's scratch
     double *long_res;              // [max_slots][2][D]: sum of steps, final accumulator
 };
 
+// What the bucket kernel leaves of runs that are cut into segments, and what their workgroups leave each other.
+struct SplitRun { uint32_t first, updates; };
+constexpr uint32_t kSplitTileWords = 2 * kMaxTiles + 1;
+struct SplitScratch {
+    SplitRun *run;                 // [kHotBuckets] by hot bucket
+    uint32_t *tiles;               // [kHotBuckets][kSplitTileWords]: updates in earlier tiles; where each tile's lie
+    uint32_t *segment_run;         // [segments]
+    uint32_t *summed;              // [segments][ceil(D / 16)]: its sum is there
+    uint32_t *arrived;             // [kHotMax][ceil(D / 16)]: segments of the stripe that are done
+    double *sums, *steps;          // [segments][D]
+};
 // The bucket path's arrays: they lie where the general path keeps its own (a call takes one path or the other).
 struct BucketScratch {
     unsigned long long *items, *dense, *tmp;   // [n] each
@@ -101,6 +113,7 @@ struct BucketScratch {
     uint32_t *tile_bad;            // [tiles]
     uint32_t *heavy;               // [2 * (n / kHeavyRunMin + 64)]
     uint32_t *hold_tiles;          // tile counts of the hold-back kernels
+    SplitScratch split;            // for batches of kSplitStripeMin updates or more
 };
 
 // Division of 32-bit numbers by a divisor fixed for the life of a context (k, S, stripes per chunk):

@@ -18,6 +18,7 @@ uint32_t plan_buckets(uint32_t n) { return bucket_plan(n).buckets; }
 uint32_t plan_heavy_run(uint32_t n) { return heavy_run(n); }
 uint32_t plan_bucket_cap() { return kBucketCap; }
 uint32_t plan_heavy_stripe(uint32_t k) { return heavy_stripe(k); }
+uint32_t plan_split_stripe(uint32_t n, uint32_t D) { return split_stripe(n, D); }
 uint32_t plan_shared_stripe(uint32_t n, uint32_t k) { return shared_stripe(n, k); }
 uint32_t plan_hot_hits(uint32_t n) { return hot_hits(n); }
 uint32_t plan_sample(uint32_t n, uint32_t *at)
@@ -61,6 +62,10 @@ def heavy_stripe(k):
 
 def shared_stripe(n, k):
     return int(lib().plan_shared_stripe(C.c_uint32(n), C.c_uint32(k)))
+
+
+def split_stripe(n, D):
+    return int(lib().plan_split_stripe(C.c_uint32(n), C.c_uint32(D)))
 
 
 def mix(stripes):

@@ -195,3 +195,37 @@ def test_stripes_shared_by_a_workgroup(D, k, S, n, parity, opt, comb):
     keys = rng.permutation(np.concatenate([keys, rng.integers(0, R, n - len(keys))])).astype(np.uint64)
     c = Case(R, D, k, S, max_batch=n, seed=79, optimizer=opt, momentum=0.9, combine=comb, propagation=0 if parity else 2)
     _check(c, keys, 79, f"shared {(D, k, n, parity, opt, comb)}")
+
+
+@pytest.mark.parametrize("opt,comb", RULES)
+@pytest.mark.parametrize("R,D,k,S,n,hot", [
+    (4 * 64, 36, 4, 5, 8203, 1.0), (4 * 64, 36, 4, 5, 8204, 1.0), (4 * 64, 132, 4, 5, 10 * 1024 + 1, 1.0), (1, 16, 1, 2, 1 << 16, 1.0),
+    (4 * 5000, 128, 4, 5, 70001, 0.5), (10 * 100, 20, 10, 11, 200003, 0.9), (63 * 3, 8, 63, 64, 50000, 0.0), (7 * 2, 1024, 7, 8, 30000, 1.0),
+    (200, 4, 4, 5, 1 << 19, 0.6)])
+def test_runs_cut_into_segments(R, D, k, S, n, hot, opt, comb):
+    """One row with a share of the batch, few rows with all of it: around the stripe length from which runs are cut into
+    segments, runs of whole segments and of one update more, entries without an update in such a stripe.  Against the
+    oracle, and twice from the same start, which has to give the same bits."""
+    rng = np.random.default_rng(n)
+    keys = rng.integers(0, R, n)
+    keys[rng.random(n) < hot] = R // 2
+    keys[:3 * k] = np.concatenate([np.arange(k), np.full(2 * k, R - 1)])
+    assert (np.bincount(keys // k).max() >= bp.split_stripe(n, D)) == (n != 8203)
+    keys = rng.permutation(keys).astype(np.uint64)
+    c = Case(R, D, k, S, max_batch=n, seed=97, optimizer=opt, momentum=0.9, combine=comb)
+    kt, g = torch.from_numpy(keys.view(np.int64)).cuda(), grads_for(97, 0, n, D)
+    tables = (c.E, c.A, c.PE, c.PA, c.ld, c.lp)
+    start, runs = [t.clone() for t in tables], []
+    for _ in range(3):
+        for t, s in zip(tables, start):
+            t.copy_(s)
+        c.ctx.update(kt, g)
+        runs.append([t.clone() for t in tables])
+    for other in runs[1:]:
+        for a, b in zip(runs[0], other):
+            assert torch.equal(a, b)
+    c.oracle_update(keys, g)
+    counts = np.bincount(keys.astype(np.int64))
+    stats = c.ctx.batch_stats()
+    assert stats["long_rows"] == int((counts > 1024).sum()) and stats["long_items"] == int(counts[counts > 1024].sum())
+    log("segments", (R, D, k, n, hot, opt, comb), c.compare("segments"))
