@@ -1,27 +1,20 @@
-"""The bucket path (batches of up to 2^19 updates) against the oracle where it can go wrong: runs around the 64 updates
-above which a workgroup's waves share a stripe, stripes around the 512 updates above which one of an oversized bucket is
-split over the columns, buckets around the 1024 items LDS takes, tiles and bucket counts at their edges, every rule,
-row widths with and without a remainder, with and without parities.  Tolerance: that of Case.compare (fp64 chains
-rounded once on both sides; a re-association moves a value across a rounding boundary with probability ~1e-6)."""
+"""The bucket path (batches of up to 2^19 updates) against the oracle where it can go wrong: runs around the 64 positions of a
+wave's window and the 128 to 256 updates of a run that may make its stripe heavy, stripes around the lengths from which
+they are shared by a workgroup, heavy, or cut into segments, buckets around the 1536 items LDS takes, tiles and bucket
+counts at their edges, every rule, row widths with and without a remainder, with and without parities.  Tolerance: that
+of Case.compare (fp64 chains rounded once on both sides; a re-association moves a value across a rounding boundary with
+probability ~1e-6)."""
 import numpy as np
 import pytest
 import torch
 
 import bucket_plan as bp
+import oracle
 import synth_inputs as si
 from ecrm_case import Case, grads_for, log
+from oracle.recovery_session import RecoverySession
 
 pytestmark = pytest.mark.gpu
-
-
-def _mix32(g):
-    m = 0xFFFFFFFF
-    g = g.astype(np.uint64)
-    g ^= g >> np.uint64(16)
-    g = (g * np.uint64(0x9E3779B1)) & np.uint64(m)
-    g ^= g >> np.uint64(15)
-    g = (g * np.uint64(0xD1B54A33)) & np.uint64(m)
-    return g ^ (g >> np.uint64(16))
 
 
 def _check(c, keys, seed, what):
@@ -60,6 +53,8 @@ def test_runs_and_stripes_around_the_thresholds(D, k, S, opt, comb):
 @pytest.mark.parametrize("R,D,k,S,n", [
     (4 * 5000, 128, 4, 5, 2049), (4 * 5000, 128, 4, 5, 32 * 512 + 1), (4 * 100000, 8, 4, 5, (1 << 17) + 1),
     (4 * 60000, 8, 4, 5, 1 << 18), (4 * 60000, 4, 4, 5, (1 << 18) + 1), (2 * 60000, 12, 2, 3, (1 << 19) - 1),
+    (2 * 60000, 12, 2, 3, 1 << 19), (2 * 60000, 12, 2, 3, (1 << 19) + 1), (4 * 31, 12, 4, 5, 1 << 18), (4 * 31, 12, 4, 5, (1 << 18) + 1),
+    (4 * 32, 12, 4, 5, (1 << 18) + 1),
     (63 * 30, 1024, 63, 64, 5000), (7, 64, 7, 8, 4000), (1 << 20, 128, 4, 5, 33)])
 def test_sizes_at_the_edges_of_the_plan(R, D, k, S, n, prop):
     c = Case(R, D, k, S, max_batch=n, seed=47, propagation=prop)
@@ -67,20 +62,30 @@ def test_sizes_at_the_edges_of_the_plan(R, D, k, S, n, prop):
 
 
 @pytest.mark.parametrize("opt,comb", RULES)
-def test_one_bucket_gets_everything(opt, comb):
-    """Keys chosen so that their stripes fall into one bucket of the plan: more stripes than the LDS table of an
-    oversized bucket holds, so the bucket is worked off in parts, light and heavy stripes in each."""
-    D, k, S, R = 20, 4, 5, 4 * (1 << 20)
-    n = 40000
-    buckets = n // 32
-    g = np.arange(R // k, dtype=np.uint64)
-    mine = g[(_mix32(g) * np.uint64(buckets)) >> np.uint64(32) == 7]
-    assert len(mine) > 800
+@pytest.mark.parametrize("D,k,S", [(20, 4, 5), (12, 10, 11)])
+def test_one_bucket_gets_everything(D, k, S, opt, comb):
+    """Keys whose stripes all fall into one bucket of the plan: more stripes than the 640 that the LDS table of an oversized
+    bucket may hold, so that it is worked off in parts, and more heavy ones than the 16 that a part may have, of 256 updates
+    (the fewest) to more than a list takes; none of them hot in the sample."""
+    n, stripes = 40000, 1 << 20
+    g = np.arange(stripes, dtype=np.uint32)
+    mine = g[bp.bucket_of(g, n) == 7]
     rng = np.random.default_rng(3)
-    stripes = np.concatenate([rng.permutation(mine)[:800].repeat(40), np.full(n - 32000 - 2000, mine[0]), np.full(2000, mine[-1])])
-    keys = rng.permutation(stripes * np.uint64(k) + rng.integers(0, k, n).astype(np.uint64))
-    c = Case(R, D, k, S, max_batch=n, seed=53, optimizer=opt, momentum=0.9, combine=comb)
-    _check(c, keys, 53, f"one bucket {(opt, comb)}")
+    mine = rng.permutation(mine)
+    assert len(mine) > 760
+    limit = bp.heavy_stripe(k)
+    heavy = [limit - 1, limit, limit + 1, 300, 511, 512, 513, bp.bucket_cap(), bp.bucket_cap() + 1, 2500] + [400] * 12
+    light = mine[len(heavy):]
+    sampled = bp.sample_positions(n)
+    rest = rng.permutation(np.setdiff1d(np.arange(n), sampled))
+    at = np.empty(n, np.int64)
+    at[sampled] = light[np.arange(len(sampled)) % len(light)]                   # the sample sees light stripes, each once
+    fill = np.repeat(mine[:len(heavy)], heavy)
+    at[rest] = np.concatenate([fill, light[np.arange(len(rest) - len(fill)) % len(light)]])
+    keys = at * k + rng.integers(0, k, n)
+    assert len(np.unique(at)) > 640 and len(bp.hot_stripes(keys, k)) == 0
+    c = Case(k * stripes, D, k, S, max_batch=n, seed=53, optimizer=opt, momentum=0.9, combine=comb)
+    _check(c, keys.astype(np.uint64), 53, f"one bucket {(k, opt, comb)}")
 
 
 def test_two_runs_are_bit_identical():
@@ -229,3 +234,38 @@ def test_runs_cut_into_segments(R, D, k, S, n, hot, opt, comb):
     stats = c.ctx.batch_stats()
     assert stats["long_rows"] == int((counts > 1024).sum()) and stats["long_items"] == int(counts[counts > 1024].sum())
     log("segments", (R, D, k, n, hot, opt, comb), c.compare("segments"))
+
+
+def test_replay_through_the_sort_of_updates_held_back_by_the_buckets():
+    """A recovery buffer of more than 2^19 updates: its replay goes through the sort, the updates before and after through
+    buckets, on the same scratch buffer."""
+    R, D, k, S, server, chunks, n, cap = 4 * 900, 20, 4, 5, 1, 3, 9000, (1 << 19) + 5
+    c = Case(R, D, k, S, max_batch=cap, seed=101)
+    c.ctx.fail_server(server)
+    oracle.fail_server(c.hE, c.hA, c.hPE, c.hPA, k, S, server)
+    bk, bg = torch.empty(2 * cap, dtype=torch.int64, device="cuda"), torch.empty(2 * cap, D, device="cuda")
+    c.ctx.recovery_begin(server, chunks, bk, bg, cap)
+    ses = RecoverySession(c.hE, c.hA, c.hPE, c.hPA, k, S, c.lr, c.eps, server, chunks, cap, c.hld, c.hlp, threads=8)
+    first = 0
+
+    def update():
+        nonlocal first
+        keys, g = si.zipf_keys(101, first, n, 1 << 14, 1 << 14) % np.uint64(R), grads_for(101, first, n, D)
+        first += n
+        c.ctx.update(torch.from_numpy(keys.view(np.int64)).cuda(), g)
+        assert ses.update(keys, g.cpu().numpy())
+
+    for _ in range(ses.chunks):
+        update()
+        c.ctx.recovery_lock()
+        ses.lock()
+        update()
+        c.ctx.recovery_decode()
+        ses.decode()
+        assert c.ctx.recovery_state()["buffered"] == len(ses.buf_keys) > 0
+        c.ctx.recovery_unlock()
+        ses.unlock()
+        update()
+    assert not c.ctx.recovery_state()["active"]
+    update()
+    log("replay through the sort", c.compare("replay through the sort"))

@@ -1,5 +1,5 @@
-"""recovery_read where its walk of the waiting updates can go wrong: runs around the 64 places it looks at together and the 8
-gradients it has in flight, the first and the last waiting entry, entries beside them with none, one waiting update in
+"""recovery_read where its walk of the waiting updates can go wrong: runs around the 64 places it looks at together and the
+16 gradients it has in flight, the first and the last waiting entry, entries beside them with none, one waiting update in
 all, repeated requests, without accumulators.  Against the protocol oracle, with the tolerance of a chain that the
 library sums in one piece (rounded once on both sides)."""
 import numpy as np
@@ -13,7 +13,7 @@ from oracle.recovery_session import RecoverySession
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("lens", [[1], [64], [1, 7, 8, 9, 63, 64, 65, 127, 128, 129, 500]])
+@pytest.mark.parametrize("lens", [[1], [64], [1, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 500]])
 @pytest.mark.parametrize("R,D,k,S,server,opt", [(4 * 3000, 128, 4, 5, 2, 0), (10 * 400, 200, 10, 11, 7, 1)])
 def test_runs_of_waiting_updates(R, D, k, S, server, opt, lens):
     rng = np.random.default_rng(len(lens))
