@@ -393,7 +393,6 @@ static int run_update(ecrm_ctx *c, const Tables &t, const Scratch &s, const Layo
         // arrival order.
         Geometry gp = c->geo;
         gp.k = 1;
-        gp.dk = make_divider(1);
         int bits = 1;
         while (bits < 32 && (1ull << bits) < c->cfg.rows / c->cfg.k) ++bits;
         if (ev) (void)hipEventRecord(ev[3], st);
@@ -490,8 +489,10 @@ int ecrm_update_static(ecrm_ctx *c, float *E, float *A, float *PE, float *PA, ui
     t.load_parity = (unsigned long long *)load_parity;
     RecoveryView none;
     memset(&none, 0, sizeof(none));
-    // the array keeps the last call's contents: the reset kernel clears every field of the header,
-    // the per-server counts and (clear_sticky) the status word; everything else is written before it is read
+    // The array keeps the last call's contents.  A batch through buckets has the status word (clear_sticky) and the fields of
+    // the header that its kernels and ecrm_batch_stats read set by the partition, and reads none of the others; a batch
+    // through the sort has all of the header and the per-server counts cleared by the reset kernel.  Everything else is
+    // written before it is read.
     rc = run_update(c, t, s, c->slay, none, true, kCallerBatch, keys, grads, (uint32_t)n, st);
     if (rc == ECRM_OK && rejected) {
         hipLaunchKernelGGL(publish_rejected_kernel, dim3(1), dim3(64), 0, st, s.hdr, rejected);
