@@ -32,13 +32,16 @@ constexpr uint32_t kBucketCap = 1536;
 constexpr uint32_t kBucketMaxServers = 64;   // per-tile load counts are kept for at most this many servers
 constexpr uint32_t kBucketChunk = 8;         // sorted positions whose stripes a wave owns at a time
 // A stripe that does not end inside a window of 64 positions leaves its bucket for heavy_stripes, which splits it over the
-// columns, if one run of heavy_run(n) updates or more makes up more than half of it: the wave that owns it would need a
-// quarter of a microsecond for each.  One whose updates are spread over its entries is shared by the waves of its
-// workgroup, as long as it has fewer than shared_stripe(n, k) updates: sharing costs little of the chip's time but takes
-// as long as its longest runs, a heavy stripe takes ~6 us for every entry in each of its D / 16 workgroups however short
-// its run is, so that few of them are a gain and many a loss.  The limits lie where batches of nothing but such
-// stripes break even: 256 updates in one of 2^14, 512 in one of 2^16, 1448 in one of 2^19 (2^19 on 2^11 rows, D = 512: 1877 us
-// when runs of 256 were always heavy, 557 shared); 16 updates to an entry (2^14 on 2520 rows, k = 63: 281 and 63 us).
+// columns, if it has a run of heavy_run(n) updates: the wave that owns it would need a quarter of a microsecond for each.  A
+// heavy stripe takes ~6 us for every entry in each of its D / 16 workgroups, however short its run is, so that few of them
+// are a gain and many a loss.  In a batch of many long stripes -- more than kManyHot hot ones in the sample: a small table --
+// a stripe that no run dominates is shared by the waves of its workgroup instead, as long as it has fewer than
+// shared_stripe(n, k) updates: that costs little of the chip's time but takes as long as its longest runs.  That limit lies
+// where batches of nothing but such stripes break even: 256 updates in one of 2^14, 512 in one of 2^16, 1448 in one of 2^19
+// (2^19 on 2^11 rows, D = 512: 1877 us when runs of 256 were always heavy, 557 shared); 16 updates to an entry (2^14 on 2520
+// rows, k = 63: 281 and 63 us).  kManyHot lies between Zipf batches, of up to ~25 hot stripes (2^16 updates: 88 us with their
+// long stripes shared, 80 with them heavy), and tables of a few hundred stripes, of 36 or more (2^16 on 1024 rows: 75 and 99).
+constexpr uint32_t kManyHot = 32;
 constexpr uint32_t kHeavyRunMin = 128, kHeavyStripeMin = 256, kHeavyEntryMin = 16;
 ECRM_HD uint32_t heavy_run(uint32_t n) { return n / 2048u > kHeavyRunMin ? n / 2048u : kHeavyRunMin; }
 // of a stripe that makes its bucket too long for LDS
@@ -50,7 +53,7 @@ ECRM_HD uint32_t shared_stripe(uint32_t n, uint32_t k)
         if ((root + bit) * (root + bit) <= 4u * n) root += bit;
     return root > heavy_stripe(k) ? root : heavy_stripe(k);
 }
-static_assert(kHeavyEntryMin * 64u <= kBucketCap, "a stripe that is not heavy fits a list");
+static_assert(kHeavyEntryMin * 64u <= kBucketCap && 4u * kBucketMaxBatch < kBucketCap * kBucketCap, "a stripe that is not heavy fits a list");
 // A stripe of the sample with split_stripe(n, D) updates has its runs cut into segments, which go to as many workgroups as
 // there are; a shorter one is walked by D / 16 workgroups, in rounds of kSplitSegment updates.  A round takes 3.5 us and a
 // segment 17, so that a batch of nothing but such stripes breaks even where a stripe's rounds take as long as all the

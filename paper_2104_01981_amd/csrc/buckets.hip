@@ -179,21 +179,14 @@ __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uin
                 }
             }
             // One branch for the step, none for its updates, whose square roots then overlap: a missing one is a zero
-            // gradient, which leaves sums and steps alone.  Momentum takes no such step: its chain is kept as it was (a
-            // rate of zero would make NaN of an infinite velocity).
+            // gradient, which leaves sums and steps alone.  Momentum takes no such step (a decay would change its velocity,
+            // and a rate of zero make NaN of an infinite one) and has no square roots: there it is left out.
             if (cnt[s]) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const bool there = MODE != kMomentumSeq || (uint32_t)u < cnt[s];
+                    if (MODE == kMomentumSeq && (uint32_t)u >= cnt[s]) break;
 #pragma unroll
-                    for (int i = 0; i < NC; ++i) {
-                        D2 G = w.G[i], acc = w.acc[i];
-                        item2<MODE>(G, acc, l[s].g[u][i], rp);
-                        w.G[i].x = there ? G.x : w.G[i].x;
-                        w.G[i].y = there ? G.y : w.G[i].y;
-                        w.acc[i].x = there ? acc.x : w.acc[i].x;
-                        w.acc[i].y = there ? acc.y : w.acc[i].y;
-                    }
+                    for (int i = 0; i < NC; ++i) item2<MODE>(w.G[i], w.acc[i], l[s].g[u][i], rp);
                 }
             }
             if (PARITY) {
@@ -585,6 +578,7 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
         h->n_heavy = 0;
         h->n_segments = 0;
         h->heavy_ticket = 0;
+        h->n_hot = n >= kSample * 4u ? s_hot.n_cand : 0u;
         for (uint32_t c = 0; c < kMidClasses; ++c) h->n_mid[c] = 0;
     }
 }
@@ -644,7 +638,7 @@ struct ListShared {
 // Applies every stripe of a sorted list of m items (m <= kBucketCap).  Chunks of CH positions are handed to the waves as
 // they come free; a wave owns the stripes that open in its chunk.  A stripe that does not end inside the wave's
 // 64-position window
-//   - is only listed in sh.heavy if it has a run of heavy_run updates and that makes up more than half of it, or if it has
+//   - is only listed in sh.heavy if it has a run of heavy_run updates and that makes up more than half of it, or it has
 //     shared_stripe updates;
 //   - is walked by the whole workgroup afterwards if its updates are spread over entries with several each (s_part: room
 //     for walk_long_stripe);
@@ -1092,6 +1086,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
         len = (uint32_t)row[1] - row[0];
         if (hot && b - member + k <= B) stripe_len = (uint32_t)row[k - member] - row[-(int)member];
     }
+    const bool many = a.hdr->n_hot > kManyHot;                       // long stripes
     const bool full = a.hdr->batch_bad != 0;                        // the recovery buffer could not take its part
     key_bad = __syncthreads_or(key_bad);
     if (key_bad || full) {
@@ -1104,7 +1099,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
     uint32_t m;
     if (hot) {
         bucket_excl_scan(stripe_len, sh.wave, m);
-        if (m < a.shared_stripe) {
+        if (m < (many ? a.shared_stripe : max(a.shared_stripe / 2u, heavy_stripe(k)))) {
             // no stripe, or one that is not as long as the sample made it look: its entries' buckets lie side by side in
             // every tile, so the first workgroup takes them as one ordinary bucket
             if (member != 0 || m == 0) return;
@@ -1181,7 +1176,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
                 __syncthreads();
             }
             if (Rule<MODE>::combine) count_list(a.geo, sh.item, list, sh.list.srv, a.load_data, a.load_parity);
-            apply_list<NC, MODE, PARITY, kBucketChunk>(a, sh.item, list, a.heavy_run, a.shared_stripe, sh.list, (double *)sh.tmp);
+            apply_list<NC, MODE, PARITY, kBucketChunk>(a, sh.item, list, a.heavy_run, many ? a.shared_stripe : 0u, sh.list, (double *)sh.tmp);
             const uint32_t nh = uniform(sh.list.n_heavy);
             if (nh && !have_base) {
                 bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, base);
@@ -1552,18 +1547,18 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
     const uint32_t ncg = (D + kHeavyCols - 1) / kHeavyCols;
     const RuleParams rp = rule_params(a.geo);
     // jobs are handed out as workgroups come free: their lengths differ by orders of magnitude
-    for (;;) {
+    auto next_job = [&]() {
         if (threadIdx.x == 0) sh.job = atomicAdd(&a.hdr->heavy_ticket, 1u);
         __syncthreads();
-        uint32_t job = uniform(sh.job);
-        if (job >= (ns + nh) * ncg) break;
-        if (job < ns * ncg) {                                       // the segments first, in order: heavy_segment relies on it
-            heavy_segment<MODE, PARITY>(a, sh, job / ncg, job % ncg);
-            __syncthreads();
-            continue;
-        }
-        job -= ns * ncg;
-        const uint32_t h = job / ncg, cg = job - h * ncg;
+        return uniform(sh.job);
+    };
+    uint32_t job = next_job();
+    for (; job < ns * ncg; job = next_job()) {                      // the segments first, in order: heavy_segment relies on it
+        heavy_segment<MODE, PARITY>(a, sh, job / ncg, job % ncg);
+        __syncthreads();
+    }
+    for (; job < (ns + nh) * ncg; job = next_job()) {
+        const uint32_t h = job / ncg - ns, cg = job % ncg;
         const uint32_t start = a.heavy[2 * h], what = a.heavy[2 * h + 1], end = start + (what & ~kCounted);
         const u64 *items = a.dense;
         const uint32_t col = cg * kHeavyCols + 2u * col_lane;

@@ -73,7 +73,8 @@ struct Header {
     uint32_t n_heavy;      // stripes the bucket kernel left to heavy_stripes (cleared by the partition)
     uint32_t heavy_ticket; // next of its jobs to be handed out (cleared by the partition)
     uint32_t n_segments;   // segments of runs that heavy_stripes cuts up (cleared by the partition)
-    uint32_t pad[39];
+    uint32_t n_hot;        // stripes that the sample took for hot (set by the partition)
+    uint32_t pad[38];
 };
 static_assert(sizeof(Header) == 256, "header is one 256-byte block");
 

@@ -164,7 +164,7 @@ def test_stripes_taken_for_hot_by_chance(n, D, k, S, opt, comb):
     keys = rng.integers(k * 16, R, n)
     off = rng.permutation(np.setdiff1d(np.arange(n), at))
     at = rng.permutation(at)
-    limit = bp.shared_stripe(n, k)
+    limit = max(bp.shared_stripe(n, k) // 2, bp.heavy_stripe(k))               # few of them are hot
     totals = [hits, hits + 1, 100, 128, 200, limit - 1, limit, limit + 1, limit + 50]
     for g, total in enumerate(totals):
         mine, at, off = np.concatenate([at[:hits], off[:total - hits]]), at[hits:], off[total - hits:]
@@ -178,11 +178,12 @@ def test_stripes_taken_for_hot_by_chance(n, D, k, S, opt, comb):
 @pytest.mark.parametrize("opt,comb", RULES)
 @pytest.mark.parametrize("D,k,S,n", [(128, 4, 5, 30000), (300, 2, 3, 60000), (36, 10, 11, 20000), (1024, 3, 5, 20000),
                                      (8, 63, 64, 40000), (64, 1, 2, 20000)])
-@pytest.mark.parametrize("parity", [True, False])
-def test_stripes_shared_by_a_workgroup(D, k, S, n, parity, opt, comb):
+@pytest.mark.parametrize("parity,many", [(True, True), (True, False), (False, True)])
+def test_stripes_shared_by_a_workgroup(D, k, S, n, parity, many, opt, comb):
     """Stripes that do not end inside a window of 64 positions: around the window, around four updates to an entry from which
     they are shared, around the length from which they are not any more; spread evenly, with one run of half and of more
-    than half of them, with an untouched entry, and with a run long enough to be heavy in a stripe that it dominates or not."""
+    than half of them, with an untouched entry, and with a run long enough to be heavy in a stripe that it dominates or not.
+    In a batch of few and of many hot stripes, which decides what becomes of such a run."""
     rng = np.random.default_rng(D + k)
     limit, run = bp.shared_stripe(n, k), bp.heavy_run(n)
     sizes = [57, 58, 63, 64, 65, 71, 4 * k - 1, 4 * k, 4 * k + 1, 128, run, 2 * run - 1, 2 * run, 2 * run + 1, limit - 1, limit, limit + 1]
@@ -196,10 +197,17 @@ def test_stripes_shared_by_a_workgroup(D, k, S, n, parity, opt, comb):
         keys.append(most + np.concatenate([np.full(size - size // 8, k // 2), rng.integers(k // 2, k, size // 8)]))
     keys = np.concatenate(keys)
     assert len(keys) < n
-    R = k * (n // 8)
-    keys = rng.permutation(np.concatenate([keys, rng.integers(0, R, n - len(keys))])).astype(np.uint64)
+    R, hits = k * (n // 8 + 40), int(bp.lib().plan_hot_hits(n))
+    at = rng.permutation(bp.sample_positions(n))[:40 * hits if many else 0]      # 40 stripes behind the others' are hot
+    rest = rng.permutation(np.setdiff1d(np.arange(n), at))
+    batch = np.empty(n, np.int64)
+    batch[at] = k * (n // 8 + np.arange(len(at)) % 40)
+    batch[rest[:len(keys)]] = keys
+    batch[rest[len(keys):]] = rng.integers(0, k * (n // 8), n - len(at) - len(keys))
+    assert (len(bp.hot_stripes(batch, k)) > 32) == many
+    keys = batch.astype(np.uint64)
     c = Case(R, D, k, S, max_batch=n, seed=79, optimizer=opt, momentum=0.9, combine=comb, propagation=0 if parity else 2)
-    _check(c, keys, 79, f"shared {(D, k, n, parity, opt, comb)}")
+    _check(c, keys, 79, f"shared {(D, k, n, parity, many, opt, comb)}")
 
 
 @pytest.mark.parametrize("opt,comb", RULES)
