@@ -27,10 +27,10 @@ LONG_RUN = 1024          # ECRM_LONG_RUN of include/ecrm.h: longer runs leave th
 # HBM bytes per launch of the apply kernel, from rocprofv3 FETCH_SIZE and WRITE_SIZE scaled by a plain copy of known
 # size (profiles/update_path_<workload>_hbm_traffic.txt).  Reported only while the code of the kernel's sources is
 # what the counters were taken on.
-TRAFFIC_BYTES_PER_LAUNCH = {"hbm_scale": 37959011840, "large_uniform": 77514076058, "large_skewed": 42567491686}
+TRAFFIC_BYTES_PER_LAUNCH = {"hbm_scale": 37958992896, "large_uniform": 77513681818, "large_skewed": 42567330509}
 TRAFFIC_SOURCES = ["paper_2104_01981_amd/csrc/update.hip", "paper_2104_01981_amd/csrc/rows.h",
                    "paper_2104_01981_amd/csrc/ecrm_internal.h"]
-TRAFFIC_SOURCES_SHA256 = "8850749e118d7d565a91d5b6ddd9ee21fe66eb208e3e985930f94a89f65f4073"
+TRAFFIC_SOURCES_SHA256 = "f257f6a948a5fbd0d6658bf9d45e51b0780c98300ecddc095c3f5987b60ead03"
 
 
 def code_digest(paths):

@@ -9,12 +9,12 @@
 //   bucket_apply      one workgroup per bucket collects the pieces in LDS, sorts them by (row, position) there and
 //                     applies the bucket's stripes.
 //   heavy_stripes     stripes with long runs: split over the columns, which are independent chains, so that each is read
-//                     once and no workgroup waits for another.
+//                     once and no workgroup waits for another -- but for very long ones, whose runs are cut up as well.
 //
 // The results are those of the general path: fp64 chains in arrival order, every touched element rounded once.
-// Measured against the general path (us a call, D = 128): 2048 updates 54 -> 21; 26 624 half Zipf 173 -> 58; 65 536
-// uniform on 2^14 rows 60 -> 50; 300 007 Zipf, combined rule 325 -> 220.  The kernels of the 26 624: partition 7.6,
-// apply 40 (97 MB, 21 us at the rate of the large batches), heavy stripes 11.
+// Measured against the general path (us a call, D = 128): 2048 updates 54 -> 19; 26 624 half Zipf 173 -> 59; 65 536
+// uniform on 2^14 rows 60 -> 46; 300 007 Zipf, combined rule 325 -> 203.  The kernels of the 26 624: partition 8.6,
+// apply 41 (97 MB, 21 us at the rate of the large batches), heavy stripes 11.
 #include "rows.h"
 
 namespace ecrm {
