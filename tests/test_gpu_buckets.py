@@ -277,3 +277,32 @@ def test_replay_through_the_sort_of_updates_held_back_by_the_buckets():
     assert not c.ctx.recovery_state()["active"]
     update()
     log("replay through the sort", c.compare("replay through the sort"))
+
+
+@pytest.mark.parametrize("opt,comb", RULES)
+def test_heavy_and_cut_up_stripes_inside_a_hip_graph(opt, comb):
+    """Replays of a captured call with a run cut into segments, heavy stripes and shared ones, each against an eager call on a
+    twin, with eager work and synchronisation in between: what a call's kernels count and hand on starts afresh."""
+    R, D, k, S, n = 4 * 2000, 36, 4, 5, 30000
+    rng = np.random.default_rng(109)
+    keys = rng.integers(0, R, n)
+    keys[::2] = 4321
+    keys[1::16] = 999
+    keys[3::32] = 1000 + rng.integers(0, 4, len(keys[3::32]))
+    keys[5::150] = 2000 + rng.integers(0, 4, len(keys[5::150]))
+    assert np.bincount(keys // k).max() >= bp.split_stripe(n, D)
+    kt, g = torch.from_numpy(keys).cuda(), grads_for(109, 0, n, D)
+    a, b = (Case(R, D, k, S, max_batch=n, seed=109, optimizer=opt, momentum=0.9, combine=comb) for _ in range(2))
+    a.ctx.update(kt, g)
+    b.ctx.update(kt, g)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        a.ctx.update(kt, g, stream=side)
+    for rep in range(4):
+        graph.replay()
+        b.ctx.update(kt, g)
+        torch.cuda.synchronize()
+        for x, y in zip((a.E, a.A, a.PE, a.PA, a.ld, a.lp), (b.E, b.A, b.PE, b.PA, b.ld, b.lp)):
+            assert torch.equal(x, y), f"replay {rep}"
+        (a.E.sum() + b.E.sum()).item()
+    assert a.ctx.status() == 0
