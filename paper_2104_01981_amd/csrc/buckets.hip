@@ -15,7 +15,7 @@
 // Measured against the general path (us a call, D = 128): 2048 updates 54 -> 19; 26 624 half Zipf 173 -> 59; 65 536
 // uniform on 2^14 rows 60 -> 46; 300 007 Zipf, combined rule 325 -> 203.  The kernels of the 26 624: partition 8.6,
 // apply 41 (97 MB, 21 us at the rate of the large batches), heavy stripes 11.
-#include "rows.h"
+#include "long_runs.h"
 
 namespace ecrm {
 
@@ -23,7 +23,6 @@ typedef unsigned long long u64;
 
 constexpr int kBucketWaves = kBucketThreads / kWave;
 constexpr int kPartWaves = kPartThreads / kWave;
-constexpr uint32_t kHeavyCols = 16;      // columns of a job of heavy_stripes
 constexpr uint32_t kLongRuns = 4;       // updates per entry from which on a stripe behind a window is walked run by run
 constexpr uint32_t kLongList = kBucketCap / (kWave - kBucketChunk);      // such stripes that a list can hold
 
@@ -1199,45 +1198,9 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
 // heavy stripes
 // ================================================================================================
 
-// (stripe, 16 columns) per workgroup: the columns of a row are independent chains, so a hot entry spreads over D / 16
-// workgroups that never wait for each other and read every gradient once (64-byte pieces).  A lane holds two columns
-// of T consecutive updates; the 64 groups of eight lanes exchange their summaries by shuffles and, across waves,
-// through LDS, and take their steps from registers: 1024 updates per round.
-constexpr int kHeavyThreads = 512;
-constexpr int kHeavyWaves = kHeavyThreads / kWave;
-
-// The decay over a number of updates, a power of mu.  One that underflows is kept at the smallest normal number unless mu
-// itself is zero: a decay of zero would make NaN of an infinite velocity, which the rule keeps infinite.  What it adds to
-// a finite one is below 1e-269, nothing in 32 bits.
-__device__ __forceinline__ double decay(double power, double mu) { return mu > 0.0 ? fmax(power, 2.2250738585072014e-308) : power; }
-
-// gradient rows of a run's updates at, at + 1 (past its end: its last update's)
-__device__ __forceinline__ void heavy_indices(const u64 *run, uint32_t L, uint32_t at, uint32_t &i0, uint32_t &i1)
-{
-    i0 = (uint32_t)run[min(at, L - 1u)];
-    i1 = (uint32_t)run[min(at + 1u, L - 1u)];
-}
-
-// two columns of the run's updates at .. at + T - 1, zeros past its end
-template <int T>
-__device__ __forceinline__ void heavy_rows(float2 (&r)[T], const float *grads, uint32_t D, uint32_t col, bool live, uint32_t i0,
-                                           uint32_t i1, uint32_t lane, uint32_t at, uint32_t L)
-{
-#pragma unroll
-    for (int u = 0; u < T; ++u) {
-        const uint32_t idx = __shfl(u & 1 ? i1 : i0, (int)((lane & 56u) + u / 2), kWave);
-        r[u] = float2{0, 0};
-        if (live && at + u < L) r[u] = *(const float2 *)(grads + (size_t)idx * D + col);
-    }
-}
-
-constexpr int kHeavyT = 16;                  // updates that a group of eight lanes takes at a time
+// (stripe, 16 columns) per workgroup: long_runs.h.
 static_assert(kSplitSegment == kHeavyThreads / 8 * kHeavyT, "a segment is one round of a workgroup");
 
-// what the waves exchange: sums (or, at the end of a run, steps) of two columns a lane, and the decay over a wave's updates
-struct HeavyExchange {
-    double sum[kHeavyWaves][8][2], dec[kHeavyWaves];
-};
 constexpr uint32_t kFoldParts = kHeavyThreads / kHeavyCols, kFoldLength = 16;       // of heavy_segment
 static_assert(kFoldParts * kFoldLength * kSplitSegment >= kBucketMaxBatch && kHeavyThreads * kSplitSegment >= kBucketMaxBatch,
               "a run's segments are folded in one go, and waited for by a thread each");
@@ -1247,91 +1210,6 @@ struct HeavyShared {
     uint32_t pref[kMaxTiles + 1], start[kMaxTiles];
     uint32_t job, last;
 };
-
-// Sums of a round: every wave leaves that of its updates in ex; returned is what lies before the lane's group inside its
-// wave, with its decay.
-template <int MODE>
-__device__ __forceinline__ D2 heavy_sums(const float2 (&gr)[kHeavyT], uint32_t cnt, const RuleParams &rp, HeavyExchange &ex,
-                                         uint32_t w, double &before_decay)
-{
-    constexpr bool kMomentum = MODE == kMomentumSeq;
-    const uint32_t lane = lane_id(), col_lane = lane & 7u;
-    D2 s = D2{-0.0, -0.0};                              // the neutral summand: +0.0 would take a -0.0's sign
-    double d = 1.0;
-#pragma unroll
-    for (int u = 0; u < kHeavyT; ++u) {
-        if ((uint32_t)u < cnt) {
-            summary2<MODE>(s, gr[u], rp);
-            if (kMomentum) d = decay(d * rp.mu, rp.mu);
-        }
-    }
-    // inclusive scan over the wave's eight groups of the maps v -> d * v + s
-#pragma unroll
-    for (int by = 8; by < kWave; by <<= 1) {
-        const double ox = __shfl_up(s.x, by, kWave), oy = __shfl_up(s.y, by, kWave);
-        const double od = kMomentum ? __shfl_up(d, by, kWave) : 1.0;
-        if (lane >= (uint32_t)by) {
-            s.x = kMomentum ? fma(d, ox, s.x) : s.x + ox;
-            s.y = kMomentum ? fma(d, oy, s.y) : s.y + oy;
-            if (kMomentum) d = decay(d * od, rp.mu);
-        }
-    }
-    if (lane >= 56u) {
-        ex.sum[w][col_lane][0] = s.x;
-        ex.sum[w][col_lane][1] = s.y;
-        if (col_lane == 0) ex.dec[w] = d;
-    }
-    D2 before = D2{__shfl_up(s.x, 8, kWave), __shfl_up(s.y, 8, kWave)};
-    before_decay = kMomentum ? __shfl_up(d, 8, kWave) : 1.0;
-    if (lane < 8u) {
-        before = D2{-0.0, -0.0};
-        before_decay = 1.0;
-    }
-    return before;
-}
-
-// behind a barrier after heavy_sums: takes `state` from the round's start to its end, returns it as the lane's group finds it
-template <int MODE>
-__device__ __forceinline__ D2 heavy_fold(D2 &state, const HeavyExchange &ex, uint32_t w, const D2 &before, double before_decay)
-{
-    constexpr bool kMomentum = MODE == kMomentumSeq;
-    const uint32_t col_lane = lane_id() & 7u;
-    D2 mine = state;
-#pragma unroll
-    for (int v = 0; v < kHeavyWaves; ++v) {
-        if ((uint32_t)v == w) mine = state;
-        const double fx = ex.sum[v][col_lane][0], fy = ex.sum[v][col_lane][1];
-        const double dv = kMomentum ? ex.dec[v] : 1.0;
-        state.x = kMomentum ? fma(dv, state.x, fx) : state.x + fx;
-        state.y = kMomentum ? fma(dv, state.y, fy) : state.y + fy;
-    }
-    mine.x = kMomentum ? fma(before_decay, mine.x, before.x) : mine.x + before.x;
-    mine.y = kMomentum ? fma(before_decay, mine.y, before.y) : mine.y + before.y;
-    return mine;
-}
-
-// sum of the groups' steps over the workgroup, for every lane; one barrier, after ex was written
-__device__ __forceinline__ D2 heavy_total(D2 acc, HeavyExchange &ex, uint32_t w)
-{
-    const uint32_t lane = lane_id(), col_lane = lane & 7u;
-#pragma unroll
-    for (int by = 8; by < kWave; by <<= 1) {
-        acc.x += __shfl_xor(acc.x, by, kWave);
-        acc.y += __shfl_xor(acc.y, by, kWave);
-    }
-    if (lane < 8u) {
-        ex.sum[w][col_lane][0] = acc.x;
-        ex.sum[w][col_lane][1] = acc.y;
-    }
-    __syncthreads();
-    acc = D2{0, 0};
-#pragma unroll
-    for (int v = 0; v < kHeavyWaves; ++v) {
-        acc.x += ex.sum[v][col_lane][0];
-        acc.y += ex.sum[v][col_lane][1];
-    }
-    return acc;
-}
 
 // ---- runs that are cut into segments -------------------------------------------------------------
 // With a batch on a handful of entries -- the smallest tables of a model, one very hot row -- a run has tens of thousands of

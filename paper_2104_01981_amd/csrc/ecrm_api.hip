@@ -605,7 +605,7 @@ int ecrm_recovery_read(ecrm_ctx *c, const uint64_t *keys, uint64_t n, float *out
     init_if_needed(c, st);
     if (!c->rv.active) {                       // no recovery in progress: a plain gather
         launch_degraded_read(c->s, c->geo, c->t.E, c->t.A, c->t.PE, c->t.PA, keys, n, ECRM_NO_SERVER, out_E, out_A,
-                             c->grid_blocks, st);
+                             c->cus, st);
         return check_launch();
     }
     // The waiting updates, grouped by entry with the update path's own sort on the list's keys.  How
@@ -616,7 +616,7 @@ int ecrm_recovery_read(ecrm_ctx *c, const uint64_t *keys, uint64_t n, float *out
     launch_sort(c->s, c->geo, none, (const uint64_t *)c->hb.list[c->buf_cur], c->hb.cap, &c->s.hdr->buf_count, kWaitingUpdates,
                 c->key_bits, false, false, &bk, &bi, st);
     launch_recovery_read(c->s, c->geo, c->rv, c->t.E, c->t.A, c->t.PE, c->t.PA, keys, n, bk, bi, &c->s.hdr->buf_count,
-                         c->hb.rows, out_E, out_A, c->grid_blocks, st);
+                         c->hb.cap, c->hb.rows, c->lay.max_batch, out_E, out_A, c->cus, st);
     return check_launch();
 }
 
@@ -650,7 +650,7 @@ int ecrm_degraded_read(ecrm_ctx *c, const uint64_t *keys, uint64_t n, uint32_t l
     if (!aligned(keys, 8) || !aligned(out_E, 16) || (out_A && !aligned(out_A, 16))) return ECRM_EINVAL;
     init_if_needed(c, (hipStream_t)stream);
     launch_degraded_read(c->s, c->geo, c->t.E, c->t.A, c->t.PE, c->t.PA, keys, n, lost_server, out_E, out_A,
-                         c->grid_blocks, (hipStream_t)stream);
+                         c->cus, (hipStream_t)stream);
     return check_launch();
 }
 

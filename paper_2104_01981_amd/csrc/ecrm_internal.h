@@ -74,7 +74,9 @@ struct Header {
     uint32_t heavy_ticket; // next of its jobs to be handed out (cleared by the partition)
     uint32_t n_segments;   // segments of runs that heavy_stripes cuts up (cleared by the partition)
     uint32_t n_hot;        // stripes that the sample took for hot (set by the partition)
-    uint32_t pad[38];
+    uint32_t n_reads;      // entries with a long waiting run that a read left to read_long_kernel (cleared by read_begin_kernel)
+    uint32_t read_ticket;  // next of its jobs to be handed out (the same)
+    uint32_t pad[36];
 };
 static_assert(sizeof(Header) == 256, "header is one 256-byte block");
 
@@ -250,8 +252,8 @@ void launch_route(const Scratch &s, const Geometry &g, const uint64_t *keys, uin
                   uint32_t *member, uint32_t *data_srv, uint32_t *parity_srv, hipStream_t st);
 void launch_recovery_read(const Scratch &s, const Geometry &g, const RecoveryView &rv, const float *E, const float *A,
                           const float *PE, const float *PA, const uint64_t *keys, uint64_t n, const uint32_t *bk,
-                          const uint32_t *bi, const uint32_t *m_dev, const float *buf_grads, float *out_E, float *out_A,
-                          int grid_blocks, hipStream_t st);
+                          const uint32_t *bi, const uint32_t *m_dev, uint32_t cap, const float *pool, uint32_t max_batch,
+                          float *out_E, float *out_A, int cus, hipStream_t st);
 void launch_clear_status(const Scratch &s, hipStream_t st);
 void launch_fail_server(const Geometry &g, float *E, float *A, float *PE, float *PA, uint32_t server,
                         int grid_blocks, hipStream_t st);
@@ -259,7 +261,7 @@ void launch_recover_server(const Geometry &g, float *E, float *A, float *PE, flo
                            int grid_blocks, hipStream_t st);
 void launch_degraded_read(const Scratch &s, const Geometry &g, const float *E, const float *A, const float *PE,
                           const float *PA, const uint64_t *keys, uint64_t n, uint32_t lost, float *out_E,
-                          float *out_A, int grid_blocks, hipStream_t st);
+                          float *out_A, int cus, hipStream_t st);
 
 // ---- small device helpers ------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & (kWave - 1); }

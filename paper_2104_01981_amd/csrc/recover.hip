@@ -1,7 +1,7 @@
 // Recovery side of ECRM (Sec. 3.4) with the r = 1 sum code of Sec. 3.2: a lost entry is the parity
 // minus the k-1 surviving entries of its stripe, a lost parity is the sum of its k entries.  All
-// kernels stream whole rows: one wavefront per stripe (or per requested key), 64 lanes x float2 per
-// 128-float slice through bounds-checked buffer resources with wave-uniform bases.
+// kernels stream whole rows: one wavefront per stripe, 64 lanes x float2 per 128-float slice through
+// bounds-checked buffer resources with wave-uniform bases.
 #include "ecrm_internal.h"
 
 namespace ecrm {
@@ -22,8 +22,6 @@ __device__ __forceinline__ void str(rsrc_t r, uint32_t slice, float2 v)
 {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)(lane_id() * 8u + slice * 512u), 0, 2);
 }
-__device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-
 __global__ __launch_bounds__(256) void fail_server_kernel(float *E, float *A, float *PE, float *PA, uint32_t stripes,
                                                           uint32_t D, uint32_t k, uint32_t S, uint32_t server)
 {
@@ -117,48 +115,6 @@ __global__ __launch_bounds__(256) void encode_kernel(const float *E, const float
     }
 }
 
-__device__ __forceinline__ void read_row(const float *T, const float *P, uint32_t x, uint32_t g, uint32_t j, bool decode,
-                                         float *out, size_t i, uint32_t D, uint32_t k)
-{
-    const uint32_t nslices = (D + 127u) / 128u;
-    const rsrc_t dst = row_of(out, i, D);
-    for (uint32_t s = 0; s < nslices; ++s) {
-        if (!decode) {
-            str(dst, s, ldr(row_of(T, x, D), s));
-            continue;
-        }
-        const float2 p = ldr(row_of(P, g, D), s);
-        double a = (double)p.x, b = (double)p.y;
-        for (uint32_t m = 0; m < k; ++m) {
-            if (m == j) continue;
-            const float2 v = ldr(row_of(T, (size_t)g * k + m, D), s);
-            a -= (double)v.x;
-            b -= (double)v.y;
-        }
-        str(dst, s, float2{(float)a, (float)b});
-    }
-}
-
-__global__ __launch_bounds__(256) void degraded_read_kernel(const float *E, const float *A, const float *PE, const float *PA,
-                                                            const uint64_t *keys, uint64_t n, uint32_t rows, uint32_t D,
-                                                            uint32_t k, uint32_t S, uint32_t lost, float *out_E, float *out_A,
-                                                            Header *hdr)
-{
-    const uint64_t w0 = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave, nw = ((uint64_t)gridDim.x * blockDim.x) / kWave;
-    for (uint64_t i = w0; i < n; i += nw) {
-        const uint64_t key = keys[i];
-        const uint32_t hi = uni((uint32_t)(key >> 32)), x = uni((uint32_t)key);
-        if (hi != 0 || x >= rows) {
-            if (lane_id() == 0) atomicOr(&hdr->err_sticky, 1u);
-            continue;
-        }
-        const uint32_t g = x / k, j = x - g * k;
-        const bool decode = lost != ECRM_NO_SERVER && (g + 1u + j) % S == lost;
-        read_row(E, PE, x, g, j, decode, out_E, i, D, k);
-        if (out_A) read_row(A, PA, x, g, j, decode, out_A, i, D, k);
-    }
-}
-
 void launch_encode(const Geometry &g, const float *E, const float *A, float *PE, float *PA,
                    int grid_blocks, hipStream_t st)
 {
@@ -195,14 +151,6 @@ void launch_recover_range(const Geometry &g, float *E, float *A, float *PE, floa
     }
     hipLaunchKernelGGL(recover_server_kernel, dim3(grid_blocks), dim3(256), 0, st, E, A, PE, PA, g_lo, g_hi, g.D, g.k, g.S,
                        server, per_wave);
-}
-
-void launch_degraded_read(const Scratch &s, const Geometry &g, const float *E, const float *A, const float *PE,
-                          const float *PA, const uint64_t *keys, uint64_t n, uint32_t lost, float *out_E,
-                          float *out_A, int grid_blocks, hipStream_t st)
-{
-    hipLaunchKernelGGL(degraded_read_kernel, dim3(grid_blocks), dim3(256), 0, st, E, A, PE, PA, keys, n, g.rows, g.D, g.k, g.S,
-                       lost, out_E, out_A, s.hdr);
 }
 
 }  // namespace ecrm

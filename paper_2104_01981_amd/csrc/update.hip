@@ -8,7 +8,7 @@
 //                   Entries that receive more than kLongRun updates in one call (the head of a skewed
 //                   key distribution) are not walked here: their totals come from chains.hip.
 //
-//   recovery_read, route, count_rows: the smaller kernels of the path.
+//   route, count_rows: the smaller kernels of the path.
 //
 // One wavefront works on one row at a time: 64 lanes x float2 = a 128-float slice, so a load
 // instruction of the wave moves 512 contiguous bytes from a wave-uniform (scalar) row address, and
@@ -584,116 +584,6 @@ __global__ __launch_bounds__(256) void count_rows_kernel(const uint32_t *sk, uin
 }
 
 // ================================================================================================
-// reads while a server is being recovered
-// ================================================================================================
-
-// Sec. 3.4 "Training during recovery" serves a locked entry that has been updated meanwhile out of
-// the buffer.  The buffer here holds updates, not entries, so the read applies them: the value
-// returned is the stored entry with its waiting updates applied in arrival order -- what the entry
-// will be once they have been replayed -- and an entry the failed server held that is not rebuilt
-// yet is first decoded from its stripe (parity minus the other members, by increasing member, rounded
-// to fp32 as the decoder stores it).  The waiting updates come grouped by entry (bk sorted, bi their
-// positions in the buffer).  One wave per requested key; nothing is modified.  Bound by the waiting runs of hot entries,
-// which every request for one walks by itself (in arrival order, so the answer is the replay's): with one update in flight
-// 65 536 Zipf requests took 470-980 us, with eight 174-360, with sixteen 157-324 (thirty-two: 159-307).
-struct ReadArgs {
-    const float *E, *A, *PE, *PA;
-    const uint64_t *keys;
-    uint64_t n;
-    const uint32_t *bk, *bi;
-    const uint32_t *m_dev;   // how many updates are waiting (device word)
-    const float *buf_grads;
-    float *out_E, *out_A;
-    Header *hdr;
-    RecoveryView rv;
-    Geometry geo;
-};
-
-template <int MODE>
-__global__ __launch_bounds__(256) void recovery_read_kernel(ReadArgs a)
-{
-    const uint32_t D = a.geo.D, k = a.geo.k, S = a.geo.S, lane = lane_id();
-    const RuleParams rp = rule_params(a.geo);
-    const uint64_t nw = wave_count();
-    const uint32_t m = uniform(*a.m_dev);
-    for (uint64_t i = wave_id(); i < a.n; i += nw) {
-        const uint64_t key = a.keys[i];
-        const uint32_t khi = uniform((uint32_t)(key >> 32)), x = uniform((uint32_t)key);
-        if (khi != 0 || x >= a.geo.rows) {
-            if (lane == 0) atomicOr(&a.hdr->err_sticky, 1u);
-            continue;
-        }
-        const uint32_t g = x / k, j = x - g * k;
-        bool decode = false;                      // the entry the failed server held, not rebuilt yet
-        if (a.rv.active) {
-            const uint32_t p = g % S;
-            if (p != a.rv.server) {
-                const uint32_t lost = (a.rv.server + S - (p + 1u) % S) % S;
-                decode = lost == j && g / a.rv.stripes_per_chunk >= a.rv.next;
-            }
-        }
-        uint32_t lo = m;                          // first waiting update of x, if it can have any
-        if (m && held_back(a.rv, x, a.geo.dk, a.geo.dS)) {
-            // 64 probes a round, the last position of as many segments: the answer lies in the first whose last is not less
-            uint32_t end = m;
-            lo = 0;
-            while (lo < end) {
-                const uint32_t step = (end - lo + kWave - 1u) / kWave, p = lo + (lane + 1u) * step - 1u;
-                const bool in = p < end;
-                lo += step * (uint32_t)__popcll(__ballot(in && a.bk[in ? p : lo] < x));
-                if (end - lo >= step) end = lo + step - 1u;
-            }
-        }
-        for (uint32_t col0 = 0; col0 < D; col0 += 128u) {
-            D2 e, s0;
-            if (decode) {
-                e = widen2(ld2<0>(row_f32(a.PE, g, D, col0), 0));
-                s0 = widen2(ld2<0>(row_f32(a.PA, g, D, col0), 0));
-                for (uint32_t mth = 0; mth < k; ++mth) {
-                    if (mth == j) continue;
-                    const D2 ve = widen2(ld2<0>(row_f32(a.E, g * k + mth, D, col0), 0));
-                    const D2 vs = widen2(ld2<0>(row_f32(a.A, g * k + mth, D, col0), 0));
-                    e.x -= ve.x; e.y -= ve.y;
-                    s0.x -= vs.x; s0.y -= vs.y;
-                }
-                e = widen2(narrow2(e));
-                s0 = widen2(narrow2(s0));
-            } else {
-                e = widen2(ld2<0>(row_f32(a.E, x, D, col0), 0));
-                s0 = widen2(ld2<0>(row_f32(a.A, x, D, col0), 0));
-            }
-            D2 G = start2<MODE>(s0), acc = D2{0, 0};
-            bool any = false;
-            for (uint32_t pos = lo; pos < m; pos += kWave) {      // 64 places at a time, U gradients in flight
-                constexpr uint32_t U = 16;
-                const bool in = pos + lane < m;
-                const uint32_t wk = in ? a.bk[pos + lane] : kNoKey, wi = in ? a.bi[pos + lane] : 0u;
-                const unsigned long long other = ~__ballot(wk == x);
-                const uint32_t cnt = other ? lowest_bit(other) : (uint32_t)kWave;     // leading run of x
-                for (uint32_t u0 = 0; u0 < cnt; u0 += U) {
-                    float2 gr[U];
-#pragma unroll
-                    for (uint32_t u = 0; u < U; ++u)
-                        gr[u] = ld2<0>(row_f32(a.buf_grads, from_lane(wi, min(u0 + u, cnt - 1u)), D, col0), 0);
-#pragma unroll
-                    for (uint32_t u = 0; u < U; ++u)
-                        if (u0 + u < cnt) item2<MODE>(G, acc, gr[u], rp);
-                }
-                any |= cnt > 0;
-                if (cnt < (uint32_t)kWave) break;
-            }
-            if (any) finish2<MODE>(G, acc, s0, rp); else G = s0;
-            const rsrc_t oe = __builtin_amdgcn_make_buffer_rsrc(a.out_E + (size_t)i * D + col0, 0, (int)((D - col0) * 4u), kRsrcFlags);
-            st2(oe, 0, narrow2(D2{e.x - acc.x, e.y - acc.y}));
-            if (a.out_A) {
-                const rsrc_t oa = __builtin_amdgcn_make_buffer_rsrc(a.out_A + (size_t)i * D + col0, 0, (int)((D - col0) * 4u), kRsrcFlags);
-                st2(oa, 0, narrow2(G));
-            }
-        }
-    }
-}
-
-// ================================================================================================
 // route
 // ================================================================================================
 
@@ -787,24 +677,6 @@ void launch_apply(const Scratch &s, const Geometry &g, const LaunchGrids &lg, fl
     ECRM_DISPATCH(apply_for, a, lg, parity, st);
 }
 #undef ECRM_DISPATCH
-
-void launch_recovery_read(const Scratch &s, const Geometry &g, const RecoveryView &rv, const float *E, const float *A,
-                          const float *PE, const float *PA, const uint64_t *keys, uint64_t n, const uint32_t *bk,
-                          const uint32_t *bi, const uint32_t *m_dev, const float *buf_grads, float *out_E, float *out_A,
-                          int grid_blocks, hipStream_t st)
-{
-    ReadArgs a;
-    a.E = E; a.A = A; a.PE = PE; a.PA = PA;
-    a.keys = keys; a.n = n; a.bk = bk; a.bi = bi; a.m_dev = m_dev; a.buf_grads = buf_grads;
-    a.out_E = out_E; a.out_A = out_A; a.hdr = s.hdr; a.rv = rv; a.geo = g;
-    const dim3 grid(grid_blocks), block(256);
-    switch (g.mode) {
-        case kAdagradSeq: hipLaunchKernelGGL(recovery_read_kernel<kAdagradSeq>, grid, block, 0, st, a); break;
-        case kMomentumSeq: hipLaunchKernelGGL(recovery_read_kernel<kMomentumSeq>, grid, block, 0, st, a); break;
-        case kAdagradCombine: hipLaunchKernelGGL(recovery_read_kernel<kAdagradCombine>, grid, block, 0, st, a); break;
-        default: hipLaunchKernelGGL(recovery_read_kernel<kMomentumCombine>, grid, block, 0, st, a); break;
-    }
-}
 
 void launch_route(const Scratch &s, const Geometry &g, const uint64_t *keys, uint64_t n, uint64_t *stripe,
                   uint32_t *member, uint32_t *data_srv, uint32_t *parity_srv, hipStream_t st)

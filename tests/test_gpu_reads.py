@@ -1,0 +1,77 @@
+"""Reads where the flat copy and the shared answers can go wrong: rows of any width beside the 16 bytes a lane moves, stripes of
+one member and of many, numbers of requests around what a wave takes (4 to 64), more requests than the scratch buffer serves at a
+time, and waiting runs on either side of what one wave walks (128) and of a workgroup's round (1024), requested many times."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth_inputs as si
+from ecrm_case import Case, grads_for
+from oracle.recovery_session import RecoverySession
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,k,S", [(4, 1, 2), (12, 3, 4), (60, 5, 7), (128, 4, 5), (260, 10, 11), (1024, 2, 5)])
+def test_degraded_read_widths(D, k, S):
+    R, n = k * 500, 3001 if D > 12 else 1100003          # the latter: 64 requests to a wave
+    c = Case(R, D, k, S, max_batch=64, seed=31)
+    lost = S - 1
+    c.ctx.fail_server(lost)
+    oracle.fail_server(c.hE, c.hA, c.hPE, c.hPA, k, S, lost)
+    keys = si.uniform_keys(32, 0, n, R)
+    he, ha = oracle.degraded_read(c.hE, c.hA, c.hPE, c.hPA, k, S, keys, lost)
+    kt = torch.from_numpy(keys.view(np.int64)).cuda()
+    for m in (1, 3, 5, 63, 64, 65, n):
+        oe, oa = torch.full((m + 1, D), -7.0, device="cuda"), torch.full((m + 1, D), -7.0, device="cuda")
+        c.ctx.degraded_read(kt[:m], lost, oe, oa)
+        np.testing.assert_array_equal(oe[:m].cpu().numpy(), he[:m])
+        np.testing.assert_array_equal(oa[:m].cpu().numpy(), ha[:m])
+        assert bool((oe[m] == -7.0).all()) and bool((oa[m] == -7.0).all())
+    assert c.ctx.status() == 0
+
+
+@pytest.mark.parametrize("D,k,S,server,opt", [(4, 3, 5, 1, 0), (128, 4, 5, 2, 0), (36, 2, 3, 0, 1), (264, 10, 11, 7, 0)])
+@pytest.mark.parametrize("locked", [False, True])
+def test_shared_answers(D, k, S, server, opt, locked):
+    R, cap = k * 600, 9000
+    rng = np.random.default_rng(D)
+    c = Case(R, D, k, S, max_batch=cap, seed=33, optimizer=opt, momentum=0.9)
+    _, _, ds, _ = oracle.route(np.arange(R, dtype=np.uint64), R, k, S)
+    rows = np.nonzero(ds == server)[0]
+    lens = [126, 127, 128, 129, 1023, 1024, 1025, 2049, 1, 2]
+    rows = rng.permutation(rows[rows < R // 2])[:len(lens)]        # of the first chunk
+    keys = rng.permutation(np.concatenate([np.repeat(rows, lens), rng.integers(0, R, 800)])).astype(np.uint64)
+    c.ctx.fail_server(server)
+    oracle.fail_server(c.hE, c.hA, c.hPE, c.hPA, k, S, server)
+    bk, bg = torch.empty(2 * cap, dtype=torch.int64, device="cuda"), torch.empty(2 * cap, D, device="cuda")
+    c.ctx.recovery_begin(server, 2, bk, bg, cap)
+    ses = RecoverySession(c.hE, c.hA, c.hPE, c.hPA, k, S, c.lr, c.eps, server, 2, cap, c.hld, c.hlp, optimizer=opt,
+                          momentum=0.9, combine=0, threads=4)
+    if locked:                                            # more waits, stored entries among it
+        c.ctx.recovery_lock()
+        ses.lock()
+    g = grads_for(33, 0, len(keys), D)
+    c.ctx.update(torch.from_numpy(keys.view(np.int64)).cuda(), g)
+    assert ses.update(keys, g.cpu().numpy())
+    # every entry many times, hot ones more often; more requests than max_batch: three parts
+    some = np.concatenate([np.arange(R), np.repeat(rows, 300)])
+    sample = rng.choice(some, 2 * cap + 77).astype(np.uint64)
+    want_e, want_a = ses.read(np.arange(R, dtype=np.uint64))
+    st = torch.from_numpy(sample.view(np.int64)).cuda()
+    oe, oa = torch.empty(len(sample), D, device="cuda"), torch.empty(len(sample), D, device="cuda")
+    for _ in range(2):
+        oe.fill_(float("nan"))
+        oa.fill_(float("nan"))
+        c.ctx.recovery_read(st, oe, oa)
+        assert c.ctx.status() == 0
+        np.testing.assert_allclose(oe.cpu().numpy(), want_e[sample], rtol=1e-5, atol=5e-7)
+        np.testing.assert_allclose(oa.cpu().numpy(), want_a[sample], rtol=1e-5, atol=1e-9)
+    only = torch.empty_like(oe)
+    c.ctx.recovery_read(st, only)
+    assert torch.equal(only, oe)
+    first = {}
+    for i, x in enumerate(sample.tolist()):               # requests for one entry get one answer
+        first.setdefault(x, i)
+    assert torch.equal(oe, oe[torch.tensor([first[x] for x in sample.tolist()], device="cuda")])
