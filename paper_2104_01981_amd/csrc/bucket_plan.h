@@ -70,17 +70,26 @@ ECRM_HD uint32_t split_segments(uint32_t n, uint32_t k)
     const uint32_t runs = n / kSplitStripeMin * k;
     return runs ? n / kSplitSegment + (runs < kHotBuckets ? runs : kHotBuckets) : 0u;
 }
+struct BucketLimits { uint32_t heavy_run, shared_stripe, split_stripe; };
+ECRM_HD BucketLimits bucket_limits(uint32_t n, uint32_t k, uint32_t D)
+{
+    return BucketLimits{heavy_run(n), shared_stripe(n, k), split_stripe(n, D)};
+}
 struct BucketPlan { uint32_t ipt, tiles, buckets; };
 // Tiles as small as kMaxTiles of them allow.  Buckets of 16 updates while that gives no more than the 1024 workgroups that
 // are resident at once -- the fewer updates a wave walks one after the other the better --, of 64 from then on, of more
 // when the largest number of buckets is reached.
+ECRM_HD uint32_t bucket_count(uint32_t n)
+{
+    const uint32_t fine = n / 16u < 1024u ? n / 16u : 1024u, most = n / 64u > fine ? n / 64u : fine;
+    return most < 1u ? 1u : most > kMaxBuckets ? kMaxBuckets : most;
+}
 ECRM_HD BucketPlan bucket_plan(uint32_t n)
 {
     BucketPlan p;
     p.ipt = n <= 1u * kPartThreads * kMaxTiles ? 1u : n <= 2u * kPartThreads * kMaxTiles ? 2u : 4u;
     p.tiles = (n + p.ipt * kPartThreads - 1) / (p.ipt * kPartThreads);
-    const uint32_t fine = n / 16u < 1024u ? n / 16u : 1024u, most = n / 64u > fine ? n / 64u : fine;
-    p.buckets = most < 1u ? 1u : most > kMaxBuckets ? kMaxBuckets : most;
+    p.buckets = bucket_count(n);
     return p;
 }
 static_assert(kBucketMaxBatch <= 4u * kPartThreads * kMaxTiles, "the plan's largest tile covers the largest batch");

@@ -367,7 +367,7 @@ struct PartitionArgs {
     u64 *items;                // [n]: tile by tile, row << 32 | position in the batch
     uint16_t *table;           // [tiles][buckets + kHotBuckets + 1]: where each bucket begins in the tile
     uint32_t *tile_cnt;        // [tiles][2S]: load counts of the tile (not for the combined rules)
-    uint32_t *tile_bad;        // [tiles]
+    uint32_t *tile_state;      // [tiles]: updates that are held back, twice, and one if a key is out of range
     Header *hdr;
     uint32_t n, buckets, rows, count;
     uint32_t clear_sticky, packed;
@@ -464,18 +464,21 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
     __shared__ __align__(16) uint16_t s_cnt[kMaxBuckets + kHotBuckets][kPartWaves];
     __shared__ HotShared s_hot;
     __shared__ uint32_t s_srv[2 * kBucketMaxServers];
-    __shared__ uint32_t s_wave[kPartWaves];
+    __shared__ uint32_t s_wave[kPartWaves], s_held;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave, tile = blockIdx.x;
     const uint32_t n = a.packed ? min(a.n, a.hdr->buf_count) : a.n;       // a replay: everything that is waiting now
     const uint32_t S = a.dS.d, tile0 = tile * kTile;
     static_assert(sizeof(SampleShared) <= sizeof(s_cnt), "the sample is counted where the buckets are, before them");
     const uint32_t n_hot = n >= kSample * 4u ? find_hot(a, n, *(SampleShared *)&s_cnt[0][0], s_hot) : 0u;
-    const uint32_t B = a.buckets + kHotBuckets;                           // buckets in the table; the last are the hot entries'
+    // a replay's buckets are those of what is waiting, not of the buffer that holds it: 4096 workgroups for 20 000 updates
+    const uint32_t ordinary = a.packed ? bucket_count(n) : a.buckets;
+    const uint32_t B = ordinary + kHotBuckets;                            // buckets in the table; the last are the hot entries'
     for (uint32_t i = tid; i < B; i += kPartThreads) *(ulonglong2 *)s_cnt[i] = ulonglong2{0, 0};
     for (uint32_t i = tid; i < 2 * S; i += kPartThreads) s_srv[i] = 0;
+    if (tid == 0) s_held = 0;
     __syncthreads();
 
-    uint32_t row[IPT], dig[IPT], rank[IPT];
+    uint32_t held = 0, row[IPT], dig[IPT], rank[IPT];
     bool in[IPT], bad = false;
 #pragma unroll
     for (int r = 0; r < IPT; ++r) {
@@ -487,14 +490,15 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
             bool out;
             in[r] = takes_part(a, a.keys[i], x, g, out);
             bad |= out;
+            held += !in[r] && !out ? 1u : 0u;
             if (in[r]) {
                 const uint32_t j = x - g * a.dk.d;
                 row[r] = x;
-                dig[r] = bucket_of(g, a.buckets);
+                dig[r] = bucket_of(g, ordinary);
                 if (n_hot) {
                     for (uint32_t s = mix32(g) & (kHotSlots - 1u); s_hot.g[s] != kNoKey; s = (s + 1u) & (kHotSlots - 1u)) {
                         if (s_hot.g[s] == g) {
-                            dig[r] = a.buckets + s_hot.h[s] * a.dk.d + j;
+                            dig[r] = ordinary + s_hot.h[s] * a.dk.d + j;
                             break;
                         }
                     }
@@ -506,7 +510,8 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
             }
         }
     }
-    const int bits = 32 - __builtin_clz(n_hot ? B - 1u : max(a.buckets - 1u, 1u));
+    if (held) atomicAdd(&s_held, held);
+    const int bits = 32 - __builtin_clz(n_hot ? B - 1u : max(ordinary - 1u, 1u));
 #pragma unroll
     for (int r = 0; r < IPT; ++r) {
         u64 peers = __ballot(in[r]);
@@ -548,7 +553,7 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
     }
     if (tid == 0) {
         out[B] = (uint16_t)carry;
-        a.tile_bad[tile] = bad ? 1u : 0u;
+        a.tile_state[tile] = 2u * s_held + (bad ? 1u : 0u);
     }
     if (a.count)
         for (uint32_t i = tid; i < 2 * S; i += kPartThreads) a.tile_cnt[(size_t)tile * 2 * S + i] = s_srv[i];
@@ -767,13 +772,14 @@ struct BucketArgs : RowArgs {
     const u64 *items;
     u64 *tmp, *dense;            // [n] each: an oversized bucket's items in arrival order; its heavy stripes', sorted
     const uint16_t *table;
-    const uint32_t *tile_cnt, *tile_bad;
+    const uint32_t *tile_cnt, *tile_state;
     uint32_t *heavy;             // [2 * (n / kHeavyRunMin + 64)]: start in `dense`, number of updates
     SplitScratch split;          // of stripes whose runs are cut up
     Header *hdr;
     u64 *load_data, *load_parity;
     uint32_t n, tile, tiles, buckets, packed;
-    uint32_t heavy_run, shared_stripe, split_stripe;         // bucket_plan.h
+    uint32_t holding;            // a recovery is in progress: the header follows what hold_tiles did
+    BucketLimits lim;
 };
 
 // gradient row of an item, from its position in the batch
@@ -1072,6 +1078,13 @@ template <int NC, int MODE, bool PARITY>
 __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_kernel(BucketArgs a)
 {
     __shared__ BucketShared sh;
+    if (a.packed) {                                                 // a replay: as many as were waiting (the partition's plan)
+        a.n = min(a.n, a.hdr->n_batch);
+        a.tiles = (a.n + a.tile - 1u) / a.tile;
+        a.buckets = bucket_count(a.n);
+        a.lim = bucket_limits(a.n, a.geo.k, a.geo.D);
+        if (blockIdx.x >= a.buckets + kHotBuckets) return;
+    }
     const uint32_t tid = threadIdx.x, B = a.buckets + kHotBuckets, S = a.geo.S, k = a.geo.k;
     // the hot stripes' buckets first: what takes longest must not begin last
     const uint32_t b = blockIdx.x < kHotBuckets ? a.buckets + blockIdx.x : blockIdx.x - kHotBuckets;
@@ -1080,7 +1093,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
     uint32_t from = 0, len = 0, stripe_len = 0;
     if (tid < a.tiles) {
         const uint16_t *row = a.table + (size_t)tid * (B + 1) + b;
-        key_bad = a.tile_bad[tid] != 0;
+        key_bad = (a.tile_state[tid] & 1u) != 0;
         from = tid * a.tile + row[0];
         len = (uint32_t)row[1] - row[0];
         if (hot && b - member + k <= B) stripe_len = (uint32_t)row[k - member] - row[-(int)member];
@@ -1098,13 +1111,13 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
     uint32_t m;
     if (hot) {
         bucket_excl_scan(stripe_len, sh.wave, m);
-        if (m < (many ? a.shared_stripe : max(a.shared_stripe / 2u, heavy_stripe(k)))) {
+        if (m < (many ? a.lim.shared_stripe : max(a.lim.shared_stripe / 2u, heavy_stripe(k)))) {
             // no stripe, or one that is not as long as the sample made it look: its entries' buckets lie side by side in
             // every tile, so the first workgroup takes them as one ordinary bucket
             if (member != 0 || m == 0) return;
             hot = false;
             len = stripe_len;
-        } else if (m >= a.split_stripe) {
+        } else if (m >= a.lim.split_stripe) {
             split_run(a, sh, b - a.buckets, from, len);
             return;
         } else if (member == 0) {
@@ -1127,6 +1140,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
             if (to) to[i < S ? i : i - S] += sh.list.srv[i];
         }
     }
+    if (a.holding && b == 0 && tid == 0) hold_commit(a.hdr, a.packed != 0);       // nothing else of this launch reads these
     if (m == 0) return;
     if (tid <= a.tiles && tid < kMaxTiles) sh.pref[tid] = at;       // [tiles] = m as well (len is 0 there)
     if (tid == 0) sh.pref[a.tiles] = m;
@@ -1175,7 +1189,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
                 __syncthreads();
             }
             if (Rule<MODE>::combine) count_list(a.geo, sh.item, list, sh.list.srv, a.load_data, a.load_parity);
-            apply_list<NC, MODE, PARITY, kBucketChunk>(a, sh.item, list, a.heavy_run, many ? a.shared_stripe : 0u, sh.list, (double *)sh.tmp);
+            apply_list<NC, MODE, PARITY, kBucketChunk>(a, sh.item, list, a.lim.heavy_run, many ? a.lim.shared_stripe : 0u, sh.list, (double *)sh.tmp);
             const uint32_t nh = uniform(sh.list.n_heavy);
             if (nh && !have_base) {
                 bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, base);
@@ -1419,6 +1433,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
     constexpr int T = kHeavyT;
     __shared__ HeavyShared sh;
     if (a.hdr->batch_bad) return;
+    if (a.packed) a.tiles = (min(a.n, a.hdr->n_batch) + a.tile - 1u) / a.tile;
     const uint32_t nh = a.hdr->n_heavy, ns = a.hdr->n_segments, D = a.geo.D, k = a.geo.k, lane = lane_id();
     if (nh + ns == 0) return;
     const uint32_t w = uniform(threadIdx.x / kWave), col_lane = lane & 7u, sub = w * 8u + lane / 8u;
@@ -1564,7 +1579,7 @@ void launch_bucket_partition(const BucketScratch &bs, Header *hdr, const Geometr
 {
     const BucketPlan p = bucket_plan(n);
     PartitionArgs a;
-    a.keys = keys; a.items = bs.items; a.table = bs.table; a.tile_cnt = bs.tile_cnt; a.tile_bad = bs.tile_bad;
+    a.keys = keys; a.items = bs.items; a.table = bs.table; a.tile_cnt = bs.tile_cnt; a.tile_state = bs.tile_state;
     a.hdr = hdr; a.n = n; a.buckets = p.buckets; a.rows = g.rows;
     a.count = (g.mode & 2u) ? 0u : 1u;               // the combined rules count per modified entry, later
     a.clear_sticky = clear_sticky ? 1u : 0u;
@@ -1580,19 +1595,18 @@ void launch_bucket_partition(const BucketScratch &bs, Header *hdr, const Geometr
 
 void launch_bucket_apply(const BucketScratch &bs, Header *hdr, const Geometry &g, float *E, float *A, float *PE, float *PA,
                          unsigned long long *load_data, unsigned long long *load_parity, const uint64_t *keys,
-                         const float *grads, uint32_t n, BatchSource src, int cus, hipStream_t st)
+                         const float *grads, uint32_t n, BatchSource src, bool holding, int cus, hipStream_t st)
 {
     const BucketPlan p = bucket_plan(n);
     BucketArgs a;
     a.E = E; a.A = A; a.PE = PE; a.PA = PA; a.grads = grads; a.geo = g;
     a.keys = keys; a.items = bs.items; a.tmp = bs.tmp; a.dense = bs.dense; a.table = bs.table;
-    a.tile_cnt = bs.tile_cnt; a.tile_bad = bs.tile_bad; a.heavy = bs.heavy; a.split = bs.split; a.hdr = hdr;
+    a.tile_cnt = bs.tile_cnt; a.tile_state = bs.tile_state; a.heavy = bs.heavy; a.split = bs.split; a.hdr = hdr;
     a.load_data = load_data; a.load_parity = load_parity;
     a.n = n; a.tile = p.ipt * kPartThreads; a.tiles = p.tiles; a.buckets = p.buckets;
     a.packed = src == kWaitingUpdates ? 1u : 0u;
-    a.heavy_run = heavy_run(n);
-    a.shared_stripe = shared_stripe(n, g.k);
-    a.split_stripe = split_stripe(n, g.D);
+    a.holding = holding ? 1u : 0u;
+    a.lim = bucket_limits(n, g.k, g.D);
     const bool heavy = n >= kHeavyRunMin;
     ECRM_DISPATCH(bucket_apply_for, a, PE != nullptr, heavy, cus, st);
 }

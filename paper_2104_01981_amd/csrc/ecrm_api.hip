@@ -15,7 +15,7 @@ struct Layout {
     size_t bytes;
     size_t off_cnt, off_keys[2], off_vals[2], off_hist, off_bintotal, off_long_slot, off_long_meta,
         off_piece_slot, off_partial, off_partial2, off_long_res, off_active;
-    size_t off_table, off_tile_cnt, off_tile_bad, off_tmp, off_heavy, off_hold_tiles, off_split_run, off_split_tiles,
+    size_t off_table, off_tile_cnt, off_tile_state, off_tmp, off_heavy, off_split_run, off_split_tiles,
         off_segment_run, off_summed, off_arrived, off_sums, off_steps;    // the bucket path's, over the others
 };
 
@@ -115,10 +115,9 @@ static Layout make_layout(uint32_t max_batch, uint32_t D, uint32_t k, uint32_t S
     const uint32_t servers = S < kBucketMaxServers ? S : kBucketMaxServers;
     l.off_table = take(table * 2);
     l.off_tile_cnt = take(tiles * 2 * servers * 4);
-    l.off_tile_bad = take(tiles * 4);
+    l.off_tile_state = take(tiles * 4);
     l.off_tmp = take((size_t)nb * 8);
     l.off_heavy = take(((size_t)nb / kHeavyRunMin + 64) * 2 * 4);
-    l.off_hold_tiles = take(((size_t)nb / kHoldTile + 1) * 4);
     const size_t segments = split_segments(nb, k), groups = (D + 15) / 16, split_runs = segments ? kHotBuckets : 0;
     l.off_split_run = take(split_runs * sizeof(SplitRun));
     l.off_split_tiles = take(split_runs * kSplitTileWords * 4);
@@ -139,10 +138,9 @@ static BucketScratch carve_buckets(const Layout &l, const Scratch &s)
     r.dense = (unsigned long long *)s.vals[0];
     r.table = (uint16_t *)(b + l.off_table);
     r.tile_cnt = (uint32_t *)(b + l.off_tile_cnt);
-    r.tile_bad = (uint32_t *)(b + l.off_tile_bad);
+    r.tile_state = (uint32_t *)(b + l.off_tile_state);
     r.tmp = (unsigned long long *)(b + l.off_tmp);
     r.heavy = (uint32_t *)(b + l.off_heavy);
-    r.hold_tiles = (uint32_t *)(b + l.off_hold_tiles);
     r.split.run = (SplitRun *)(b + l.off_split_run);
     r.split.tiles = (uint32_t *)(b + l.off_split_tiles);
     r.split.segment_run = (uint32_t *)(b + l.off_segment_run);
@@ -357,13 +355,12 @@ static int run_update(ecrm_ctx *c, const Tables &t, const Scratch &s, const Layo
         const bool diff = c->cfg.propagation == ECRM_PROP_DIFFERENCE;
         if (ev) (void)hipEventRecord(ev[0], st);
         launch_bucket_partition(bs, s.hdr, c->geo, rv, keys, n32, src, clear_sticky, st);
-        if (rv.active || src == kWaitingUpdates)
-            launch_hold_back(s.hdr, bs.hold_tiles, bs.tile_bad, bucket_plan(n32).tiles, c->geo, rv, keys, grads, n32, src,
-                             c->hb, c->buf_cur, st);
+        const bool holding = rv.active || src == kWaitingUpdates;
+        if (holding) launch_hold_tiles(s.hdr, bs.tile_state, c->geo, rv, keys, grads, n32, src, c->hb, c->buf_cur, st);
         if (ev) (void)hipEventRecord(ev[1], st);
         if (ev) (void)hipEventRecord(ev[2], st);
         launch_bucket_apply(bs, s.hdr, c->geo, t.E, t.A, diff ? t.PE : nullptr, diff ? t.PA : nullptr, t.load_data,
-                            diff ? t.load_parity : nullptr, keys, grads, n32, src, c->cus, st);
+                            diff ? t.load_parity : nullptr, keys, grads, n32, src, holding, c->cus, st);
         if (ev) (void)hipEventRecord(ev[3], st);
         return check_launch();
     }
@@ -378,7 +375,7 @@ static int run_update(ecrm_ctx *c, const Tables &t, const Scratch &s, const Layo
     uint32_t *sk = nullptr, *si = nullptr;
     launch_sort(s, c->geo, rv, keys, n32, n_dev, src, key_bits, false, true, &sk, &si, st);
     if (rv.active || src == kWaitingUpdates)
-        launch_hold_back(s.hdr, s.long_slot, nullptr, 0, c->geo, rv, keys, grads, n32, src, c->hb, c->buf_cur, st);
+        launch_hold_back(s.hdr, s.long_slot, c->geo, rv, keys, grads, n32, src, c->hb, c->buf_cur, st);
     if (ev) (void)hipEventRecord(ev[1], st);
     launch_chains(s, c->geo, lg, t.A, grads, sk, si, n32, l.max_slots, l.max_pieces, c->cus, st);
     launch_active_groups(s, c->geo, sk, n32, st);

@@ -113,9 +113,8 @@ struct BucketScratch {
     unsigned long long *items, *dense, *tmp;   // [n] each
     uint16_t *table;               // [tiles][buckets + kHotBuckets + 1]
     uint32_t *tile_cnt;            // [tiles][2 * S]
-    uint32_t *tile_bad;            // [tiles]
+    uint32_t *tile_state;          // [tiles]: held-back updates, twice, and one if a key is out of range
     uint32_t *heavy;               // [2 * (n / kHeavyRunMin + 64)]
-    uint32_t *hold_tiles;          // tile counts of the hold-back kernels
     SplitScratch split;            // for batches of kSplitStripeMin updates or more
 };
 
@@ -226,16 +225,18 @@ void launch_reset(const Scratch &s, uint32_t S, uint32_t n, bool clear_sticky, B
 void launch_sort(const Scratch &s, const Geometry &g, const RecoveryView &rv, const uint64_t *keys, uint32_t n,
                  const uint32_t *n_dev, BatchSource src, int key_bits, bool by_stripe, bool count_servers,
                  uint32_t **sorted_keys, uint32_t **sorted_vals, hipStream_t st);
-// tile_count: scratch for the tiles' counts; tile_bad (may be null): per partition tile, whether it carried a bad key
-void launch_hold_back(Header *hdr, uint32_t *tile_count, const uint32_t *tile_bad, uint32_t bad_tiles, const Geometry &g,
-                      const RecoveryView &rv, const uint64_t *keys, const float *grads, uint32_t n, BatchSource src,
-                      const HoldBuffer &hb, uint32_t cur, hipStream_t st);
+// tile_count: scratch for the tiles' counts
+void launch_hold_back(Header *hdr, uint32_t *tile_count, const Geometry &g, const RecoveryView &rv, const uint64_t *keys,
+                      const float *grads, uint32_t n, BatchSource src, const HoldBuffer &hb, uint32_t cur, hipStream_t st);
+// the same for a batch that bucket_partition has been over; bucket_apply then brings the header up to date
+void launch_hold_tiles(Header *hdr, const uint32_t *tile_state, const Geometry &g, const RecoveryView &rv, const uint64_t *keys,
+                       const float *grads, uint32_t n, BatchSource src, const HoldBuffer &hb, uint32_t cur, hipStream_t st);
 constexpr uint32_t kHoldTile = 2048;
 void launch_bucket_partition(const BucketScratch &bs, Header *hdr, const Geometry &g, const RecoveryView &rv,
                              const uint64_t *keys, uint32_t n, BatchSource src, bool clear_sticky, hipStream_t st);
 void launch_bucket_apply(const BucketScratch &bs, Header *hdr, const Geometry &g, float *E, float *A, float *PE, float *PA,
                          unsigned long long *load_data, unsigned long long *load_parity, const uint64_t *keys,
-                         const float *grads, uint32_t n, BatchSource src, int cus, hipStream_t st);
+                         const float *grads, uint32_t n, BatchSource src, bool holding, int cus, hipStream_t st);
 void launch_recover_range(const Geometry &g, float *E, float *A, float *PE, float *PA, uint32_t server,
                           uint32_t g_lo, uint32_t g_hi, int grid_blocks, hipStream_t st);
 void launch_clear_buffer(const Scratch &s, hipStream_t st);
@@ -263,7 +264,24 @@ void launch_degraded_read(const Scratch &s, const Geometry &g, const float *E, c
                           const float *PA, const uint64_t *keys, uint64_t n, uint32_t lost, float *out_E,
                           float *out_A, int cus, hipStream_t st);
 
+// What a batch that was held back in part, or a replay, leaves of the recovery buffer (one thread, after everything of the
+// batch has been appended or released).
+__device__ __forceinline__ void hold_commit(Header *hdr, bool replay)
+{
+    const uint32_t held = hdr->n_held;
+    if (replay) {                                  // the other list, and the released slots
+        hdr->free_count += hdr->n_batch - held;
+        hdr->buf_count = held;
+    } else {
+        const uint32_t free = hdr->free_count, reused = held < free ? held : free;
+        hdr->free_count = free - reused;
+        hdr->bump += held - reused;
+        hdr->buf_count += held;
+    }
+}
+
 // ---- small device helpers ------------------------------------------------------------------------
+__device__ __forceinline__ float4 load4(const float *p) { return *(const float4 *)p; }      // p aligned to 16 bytes
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & (kWave - 1); }
 
 // One Adagrad step of the printed rule on one parameter, carried in fp64:

@@ -59,14 +59,10 @@ __global__ __launch_bounds__(kHoldThreads) void hold_count_kernel(const uint64_t
 
 // pass 2 (one block): exclusive scan of the tile counts; totals and the capacity check
 __global__ __launch_bounds__(1024) void hold_scan_kernel(uint32_t *tile_count, uint32_t ntiles, Header *hdr, uint32_t n,
-                                                         const uint32_t *n_dev, uint32_t packed, uint32_t buf_cap,
-                                                         const uint32_t *tile_bad, uint32_t bad_tiles)
+                                                         const uint32_t *n_dev, uint32_t packed, uint32_t buf_cap)
 {
     __shared__ uint32_t s_w[16];
     __shared__ uint32_t s_carry;
-    bool bad = false;                              // a key out of range anywhere: nothing of the batch may be appended
-    for (uint32_t t = threadIdx.x; t < bad_tiles; t += 1024) bad |= tile_bad[t] != 0;
-    bad = __syncthreads_or(bad);
     if (n_dev) n = min(n, *n_dev);
     if (threadIdx.x == 0) s_carry = 0;
     __syncthreads();
@@ -95,10 +91,6 @@ __global__ __launch_bounds__(1024) void hold_scan_kernel(uint32_t *tile_count, u
         const uint32_t held = s_carry;
         hdr->n_held = held;
         hdr->n_valid = n - held;
-        if (bad) {
-            hdr->batch_bad = 1;
-            hdr->err_sticky |= 1u;
-        }
         // no room: the batch is rejected as a whole (a replay only ever shrinks the list)
         if (!packed && (unsigned long long)hdr->buf_count + held > buf_cap) {
             hdr->batch_bad = 1;
@@ -197,21 +189,128 @@ __global__ __launch_bounds__(kHoldThreads) void hold_scatter_kernel(const uint64
 __global__ void hold_commit_kernel(Header *hdr, uint32_t packed)
 {
     if (threadIdx.x != 0 || hdr->batch_bad) return;
-    const uint32_t held = hdr->n_held;
-    if (packed) {                                  // after a replay: the other list, and the released slots
-        hdr->free_count += hdr->n_batch - held;
-        hdr->buf_count = held;
-    } else {
-        const uint32_t reused = min(held, hdr->free_count);
-        hdr->free_count -= reused;
-        hdr->bump += held - reused;
-        hdr->buf_count += held;
+    hold_commit(hdr, packed != 0);
+}
+
+// The three passes in one launch, for a batch that the partition (buckets.hip) has been over: it has counted what is held
+// back in each of its tiles, at most kMaxTiles of them, so that every workgroup adds up those before its own.  A workgroup
+// takes one of the partition's tiles, and its rows are a flat copy, 16 bytes a lane.  20 batches of 65 536 and ten replays,
+// a fifth of each held back: four launches of 46 us together in tiles of 2048 -- 32 workgroups --, now one of 8 us, 4 for a replay.
+// The header is brought up to date by bucket_apply: here every workgroup reads it.
+struct HoldArgs {
+    const uint64_t *keys;
+    const float *grads;
+    const uint32_t *tile_state;
+    uint32_t n, tiles, rows, packed, cap;
+    Geometry geo;
+    Divider d4;
+    RecoveryView rv;
+    Header *hdr;
+    unsigned long long *list_out;
+    float *pool;
+    uint32_t *free_list;
+};
+
+template <int IPT>
+__global__ __launch_bounds__(kPartThreads) void hold_tiles_kernel(HoldArgs a)
+{
+    constexpr uint32_t kTile = kPartThreads * IPT, kWaves = kPartThreads / kWave;
+    static_assert(kMaxTiles <= kPartThreads, "a thread per tile");
+    __shared__ uint2 s_row[kTile];                 // the tile's held-back items, in order: item, slot
+    __shared__ uint32_t s_before[kWaves], s_all[kWaves], s_cnt[kWaves][IPT];
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    const uint32_t n = a.packed ? min(a.n, a.hdr->n_batch) : a.n;
+    const uint32_t free0 = a.hdr->free_count, bump0 = a.hdr->bump, list0 = a.packed ? 0u : a.hdr->buf_count;
+    const uint32_t state = tid < a.tiles ? a.tile_state[tid] : 0u;
+    uint32_t all = state >> 1, before = tid < blockIdx.x ? all : 0u;
+    const bool bad = __syncthreads_or(state & 1u);
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+        all += __shfl_xor(all, d, kWave);
+        before += __shfl_xor(before, d, kWave);
+    }
+    if (lane == 0) {
+        s_all[wave] = all;
+        s_before[wave] = before;
+    }
+    // the tile's items in the partition's order -- (wave, r, lane) --, ranked among the held-back ones by ballots
+    const uint32_t tile0 = blockIdx.x * kTile;
+    uint64_t key[IPT];
+    uint32_t below[IPT], held = 0;
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const uint32_t i = tile0 + wave * (kWave * IPT) + r * kWave + lane;
+        key[r] = i < n ? a.keys[i] : 0ull;
+        const bool h = i < n && (a.packed || key[r] < (uint64_t)a.rows) && held_back(a.rv, (uint32_t)key[r], a.geo.dk, a.geo.dS);
+        const unsigned long long m = __ballot(h);
+        held |= h ? 1u << r : 0u;
+        below[r] = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (lane == 0) s_cnt[wave][r] = (uint32_t)__popcll(m);
+    }
+    __syncthreads();
+    all = before = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kWaves; ++w) {
+        all += s_all[w];
+        before += s_before[w];
+    }
+    // no room: the batch is rejected as a whole (a replay only ever shrinks the list)
+    const bool full = !a.packed && (uint64_t)list0 + all > a.cap;
+    if (blockIdx.x == 0 && tid == 0) {
+        a.hdr->n_held = all;
+        a.hdr->n_valid = n - all;
+        if (bad || full) {
+            a.hdr->batch_bad = 1;
+            a.hdr->err_sticky |= (bad ? 1u : 0u) | (full ? 2u : 0u);
+        }
+    }
+    if (bad || full) return;                       // the same in every workgroup
+    uint32_t own = 0, at = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kWaves; ++w) {
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) {
+            if (w < wave) at += s_cnt[w][r];
+            own += s_cnt[w][r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const uint32_t pos = wave * (kWave * IPT) + r * kWave + lane, i = tile0 + pos, rank = at + below[r];
+        at += s_cnt[wave][r];
+        if (i >= n) continue;
+        if (a.packed) {
+            if ((held >> r) & 1u) a.list_out[before + rank] = key[r];                       // goes on waiting, row in place
+            else a.free_list[free0 + (tile0 - before) + (pos - rank)] = (uint32_t)(key[r] >> 32);   // slot released
+        } else if ((held >> r) & 1u) {             // a released slot, the last first, or one never used
+            const uint32_t nth = before + rank;
+            const uint32_t slot = nth < free0 ? a.free_list[free0 - 1u - nth] : bump0 + (nth - free0);
+            a.list_out[(size_t)list0 + nth] = key[r] | ((unsigned long long)slot << 32);
+            s_row[rank] = uint2{i, slot};
+        }
+    }
+    if (a.packed) return;
+    __syncthreads();
+    constexpr uint32_t U = 4;
+    const uint32_t D = a.geo.D, total = own * (D / 4u);
+    for (uint32_t u0 = 0; u0 < total; u0 += U * kPartThreads) {
+        float4 v[U];
+        size_t to[U];
+#pragma unroll
+        for (uint32_t q = 0; q < U; ++q) {
+            const uint32_t u = min(u0 + q * kPartThreads + tid, total - 1u), r = a.d4.div(u), c = (u - r * a.d4.d) * 4u;
+            const uint2 what = s_row[r];
+            v[q] = load4(a.grads + (size_t)what.x * D + c);
+            to[q] = (size_t)what.y * D + c;
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < U; ++q)
+            if (u0 + q * kPartThreads + tid < total) *(float4 *)(a.pool + to[q]) = v[q];
     }
 }
 
-void launch_hold_back(Header *hdr, uint32_t *tile_count, const uint32_t *tile_bad, uint32_t bad_tiles, const Geometry &g,
-                      const RecoveryView &rv, const uint64_t *keys, const float *grads, uint32_t n, BatchSource src,
-                      const HoldBuffer &hb, uint32_t cur, hipStream_t st)
+void launch_hold_back(Header *hdr, uint32_t *tile_count, const Geometry &g, const RecoveryView &rv, const uint64_t *keys,
+                      const float *grads, uint32_t n, BatchSource src, const HoldBuffer &hb, uint32_t cur, hipStream_t st)
 {
     const uint32_t packed = src == kWaitingUpdates ? 1u : 0u;
     const uint32_t *n_dev = packed ? &hdr->n_batch : nullptr;
@@ -220,11 +319,28 @@ void launch_hold_back(Header *hdr, uint32_t *tile_count, const uint32_t *tile_ba
     unsigned long long *list_out = packed ? hb.list[cur ^ 1u] : hb.list[cur];
     hipLaunchKernelGGL(hold_count_kernel, dim3(ntiles), dim3(kHoldThreads), 0, st, keys, n, n_dev, g.rows, g.dk, g.dS, rv,
                        packed, tile_count);
-    hipLaunchKernelGGL(hold_scan_kernel, dim3(1), dim3(1024), 0, st, tile_count, ntiles, hdr, n, n_dev, packed, hb.cap,
-                       tile_bad, bad_tiles);
+    hipLaunchKernelGGL(hold_scan_kernel, dim3(1), dim3(1024), 0, st, tile_count, ntiles, hdr, n, n_dev, packed, hb.cap);
     hipLaunchKernelGGL(hold_scatter_kernel, dim3(ntiles), dim3(kHoldThreads), 0, st, keys, grads, n, n_dev, g.rows, g.D, g.dk,
                        g.dS, rv, packed, tile_count, hdr, list_out, hb.rows, hb.free_list);
     hipLaunchKernelGGL(hold_commit_kernel, dim3(1), dim3(64), 0, st, hdr, packed);
+}
+
+void launch_hold_tiles(Header *hdr, const uint32_t *tile_state, const Geometry &g, const RecoveryView &rv, const uint64_t *keys,
+                       const float *grads, uint32_t n, BatchSource src, const HoldBuffer &hb, uint32_t cur, hipStream_t st)
+{
+    const BucketPlan p = bucket_plan(n);
+    HoldArgs a;
+    a.keys = keys; a.grads = grads; a.tile_state = tile_state;
+    a.n = n; a.tiles = p.tiles; a.rows = g.rows; a.packed = src == kWaitingUpdates ? 1u : 0u; a.cap = hb.cap;
+    a.geo = g; a.d4 = make_divider(g.D / 4u); a.rv = rv; a.hdr = hdr;
+    a.list_out = a.packed ? hb.list[cur ^ 1u] : hb.list[cur];
+    a.pool = hb.rows; a.free_list = hb.free_list;
+    const dim3 grid(p.tiles), block(kPartThreads);
+    switch (p.ipt) {
+        case 1: hipLaunchKernelGGL(hold_tiles_kernel<1>, grid, block, 0, st, a); break;
+        case 2: hipLaunchKernelGGL(hold_tiles_kernel<2>, grid, block, 0, st, a); break;
+        default: hipLaunchKernelGGL(hold_tiles_kernel<4>, grid, block, 0, st, a); break;
+    }
 }
 
 }  // namespace ecrm

@@ -49,7 +49,6 @@ __device__ __forceinline__ bool is_lost(const ReadArgs &a, uint32_t g, uint32_t 
     return !a.rv.active || a.rv.dspc.div(g) >= a.rv.next;
 }
 
-__device__ __forceinline__ float4 load4(const float *p) { return *(const float4 *)p; }
 __device__ __forceinline__ void store4(float *p, float4 v)               // written once, read by somebody else later
 {
     typedef float f4 __attribute__((ext_vector_type(4)));
