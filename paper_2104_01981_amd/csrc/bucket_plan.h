@@ -32,7 +32,8 @@ constexpr uint32_t kBucketCap = 1536;
 constexpr uint32_t kBucketMaxServers = 64;   // per-tile load counts are kept for at most this many servers
 constexpr uint32_t kBucketChunk = 8;         // sorted positions whose stripes a wave owns at a time
 // A stripe that does not end inside a window of 64 positions leaves its bucket for heavy_stripes, which splits it over the
-// columns, if it has a run of heavy_run(n) updates: the wave that owns it would need a quarter of a microsecond for each.  A
+// columns, if it has a run of heavy_run(n) updates: its workgroup would take 25 of them per us, where heavy_stripes takes 300
+// (at 256 instead of 128, of Zipf batches: 65 536 half Zipf 89.5 -> 87.6, 20 000 of k = 2 48.2 -> 50.0, 256 floats 200 -> 203).  A
 // heavy stripe takes ~6 us for every entry in each of its D / 16 workgroups, however short its run is, so that few of them
 // are a gain and many a loss.  In a batch of many long stripes -- more than kManyHot hot ones in the sample: a small table --
 // a stripe that no run dominates is shared by the waves of its workgroup instead, as long as it has fewer than
@@ -76,12 +77,12 @@ ECRM_HD BucketLimits bucket_limits(uint32_t n, uint32_t k, uint32_t D)
     return BucketLimits{heavy_run(n), shared_stripe(n, k), split_stripe(n, D)};
 }
 struct BucketPlan { uint32_t ipt, tiles, buckets; };
-// Tiles as small as kMaxTiles of them allow.  Buckets of 16 updates while that gives no more than the 1024 workgroups that
-// are resident at once -- the fewer updates a wave walks one after the other the better --, of 64 from then on, of more
-// when the largest number of buckets is reached.
+// Tiles as small as kMaxTiles of them allow.  Buckets of 8 updates while that gives no more than the 1024 workgroups that
+// are resident at once -- the fewer updates a wave walks one after the other the better (2048 uniform updates: 19.0 us with 16 to a bucket, 16.7 with 8, 17.4 with 4) --, of 64 from
+// then on, of more when the largest number of buckets is reached.
 ECRM_HD uint32_t bucket_count(uint32_t n)
 {
-    const uint32_t fine = n / 16u < 1024u ? n / 16u : 1024u, most = n / 64u > fine ? n / 64u : fine;
+    const uint32_t fine = n / 8u < 1024u ? n / 8u : 1024u, most = n / 64u > fine ? n / 64u : fine;
     return most < 1u ? 1u : most > kMaxBuckets ? kMaxBuckets : most;
 }
 ECRM_HD BucketPlan bucket_plan(uint32_t n)
@@ -94,8 +95,8 @@ ECRM_HD BucketPlan bucket_plan(uint32_t n)
 }
 static_assert(kBucketMaxBatch <= 4u * kPartThreads * kMaxTiles, "the plan's largest tile covers the largest batch");
 
-// Bijective mix of a stripe number: the high part selects the bucket, the low bits split a bucket further.
-ECRM_HD uint32_t mix32(uint32_t g)
+// Bijective mix of a stripe number: its low bits split a bucket further, and number the slots of tables in LDS.
+ECRM_HD uint32_t scramble32(uint32_t g)
 {
     g ^= g >> 16;
     g *= 0x9E3779B1u;
@@ -103,6 +104,12 @@ ECRM_HD uint32_t mix32(uint32_t g)
     g *= 0xD1B54A33u;
     return g ^ (g >> 16);
 }
+// Its high part selects the bucket.  Multiples of the golden ratio spread any range of numbers evenly, so that buckets of a
+// table whose every stripe is touched get equally many; at random, as by the mix above, 4096 stripes in 1024 buckets are up
+// to 13 to a bucket, and the call waits for that one (65 536 updates on 2^14 rows 47.1 us, now 43.2; 300 007 on 100 000 136, now 130).  The multiples start over somewhere else every 4096 stripes, so that
+// a batch of one stripe out of a few thousand is spread as by the mix: a stride that meets a Fibonacci number would keep
+// the multiples themselves close together.
+ECRM_HD uint32_t mix32(uint32_t g) { return (g & 4095u) * 0x9E3779B1u + scramble32(g >> 12); }
 ECRM_HD uint32_t bucket_of(uint32_t g, uint32_t buckets) { return (uint32_t)(((uint64_t)mix32(g) * buckets) >> 32); }
 
 // The sample in which stripes with about kHotRun updates or more are looked for: one key out of each of 2^sample_bits(n)
@@ -120,7 +127,7 @@ ECRM_HD uint32_t sample_position(uint32_t i, uint32_t n)
 {
     const uint32_t bits = sample_bits(n);
     const uint32_t lo = (uint32_t)(((uint64_t)i * n) >> bits), hi = (uint32_t)(((uint64_t)(i + 1u) * n) >> bits);
-    return lo + (uint32_t)(((uint64_t)mix32(i) * (hi - lo)) >> 32);
+    return lo + (uint32_t)(((uint64_t)scramble32(i) * (hi - lo)) >> 32);
 }
 // hits from which on a stripe counts as hot
 ECRM_HD uint32_t hot_hits(uint32_t n)

@@ -23,7 +23,7 @@ typedef unsigned long long u64;
 
 constexpr int kBucketWaves = kBucketThreads / kWave;
 constexpr int kPartWaves = kPartThreads / kWave;
-constexpr uint32_t kLongRuns = 4;       // updates per entry from which on a stripe behind a window is walked run by run
+constexpr uint32_t kTogether = 32;       // updates of a run from which on the waves of a workgroup share its columns
 constexpr uint32_t kLongList = kBucketCap / (kWave - kBucketChunk);      // such stripes that a list can hold
 
 __device__ __forceinline__ uint32_t item_row(u64 it) { return (uint32_t)(it >> 32); }
@@ -76,9 +76,9 @@ struct StepLoads {
     float2 a[NC], e[NC], g[U][NC], pe[NC], pa[NC];
 };
 
-// The chain of the entry in work and the parity rows of its stripe; carried from window to window where a stripe or a
-// run does not end inside one.  A step that brings no rows leaves those of the entry and the stripe in work as they are:
-// taking a set of loads in is a select and needs no branch (added to zeros instead, a stored -0.0 became +0.0).
+// The chain of the entry in work and the parity rows of its stripe.  A step that brings no rows leaves those of the entry
+// and the stripe in work as they are: taking a set of loads in is a select and needs no branch (added to zeros instead, a
+// stored -0.0 became +0.0).
 template <int NC>
 struct Walk {
     D2 G[NC], acc[NC], pe[NC], pa[NC];
@@ -140,16 +140,16 @@ __device__ __forceinline__ uint32_t issue_step(StepLoads<NC, U> &l, const RowArg
     return cnt;
 }
 
-// The updates in lanes [first, end) of a window, in order.  A run or a stripe may begin before the window (its state is
-// in w) and end behind it (`run_goes_on`, `stripe_goes_on`: its state stays there).
+// The updates in lanes [first, end) of a window, in order: whole stripes.
 template <int NC, int MODE, bool PARITY, int Q, int U>
 __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uint32_t widx, u64 rowheads, u64 stripeheads,
-                                            uint32_t first, uint32_t end, uint32_t cb, Walk<NC> &w, bool run_goes_on,
-                                            bool stripe_goes_on)
+                                            uint32_t first, uint32_t end, uint32_t cb)
 {
     const uint32_t D = a.geo.D;
     const RuleParams rp = rule_params(a.geo);
     const uint32_t col0 = cb * NC * 128u;
+    Walk<NC> w;
+    w.begin();
     StepLoads<NC, U> l[Q];
     uint32_t at[Q], cnt[Q], next = first;          // lane a step in flight starts in, and how many updates it takes
 #pragma unroll
@@ -211,7 +211,7 @@ __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uin
             cnt[s] = issue_step<NC, U, PARITY>(l[s], a, col0, wkey, widx, rowheads, stripeheads, next, end);
             next += cnt[s];
             const bool last = t1 >= end;
-            if (took && (last ? !run_goes_on : (bool)((rowheads >> t1) & 1ull))) {          // the entry is complete
+            if (took && (last || (bool)((rowheads >> t1) & 1ull))) {          // the entry is complete
                 const uint32_t x = from_lane(wkey, t);
                 const rsrc_t erow = row_f32(a.E, x, D, col0), arow = row_f32(a.A, x, D, col0);
 #pragma unroll
@@ -227,7 +227,7 @@ __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uin
                         w.pa[i].y += w.G[i].y - a64.y;
                     }
                 }
-                if (PARITY && (last ? !stripe_goes_on : (bool)((stripeheads >> t1) & 1ull))) {
+                if (PARITY && (last || (bool)((stripeheads >> t1) & 1ull))) {
                     const uint32_t g = a.geo.dk.div(x);
                     const rsrc_t perow = row_f32(a.PE, g, D, col0), parow = row_f32(a.PA, g, D, col0);
 #pragma unroll
@@ -242,10 +242,21 @@ __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uin
     }
 }
 
-// The runs of one long stripe, [start, end) of a sorted list: a wave takes every kBucketWaves-th of them, from the w-th on,
-// and leaves the sums of their differences in dpe and dpa.  Per run, the rows of the entry are asked for together with the
-// first gradients, and the gradients of U updates are in flight while the U before them are applied: 8 updates per us, twice
-// as many as the steps of the window walk, which carry the loads of rows that most of them do not need.
+// where the run of entry x that begins at pos ends, in the sorted list's [.., end)
+__device__ __forceinline__ uint32_t run_of(const u64 *items, uint32_t pos, uint32_t end, uint32_t x)
+{
+    for (uint32_t q = pos;; q += kWave) {
+        const uint32_t p = q + lane_id();
+        const u64 other = __ballot(p >= end || item_row(items[min(p, end - 1u)]) != x);
+        if (other) return q + lowest_bit(other);
+    }
+}
+
+// The runs of one long stripe with fewer than kTogether updates, [start, end) of a sorted list: a wave takes every
+// kBucketWaves-th of them, from the w-th on, and leaves the sums of their differences in dpe and dpa.  Per run, the rows of
+// the entry are asked for together with the first gradients, and the gradients of U updates are in flight while the U
+// before them are applied: 8 updates per us, twice as many as the steps of the window walk, which carry the loads of rows
+// that most of them do not need.
 template <int NC, int MODE>
 __device__ __forceinline__ void walk_runs(const RowArgs &a, const u64 *items, uint32_t start, uint32_t end, uint32_t cb,
                                           uint32_t w, D2 (&dpe)[NC], D2 (&dpa)[NC])
@@ -253,16 +264,10 @@ __device__ __forceinline__ void walk_runs(const RowArgs &a, const u64 *items, ui
     constexpr uint32_t U = NC == 1 ? 8 : 4;
     const uint32_t D = a.geo.D, lane = lane_id(), col0 = cb * NC * 128u;
     const RuleParams rp = rule_params(a.geo);
-    for (uint32_t pos = start, r = 0, run_end; pos < end; pos = run_end, ++r) {
+    for (uint32_t pos = start, r = 0, run_end; pos < end; pos = run_end) {
         const uint32_t x = uniform(item_row(items[pos]));
-        for (run_end = pos;; run_end += kWave) {
-            const uint32_t p = run_end + lane;
-            const u64 other = __ballot(p >= end || item_row(items[min(p, end - 1u)]) != x);
-            if (!other) continue;
-            run_end += lowest_bit(other);
-            break;
-        }
-        if (r % kBucketWaves != w) continue;
+        run_end = run_of(items, pos, end, x);
+        if (run_end - pos >= kTogether || r++ % kBucketWaves != w) continue;
         const rsrc_t erow = row_f32(a.E, x, D, col0), arow = row_f32(a.A, x, D, col0);
         float2 e[NC], a0[NC], now[U][NC], next[U][NC];
 #pragma unroll
@@ -316,16 +321,119 @@ __device__ __forceinline__ void walk_runs(const RowArgs &a, const u64 *items, ui
     }
 }
 
-// A long stripe by the whole workgroup: its entries are independent, only their differences meet in the parity rows, so the
-// waves share the runs and add their sums up through LDS (s_part: kBucketWaves * NC * 128 doubles).  Every wave calls this.
-// 16 384 updates on 256 rows, 256 to a stripe: 100 us a call when the owner walked it alone, 79 run by run, 58 shared.
+// One run of many updates, [pos, end) of a sorted list, 32 columns (from col0 on) by a wave: the four groups of sixteen lanes
+// take T consecutive updates each and keep their gradients in registers, exchange the updates' sums by shuffles, and apply
+// the updates: 32 to a trip to memory, and no wave waits for another.  The differences are added to dpe and dpa of every lane.
+// Bound by that trip: 25 updates per us, where one wave walking whole rows takes 8 (with T = 16 the same, and the registers it
+// takes slow everything else down).
+template <int MODE>
+__device__ __forceinline__ void walk_columns(const RowArgs &a, const u64 *items, uint32_t pos, uint32_t end, uint32_t col0,
+                                             D2 &dpe, D2 &dpa)
+{
+    constexpr uint32_t T = 8, G = 16, kStep = kWave / G * T;         // updates of a group, lanes of one, updates of a round
+    constexpr bool kMomentum = MODE == kMomentumSeq;
+    const uint32_t D = a.geo.D, lane = lane_id(), first = (lane / G) * T, col_lane = lane % G;
+    const bool live = col0 + 2u * col_lane < D;              // D is a multiple of 4: both columns or none
+    const uint32_t col = live ? col0 + 2u * col_lane : 0u, x = item_row(items[pos]);
+    const RuleParams rp = rule_params(a.geo);
+    float *erow = a.E + (size_t)x * D + col, *arow = a.A + (size_t)x * D + col;
+    float2 g[T];
+    auto load = [&](uint32_t t) {                            // past the run's end: the last update's
+#pragma unroll
+        for (uint32_t u = 0; u < T; ++u)
+            g[u] = *(const float2 *)(a.grads + (size_t)(uint32_t)items[min(t + first + u, end - 1u)] * D + col);
+    };
+    load(pos);
+    const float2 e = *(const float2 *)erow, a0 = *(const float2 *)arow;
+    D2 state = start2<MODE>(widen2(a0)), acc = D2{0, 0};
+    for (uint32_t t = pos;; t += kStep) {
+        const uint32_t cnt = t + first < end ? min(T, end - t - first) : 0u;
+        if (Rule<MODE>::combine) {
+#pragma unroll
+            for (uint32_t u = 0; u < T; ++u)
+                if (u < cnt) item2<MODE>(state, acc, g[u], rp);
+        } else {
+            D2 s = D2{-0.0, -0.0};                           // the neutral summand
+            double d = kMomentum ? decay_over(cnt, rp.mu) : 1.0;
+#pragma unroll
+            for (uint32_t u = 0; u < T; ++u)
+                if (u < cnt) summary2<MODE>(s, g[u], rp);
+            // inclusive scan over the groups of the maps v -> d * v + s, then the state before each group and after all
+#pragma unroll
+            for (int by = G; by < kWave; by <<= 1) {
+                const double ox = __shfl_up(s.x, by, kWave), oy = __shfl_up(s.y, by, kWave);
+                const double od = kMomentum ? __shfl_up(d, by, kWave) : 1.0;
+                if (lane >= (uint32_t)by) {
+                    s.x = kMomentum ? fma(d, ox, s.x) : s.x + ox;
+                    s.y = kMomentum ? fma(d, oy, s.y) : s.y + oy;
+                    if (kMomentum) d = decay(d * od, rp.mu);
+                }
+            }
+            const double bx = __shfl_up(s.x, G, kWave), by = __shfl_up(s.y, G, kWave), bd = kMomentum ? __shfl_up(d, G, kWave) : 1.0;
+            D2 mine = state;
+            if (lane >= G) {
+                mine.x = kMomentum ? fma(bd, state.x, bx) : state.x + bx;
+                mine.y = kMomentum ? fma(bd, state.y, by) : state.y + by;
+            }
+            const int last = (int)(kWave - G + col_lane);
+            const double lx = __shfl(s.x, last, kWave), ly = __shfl(s.y, last, kWave), ld = kMomentum ? __shfl(d, last, kWave) : 1.0;
+            state.x = kMomentum ? fma(ld, state.x, lx) : state.x + lx;
+            state.y = kMomentum ? fma(ld, state.y, ly) : state.y + ly;
+            // the gradients are widened once more: kept in 64 bits from their sum on, they would spill
+#pragma unroll
+            for (uint32_t u = 0; u < T; ++u) asm volatile("" : "+v"(g[u].x), "+v"(g[u].y));
+#pragma unroll
+            for (uint32_t u = 0; u < T; ++u)
+                if (u < cnt) item2<MODE>(mine, acc, g[u], rp);
+        }
+        if (t + kStep >= end) break;
+        load(t + kStep);
+    }
+    D2 &sum = Rule<MODE>::combine ? state : acc;             // over the groups
+#pragma unroll
+    for (int by = G; by < kWave; by <<= 1) {
+        sum.x += __shfl_xor(sum.x, by, kWave);
+        sum.y += __shfl_xor(sum.y, by, kWave);
+    }
+    const D2 e64 = widen2(e), a64 = widen2(a0);
+    finish2<MODE>(state, acc, a64, rp);
+    if (live && lane < G) {
+        *(float2 *)erow = narrow2(D2{e64.x - acc.x, e64.y - acc.y});
+        *(float2 *)arow = narrow2(state);
+    }
+    dpe.x -= acc.x;
+    dpe.y -= acc.y;
+    dpa.x += state.x - a64.x;
+    dpa.y += state.y - a64.y;
+}
+
+// A long stripe by the whole workgroup: its entries are independent, only their differences meet in the parity rows.  The waves
+// share the columns of the long runs, and the short runs as a whole, and add their sums up through LDS (s_part: 6 * NC * 128
+// doubles).  Every wave calls this.
+// 16 384 updates on 256 rows, 256 to a stripe: 100 us a call when the owner walked it alone, 79 run by run, 58 with the runs
+// shared.  With the columns of the long ones shared as well: 26 624 half Zipf 62.6 -> 55.2, 8192 half Zipf 47.7 -> 40.8, 20 000
+// Zipf, k = 2, 52.9 -> 48.2, 150 000 Zipf of 256 floats 207 -> 200.
 template <int NC, int MODE, bool PARITY>
 __device__ __forceinline__ void walk_long_stripe(const RowArgs &a, const u64 *items, uint32_t start, uint32_t end, double *s_part)
 {
     const uint32_t w = uniform(threadIdx.x / kWave), lane = lane_id(), D = a.geo.D;
     const uint32_t g = a.geo.dk.div(uniform(item_row(items[start])));
     for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
-        D2 d[2][NC];                                    // the neutral summand
+#pragma unroll 1
+        for (int i = 0; i < NC; ++i) {
+            const uint32_t col0 = (cb * NC + i) * 128u + w * 32u;
+            D2 c[2] = {D2{-0.0, -0.0}, D2{-0.0, -0.0}}; // the neutral summand
+            for (uint32_t pos = start, run_end; pos < end && col0 < D; pos = run_end) {
+                run_end = run_of(items, pos, end, uniform(item_row(items[pos])));
+                if (run_end - pos >= kTogether) walk_columns<MODE>(a, items, pos, run_end, col0, c[0], c[1]);
+            }
+            if (lane < 16u) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    *(double2 *)(s_part + ((kBucketWaves + q) * NC + i) * 128u + w * 32u + 2u * lane) = double2{c[q].x, c[q].y};
+            }
+        }
+        D2 d[2][NC];
 #pragma unroll
         for (int i = 0; i < NC; ++i) d[0][i] = d[1][i] = D2{-0.0, -0.0};
         walk_runs<NC, MODE>(a, items, start, end, cb, w, d[0], d[1]);
@@ -345,8 +453,9 @@ __device__ __forceinline__ void walk_long_stripe(const RowArgs &a, const u64 *it
                 for (int i = 0; i < NC; ++i) {
                     D2 sum = widen2(old[i]);
 #pragma unroll
-                    for (int v = 0; v < kBucketWaves; ++v) {
-                        const double2 part = *(const double2 *)(s_part + (v * NC + i) * 128u + 2u * lane);
+                    for (int v = 0; v <= kBucketWaves; ++v) {
+                        const int at = v < kBucketWaves ? v : kBucketWaves + q;
+                        const double2 part = *(const double2 *)(s_part + (at * NC + i) * 128u + 2u * lane);
                         sum.x += part.x;
                         sum.y += part.y;
                     }
@@ -421,7 +530,7 @@ __device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n,
         uint32_t x, g;
         bool bad;
         if (r * kPartThreads >= sample || !takes_part(a, key[r], x, g, bad)) continue;
-        for (uint32_t s = mix32(g) & (kSampleSlots - 1u);; s = (s + 1u) & (kSampleSlots - 1u)) {   // at most kSample slots fill
+        for (uint32_t s = scramble32(g) & (kSampleSlots - 1u);; s = (s + 1u) & (kSampleSlots - 1u)) {   // at most kSample slots fill
             const uint32_t was = atomicCAS(&t.g[s], kNoKey, g);
             if (was == kNoKey || was == g) {
                 atomicAdd(&t.c[s], 1u);
@@ -445,7 +554,7 @@ __device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n,
         for (uint32_t i = 0; i < nc; ++i)
             rank += t.cand_c[i] > c || (t.cand_c[i] == c && t.cand_g[i] < g) ? 1u : 0u;
         if (rank < cap) {
-            uint32_t s = mix32(g) & (kHotSlots - 1u);
+            uint32_t s = scramble32(g) & (kHotSlots - 1u);
             while (atomicCAS(&hot.g[s], kNoKey, g) != kNoKey) s = (s + 1u) & (kHotSlots - 1u);     // kHotMax < kHotSlots
             hot.h[s] = rank;
         }
@@ -496,7 +605,7 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
                 row[r] = x;
                 dig[r] = bucket_of(g, ordinary);
                 if (n_hot) {
-                    for (uint32_t s = mix32(g) & (kHotSlots - 1u); s_hot.g[s] != kNoKey; s = (s + 1u) & (kHotSlots - 1u)) {
+                    for (uint32_t s = scramble32(g) & (kHotSlots - 1u); s_hot.g[s] != kNoKey; s = (s + 1u) & (kHotSlots - 1u)) {
                         if (s_hot.g[s] == g) {
                             dig[r] = ordinary + s_hot.h[s] * a.dk.d + j;
                             break;
@@ -639,16 +748,14 @@ struct ListShared {
     uint32_t srv[2 * kBucketMaxServers];
 };
 
-// Applies every stripe of a sorted list of m items (m <= kBucketCap).  Chunks of CH positions are handed to the waves as
+// Applies every stripe of a sorted list of m items (m <= kBucketCap).  Chunks of a few positions are handed to the waves as
 // they come free; a wave owns the stripes that open in its chunk.  A stripe that does not end inside the wave's
 // 64-position window
 //   - is only listed in sh.heavy if it has a run of heavy_run updates and that makes up more than half of it, or it has
 //     shared_stripe updates;
-//   - is walked by the whole workgroup afterwards if its updates are spread over entries with several each (s_part: room
-//     for walk_long_stripe);
-//   - is walked by its owner otherwise, window by window with its state in registers: there is nothing to share.
+//   - is walked by the whole workgroup afterwards otherwise (s_part: room for walk_long_stripe).
 // A barrier has to lie between the last write of the list and this call; the call ends with one.
-template <int NC, int MODE, bool PARITY, uint32_t CH>
+template <int NC, int MODE, bool PARITY>
 __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, uint32_t m, uint32_t heavy_run,
                                            uint32_t shared_stripe, ListShared &sh, double *s_part)
 {
@@ -660,6 +767,8 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
         sh.chunk = kBucketWaves;
     }
     __syncthreads();
+    // a chunk for each wave of a short list
+    const uint32_t CH = min(kBucketChunk, max(1u, (m + kBucketWaves - 1u) / kBucketWaves));
     for (uint32_t c = uniform(threadIdx.x / kWave); c * CH < m;) {
         const uint32_t p0 = c * CH;
         if (lane == 0) c = atomicAdd(&sh.chunk, 1u);         // the chunk after this one
@@ -680,7 +789,6 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
         // the stripe that goes on behind the window: where it ends, and how long its runs are
         const uint32_t big_start = p0 + last;
         uint32_t big_end = big_start;
-        bool heavy = false, shared = false;
         if (!inside) {
             const uint32_t g = dk.div(from_lane(wkey, last));
             bool long_run = false, one_run = false;                 // of heavy_run updates; of more than half of the stripe
@@ -697,40 +805,19 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
                 big_end += kWave;
             }
             const uint32_t size = big_end - big_start, half = size / 2u;
-            for (uint32_t q = big_start; q + half < big_end; q += kWave) {
+            for (uint32_t q = big_start; long_run && q + half < big_end; q += kWave) {
                 const uint32_t p = min(q + lane, big_end - half - 1u);
                 if (__ballot(item_row(items[p + half]) == item_row(items[p]))) one_run = true;
             }
-            heavy = long_run && (one_run || size >= shared_stripe);
-            shared = !heavy && !one_run && size >= kLongRuns * dk.d;
-            if (lane == 0 && heavy) sh.heavy[atomicAdd(&sh.n_heavy, 1u)] = big_start | (big_end << 16);
-            if (lane == 0 && shared) sh.longs[atomicAdd(&sh.n_long, 1u)] = big_start | (big_end << 16);
-        }
-        for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
-            Walk<NC> walk;
-            walk.begin();
-            // the window, then the windows of the stripe that goes on behind it
-            uint32_t wk = wkey, wi = widx, from = first, to = end, p = p0;
-            u64 rh = rowheads, sth = stripeheads;
-            bool run_on = false, stripe_on = false;
-            for (bool more = !inside && !heavy && !shared;;) {
-                walk_window<NC, MODE, PARITY, kQ, kU>(a, wk, wi, rh, sth, from, to, cb, walk, run_on, stripe_on);
-                if (!more) break;
-                p = stripe_on ? p + kWave : big_start;
-                const u64 nx = p + lane < big_end ? items[p + lane] : ~0ull;
-                wk = item_row(nx);
-                wi = (uint32_t)nx;
-                uint32_t lk = __shfl_up(wk, 1, kWave);
-                if (lane == 0) lk = p > big_start ? item_row(items[p - 1]) : kNoKey;
-                rh = __ballot(lk != wk);
-                sth = p == big_start ? 1ull : 0ull;
-                from = 0;
-                stripe_on = p + kWave < big_end;
-                to = stripe_on ? (uint32_t)kWave : big_end - p;
-                run_on = stripe_on && uniform(item_row(items[stripe_on ? p + kWave : p])) == from_lane(wk, kWave - 1);
-                more = stripe_on;
+            const uint32_t what = big_start | (big_end << 16);
+            if (lane == 0) {
+                if (long_run && (one_run || size >= shared_stripe)) sh.heavy[atomicAdd(&sh.n_heavy, 1u)] = what;
+                else sh.longs[atomicAdd(&sh.n_long, 1u)] = what;
             }
         }
+        if (first < end)
+            for (uint32_t cb = 0; cb < a.geo.ncb; ++cb)
+                walk_window<NC, MODE, PARITY, kQ, kU>(a, wkey, widx, rowheads, stripeheads, first, end, cb);
     }
     __syncthreads();
     const uint32_t n_long = uniform(sh.n_long);
@@ -781,6 +868,46 @@ struct BucketArgs : RowArgs {
     uint32_t holding;            // a recovery is in progress: the header follows what hold_tiles did
     BucketLimits lim;
 };
+
+// A replay has as many updates as were waiting, not as many as the buffer holds: the partition's plan.
+__device__ __forceinline__ void plan_replay(BucketArgs &a)
+{
+    if (!a.packed) return;
+    a.n = min(a.n, a.hdr->n_batch);
+    a.tiles = (a.n + a.tile - 1u) / a.tile;
+    a.buckets = bucket_count(a.n);
+    a.lim = bucket_limits(a.n, a.geo.k, a.geo.D);
+}
+
+// The kernel's arguments, read once more: what is needed on rare paths only is not kept in scalar registers across the walk,
+// which needs all of them (a hundred were spilled).  The pointers are read as pointers to device memory: after a flat access
+// the compiler has the walk wait for all of its loads.
+template <typename T>
+__device__ __forceinline__ void read_global(T *&p, const __attribute__((address_space(4))) char *from)
+{
+    typedef __attribute__((address_space(1))) T *global;
+    p = (T *)*(const __attribute__((address_space(4))) global *)from;
+}
+__device__ __forceinline__ BucketArgs args_again()
+{
+    typedef __attribute__((address_space(4))) const char byte;
+    typedef __attribute__((address_space(4))) const u64 word;
+    static_assert(sizeof(BucketArgs) % sizeof(u64) == 0 && alignof(BucketArgs) == alignof(u64), "copied word by word");
+    byte *p = (byte *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    u64 w[sizeof(BucketArgs) / sizeof(u64)];
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(BucketArgs) / sizeof(u64); ++i) w[i] = ((word *)p)[i];
+    BucketArgs a;
+    __builtin_memcpy(&a, w, sizeof(a));
+    auto again = [&](auto &field) { read_global(field, p + ((const char *)&field - (const char *)&a)); };
+    again(a.E); again(a.A); again(a.PE); again(a.PA); again(a.grads); again(a.keys); again(a.items); again(a.tmp);
+    again(a.dense); again(a.table); again(a.tile_cnt); again(a.tile_state); again(a.heavy); again(a.split.run);
+    again(a.split.tiles); again(a.split.segment_run); again(a.split.summed); again(a.split.arrived); again(a.split.sums);
+    again(a.split.steps); again(a.hdr); again(a.load_data); again(a.load_parity);
+    plan_replay(a);
+    return a;
+}
 
 // gradient row of an item, from its position in the batch
 __device__ __forceinline__ u64 resolved(const BucketArgs &a, u64 it)
@@ -923,12 +1050,12 @@ __device__ __forceinline__ uint32_t oversized_part(const BucketArgs &a, BucketSh
         }
         if (tid == 0) sh.fill = sh.light = sh.n_light = sh.over = sh.hv_n = 0;
         __syncthreads();
-        volatile uint32_t *over = &sh.over;
+        auto *over = (volatile __attribute__((address_space(3))) uint32_t *)&sh.over;
         stream_items(tmp, 0, m, tid, kBucketThreads, [&](u64 it) {
             const uint32_t g = dk.div(item_row(it));
             // one lane for all of the wave's items of its stripe: a hot stripe's counter, updated by every lane, is
             // what this pass would wait for
-            bool in = it != ~0ull && (mix32(g) & mask) == part;
+            bool in = it != ~0ull && (scramble32(g) & mask) == part;
             uint32_t c = 0;
             for (u64 todo = __ballot(in); todo;) {
                 const u64 same = __ballot(in && g == from_lane(g, lowest_bit(todo)));
@@ -969,7 +1096,7 @@ __device__ __forceinline__ uint32_t oversized_part(const BucketArgs &a, BucketSh
     if (light)
         stream_items(tmp, 0, m, tid, kBucketThreads, [&](u64 it) {
             const uint32_t g = dk.div(item_row(it));
-            if (it == ~0ull || (mix32(g) & mask) != part) return;
+            if (it == ~0ull || (scramble32(g) & mask) != part) return;
             if (sh.tab_c[stripe_slot(sh.tab_g, g)] < heavy) sh.item[atomicAdd(&sh.n_light, 1u)] = it;
         });
     // ---- the heavy ones: a stable partition by member, every wave a contiguous quarter of the items
@@ -1072,19 +1199,14 @@ __device__ __forceinline__ void split_run(const BucketArgs &a, BucketShared &sh,
         for (uint32_t i = tid; i < ncg; i += kBucketThreads) a.split.arrived[r / a.geo.k * ncg + i] = 0;
 }
 
-static_assert(sizeof(BucketShared::tmp) >= kBucketWaves * 2 * 128 * sizeof(double), "walk_long_stripe's sums for NC = 2");
+static_assert(sizeof(BucketShared::tmp) >= (kBucketWaves + 2) * 2 * 128 * sizeof(double), "walk_long_stripe's sums for NC = 2");
 
 template <int NC, int MODE, bool PARITY>
 __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_kernel(BucketArgs a)
 {
     __shared__ BucketShared sh;
-    if (a.packed) {                                                 // a replay: as many as were waiting (the partition's plan)
-        a.n = min(a.n, a.hdr->n_batch);
-        a.tiles = (a.n + a.tile - 1u) / a.tile;
-        a.buckets = bucket_count(a.n);
-        a.lim = bucket_limits(a.n, a.geo.k, a.geo.D);
-        if (blockIdx.x >= a.buckets + kHotBuckets) return;
-    }
+    plan_replay(a);
+    if (blockIdx.x >= a.buckets + kHotBuckets) return;
     const uint32_t tid = threadIdx.x, B = a.buckets + kHotBuckets, S = a.geo.S, k = a.geo.k;
     // the hot stripes' buckets first: what takes longest must not begin last
     const uint32_t b = blockIdx.x < kHotBuckets ? a.buckets + blockIdx.x : blockIdx.x - kHotBuckets;
@@ -1163,45 +1285,53 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
     } else if (tid == 0) {
         sh.dense_used = 0;
     }
-    for (;;) {
-        uint32_t list = m;
-        if (oversized) {
-            list = oversized_part(a, sh, m, base, walk);
-        } else {
-            constexpr int P = kBucketCap / kBucketThreads;
-            u64 it[P];
+    uint32_t list = m;
+    if (!oversized) {
+        constexpr int P = kBucketCap / kBucketThreads;
+        u64 it[P];
 #pragma unroll
-            for (int c = 0; c < P; ++c) {
-                const uint32_t q = c * kBucketThreads + tid;
-                if (q < m) it[c] = a.items[place_of(sh.pref, sh.start, a.tiles, q)];
-            }
-#pragma unroll
-            for (int c = 0; c < P; ++c) {
-                const uint32_t q = c * kBucketThreads + tid;
-                if (q < m) sh.item[q] = it[c];
-            }
-            __syncthreads();
+        for (int c = 0; c < P; ++c) {
+            const uint32_t q = c * kBucketThreads + tid;
+            if (q < m) it[c] = a.items[place_of(sh.pref, sh.start, a.tiles, q)];
         }
+#pragma unroll
+        for (int c = 0; c < P; ++c) {
+            const uint32_t q = c * kBucketThreads + tid;
+            if (q < m) sh.item[q] = it[c];
+        }
+        __syncthreads();
+    }
+    const RowArgs rows = a;
+    const uint32_t heavy_run = a.lim.heavy_run, shared = many ? a.lim.shared_stripe : 0u, packed = a.packed;
+    for (;;) {
+        if (oversized) list = oversized_part(args_again(), sh, m, base, walk);
         if (list) {
             sort_items(sh.item, sh.tmp, list);
-            if (a.packed) {
-                for (uint32_t i = tid; i < list; i += kBucketThreads) sh.item[i] = resolved(a, sh.item[i]);
+            if (packed) {
+                const BucketArgs b2 = args_again();
+                for (uint32_t i = tid; i < list; i += kBucketThreads) sh.item[i] = resolved(b2, sh.item[i]);
                 __syncthreads();
             }
-            if (Rule<MODE>::combine) count_list(a.geo, sh.item, list, sh.list.srv, a.load_data, a.load_parity);
-            apply_list<NC, MODE, PARITY, kBucketChunk>(a, sh.item, list, a.lim.heavy_run, many ? a.lim.shared_stripe : 0u, sh.list, (double *)sh.tmp);
+            if (Rule<MODE>::combine) {
+                const BucketArgs b2 = args_again();
+                count_list(b2.geo, sh.item, list, sh.list.srv, b2.load_data, b2.load_parity);
+            }
+            apply_list<NC, MODE, PARITY>(rows, sh.item, list, heavy_run, shared, sh.list, (double *)sh.tmp);
             const uint32_t nh = uniform(sh.list.n_heavy);
-            if (nh && !have_base) {
-                bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, base);
-                have_base = true;
-            }
-            for (uint32_t h = 0; h < nh; ++h) {                     // the long runs' stripes, sorted as they are
-                const uint32_t at0 = uniform(sh.dense_used), hs = uniform(sh.list.heavy[h]);
-                const uint32_t start = hs & 0xFFFFu, count = (hs >> 16) - start;
-                for (uint32_t i = tid; i < count; i += kBucketThreads) a.dense[base + at0 + i] = sh.item[start + i];
-                __syncthreads();                                    // every wave has taken at0
-                if (tid == 0) list_heavy(a, sh.dense_used, base, at0, count, true);
-                __syncthreads();
+            if (nh) {
+                const BucketArgs b2 = args_again();
+                if (!have_base) {
+                    bucket_excl_scan(tid < b2.tiles ? from - tid * b2.tile : 0u, sh.wave, base);
+                    have_base = true;
+                }
+                for (uint32_t h = 0; h < nh; ++h) {                 // the long runs' stripes, sorted as they are
+                    const uint32_t at0 = uniform(sh.dense_used), hs = uniform(sh.list.heavy[h]);
+                    const uint32_t start = hs & 0xFFFFu, count = (hs >> 16) - start;
+                    for (uint32_t i = tid; i < count; i += kBucketThreads) b2.dense[base + at0 + i] = sh.item[start + i];
+                    __syncthreads();                                // every wave has taken at0
+                    if (tid == 0) list_heavy(b2, sh.dense_used, base, at0, count, true);
+                    __syncthreads();
+                }
             }
         }
         if (!oversized || walk.depth < 0) break;
@@ -1278,17 +1408,6 @@ __device__ __forceinline__ void fold_segments(const BucketArgs &a, HeavyShared &
     if (ROWS == 2) sh.part[1][part][c] = steps;
     if (c == 0) sh.dec[part] = d;
     __syncthreads();
-}
-
-// the decay over m updates
-__device__ __forceinline__ double decay_over(uint32_t m, double mu)
-{
-    double r = 1.0, p = mu;
-    for (; m; m >>= 1) {
-        if (m & 1u) r = decay(r * p, mu);
-        p = decay(p * p, mu);
-    }
-    return r;
 }
 
 // The last workgroup of a stripe applies what its segments have left: 16 columns, a thread each.
@@ -1433,7 +1552,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
     constexpr int T = kHeavyT;
     __shared__ HeavyShared sh;
     if (a.hdr->batch_bad) return;
-    if (a.packed) a.tiles = (min(a.n, a.hdr->n_batch) + a.tile - 1u) / a.tile;
+    plan_replay(a);
     const uint32_t nh = a.hdr->n_heavy, ns = a.hdr->n_segments, D = a.geo.D, k = a.geo.k, lane = lane_id();
     if (nh + ns == 0) return;
     const uint32_t w = uniform(threadIdx.x / kWave), col_lane = lane & 7u, sub = w * 8u + lane / 8u;

@@ -19,6 +19,17 @@ constexpr int kHeavyT = 16;                  // updates that a group of eight la
 // a finite one is below 1e-269, nothing in 32 bits.
 __device__ __forceinline__ double decay(double power, double mu) { return mu > 0.0 ? fmax(power, 2.2250738585072014e-308) : power; }
 
+// the decay over m updates
+__device__ __forceinline__ double decay_over(uint32_t m, double mu)
+{
+    double r = 1.0, p = mu;
+    for (; m; m >>= 1) {
+        if (m & 1u) r = decay(r * p, mu);
+        p = decay(p * p, mu);
+    }
+    return r;
+}
+
 // gradient rows of a run's updates at, at + 1 (past its end: its last update's)
 template <typename I>
 __device__ __forceinline__ void heavy_indices(const I *run, uint32_t L, uint32_t at, uint32_t &i0, uint32_t &i1)
