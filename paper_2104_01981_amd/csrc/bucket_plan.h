@@ -33,7 +33,8 @@ constexpr uint32_t kBucketMaxServers = 64;   // per-tile load counts are kept fo
 constexpr uint32_t kBucketChunk = 8;         // sorted positions whose stripes a wave owns at a time
 // A stripe that does not end inside a window of 64 positions leaves its bucket for heavy_stripes, which splits it over the
 // columns, if it has a run of heavy_run(n) updates: its workgroup would take 25 of them per us, where heavy_stripes takes 300
-// (at 256 instead of 128, of Zipf batches: 65 536 half Zipf 89.5 -> 87.6, 20 000 of k = 2 48.2 -> 50.0, 256 floats 200 -> 203).  A
+// but begins when the buckets are done.  With runs from 128 on heavy, n / 2048 in large batches: 26 624 half Zipf 55.0, now 48.4;
+// 8192 half Zipf 39.5, 33.0; 65 536 half Zipf 89.4, 84.9; 300 007 Zipf combined 197, 182; 2^19 Zipf 324, 293.  A
 // heavy stripe takes ~6 us for every entry in each of its D / 16 workgroups, however short its run is, so that few of them
 // are a gain and many a loss.  In a batch of many long stripes -- more than kManyHot hot ones in the sample: a small table --
 // a stripe that no run dominates is shared by the waves of its workgroup instead, as long as it has fewer than
@@ -44,7 +45,7 @@ constexpr uint32_t kBucketChunk = 8;         // sorted positions whose stripes a
 // long stripes shared, 80 with them heavy), and tables of a few hundred stripes, of 36 or more (2^16 on 1024 rows: 75 and 99).
 constexpr uint32_t kManyHot = 32;
 constexpr uint32_t kHeavyRunMin = 128, kHeavyStripeMin = 256, kHeavyEntryMin = 16;
-ECRM_HD uint32_t heavy_run(uint32_t n) { return n / 2048u > kHeavyRunMin ? n / 2048u : kHeavyRunMin; }
+ECRM_HD uint32_t heavy_run(uint32_t n) { return n / 640u > 2u * kHeavyRunMin ? n / 640u : 2u * kHeavyRunMin; }
 // of a stripe that makes its bucket too long for LDS
 ECRM_HD uint32_t heavy_stripe(uint32_t k) { return kHeavyEntryMin * k > kHeavyStripeMin ? kHeavyEntryMin * k : kHeavyStripeMin; }
 ECRM_HD uint32_t shared_stripe(uint32_t n, uint32_t k)
@@ -71,10 +72,16 @@ ECRM_HD uint32_t split_segments(uint32_t n, uint32_t k)
     const uint32_t runs = n / kSplitStripeMin * k;
     return runs ? n / kSplitSegment + (runs < kHotBuckets ? runs : kHotBuckets) : 0u;
 }
-struct BucketLimits { uint32_t heavy_run, shared_stripe, split_stripe; };
+// A hot stripe of up to this many updates is worked off beside the buckets, 100 updates per us, a longer one by heavy_stripes
+// behind them, 300 per us: what takes longer than the buckets do should not be in their launch (twice as much: no change).
+// Nor one of more entries than this: each costs its workgroups a few more trips to memory than in heavy_stripes (2^16 updates on
+// 2520 rows, k = 63: 594 us there, 782 in place).
+constexpr uint32_t kInPlaceEntries = 16;
+ECRM_HD uint32_t hot_in_place(uint32_t n) { return n / 16u > 2048u ? n / 16u : 2048u; }
+struct BucketLimits { uint32_t heavy_run, shared_stripe, split_stripe, hot_in_place; };
 ECRM_HD BucketLimits bucket_limits(uint32_t n, uint32_t k, uint32_t D)
 {
-    return BucketLimits{heavy_run(n), shared_stripe(n, k), split_stripe(n, D)};
+    return BucketLimits{heavy_run(n), shared_stripe(n, k), split_stripe(n, D), hot_in_place(n)};
 }
 struct BucketPlan { uint32_t ipt, tiles, buckets; };
 // Tiles as small as kMaxTiles of them allow.  Buckets of 8 updates while that gives no more than the 1024 workgroups that

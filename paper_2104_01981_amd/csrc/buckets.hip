@@ -7,14 +7,14 @@
 //                     load counts of the tile are done on the way.  No scan over tiles: a bucket is the list of its
 //                     pieces in the tiles.  The entries of hot stripes, found in a sample, get buckets of their own.
 //   bucket_apply      one workgroup per bucket collects the pieces in LDS, sorts them by (row, position) there and
-//                     applies the bucket's stripes.
-//   heavy_stripes     stripes with long runs: split over the columns, which are independent chains, so that each is read
-//                     once and no workgroup waits for another -- but for very long ones, whose runs are cut up as well.
+//                     applies the bucket's stripes.  Hot stripes are split over their columns, which are independent
+//                     chains, by workgroups that begin before the buckets'.
+//   heavy_stripes     stripes with long runs that were found late, or are too long to be worked off beside the buckets:
+//                     split over the columns; of very long ones the runs are cut up as well.
 //
 // The results are those of the general path: fp64 chains in arrival order, every touched element rounded once.
-// Measured against the general path (us a call, D = 128): 2048 updates 54 -> 19; 26 624 half Zipf 173 -> 59; 65 536
-// uniform on 2^14 rows 60 -> 46; 300 007 Zipf, combined rule 325 -> 203.  The kernels of the 26 624: partition 8.6,
-// apply 41 (97 MB, 21 us at the rate of the large batches), heavy stripes 11.
+// Measured against the general path (us a call, D = 128): 2048 updates 54 -> 17; 26 624 half Zipf 173 -> 49; 65 536
+// uniform on 2^14 rows 60 -> 44; 300 007 Zipf, combined rule 325 -> 182.
 #include "long_runs.h"
 
 namespace ecrm {
@@ -23,7 +23,11 @@ typedef unsigned long long u64;
 
 constexpr int kBucketWaves = kBucketThreads / kWave;
 constexpr int kPartWaves = kPartThreads / kWave;
-constexpr uint32_t kTogether = 32;       // updates of a run from which on the waves of a workgroup share its columns
+// Updates of a run from which on the waves of a workgroup share its columns; and it has to be a third of its stripe: of more
+// runs of a kind the waves take one each (2^19 updates on 2^14 rows, 128 to a stripe: 161 us with every run's columns
+// shared, 124 so; on 2^13 rows of 512 floats 402 and 292).
+constexpr uint32_t kTogether = 32;
+__device__ __forceinline__ uint32_t together(uint32_t stripe) { return max(kTogether, stripe / 3u); }
 constexpr uint32_t kLongList = kBucketCap / (kWave - kBucketChunk);      // such stripes that a list can hold
 
 __device__ __forceinline__ uint32_t item_row(u64 it) { return (uint32_t)(it >> 32); }
@@ -252,14 +256,14 @@ __device__ __forceinline__ uint32_t run_of(const u64 *items, uint32_t pos, uint3
     }
 }
 
-// The runs of one long stripe with fewer than kTogether updates, [start, end) of a sorted list: a wave takes every
+// The runs of one long stripe with fewer than `least` updates, [start, end) of a sorted list: a wave takes every
 // kBucketWaves-th of them, from the w-th on, and leaves the sums of their differences in dpe and dpa.  Per run, the rows of
 // the entry are asked for together with the first gradients, and the gradients of U updates are in flight while the U
 // before them are applied: 8 updates per us, twice as many as the steps of the window walk, which carry the loads of rows
 // that most of them do not need.
 template <int NC, int MODE>
 __device__ __forceinline__ void walk_runs(const RowArgs &a, const u64 *items, uint32_t start, uint32_t end, uint32_t cb,
-                                          uint32_t w, D2 (&dpe)[NC], D2 (&dpa)[NC])
+                                          uint32_t w, uint32_t least, D2 (&dpe)[NC], D2 (&dpa)[NC])
 {
     constexpr uint32_t U = NC == 1 ? 8 : 4;
     const uint32_t D = a.geo.D, lane = lane_id(), col0 = cb * NC * 128u;
@@ -267,7 +271,7 @@ __device__ __forceinline__ void walk_runs(const RowArgs &a, const u64 *items, ui
     for (uint32_t pos = start, r = 0, run_end; pos < end; pos = run_end) {
         const uint32_t x = uniform(item_row(items[pos]));
         run_end = run_of(items, pos, end, x);
-        if (run_end - pos >= kTogether || r++ % kBucketWaves != w) continue;
+        if (run_end - pos >= least || r++ % kBucketWaves != w) continue;
         const rsrc_t erow = row_f32(a.E, x, D, col0), arow = row_f32(a.A, x, D, col0);
         float2 e[NC], a0[NC], now[U][NC], next[U][NC];
 #pragma unroll
@@ -417,15 +421,20 @@ template <int NC, int MODE, bool PARITY>
 __device__ __forceinline__ void walk_long_stripe(const RowArgs &a, const u64 *items, uint32_t start, uint32_t end, double *s_part)
 {
     const uint32_t w = uniform(threadIdx.x / kWave), lane = lane_id(), D = a.geo.D;
-    const uint32_t g = a.geo.dk.div(uniform(item_row(items[start])));
+    const uint32_t g = a.geo.dk.div(uniform(item_row(items[start]))), least = together(end - start);
+    bool any = false;                                   // one of `least` updates: most stripes of many entries have none
+    for (uint32_t q = start; q + least <= end; q += kWave) {
+        const uint32_t p = min(q + lane, end - least);
+        any |= __ballot(item_row(items[p]) == item_row(items[p + least - 1u])) != 0;
+    }
     for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
 #pragma unroll 1
         for (int i = 0; i < NC; ++i) {
             const uint32_t col0 = (cb * NC + i) * 128u + w * 32u;
             D2 c[2] = {D2{-0.0, -0.0}, D2{-0.0, -0.0}}; // the neutral summand
-            for (uint32_t pos = start, run_end; pos < end && col0 < D; pos = run_end) {
+            for (uint32_t pos = start, run_end; any && pos < end && col0 < D; pos = run_end) {
                 run_end = run_of(items, pos, end, uniform(item_row(items[pos])));
-                if (run_end - pos >= kTogether) walk_columns<MODE>(a, items, pos, run_end, col0, c[0], c[1]);
+                if (run_end - pos >= least) walk_columns<MODE>(a, items, pos, run_end, col0, c[0], c[1]);
             }
             if (lane < 16u) {
 #pragma unroll
@@ -436,7 +445,7 @@ __device__ __forceinline__ void walk_long_stripe(const RowArgs &a, const u64 *it
         D2 d[2][NC];
 #pragma unroll
         for (int i = 0; i < NC; ++i) d[0][i] = d[1][i] = D2{-0.0, -0.0};
-        walk_runs<NC, MODE>(a, items, start, end, cb, w, d[0], d[1]);
+        walk_runs<NC, MODE>(a, items, start, end, cb, w, least, d[0], d[1]);
         if (!PARITY) continue;
 #pragma unroll
         for (uint32_t q = 0; q < 2; ++q) {              // the parity entry, by wave 0; its state, by wave 1
@@ -936,6 +945,7 @@ struct BucketShared {
     union {
         __align__(16) u64 tmp[kBucketCap];                     // of the sort, and sums of walk_long_stripe
         struct { uint32_t tab_g[kStripeSlots], tab_c[kStripeSlots]; };     // of an oversized bucket, before it
+        ExchangeOf<kBucketWaves> ex[2];                        // of a hot stripe
     };
     ListShared list;
     uint32_t pref[kMaxTiles + 1], start[kMaxTiles], wave[kBucketWaves];
@@ -1199,6 +1209,193 @@ __device__ __forceinline__ void split_run(const BucketArgs &a, BucketShared &sh,
         for (uint32_t i = tid; i < ncg; i += kBucketThreads) a.split.arrived[r / a.geo.k * ncg + i] = 0;
 }
 
+// ---- hot stripes -----------------------------------------------------------------------------------
+// The stripes that the sample took for hot, numbered as they are ranked.  The first kHotMax workgroups look after one each,
+// should it be short after all; the others of the hot buckets' kHotBuckets take (stripe, 16 columns) jobs, so that what takes
+// long begins first and beside everything else: as a launch of its own behind this one it was 7 to 11 us of a call.
+
+// one entry's updates, or a whole stripe's: how many, where each tile's lie
+struct HotSpan { uint32_t from, len; };
+__device__ __forceinline__ HotSpan hot_span(const BucketArgs &a, uint32_t first_bucket, uint32_t buckets)
+{
+    HotSpan s{0, 0};
+    if (threadIdx.x < a.tiles) {
+        const uint16_t *row = a.table + (size_t)threadIdx.x * (a.buckets + kHotBuckets + 1) + first_bucket;
+        s.from = threadIdx.x * a.tile + row[0];
+        s.len = (uint32_t)row[buckets] - row[0];
+    }
+    return s;
+}
+
+// 16 columns of hot stripe h, whose updates are left where the partition put them.  As in long_runs.h, with T updates to a
+// group of eight lanes and 32 groups: 256 updates a round.
+template <int MODE, bool PARITY>
+__device__ __forceinline__ void hot_job(const BucketArgs &a, BucketShared &sh, uint32_t h, uint32_t cg)
+{
+    constexpr int T = 8;
+    constexpr uint32_t kRound = kBucketThreads / 8 * T;
+    const uint32_t D = a.geo.D, k = a.geo.k, tid = threadIdx.x, lane = lane_id(), w = uniform(tid / kWave);
+    const uint32_t col_lane = lane & 7u, sub = w * 8u + lane / 8u, col = cg * kHeavyCols + 2u * col_lane;
+    const bool live = col < D;                                      // D is a multiple of 4: both columns or none
+    const RuleParams rp = rule_params(a.geo);
+    uint32_t g = kNoKey, buf = 0;
+    D2 pe = D2{-0.0, -0.0}, pa = D2{-0.0, -0.0};                    // the differences; the neutral summand
+    for (uint32_t j = 0; j < k; ++j) {
+        const HotSpan s = hot_span(a, a.buckets + h * k + j, 1);
+        uint32_t L;
+        const uint32_t at = bucket_excl_scan(s.len, sh.wave, L);
+        if (L == 0) continue;
+        if (tid < a.tiles) {
+            sh.pref[tid] = at;
+            sh.start[tid] = s.from;
+        }
+        if (tid == 0) sh.pref[a.tiles] = L;
+        __syncthreads();
+        // the lanes of a group look up an update each (past the run's end: the last one)
+        auto look = [&](uint32_t r0) {
+            return resolved(a, a.items[place_of(sh.pref, sh.start, a.tiles, min(r0 + sub * T + col_lane, L - 1u))]);
+        };
+        float2 gr[T], nx[T];
+        auto rows = [&](uint32_t idx, uint32_t r0) {
+#pragma unroll
+            for (int u = 0; u < T; ++u) {
+                const uint32_t i = __shfl(idx, (int)((lane & 56u) + u), kWave);
+                nx[u] = float2{0, 0};
+                if (live && r0 + sub * T + u < L) nx[u] = *(const float2 *)(a.grads + (size_t)i * D + col);
+            }
+        };
+        const u64 it = look(0);
+        uint32_t idx = (uint32_t)it;
+        const uint32_t x = uniform(item_row(it));
+        rows(idx, 0);
+        idx = (uint32_t)look(kRound);
+        g = a.geo.dk.div(x);
+        float2 a0 = float2{0, 0};
+        if (live) a0 = *(const float2 *)(a.A + (size_t)x * D + col);
+        D2 state = start2<MODE>(widen2(a0)), acc = D2{0, 0};
+        for (uint32_t r0 = 0; r0 < L; r0 += kRound) {
+            const uint32_t off = r0 + sub * T, cnt = off < L ? min((uint32_t)T, L - off) : 0u;
+#pragma unroll
+            for (int u = 0; u < T; ++u) gr[u] = nx[u];
+            if (r0 + kRound < L) {
+                rows(idx, r0 + kRound);
+                idx = (uint32_t)look(r0 + 2u * kRound);
+            }
+            if (Rule<MODE>::combine) {                              // a sum: nothing to exchange before the run's end
+#pragma unroll
+                for (int u = 0; u < T; ++u) {                       // zeros past the end of the run
+                    acc.x += (double)gr[u].x;
+                    acc.y += (double)gr[u].y;
+                }
+                continue;
+            }
+            double ed;
+            const D2 ex = heavy_sums<MODE>(gr, cnt, rp, sh.ex[buf], w, ed);
+            __syncthreads();
+            D2 mine = heavy_fold<MODE>(state, sh.ex[buf], w, ex, ed);
+#pragma unroll
+            for (int u = 0; u < T; ++u) asm volatile("" : "+v"(gr[u].x), "+v"(gr[u].y));     // widened once more (walk_columns)
+#pragma unroll
+            for (int u = 0; u < T; ++u) {
+                if ((uint32_t)u < cnt) item2<MODE>(mine, acc, gr[u], rp);
+            }
+            buf ^= 1u;                                              // a half is written again only behind the other's barrier
+        }
+        acc = heavy_total(acc, sh.ex[buf], w);
+        buf ^= 1u;
+        if (Rule<MODE>::combine) {
+            state = acc;
+            acc = D2{0, 0};
+        }
+        const D2 a64 = widen2(a0);
+        finish2<MODE>(state, acc, a64, rp);
+        if (live && sub == 0) {
+            float2 *e = (float2 *)(a.E + (size_t)x * D + col);
+            const D2 e64 = widen2(*e);
+            *e = narrow2(D2{e64.x - acc.x, e64.y - acc.y});
+            *(float2 *)(a.A + (size_t)x * D + col) = narrow2(state);
+        }
+        pe.x -= acc.x;
+        pe.y -= acc.y;
+        pa.x += state.x - a64.x;
+        pa.y += state.y - a64.y;
+        if (cg == 0 && tid == 0) {
+            if (L > kLongRun) {                                     // reported by ecrm_batch_stats
+                atomicAdd(&a.hdr->n_long, 1u);
+                atomicAdd(&a.hdr->n_long_items, (u64)L);
+            }
+            if (Rule<MODE>::combine) {
+                atomicAdd(&a.load_data[a.geo.dS.mod(g + 1 + (x - g * k))], 1ull);
+                if (a.load_parity) atomicAdd(&a.load_parity[a.geo.dS.mod(g)], 1ull);
+            }
+        }
+        __syncthreads();                                            // sh.pref and sh.start are free for the next entry
+    }
+    if (PARITY && live && sub == 0 && g != kNoKey) {
+        float2 *to = (float2 *)(a.PE + (size_t)g * D + col), *state = (float2 *)(a.PA + (size_t)g * D + col);
+        const D2 pe64 = widen2(*to), pa64 = widen2(*state);
+        *to = narrow2(D2{pe64.x + pe.x, pe64.y + pe.y});
+        *state = narrow2(D2{pa64.x + pa.x, pa64.y + pa.y});
+    }
+}
+
+// What a workgroup of the hot buckets has to do; true: it goes on with the ordinary bucket of len updates at `from` a tile.
+template <int MODE, bool PARITY>
+__device__ __forceinline__ bool hot_block(const BucketArgs &a, BucketShared &sh, uint32_t n_hot, uint32_t &from, uint32_t &len)
+{
+    const uint32_t k = a.geo.k, tid = threadIdx.x, ncg = (a.geo.D + kHeavyCols - 1) / kHeavyCols;
+    const uint32_t hot = min(n_hot, min(kHotMax, kHotBuckets / k));
+    // no stripe, or one that is not as long as the sample made it look: its entries' buckets lie side by side in every tile,
+    // so a workgroup takes them as one ordinary bucket
+    const uint32_t least = n_hot > kManyHot ? a.lim.shared_stripe : max(a.lim.shared_stripe / 2u, heavy_stripe(k));
+    if (blockIdx.x < kHotMax) {
+        if (blockIdx.x >= hot) return false;
+        const HotSpan s = hot_span(a, a.buckets + blockIdx.x * k, k);
+        uint32_t m;
+        bucket_excl_scan(s.len, sh.wave, m);
+        from = s.from;
+        len = s.len;
+        return m < least;
+    }
+    for (uint32_t job = blockIdx.x - kHotMax; job < hot * ncg; job += kHotBuckets - kHotMax) {
+        const uint32_t h = job / ncg, cg = job % ncg;
+        const HotSpan s = hot_span(a, a.buckets + h * k, k);
+        HotSpan e = hot_span(a, a.buckets + h * k + min(cg, k - 1u), 1);
+        uint32_t m;
+        bucket_excl_scan(s.len, sh.wave, m);
+        if (m < least) continue;
+        if (m <= a.lim.hot_in_place && k <= kInPlaceEntries) {
+            hot_job<MODE, PARITY>(a, sh, h, cg);
+            continue;
+        }
+        // left to heavy_stripes: the entries of the longest are described to it, the others copied, in arrival order
+        for (uint32_t j = cg; j < k; j += ncg) {
+            if (j != cg) e = hot_span(a, a.buckets + h * k + j, 1);
+            if (m >= a.lim.split_stripe) {
+                split_run(a, sh, h * k + j, e.from, e.len);
+                __syncthreads();                                    // sh.fill
+                continue;
+            }
+            uint32_t L, start, begin;
+            const uint32_t at = bucket_excl_scan(e.len, sh.wave, L);
+            bucket_excl_scan(tid < a.tiles ? e.from - tid * a.tile : 0u, sh.wave, start);
+            if (j == 0) {
+                bucket_excl_scan(tid < a.tiles ? s.from - tid * a.tile : 0u, sh.wave, begin);
+                if (tid == 0) list_heavy(a, sh.dense_used, begin, 0, m, false);
+            }
+            if (tid < a.tiles) {
+                sh.pref[tid] = at;
+                sh.start[tid] = e.from;
+            }
+            if (tid == 0) sh.pref[a.tiles] = L;
+            __syncthreads();
+            copy_bucket<true>(a, sh, a.dense + start);
+            __syncthreads();
+        }
+    }
+    return false;
+}
+
 static_assert(sizeof(BucketShared::tmp) >= (kBucketWaves + 2) * 2 * 128 * sizeof(double), "walk_long_stripe's sums for NC = 2");
 
 template <int NC, int MODE, bool PARITY>
@@ -1207,20 +1404,22 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
     __shared__ BucketShared sh;
     plan_replay(a);
     if (blockIdx.x >= a.buckets + kHotBuckets) return;
-    const uint32_t tid = threadIdx.x, B = a.buckets + kHotBuckets, S = a.geo.S, k = a.geo.k;
-    // the hot stripes' buckets first: what takes longest must not begin last
-    const uint32_t b = blockIdx.x < kHotBuckets ? a.buckets + blockIdx.x : blockIdx.x - kHotBuckets;
-    bool hot = b >= a.buckets, key_bad = false;                     // hot: an entry of a hot stripe, the member-th
-    const uint32_t member = hot ? (b - a.buckets) % k : 0u;
-    uint32_t from = 0, len = 0, stripe_len = 0;
+    const uint32_t tid = threadIdx.x, B = a.buckets + kHotBuckets, S = a.geo.S;
+    // the hot stripes first: what takes longest must not begin last
+    const bool of_hot = blockIdx.x < kHotBuckets;
+    const uint32_t b = of_hot ? kNoKey : blockIdx.x - kHotBuckets;
+    bool key_bad = false;
+    uint32_t from = 0, len = 0;
     if (tid < a.tiles) {
-        const uint16_t *row = a.table + (size_t)tid * (B + 1) + b;
         key_bad = (a.tile_state[tid] & 1u) != 0;
-        from = tid * a.tile + row[0];
-        len = (uint32_t)row[1] - row[0];
-        if (hot && b - member + k <= B) stripe_len = (uint32_t)row[k - member] - row[-(int)member];
+        if (!of_hot) {
+            const uint16_t *row = a.table + (size_t)tid * (B + 1) + b;
+            from = tid * a.tile + row[0];
+            len = (uint32_t)row[1] - row[0];
+        }
     }
-    const bool many = a.hdr->n_hot > kManyHot;                       // long stripes
+    const uint32_t n_hot = a.hdr->n_hot;
+    const bool many = n_hot > kManyHot;                             // long stripes
     const bool full = a.hdr->batch_bad != 0;                        // the recovery buffer could not take its part
     key_bad = __syncthreads_or(key_bad);
     if (key_bad || full) {
@@ -1230,24 +1429,8 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
         }
         return;
     }
+    if (of_hot && !hot_block<MODE, PARITY>(args_again(), sh, n_hot, from, len)) return;
     uint32_t m;
-    if (hot) {
-        bucket_excl_scan(stripe_len, sh.wave, m);
-        if (m < (many ? a.lim.shared_stripe : max(a.lim.shared_stripe / 2u, heavy_stripe(k)))) {
-            // no stripe, or one that is not as long as the sample made it look: its entries' buckets lie side by side in
-            // every tile, so the first workgroup takes them as one ordinary bucket
-            if (member != 0 || m == 0) return;
-            hot = false;
-            len = stripe_len;
-        } else if (m >= a.lim.split_stripe) {
-            split_run(a, sh, b - a.buckets, from, len);
-            return;
-        } else if (member == 0) {
-            uint32_t start;
-            bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, start);
-            if (tid == 0) list_heavy(a, sh.dense_used, start, 0, m, false);
-        }
-    }
     const uint32_t at = bucket_excl_scan(len, sh.wave, m);
     if (!Rule<MODE>::combine && b == 0) {                           // the batch is valid: publish its per-server counts
         for (uint32_t i = tid; i < 2 * S; i += kBucketThreads) sh.list.srv[i] = 0;
@@ -1268,12 +1451,6 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
     if (tid == 0) sh.pref[a.tiles] = m;
     if (tid < a.tiles) sh.start[tid] = from;
     __syncthreads();
-    if (hot) {                                                      // one entry's updates, in arrival order as they are
-        uint32_t start;
-        bucket_excl_scan(tid < a.tiles ? from - tid * a.tile : 0u, sh.wave, start);
-        copy_bucket<true>(a, sh, a.dense + start);
-        return;
-    }
     // An ordinary bucket is one list; an oversized one comes in parts, one list after the other.
     const bool oversized = m > kBucketCap;
     uint32_t base = 0;                                              // items of the batch in earlier buckets

@@ -52,25 +52,24 @@ __device__ __forceinline__ void heavy_rows(float2 (&r)[T], const float *grads, u
 }
 
 // what the waves exchange: sums (or, at the end of a run, steps) of two columns a lane, and the decay over a wave's updates
-struct HeavyExchange {
-    double sum[kHeavyWaves][8][2], dec[kHeavyWaves];
+template <int WAVES>
+struct ExchangeOf {
+    double sum[WAVES][8][2], dec[WAVES];
 };
+using HeavyExchange = ExchangeOf<kHeavyWaves>;
 // Sums of a round: every wave leaves that of its updates in ex; returned is what lies before the lane's group inside its
 // wave, with its decay.
-template <int MODE>
-__device__ __forceinline__ D2 heavy_sums(const float2 (&gr)[kHeavyT], uint32_t cnt, const RuleParams &rp, HeavyExchange &ex,
+template <int MODE, int T, int WAVES>
+__device__ __forceinline__ D2 heavy_sums(const float2 (&gr)[T], uint32_t cnt, const RuleParams &rp, ExchangeOf<WAVES> &ex,
                                          uint32_t w, double &before_decay)
 {
     constexpr bool kMomentum = MODE == kMomentumSeq;
     const uint32_t lane = lane_id(), col_lane = lane & 7u;
     D2 s = D2{-0.0, -0.0};                              // the neutral summand: +0.0 would take a -0.0's sign
-    double d = 1.0;
+    double d = kMomentum ? decay_over(cnt, rp.mu) : 1.0;
 #pragma unroll
-    for (int u = 0; u < kHeavyT; ++u) {
-        if ((uint32_t)u < cnt) {
-            summary2<MODE>(s, gr[u], rp);
-            if (kMomentum) d = decay(d * rp.mu, rp.mu);
-        }
+    for (int u = 0; u < T; ++u) {
+        if ((uint32_t)u < cnt) summary2<MODE>(s, gr[u], rp);
     }
     // inclusive scan over the wave's eight groups of the maps v -> d * v + s
 #pragma unroll
@@ -98,14 +97,14 @@ __device__ __forceinline__ D2 heavy_sums(const float2 (&gr)[kHeavyT], uint32_t c
 }
 
 // behind a barrier after heavy_sums: takes `state` from the round's start to its end, returns it as the lane's group finds it
-template <int MODE>
-__device__ __forceinline__ D2 heavy_fold(D2 &state, const HeavyExchange &ex, uint32_t w, const D2 &before, double before_decay)
+template <int MODE, int WAVES>
+__device__ __forceinline__ D2 heavy_fold(D2 &state, const ExchangeOf<WAVES> &ex, uint32_t w, const D2 &before, double before_decay)
 {
     constexpr bool kMomentum = MODE == kMomentumSeq;
     const uint32_t col_lane = lane_id() & 7u;
     D2 mine = state;
 #pragma unroll
-    for (int v = 0; v < kHeavyWaves; ++v) {
+    for (int v = 0; v < WAVES; ++v) {
         if ((uint32_t)v == w) mine = state;
         const double fx = ex.sum[v][col_lane][0], fy = ex.sum[v][col_lane][1];
         const double dv = kMomentum ? ex.dec[v] : 1.0;
@@ -118,7 +117,8 @@ __device__ __forceinline__ D2 heavy_fold(D2 &state, const HeavyExchange &ex, uin
 }
 
 // sum of the groups' steps over the workgroup, for every lane; one barrier, after ex was written
-__device__ __forceinline__ D2 heavy_total(D2 acc, HeavyExchange &ex, uint32_t w)
+template <int WAVES>
+__device__ __forceinline__ D2 heavy_total(D2 acc, ExchangeOf<WAVES> &ex, uint32_t w)
 {
     const uint32_t lane = lane_id(), col_lane = lane & 7u;
 #pragma unroll
@@ -133,7 +133,7 @@ __device__ __forceinline__ D2 heavy_total(D2 acc, HeavyExchange &ex, uint32_t w)
     __syncthreads();
     acc = D2{0, 0};
 #pragma unroll
-    for (int v = 0; v < kHeavyWaves; ++v) {
+    for (int v = 0; v < WAVES; ++v) {
         acc.x += ex.sum[v][col_lane][0];
         acc.y += ex.sum[v][col_lane][1];
     }
