@@ -23,7 +23,7 @@ namespace ecrm {
 // apply
 // ================================================================================================
 
-constexpr uint32_t kGroupsPerTicket = 8;
+constexpr uint32_t kGroupsPerTicket = 8, kNarrowGroupsPerTicket = 16;
 constexpr int kListThreads = 256;
 constexpr uint32_t kListMaxTiles = 4;
 // A stripe of more updates than this goes to the end of the list, which the apply kernel takes first.  64 costs the list
@@ -137,10 +137,10 @@ struct ApplyArgs {
     Geometry geo;
 };
 
-// General path: the stripe whose first item sits at sorted position `pos` (wave-uniform), walked
+// General path, U gradients in flight: as many as cost no registers beside the window path's.  The stripe whose first item sits at sorted position `pos` (wave-uniform), walked
 // through memory.  Used when the stripe does not fit the wave's window: runs of more than a few
 // dozen updates, and entries whose totals come from the split-chain path.
-template <int NC, int MODE, bool PARITY>
+template <int NC, int MODE, bool PARITY, int U = 8>
 __device__ __forceinline__ void apply_stripe_general(const ApplyArgs &a, uint32_t n, uint32_t pos, uint32_t cb)
 {
     const uint32_t D = a.geo.D, k = a.geo.k;
@@ -190,7 +190,6 @@ __device__ __forceinline__ void apply_stripe_general(const ApplyArgs &a, uint32_
                 acc[i] = D2{0, 0};
             }
             // the run is at most kLongRun long: walk it 64 positions at a time, U gradients in flight
-            constexpr int U = 8;
             bool done = false;
             while (!done) {
                 const uint32_t lane = lane_id();
@@ -208,6 +207,7 @@ __device__ __forceinline__ void apply_stripe_general(const ApplyArgs &a, uint32_
 #pragma unroll
                         for (int i = 0; i < NC; ++i) gr[u][i] = ldg2(r, i);
                     }
+                    asm volatile("" ::: "memory");       // all of them now: each would be moved to where it is used
 #pragma unroll
                     for (int u = 0; u < U; ++u)
                         if (u0 + u < cnt) {
@@ -403,23 +403,170 @@ __device__ __forceinline__ void apply_window(const ApplyArgs &a, uint32_t wkey, 
     }
 }
 
+// The same for rows of at most 64 (P = 2) or 32 (P = 4) floats: a step takes up to P consecutive entries, one to each group of
+// 64 / P lanes, so that one instruction moves P rows; with one row to a wave half of the lanes, or more, had nothing to do, and
+// the instructions, not the memory, set the pace (1.5 M half-Zipf momentum updates, k = 2: 64 floats 533 us, now 458, at
+// 4.4 TB/s; a call of 32 floats 678 us, now 497; 3 M of 16 floats 850, now 580).  All control flow is that of the wave: the
+// entries' numbers of updates and stripes differ from group to group, and what a group has no part in is masked; every exchange
+// between groups is executed by all lanes.  Rows are read through per-lane addresses.
+template <int P>
+struct NarrowLoads {
+    float2 e, a, g, pe, pa;
+    uint32_t x, j, cnt;          // the group's entry: row, first position of the window, updates (0: no entry)
+    bool opens, closes;          // the first, the last entry of its stripe
+    uint32_t most, groups;       // of the step (wave-uniform): updates of its longest entry, entries
+};
+
+__device__ __forceinline__ float2 load2(const float *p)
+{
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(float2, __builtin_nontemporal_load((const f2 *)p));
+}
+__device__ __forceinline__ void store2(float *p, float2 v)
+{
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    __builtin_nontemporal_store(__builtin_bit_cast(f2, v), (f2 *)p);
+}
+
+// takes the next entries from todo (not empty)
+template <int P, bool PARITY>
+__device__ __forceinline__ void issue_narrow(NarrowLoads<P> &r, const ApplyArgs &a, uint32_t col, uint32_t wkey, uint32_t widx,
+                                             unsigned long long stripeheads, unsigned long long &todo, uint32_t end)
+{
+    const uint32_t D = a.geo.D, mine = lane_id() / (kWave / P);
+    r.most = r.groups = 0;
+    r.cnt = 0;
+    r.x = r.j = 0;
+    r.opens = r.closes = false;
+#pragma unroll
+    for (uint32_t q = 0; q < (uint32_t)P; ++q) {
+        if (!todo) break;
+        const uint32_t j = lowest_bit(todo);
+        todo &= todo - 1ull;
+        const uint32_t next = todo ? lowest_bit(todo) : end, x = from_lane(wkey, j);
+        const bool opens = (stripeheads >> j) & 1ull, closes = !todo || ((stripeheads >> next) & 1ull);
+        r.most = max(r.most, next - j);
+        r.groups = q + 1u;
+        // the groups behind the last entry load its rows as well, and leave them alone
+        r.x = mine >= q ? x : r.x;
+        r.j = mine >= q ? j : r.j;
+        r.cnt = mine == q ? next - j : mine > q ? 0u : r.cnt;
+        r.opens = mine == q ? opens : mine > q ? false : r.opens;
+        r.closes = mine == q ? closes : mine > q ? false : r.closes;
+    }
+    const uint32_t idx = __shfl(widx, (int)r.j, kWave);
+    r.a = load2(a.A + (size_t)r.x * D + col);
+    r.g = load2(a.grads + (size_t)idx * D + col);
+    r.e = load2(a.E + (size_t)r.x * D + col);
+    r.pe = r.pa = float2{0, 0};
+    if (PARITY && r.opens) {
+        const size_t at = (size_t)a.geo.dk.div(r.x) * D + col;
+        r.pe = load2(a.PE + at);
+        r.pa = load2(a.PA + at);
+    }
+}
+
+template <int P, int MODE, bool PARITY>
+__device__ __forceinline__ void apply_window_narrow(const ApplyArgs &a, uint32_t wkey, uint32_t widx, unsigned long long rowheads,
+                                                    unsigned long long stripeheads, uint32_t first, uint32_t end)
+{
+    constexpr uint32_t kLanes = kWave / P;
+    const uint32_t D = a.geo.D, lane = lane_id(), group = lane / kLanes, col_lane = lane % kLanes;
+    const bool live = 2u * col_lane < D;                   // D is a multiple of 4: both columns or none
+    const uint32_t col = live ? 2u * col_lane : 0u;
+    const RuleParams rp = rule_params(a.geo);
+    unsigned long long todo = rowheads & bits_below(end) & ~bits_below(first);
+    if (!todo) return;
+    NarrowLoads<P> next;
+    issue_narrow<P, PARITY>(next, a, col, wkey, widx, stripeheads, todo, end);
+    D2 pe = D2{0, 0}, pa = D2{0, 0};                       // parity rows of the stripe that goes on into the next step
+    for (bool more = true; more;) {
+        const NarrowLoads<P> cur = next;
+        more = todo != 0;
+        if (more) issue_narrow<P, PARITY>(next, a, col, wkey, widx, stripeheads, todo, end);
+        D2 G = start2<MODE>(widen2(cur.a)), acc = D2{0, 0};
+        // the entries' updates, those of the next few in flight (apply_window); past an entry's end: its last one again
+        constexpr int AH = ECRM_ITEM_AHEAD - 1;
+        const uint32_t last = cur.j + max(cur.cnt, 1u) - 1u;
+        float2 gr = cur.g, nx[AH];
+        auto gradient = [&](uint32_t u) {
+            const uint32_t idx = __shfl(widx, (int)min(cur.j + u, last), kWave);
+            return load2(a.grads + (size_t)idx * D + col);
+        };
+#pragma unroll
+        for (int q = 0; q < AH; ++q) {
+            nx[q] = float2{0, 0};
+            if (1u + q < cur.most) nx[q] = gradient(1u + q);
+        }
+        for (uint32_t u = 0;;) {
+            float2 in = float2{0, 0};
+            if (u + 1 + AH < cur.most) in = gradient(u + 1 + AH);
+            if (u < cur.cnt) item2<MODE>(G, acc, gr, rp);
+            if (++u >= cur.most) break;
+            gr = nx[0];
+#pragma unroll
+            for (int q = 0; q + 1 < AH; ++q) nx[q] = nx[q + 1];
+            nx[AH - 1] = in;
+        }
+        const D2 e64 = widen2(cur.e), a64 = widen2(cur.a);
+        finish2<MODE>(G, acc, a64, rp);
+        const bool mine = cur.cnt != 0 && live;
+        if (mine) {
+            store2(a.E + (size_t)cur.x * D + col, narrow2(D2{e64.x - acc.x, e64.y - acc.y}));
+            store2(a.A + (size_t)cur.x * D + col, narrow2(G));
+        }
+        if (PARITY) {
+            // from group to group: the parity rows as they are after the group's entry
+            if (cur.opens) {
+                pe = widen2(cur.pe);
+                pa = widen2(cur.pa);
+            }
+            const D2 dpa = D2{G.x - a64.x, G.y - a64.y};
+            D2 ve = D2{pe.x - acc.x, pe.y - acc.y}, va = D2{pa.x + dpa.x, pa.y + dpa.y};
+#pragma unroll
+            for (uint32_t q = 1; q < (uint32_t)P; ++q) {
+                const int from = (int)((q - 1u) * kLanes + col_lane);
+                const D2 fe = D2{__shfl(ve.x, from, kWave), __shfl(ve.y, from, kWave)};
+                const D2 fa = D2{__shfl(va.x, from, kWave), __shfl(va.y, from, kWave)};
+                if (group == q && !cur.opens) {
+                    ve = D2{fe.x - acc.x, fe.y - acc.y};
+                    va = D2{fa.x + dpa.x, fa.y + dpa.y};
+                }
+            }
+            if (mine && cur.closes) {
+                const size_t at = (size_t)a.geo.dk.div(cur.x) * D + col;
+                store2(a.PE + at, narrow2(ve));
+                store2(a.PA + at, narrow2(va));
+            }
+            const int from = (int)((cur.groups - 1u) * kLanes + col_lane);
+            pe = D2{__shfl(ve.x, from, kWave), __shfl(ve.y, from, kWave)};
+            pa = D2{__shfl(va.x, from, kWave), __shfl(va.y, from, kWave)};
+        }
+    }
+}
+
 // The groups of kChunk sorted positions in which a stripe begins (active_groups_kernel lists them) are handed out through a
 // counter instead of by a fixed stride: the work per group varies (runs, long stripes), and with a fixed stride the
 // slowest wave set the kernel's time (6.50 -> 6.22 ms).  One ticket covers kGroupsPerTicket listed groups: one group per
 // ticket made the counter itself the bottleneck (12.5 ms), 64 per ticket is too coarse again.  A wave's first ticket is
 // its own number (no counter traffic at start-up, which is all a small batch consists of); later ones come from the
-// counter.  Small batches get smaller tickets, so that every wave has work.  Groups with a long stripe come first, one to
+// counter.  Small batches get smaller tickets, so that every wave has work: four to a wave, but no more than two once that
+// would make a ticket shorter than half of the largest: a counter update takes as long as the memory takes to move a group or
+// two (at least one group to a ticket, us a call: 600 000 uniform updates 585, now 465; 2 M Zipf, k = 10, 905, now 650; two
+// tickets to a wave in larger batches as well: 2 M half Zipf 1160, then 1182).  Narrow rows, twice the groups: 3 M half-Zipf
+// updates of 16 floats 570, now 547; 1.5 M Zipf of 48, combined, 449, now 372.  Groups with a long stripe come first, one to
 // a ticket: one wave walks such a stripe for up to 150 us, and where it came late the others were idle meanwhile (apply
 // kernels of Zipf and half-Zipf batches: 617 -> 535, 2226 -> 2110, 2390 -> 2263, 7770 -> 7672 us).
 struct GroupTickets {
     uint32_t nslow, nact, per, ticket;
     bool first;
-    __device__ __forceinline__ void init(const ApplyArgs &a, uint32_t n)
+    __device__ __forceinline__ void init(const ApplyArgs &a, uint32_t n, uint32_t most)
     {
         const uint32_t ngroups = (n + kChunk - 1) / kChunk;
         nslow = a.active ? min(a.hdr->n_heavy, ngroups) : 0u;
         nact = a.active ? min(a.hdr->n_active, ngroups) : ngroups;   // no list (a small batch): every group
-        per = min(kGroupsPerTicket, max(1u, nact / (4u * wave_count())));
+        const uint32_t waves = wave_count();
+        per = max(max(min(most / 2u, (nact + 2u * waves - 1u) / (2u * waves)), min(most, nact / (4u * waves))), 1u);
         ticket = wave_id();
         first = true;
     }
@@ -487,14 +634,15 @@ __device__ __forceinline__ Window look_at(uint32_t wkey, uint32_t prevk, uint32_
     return w;
 }
 
-template <int NC, int MODE, bool PARITY>
+// P: entries to a wave at a time
+template <int NC, int MODE, bool PARITY, int P = 1>
 __device__ __forceinline__ void apply_stripes_body(const ApplyArgs &a)
 {
     if (a.hdr->batch_bad) return;
     publish_counts(a);
     const uint32_t n = min(a.n, a.hdr->n_valid), k = a.geo.k, lane = lane_id();
     GroupTickets tickets;
-    tickets.init(a, n);
+    tickets.init(a, n, P > 1 ? kNarrowGroupsPerTicket : kGroupsPerTicket);
     uint32_t left = 0, taken = 0, listed = 0;          // groups left in the ticket, taken from it; lane i: its group i
     uint32_t pf_ch = 0xFFFFFFFFu, pf_key = 0, pf_idx = 0, pf_prev = 0;
     for (;;) {
@@ -527,14 +675,19 @@ __device__ __forceinline__ void apply_stripes_body(const ApplyArgs &a)
         }
         const Window w = look_at(wkey, prevk, p0, n, k);
         if (!w.any) continue;
+        if (P > 1) {
+            apply_window_narrow<P, MODE, PARITY>(a, wkey, widx, w.rowheads, w.stripeheads, w.first, w.end);
+            if (!w.last_inside) apply_stripe_general<NC, MODE, PARITY, 16>(a, n, p0 + w.last, 0);
+            continue;
+        }
         for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
             apply_window<NC, MODE, PARITY>(a, wkey, widx, w.rowheads, w.stripeheads, w.first, w.end, cb);
-            if (!w.last_inside) apply_stripe_general<NC, MODE, PARITY>(a, n, p0 + w.last, cb);
+            if (!w.last_inside) apply_stripe_general<NC, MODE, PARITY, NC == 1 ? 8 : 12>(a, n, p0 + w.last, cb);
         }
     }
 }
 
-// D <= 128: one 128-float slice per lane pair; D > 128: two slices per lane.
+// D <= 128: one 128-float slice per lane pair; D > 128: two slices per lane.  The narrow ones: D <= 64 (P = 2), D <= 32 (4).
 template <int MODE>
 __global__ __launch_bounds__(256) void apply_stripes_kernel_d128(ApplyArgs a)
 {
@@ -544,6 +697,11 @@ template <int MODE>
 __global__ __launch_bounds__(256) void apply_stripes_kernel_d256(ApplyArgs a)
 {
     apply_stripes_body<2, MODE, true>(a);
+}
+template <int MODE, bool PARITY, int P>
+__global__ __launch_bounds__(256) void apply_narrow_kernel(ApplyArgs a)
+{
+    apply_stripes_body<1, MODE, PARITY, P>(a);
 }
 // The same walk with the parity rows left alone: entries and their state only.  This is the update
 // of a system without redundancy (the baseline the overheads of Sec. 4.3 are quoted against), and
@@ -611,35 +769,35 @@ __global__ __launch_bounds__(256) void route_kernel(const uint64_t *keys, uint64
 // host side
 // ================================================================================================
 
+// the apply kernel for rows of D floats
+typedef void (*ApplyKernel)(ApplyArgs);
 template <int NC, int MODE>
-static bool apply_grids_for(int cus, LaunchGrids *out)
+static ApplyKernel apply_kernel(uint32_t D, bool parity)
 {
-    if (NC == 1) {
-        out->apply = resident_grid(apply_stripes_kernel_d128<MODE>, cus);
-        out->rows = resident_grid(apply_rows_kernel_d128<MODE>, cus);
-    } else {
-        out->apply = resident_grid(apply_stripes_kernel_d256<MODE>, cus);
-        out->rows = resident_grid(apply_rows_kernel_d256<MODE>, cus);
-    }
+    if (D <= 32) return parity ? apply_narrow_kernel<MODE, true, 4> : apply_narrow_kernel<MODE, false, 4>;
+    if (D <= 64) return parity ? apply_narrow_kernel<MODE, true, 2> : apply_narrow_kernel<MODE, false, 2>;
+    if (NC == 1) return parity ? apply_stripes_kernel_d128<MODE> : apply_rows_kernel_d128<MODE>;
+    return parity ? apply_stripes_kernel_d256<MODE> : apply_rows_kernel_d256<MODE>;
+}
+
+template <int NC, int MODE>
+static bool apply_grids_for(uint32_t D, int cus, LaunchGrids *out)
+{
+    out->apply = resident_grid(apply_kernel<NC, MODE>(D, true), cus);
+    out->rows = resident_grid(apply_kernel<NC, MODE>(D, false), cus);
     return out->apply > 0 && out->rows > 0;
 }
 
 template <int NC, int MODE>
 static void apply_for(const ApplyArgs &a, const LaunchGrids &lg, bool parity, hipStream_t st)
 {
-    if (parity) {
-        if (NC == 1) hipLaunchKernelGGL(apply_stripes_kernel_d128<MODE>, dim3(lg.apply), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(apply_stripes_kernel_d256<MODE>, dim3(lg.apply), dim3(256), 0, st, a);
-    } else {
-        if (NC == 1) hipLaunchKernelGGL(apply_rows_kernel_d128<MODE>, dim3(lg.rows), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(apply_rows_kernel_d256<MODE>, dim3(lg.rows), dim3(256), 0, st, a);
-    }
+    hipLaunchKernelGGL((apply_kernel<NC, MODE>(a.geo.D, parity)), dim3(parity ? lg.apply : lg.rows), dim3(256), 0, st, a);
 }
 
 bool query_launch_grids(const Geometry &g, int cus, LaunchGrids *out)
 {
     bool ok = false;
-    ECRM_DISPATCH(ok = apply_grids_for, cus, out);
+    ECRM_DISPATCH(ok = apply_grids_for, g.D, cus, out);
     return ok && query_chain_grids(g, cus, out);
 }
 
