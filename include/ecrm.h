@@ -243,7 +243,8 @@ int ecrm_clear_status(ecrm_ctx *ctx, void *hip_stream);
  * defaults).  ECRM_TUNE_MID_MIN_ROWS: on the Adagrad rule an entry with more than ECRM_LONG_RUN and at most
  * ECRM_MID_RUN updates in a call is walked by one workgroup -- one read of its gradients instead of two --
  * but only in calls with at least this many such long entries, since one workgroup is slow and pays only
- * when all of them are busy.  Default (value 0): four per workgroup the device holds at once.  Any other value
+ * when all of them are busy.  Default (value 0): in calls of 2^21 updates or more with 400 such entries (2048 of at
+ * most 64 floats), those of up to 12 updates for each of them.  Any other value
  * also sends batches of every size through the sort and the chain tiers; by default those of up to 2^19 updates (2^18 on a
  * table of fewer than 128 rows) are grouped in buckets instead (same results; out[1] and out[4] of ecrm_batch_stats are 0
  * then).  EINVAL for

@@ -52,13 +52,13 @@ __global__ __launch_bounds__(256) void long_find_kernel(const uint32_t *sk, uint
 
 // Length of each long run (binary search for its end) and its cut into pieces.  One wave per run.
 // A run of at most mid_max updates gets no pieces: its slot goes on the list of its length class
-// (mid_chain_kernel) -- provided the batch has at least mid_min_rows long rows.
+// (mid_chain_kernel) -- provided the batch has at least mid_min_rows long rows, or, if that is 0, mid_enough of them, and as long as kMidShare allows.
 constexpr int kPlanWaves = 16;      // runs a block of the plan kernel looks at together
 
 __global__ __launch_bounds__(kPlanWaves * kWave) void long_plan_kernel(
     const uint32_t *sk, uint32_t n, Header *hdr, const uint32_t *long_head, uint32_t *long_len, uint32_t *long_piece,
     uint32_t *long_count, uint32_t *long_base, uint32_t *piece_slot, uint32_t *mid_list, uint32_t mid_max,
-    uint32_t mid_min_rows, uint32_t piece_waves, uint32_t max_slots, uint32_t max_pieces)
+    uint32_t mid_min_rows, uint32_t mid_enough, uint32_t piece_waves, uint32_t max_slots, uint32_t max_pieces)
 {
     // what each wave found, and where its run's pieces (or its place in a list) begin
     __shared__ uint32_t s_pieces[kPlanWaves], s_len[kPlanWaves], s_class[kPlanWaves], s_start[kPlanWaves];
@@ -66,7 +66,11 @@ __global__ __launch_bounds__(kPlanWaves * kWave) void long_plan_kernel(
     if (hdr->batch_bad) return;
     n = min(n, hdr->n_valid);
     const uint32_t nl = min(hdr->n_long, max_slots);
-    if (nl < mid_min_rows) mid_max = 0;
+    if (mid_min_rows) {
+        if (nl < mid_min_rows) mid_max = 0;
+    } else {
+        mid_max = nl < mid_enough ? 0u : min(mid_max, nl * kMidShare);     // nl < 2^21: no overflow
+    }
     // Smallest piece: a piece costs its wave a few memory latencies before the first gradient arrives, so pieces
     // should be as long as the work allows while there are still several per wave of the piece kernels.  How much
     // work there is is not known yet; the number of long rows is, and such a row has kLongRowGuess updates on
@@ -163,75 +167,83 @@ __global__ __launch_bounds__(kPlanWaves * kWave) void long_plan_kernel(
 //                           its steps on exit (sequential rules only).
 // One wave per piece; the item indices of 64 positions are fetched with one coalesced load and
 // handed out lane by lane, and U gradient rows are in flight at a time.
+struct PieceArgs {
+    const uint32_t *si;
+    const float *grads;
+    const uint32_t *long_head, *long_len, *long_piece, *long_base, *piece_slot;
+    double *partial, *partial2;
+    uint32_t max_pieces;
+    uint32_t merged_from;        // long rows from which on mid_chain_kernel takes the first pass over the pieces
+};
 template <int NC, bool STEPS, int MODE>
-__global__ __launch_bounds__(256) void long_piece_kernel(const uint32_t *si, const float *grads, Header *hdr,
-                                                         const uint32_t *long_head, const uint32_t *long_len,
-                                                         const uint32_t *long_piece, const uint32_t *long_base,
-                                                         const uint32_t *piece_slot, double *partial,
-                                                         double *partial2, uint32_t max_pieces, Geometry geo)
+__device__ __forceinline__ void long_piece(const PieceArgs &a, const Geometry &geo, uint32_t pc)
 {
     constexpr bool kVelSum = !STEPS && MODE == kMomentumSeq;
-    if (hdr->batch_bad) return;
-    const uint32_t np = min(hdr->n_pieces, max_pieces);
     const uint32_t D = geo.D, lane = lane_id();
     const RuleParams rp = rule_params(geo);
     constexpr int U = 16;
-    for (uint32_t pc = wave_id(); pc < np; pc += wave_count()) {
-        const uint32_t slot = uniform(piece_slot[pc]);
-        const uint32_t j = pc - uniform(long_base[slot]);
-        const uint32_t head = uniform(long_head[slot]), L = uniform(long_len[slot]), C = uniform(long_piece[slot]);
-        const uint32_t start = head + j * C;
-        const uint32_t end = min(start + C, head + L);
-        for (uint32_t cb = 0; cb < geo.ncb; ++cb) {
-            const uint32_t col0 = cb * NC * 128u;
-            const rsrc_t part = row_f64(partial, pc, D, col0);
-            D2 G[NC], acc[NC], vs[NC];
+    const uint32_t slot = uniform(a.piece_slot[pc]);
+    const uint32_t j = pc - uniform(a.long_base[slot]);
+    const uint32_t head = uniform(a.long_head[slot]), L = uniform(a.long_len[slot]), C = uniform(a.long_piece[slot]);
+    const uint32_t start = head + j * C;
+    const uint32_t end = min(start + C, head + L);
+    for (uint32_t cb = 0; cb < geo.ncb; ++cb) {
+        const uint32_t col0 = cb * NC * 128u;
+        const rsrc_t part = row_f64(a.partial, pc, D, col0);
+        D2 G[NC], acc[NC], vs[NC];
 #pragma unroll
-            for (int i = 0; i < NC; ++i) {
-                acc[i] = vs[i] = D2{0, 0};
-                G[i] = STEPS ? ldd2(part, i) : D2{0, 0};
-            }
-            uint32_t widx = start + lane < end ? si[start + lane] : 0u;
-            for (uint32_t base = start; base < end; base += kWave) {
-                const uint32_t cnt = min((uint32_t)kWave, end - base);
-                const uint32_t cur_idx = widx;
-                if (base + kWave < end)            // next window in flight while this one is consumed
-                    widx = base + kWave + lane < end ? si[base + kWave + lane] : 0u;
-                for (uint32_t u0 = 0; u0 < cnt; u0 += U) {
-                    float2 g[U][NC];
+        for (int i = 0; i < NC; ++i) {
+            acc[i] = vs[i] = D2{0, 0};
+            G[i] = STEPS ? ldd2(part, i) : D2{0, 0};
+        }
+        uint32_t widx = start + lane < end ? a.si[start + lane] : 0u;
+        for (uint32_t base = start; base < end; base += kWave) {
+            const uint32_t cnt = min((uint32_t)kWave, end - base);
+            const uint32_t cur_idx = widx;
+            if (base + kWave < end)            // next window in flight while this one is consumed
+                widx = base + kWave + lane < end ? a.si[base + kWave + lane] : 0u;
+            for (uint32_t u0 = 0; u0 < cnt; u0 += U) {
+                float2 g[U][NC];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        // lanes past the end of the piece re-read its last item; their values are not used
-                        const uint32_t idx = from_lane(cur_idx, min(u0 + u, cnt - 1));
-                        const rsrc_t r = row_f32(grads, idx, D, col0);
+                for (int u = 0; u < U; ++u) {
+                    // lanes past the end of the piece re-read its last item; their values are not used
+                    const uint32_t idx = from_lane(cur_idx, min(u0 + u, cnt - 1));
+                    const rsrc_t r = row_f32(a.grads, idx, D, col0);
 #pragma unroll
-                        for (int i = 0; i < NC; ++i) g[u][i] = ldg2(r, i);
-                    }
+                    for (int i = 0; i < NC; ++i) g[u][i] = ldg2(r, i);
+                }
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        if (u0 + u < cnt) {
+                for (int u = 0; u < U; ++u) {
+                    if (u0 + u < cnt) {
 #pragma unroll
-                            for (int i = 0; i < NC; ++i) {
-                                if (STEPS) item2<MODE>(G[i], acc[i], g[u][i], rp);
-                                else summary2<MODE>(acc[i], g[u][i], rp);
-                                if (kVelSum) {
-                                    vs[i].x += acc[i].x;
-                                    vs[i].y += acc[i].y;
-                                }
+                        for (int i = 0; i < NC; ++i) {
+                            if (STEPS) item2<MODE>(G[i], acc[i], g[u][i], rp);
+                            else summary2<MODE>(acc[i], g[u][i], rp);
+                            if (kVelSum) {
+                                vs[i].x += acc[i].x;
+                                vs[i].y += acc[i].y;
                             }
                         }
                     }
                 }
             }
+        }
 #pragma unroll
-            for (int i = 0; i < NC; ++i) std2(part, i, acc[i]);
-            if (kVelSum) {
-                const rsrc_t part2 = row_f64(partial2, pc, D, col0);
+        for (int i = 0; i < NC; ++i) std2(part, i, acc[i]);
+        if (kVelSum) {
+            const rsrc_t part2 = row_f64(a.partial2, pc, D, col0);
 #pragma unroll
-                for (int i = 0; i < NC; ++i) std2(part2, i, vs[i]);
-            }
+            for (int i = 0; i < NC; ++i) std2(part2, i, vs[i]);
         }
     }
+}
+
+template <int NC, bool STEPS, int MODE>
+__global__ __launch_bounds__(256) void long_piece_kernel(PieceArgs a, Header *hdr, Geometry geo)
+{
+    if (hdr->batch_bad || (!STEPS && hdr->n_long >= a.merged_from)) return;
+    const uint32_t np = min(hdr->n_pieces, a.max_pieces);
+    for (uint32_t pc = wave_id(); pc < np; pc += wave_count()) long_piece<NC, STEPS, MODE>(a, geo, pc);
 }
 
 constexpr int kRowWaves = 16;      // waves that share one long row in the scan and reduce kernels
@@ -451,13 +463,16 @@ __global__ __launch_bounds__(kRowWaves * kWave) void long_reduce_kernel(Header *
 // it sums their squares, the waves exchange these sums through LDS -- so that each knows the accumulator
 // its updates start from -- and it then takes its steps from the registers.  The accumulator is carried
 // from round to round; the waves' step sums are added up once, at the end of the run.  Runs are taken
-// longest first (the lists are by length class), so that the longest one does not end the kernel alone.
+// longest first (the lists are by length class).  A wave that finds no run any more goes on with the first pass over the
+// pieces of the longer ones: while the last of these runs are walked -- half a millisecond for one of kMidMax -- the others
+// read at the memory's pace.  (As a launch of its own before the pieces' the tier paid only with 2048 long rows; with a few
+// dozen of them the waves of this kernel are too few: 2 M half-Zipf updates of 256 floats 2345 us, merged 2412.)
 // long_res[slot] receives what the pieces' kernels would have left there: the sum of the steps and the
 // accumulator after the run.
 template <int NC>
 __global__ __launch_bounds__(kMidWaves * kWave, 4) void mid_chain_kernel(
-    const uint32_t *sk, const uint32_t *si, const float *grads, const float *A, Header *hdr, const uint32_t *long_head,
-    const uint32_t *long_len, const uint32_t *mid_list, double *long_res, uint32_t max_slots, Geometry geo)
+    PieceArgs a, const uint32_t *sk, const float *A, Header *hdr, const uint32_t *mid_list, double *long_res, uint32_t max_slots,
+    Geometry geo)
 {
     constexpr int T = 32 / NC;                               // gradient rows a wave holds
     constexpr uint32_t R = kMidWaves * T;                    // updates per round
@@ -484,7 +499,7 @@ __global__ __launch_bounds__(kMidWaves * kWave, 4) void mid_chain_kernel(
             --c;
         }
         const uint32_t slot = uniform(mid_list[(size_t)c * max_slots + t]);
-        const uint32_t head = uniform(long_head[slot]), L = uniform(long_len[slot]), x = uniform(sk[head]);
+        const uint32_t head = uniform(a.long_head[slot]), L = uniform(a.long_len[slot]), x = uniform(sk[head]);
         for (uint32_t cb = 0; cb < geo.ncb; ++cb) {
             const uint32_t col0 = cb * NC * 128u;
             const rsrc_t arow = row_f32(A, x, D, col0);
@@ -499,11 +514,11 @@ __global__ __launch_bounds__(kMidWaves * kWave, 4) void mid_chain_kernel(
                 const uint32_t off = r0 + w * T;             // this wave's first update, counted from the head
                 const uint32_t cnt = off < L ? min((uint32_t)T, L - off) : 0u;
                 // positions past the end of the run re-read its last update; their values are not used
-                const uint32_t my_idx = si[head + min(off + lane, L - 1u)];
+                const uint32_t my_idx = a.si[head + min(off + lane, L - 1u)];
                 float2 g[T][NC];
 #pragma unroll
                 for (int u = 0; u < T; ++u) {
-                    const rsrc_t r = row_f32(grads, from_lane(my_idx, u), D, col0);
+                    const rsrc_t r = row_f32(a.grads, from_lane(my_idx, u), D, col0);
 #pragma unroll
                     for (int i = 0; i < NC; ++i) g[u][i] = ldg2(r, i);
                 }
@@ -578,6 +593,15 @@ __global__ __launch_bounds__(kMidWaves * kWave, 4) void mid_chain_kernel(
             __syncthreads();                                 // s_part is free for the next run
         }
     }
+    // the pieces of the longer runs, in order, as the waves come free
+    const uint32_t np = hdr->n_long >= a.merged_from ? min(hdr->n_pieces, a.max_pieces) : 0u;
+    while (np) {
+        uint32_t pc = 0;
+        if (lane == 0) pc = atomicAdd(&hdr->piece_ticket, 1u);
+        pc = uniform(pc);
+        if (pc >= np) break;                                 // every wave draws one number past the last piece
+        long_piece<NC, false, kAdagradSeq>(a, geo, pc);
+    }
 }
 
 // ================================================================================================
@@ -590,7 +614,7 @@ static bool chain_grids_for(int cus, LaunchGrids *out)
     out->p1 = resident_grid(long_piece_kernel<NC, false, MODE>, cus);
     out->p3 = resident_grid(long_piece_kernel<NC, true, MODE>, cus);
     out->mid = resident_grid(mid_chain_kernel<NC>, cus, kMidWaves * kWave);
-    out->mid_min_rows = kMidMinRowsPerBlock * (uint32_t)(out->mid > 0 ? out->mid : 0);
+    out->mid_min_rows = 0;               // by the number of long rows
     return out->p1 > 0 && out->p3 > 0 && out->mid > 0;
 }
 
@@ -601,22 +625,24 @@ static void chains_for(const Scratch &s, const Geometry &g, const LaunchGrids &l
 {
     const dim3 grid(cus * 8), block(256);
     hipLaunchKernelGGL(long_find_kernel, grid, block, 0, st, sk, n, s.hdr, s.long_slot, s.long_head, max_slots);
-    const uint32_t mid_max = MODE == kAdagradSeq ? kMidMax : 0u;     // the other rules read a long run once anyway
+    // The other rules read a long run once anyway.  A caller that sets the knob gets that tier and the pieces one after the
+    // other; by itself it is considered in batches that pay for its launch when there is nothing for it to do.
+    const bool mid = MODE == kAdagradSeq && (lg.mid_min_rows ? n / (kLongRun + 1u) >= lg.mid_min_rows : n >= kMidMinBatch);
+    const uint32_t mid_max = mid ? kMidMax : 0u, enough = g.D > 64 ? kMidMinRows : kMidMinNarrowRows;
     hipLaunchKernelGGL(long_plan_kernel, dim3(cus * 2), dim3(kPlanWaves * kWave), 0, st, sk, n, s.hdr, s.long_head, s.long_len,
-                       s.long_piece, s.long_count, s.long_base, s.piece_slot, s.mid_list, mid_max, lg.mid_min_rows,
+                       s.long_piece, s.long_count, s.long_base, s.piece_slot, s.mid_list, mid_max, lg.mid_min_rows, enough,
                        (uint32_t)lg.p1 * (256u / kWave), max_slots, max_pieces);
-    if (mid_max > kLongRun && n / (kLongRun + 1u) >= lg.mid_min_rows)       // else the plan kernel lists no such run
-        hipLaunchKernelGGL((mid_chain_kernel<NC>), dim3(lg.mid), dim3(kMidWaves * kWave), 0, st, sk, si, grads, A, s.hdr,
-                           s.long_head, s.long_len, s.mid_list, s.long_res, max_slots, g);
-    hipLaunchKernelGGL((long_piece_kernel<NC, false, MODE>), dim3(lg.p1), block, 0, st, si, grads, s.hdr, s.long_head,
-                       s.long_len, s.long_piece, s.long_base, s.piece_slot, s.partial, s.partial2, max_pieces, g);
+    const PieceArgs a{si, grads, s.long_head, s.long_len, s.long_piece, s.long_base, s.piece_slot, s.partial, s.partial2, max_pieces,
+                      mid && !lg.mid_min_rows ? enough : 0xFFFFFFFFu};
+    if (mid)
+        hipLaunchKernelGGL((mid_chain_kernel<NC>), dim3(lg.mid), dim3(kMidWaves * kWave), 0, st, a, sk, A, s.hdr, s.mid_list,
+                           s.long_res, max_slots, g);
+    hipLaunchKernelGGL((long_piece_kernel<NC, false, MODE>), dim3(lg.p1), block, 0, st, a, s.hdr, g);
     if (!Rule<MODE>::combine) {
         hipLaunchKernelGGL((long_scan_kernel<NC, MODE>), dim3(cus * 2), dim3(kRowWaves * kWave), 0, st, sk, A, s.hdr, s.long_head, s.long_count,
                            s.long_base, s.long_len, s.long_piece, s.partial, s.partial2, s.long_res, max_slots, g);
         if (MODE != kMomentumSeq)        // momentum's steps came out of the scan: no second pass over the gradients
-            hipLaunchKernelGGL((long_piece_kernel<NC, true, MODE>), dim3(lg.p3), block, 0, st, si, grads, s.hdr,
-                               s.long_head, s.long_len, s.long_piece, s.long_base, s.piece_slot, s.partial, s.partial2,
-                               max_pieces, g);
+            hipLaunchKernelGGL((long_piece_kernel<NC, true, MODE>), dim3(lg.p3), block, 0, st, a, s.hdr, g);
     }
     hipLaunchKernelGGL((long_reduce_kernel<NC>), dim3(cus * 2), dim3(kRowWaves * kWave), 0, st, s.hdr, s.long_count, s.long_base, s.partial,
                        s.long_res, max_slots, g);

@@ -37,12 +37,14 @@ constexpr uint32_t kPieceMaxCount = 1024;     // a chain is cut into at most thi
 // Adagrad runs of more than kLongRun and at most kMidMax updates are walked by ONE workgroup that keeps the
 // gradients in registers between the sum of squares and the steps (one read); only longer runs, which need
 // many workgroups, go through the pieces and read their gradients twice.  0 = no such tier.  One workgroup
-// takes ~0.5 ms over 32768 updates, so this pays only when there are enough such runs to keep every
-// workgroup busy meanwhile: with fewer than kMidMinRowsPerBlock long rows per resident workgroup all runs
-// go through the pieces (measured: 3801 long rows, 49 % of 2^26 updates -- chains 6.8 -> 5.2 ms; 420 long
-// rows in 2^24 updates -- 0.66 -> 1.1 ms if the tier were used there).
+// takes ~0.5 ms over 32768 updates, beside the first pass over the pieces, and that pass takes as long as the
+// batch has long rows: with kMidMinRows of them, runs of up to kMidShare updates for each are walked so.  us a
+// call without / with 12 / with 24 of them: 2^24 Zipf updates, 1066 long rows, 4050 / 3829 / 3886; 2^23, 553,
+// 1987 / 1917 / 1965; 2^24 half Zipf, 420, 8097 / 8053 / 8082; 2^22, 287, 1141 / 1169 / 1181.
 constexpr uint32_t kMidMax = ECRM_MID_RUN;
-constexpr uint32_t kMidMinRowsPerBlock = 4;
+// Rows of at most 64 floats leave half of its waves idle (6 M Zipf updates of 64 floats: 1060 without, 1100 with).
+constexpr uint32_t kMidMinRows = 400, kMidMinNarrowRows = 2048, kMidShare = 12;
+constexpr uint32_t kMidMinBatch = 1u << 21;
 constexpr int kMidWaves = 8;         // waves of the workgroup that walks such a run
 constexpr uint32_t kMidClasses = 7;  // the runs are listed by length (x2 per class) and taken longest first
 #ifndef ECRM_CHUNK
@@ -76,7 +78,8 @@ struct Header {
     uint32_t n_hot;        // stripes that the sample took for hot (set by the partition)
     uint32_t n_reads;      // entries with a long waiting run that a read left to read_long_kernel (cleared by read_begin_kernel)
     uint32_t read_ticket;  // next of its jobs to be handed out (the same)
-    uint32_t pad[36];
+    uint32_t piece_ticket; // next chain piece to be handed out (cleared by reset)
+    uint32_t pad[35];
 };
 static_assert(sizeof(Header) == 256, "header is one 256-byte block");
 
@@ -201,7 +204,7 @@ struct Geometry {
 struct LaunchGrids {
     int p1, p3;            // chain pieces: summaries, steps
     int mid;               // runs walked by one workgroup
-    uint32_t mid_min_rows; // ... which is done only in batches with at least this many long rows
+    uint32_t mid_min_rows; // ... only in batches with at least this many long rows; 0: kMidMinRows, and by kMidShare
     int apply, rows;       // apply with / without the parity rows
 };
 bool query_launch_grids(const Geometry &g, int cus, LaunchGrids *out);   // false: an occupancy query failed
