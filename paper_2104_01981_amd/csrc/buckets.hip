@@ -1364,7 +1364,7 @@ __device__ __forceinline__ bool hot_block(const BucketArgs &a, BucketShared &sh,
         uint32_t m;
         bucket_excl_scan(s.len, sh.wave, m);
         if (m < least) continue;
-        if (m <= a.lim.hot_in_place && k <= kInPlaceEntries) {
+        if (m <= a.lim.hot_in_place && m < a.lim.split_stripe && k <= kInPlaceEntries) {
             hot_job<MODE, PARITY>(a, sh, h, cg);
             continue;
         }
