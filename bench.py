@@ -27,10 +27,10 @@ LONG_RUN = 1024          # ECRM_LONG_RUN of include/ecrm.h: longer runs leave th
 # HBM bytes per launch of the apply kernel, from rocprofv3 FETCH_SIZE and WRITE_SIZE scaled by a plain copy of known
 # size (profiles/update_path_<workload>_hbm_traffic.txt).  Reported only while the code of the kernel's sources is
 # what the counters were taken on.
-TRAFFIC_BYTES_PER_LAUNCH = {"hbm_scale": 37958992896, "large_uniform": 77513681818, "large_skewed": 42567330509}
+TRAFFIC_BYTES_PER_LAUNCH = {"hbm_scale": 37958642995, "large_uniform": 77514097152, "large_skewed": 42561777562}
 TRAFFIC_SOURCES = ["paper_2104_01981_amd/csrc/update.hip", "paper_2104_01981_amd/csrc/rows.h",
                    "paper_2104_01981_amd/csrc/ecrm_internal.h"]
-TRAFFIC_SOURCES_SHA256 = "f257f6a948a5fbd0d6658bf9d45e51b0780c98300ecddc095c3f5987b60ead03"
+TRAFFIC_SOURCES_SHA256 = "2cbe171c465a0fd1884bd74602a1a11e50be6f7b7f2e544d20a64f53dc8bad33"
 
 
 def code_digest(paths):
