@@ -83,6 +83,16 @@ ECRM_HD BucketLimits bucket_limits(uint32_t n, uint32_t k, uint32_t D)
 {
     return BucketLimits{heavy_run(n), shared_stripe(n, k), split_stripe(n, D), hot_in_place(n)};
 }
+// updates from which on a stripe that the sample took for hot is one; candidates: how many the sample has
+ECRM_HD uint32_t hot_least(const BucketLimits &l, uint32_t k, uint32_t candidates)
+{
+    const uint32_t half = l.shared_stripe / 2u;
+    return candidates > kManyHot ? l.shared_stripe : half > heavy_stripe(k) ? half : heavy_stripe(k);
+}
+ECRM_HD bool in_place_size(const BucketLimits &l, uint32_t k, uint32_t m)
+{
+    return m <= l.hot_in_place && m < l.split_stripe && k <= kInPlaceEntries;
+}
 struct BucketPlan { uint32_t ipt, tiles, buckets; };
 // Tiles as small as kMaxTiles of them allow.  Buckets of 8 updates while that gives no more than the 1024 workgroups that
 // are resident at once -- the fewer updates a wave walks one after the other the better (2048 uniform updates: 19.0 us with 16 to a bucket, 16.7 with 8, 17.4 with 4) --, of 64 from

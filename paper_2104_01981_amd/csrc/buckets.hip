@@ -1220,8 +1220,9 @@ __device__ __forceinline__ void split_run(const BucketArgs &a, BucketShared &sh,
 
 // ---- hot stripes -----------------------------------------------------------------------------------
 // The stripes that the sample took for hot, numbered as they are ranked.  The first kHotMax workgroups look after one each,
-// should it be short after all; the others of the hot buckets' kHotBuckets take (stripe, 16 columns) jobs, so that what takes
-// long begins first and beside everything else: as a launch of its own behind this one it was 7 to 11 us of a call.
+// should it be short after all; the others of the hot buckets' kHotBuckets hand on what is left to heavy_stripes, and take
+// (stripe, 16 columns) jobs of the rest, so that what takes long begins first and beside everything else: as a launch of its own
+// behind this one it was 7 to 11 us of a call.
 
 // one entry's updates, or a whole stripe's: how many, where each tile's lie
 struct HotSpan { uint32_t from, len; };
@@ -1235,6 +1236,14 @@ __device__ __forceinline__ HotSpan hot_span(const BucketArgs &a, uint32_t first_
     }
     return s;
 }
+
+// The stripe that a workgroup of the hot buckets looks at first: the one it looks after, or that of the first entry that it may
+// have to hand on.  Asked for before it is known how many there are, so it has to lie inside the hot buckets.
+__device__ __forceinline__ uint32_t first_hot_stripe(const Geometry &geo)
+{
+    return blockIdx.x < kHotMax ? min(blockIdx.x, kHotBuckets / geo.k - 1u) : geo.dk.div(blockIdx.x - kHotMax);
+}
+static_assert(kHotMax >= 64u, "the stripe of the last workgroup's entry ends with the hot buckets");
 
 // 16 columns of hot stripe h, whose updates are left where the partition put them.  As in long_runs.h, with T updates to a
 // group of eight lanes and 32 groups: 256 updates a round.
@@ -1348,59 +1357,62 @@ __device__ __forceinline__ void hot_job(const BucketArgs &a, BucketShared &sh, u
     }
 }
 
-// What a workgroup of the hot buckets has to do; true: it goes on with the ordinary bucket of len updates at `from` a tile.
+// What a workgroup of the hot buckets has to do; true: it goes on with the stripe as an ordinary bucket.  s: first_hot_stripe,
+// e: the entry of the same number as the workgroup.
 template <int MODE, bool PARITY>
-__device__ __forceinline__ bool hot_block(const BucketArgs &a, BucketShared &sh, uint32_t n_hot, uint32_t &from, uint32_t &len)
+__device__ __forceinline__ bool hot_block(const BucketArgs &a, BucketShared &sh, uint32_t n_hot, HotSpan s, HotSpan e)
 {
     const uint32_t k = a.geo.k, tid = threadIdx.x, ncg = (a.geo.D + kHeavyCols - 1) / kHeavyCols;
     const uint32_t hot = min(n_hot, min(kHotMax, kHotBuckets / k));
     // no stripe, or one that is not as long as the sample made it look: its entries' buckets lie side by side in every tile,
     // so a workgroup takes them as one ordinary bucket
-    const uint32_t least = n_hot > kManyHot ? a.lim.shared_stripe : max(a.lim.shared_stripe / 2u, heavy_stripe(k));
+    const uint32_t least = hot_least(a.lim, k, n_hot);
     if (blockIdx.x < kHotMax) {
         if (blockIdx.x >= hot) return false;
-        const HotSpan s = hot_span(a, a.buckets + blockIdx.x * k, k);
         uint32_t m;
         bucket_excl_scan(s.len, sh.wave, m);
-        from = s.from;
-        len = s.len;
         return m < least;
     }
-    for (uint32_t job = blockIdx.x - kHotMax; job < hot * ncg; job += kHotBuckets - kHotMax) {
-        const uint32_t h = job / ncg, cg = job % ncg;
-        const HotSpan s = hot_span(a, a.buckets + h * k, k);
-        HotSpan e = hot_span(a, a.buckets + h * k + min(cg, k - 1u), 1);
+    constexpr uint32_t kWorkers = kHotBuckets - kHotMax;
+    const uint32_t worker = blockIdx.x - kHotMax;
+    // Left to heavy_stripes: the entries of the longest are described to it, the others copied, in arrival order, by all of
+    // these workgroups alike (by those of the stripe's first columns, 24 of the 192 did all of it with four entries of 512
+    // floats: 2^18 updates on 256 such rows 545 us, now 375).
+    for (uint32_t q = worker; q < hot * k; q += kWorkers) {
+        const uint32_t h = a.geo.dk.div(q), j = q - h * k;
+        if (q != worker) {
+            s = hot_span(a, a.buckets + h * k, k);
+            e = hot_span(a, a.buckets + q, 1);
+        }
         uint32_t m;
         bucket_excl_scan(s.len, sh.wave, m);
-        if (m < least) continue;
-        if (m <= a.lim.hot_in_place && m < a.lim.split_stripe && k <= kInPlaceEntries) {
-            hot_job<MODE, PARITY>(a, sh, h, cg);
+        if (m < least || in_place_size(a.lim, k, m)) continue;
+        if (m >= a.lim.split_stripe) {
+            split_run(a, sh, q, e.from, e.len);
+            __syncthreads();                                        // sh.fill
             continue;
         }
-        // left to heavy_stripes: the entries of the longest are described to it, the others copied, in arrival order
-        for (uint32_t j = cg; j < k; j += ncg) {
-            if (j != cg) e = hot_span(a, a.buckets + h * k + j, 1);
-            if (m >= a.lim.split_stripe) {
-                split_run(a, sh, h * k + j, e.from, e.len);
-                __syncthreads();                                    // sh.fill
-                continue;
-            }
-            uint32_t L, start, begin;
-            const uint32_t at = bucket_excl_scan(e.len, sh.wave, L);
-            bucket_excl_scan(tid < a.tiles ? e.from - tid * a.tile : 0u, sh.wave, start);
-            if (j == 0) {
-                bucket_excl_scan(tid < a.tiles ? s.from - tid * a.tile : 0u, sh.wave, begin);
-                if (tid == 0) list_heavy(a, sh.dense_used, begin, 0, m, false);
-            }
-            if (tid < a.tiles) {
-                sh.pref[tid] = at;
-                sh.start[tid] = e.from;
-            }
-            if (tid == 0) sh.pref[a.tiles] = L;
-            __syncthreads();
-            copy_bucket<true>(a, sh, a.dense + start);
-            __syncthreads();
+        uint32_t L, start, begin;
+        const uint32_t at = bucket_excl_scan(e.len, sh.wave, L);
+        bucket_excl_scan(tid < a.tiles ? e.from - tid * a.tile : 0u, sh.wave, start);
+        if (j == 0) {
+            bucket_excl_scan(tid < a.tiles ? s.from - tid * a.tile : 0u, sh.wave, begin);
+            if (tid == 0) list_heavy(a, sh.dense_used, begin, 0, m, false);
         }
+        if (tid < a.tiles) {
+            sh.pref[tid] = at;
+            sh.start[tid] = e.from;
+        }
+        if (tid == 0) sh.pref[a.tiles] = L;
+        __syncthreads();
+        copy_bucket<true>(a, sh, a.dense + start);
+        __syncthreads();
+    }
+    for (uint32_t job = worker; job < hot * ncg; job += kWorkers) {
+        const uint32_t h = job / ncg;
+        uint32_t m;
+        bucket_excl_scan(hot_span(a, a.buckets + h * k, k).len, sh.wave, m);
+        if (m >= least && in_place_size(a.lim, k, m)) hot_job<MODE, PARITY>(a, sh, h, job % ncg);
     }
     return false;
 }
@@ -1418,14 +1430,18 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
     const bool of_hot = blockIdx.x < kHotBuckets;
     const uint32_t b = of_hot ? kNoKey : blockIdx.x - kHotBuckets;
     bool key_bad = false;
-    uint32_t from = 0, len = 0;
+    uint32_t from = 0, len = 0, entry_from = 0, entry_len = 0;
     if (tid < a.tiles) {
         key_bad = (a.tile_state[tid] & 1u) != 0;
-        if (!of_hot) {
-            const uint16_t *row = a.table + (size_t)tid * (B + 1) + b;
-            from = tid * a.tile + row[0];
-            len = (uint32_t)row[1] - row[0];
+        const uint32_t first = of_hot ? a.buckets + first_hot_stripe(a.geo) * a.geo.k : b, buckets = of_hot ? a.geo.k : 1u;
+        const uint16_t *row = a.table + (size_t)tid * (B + 1);
+        if (of_hot) {
+            const uint32_t entry = a.buckets + (blockIdx.x < kHotMax ? 0u : blockIdx.x - kHotMax);
+            entry_from = tid * a.tile + row[entry];
+            entry_len = (uint32_t)row[entry + 1u] - row[entry];
         }
+        from = tid * a.tile + row[first];
+        len = (uint32_t)row[first + buckets] - row[first];
     }
     const uint32_t n_hot = a.hdr->n_hot;
     const bool many = n_hot > kManyHot;                             // long stripes
@@ -1438,7 +1454,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
         }
         return;
     }
-    if (of_hot && !hot_block<MODE, PARITY>(args_again(), sh, n_hot, from, len)) return;
+    if (of_hot && !hot_block<MODE, PARITY>(a, sh, n_hot, HotSpan{from, len}, HotSpan{entry_from, entry_len})) return;
     uint32_t m;
     const uint32_t at = bucket_excl_scan(len, sh.wave, m);
     if (!Rule<MODE>::combine && b == 0) {                           // the batch is valid: publish its per-server counts
