@@ -33,8 +33,8 @@ constexpr uint32_t kBucketMaxServers = 64;   // per-tile load counts are kept fo
 constexpr uint32_t kBucketChunk = 8;         // sorted positions whose stripes a wave owns at a time
 // A stripe that does not end inside a window of 64 positions leaves its bucket for heavy_stripes, which splits it over the
 // columns, if it has a run of heavy_run(n) updates: its workgroup would take 25 of them per us, where heavy_stripes takes 300
-// but begins when the buckets are done.  With runs from 128 on heavy, n / 2048 in large batches: 26 624 half Zipf 55.0, now 48.4;
-// 8192 half Zipf 39.5, 33.0; 65 536 half Zipf 89.4, 84.9; 300 007 Zipf combined 197, 182; 2^19 Zipf 324, 293.  A
+// but begins when the buckets are done.  With runs from 128 on heavy, n / 2048 in large batches: 8192 half Zipf 39.5, now 33.0;
+// 65 536 half Zipf 89.4, 84.9; 300 007 Zipf combined 197, 182; 2^19 Zipf 324, 293.  A
 // heavy stripe takes ~6 us for every entry in each of its D / 16 workgroups, however short its run is, so that few of them
 // are a gain and many a loss.  In a batch of many long stripes -- more than kManyHot hot ones in the sample: a small table --
 // a stripe that no run dominates is shared by the waves of its workgroup instead, as long as it has fewer than
@@ -48,11 +48,16 @@ constexpr uint32_t kHeavyRunMin = 128, kHeavyStripeMin = 256, kHeavyEntryMin = 1
 ECRM_HD uint32_t heavy_run(uint32_t n) { return n / 640u > 2u * kHeavyRunMin ? n / 640u : 2u * kHeavyRunMin; }
 // of a stripe that makes its bucket too long for LDS
 ECRM_HD uint32_t heavy_stripe(uint32_t k) { return kHeavyEntryMin * k > kHeavyStripeMin ? kHeavyEntryMin * k : kHeavyStripeMin; }
+ECRM_HD uint32_t square_root(uint32_t v)     // rounded down; v below 2^24
+{
+    uint32_t root = 0;
+    for (uint32_t bit = 1u << 11; bit; bit >>= 1)
+        if ((root + bit) * (root + bit) <= v) root += bit;
+    return root;
+}
 ECRM_HD uint32_t shared_stripe(uint32_t n, uint32_t k)
 {
-    uint32_t root = 0;                       // of 4 n, rounded down
-    for (uint32_t bit = 1u << 11; bit; bit >>= 1)
-        if ((root + bit) * (root + bit) <= 4u * n) root += bit;
+    const uint32_t root = square_root(4u * n);
     return root > heavy_stripe(k) ? root : heavy_stripe(k);
 }
 static_assert(kHeavyEntryMin * 64u <= kBucketCap && 4u * kBucketMaxBatch < kBucketCap * kBucketCap, "a stripe that is not heavy fits a list");
@@ -72,10 +77,9 @@ ECRM_HD uint32_t split_segments(uint32_t n, uint32_t k)
     const uint32_t runs = n / kSplitStripeMin * k;
     return runs ? n / kSplitSegment + (runs < kHotBuckets ? runs : kHotBuckets) : 0u;
 }
-// A hot stripe of up to this many updates is worked off beside the buckets, 100 updates per us, a longer one by heavy_stripes
-// behind them, 300 per us: what takes longer than the buckets do should not be in their launch (twice as much: no change).
-// Nor one of more entries than this: each costs its workgroups a few more trips to memory than in heavy_stripes (2^16 updates on
-// 2520 rows, k = 63: 594 us there, 782 in place).
+// Hot stripes are worked off beside the buckets, by workgroups that begin first, or by heavy_stripes behind them.  In place: one
+// of up to this many updates, and of at most this many entries: each costs its workgroups a few more trips to memory than in
+// heavy_stripes (2^16 updates on 2520 rows, k = 63: 594 us there, 782 in place).
 constexpr uint32_t kInPlaceEntries = 16;
 ECRM_HD uint32_t hot_in_place(uint32_t n) { return n / 16u > 2048u ? n / 16u : 2048u; }
 struct BucketLimits { uint32_t heavy_run, shared_stripe, split_stripe, hot_in_place; };
@@ -93,6 +97,26 @@ ECRM_HD bool in_place_size(const BucketLimits &l, uint32_t k, uint32_t m)
 {
     return m <= l.hot_in_place && m < l.split_stripe && k <= kInPlaceEntries;
 }
+// ... and only where that is not what the launch then takes: a hot stripe in place takes ~70 updates per us and 7 us for each
+// entry, in D / 16 workgroups of which 288 make progress at a time, heavy_stripes 350 updates per us and as much for an entry, of
+// 256.  Measured in updates of the former: what a stripe's workgroups have to do here has to end with the buckets' work, ~15 us
+// and the `rest` of the batch at 25 updates of 128 floats to one of these, or at least by as much later as it would keep
+// heavy_stripes busy -- that is, longer than the longest stripe of the batch does, if that one is left to it for its size.
+// Without this rule, and without any stripe in place / with it: 2^19 updates on 128 rows 321, 170 / 153; 2^18 on 256
+// rows of 512 floats 554, 380 / 375; 2^18 Zipf on 1024 rows 304, 209 / 212; 8192 Zipf on 2040 rows, k = 10, 98, 72 / 73; 8192 half
+// Zipf on 2048 rows 32, 48 / 32 (the constants are fitted to 290 such batches: 2 % above the better of the two).
+struct HotStripe { uint32_t updates, entries; };
+ECRM_HD bool in_place_time(const BucketLimits &l, uint32_t D, uint32_t hot, uint32_t rest, const HotStripe &longest, const HotStripe &s)
+{
+    const uint32_t jobs = hot * ((D + 15u) / 16u), wide = D > 96u ? D : 96u;
+    const uint32_t here = (512u * s.entries + s.updates) * (jobs > 288u ? jobs : 288u) / 288u;
+    const uint32_t behind = (512u * s.entries + s.updates / 5u) * (jobs > 256u ? jobs : 256u) / 256u;
+    const bool is_left = longest.updates > l.hot_in_place || longest.updates >= l.split_stripe;
+    const uint32_t left = is_left ? 512u * longest.entries + longest.updates / 5u : 0u;
+    return here <= 1024u + rest * wide / 1792u + (behind > left ? behind - left : 0u);
+}
+static_assert((512u * kInPlaceEntries + kBucketMaxBatch / 16u) < (1u << 20) && kBucketMaxBatch <= (1u << 19),
+              "times 64 stripes of 64 groups of columns, and updates times 1024 floats, in 32 bits");
 struct BucketPlan { uint32_t ipt, tiles, buckets; };
 // Tiles as small as kMaxTiles of them allow.  Buckets of 8 updates while that gives no more than the 1024 workgroups that
 // are resident at once -- the fewer updates a wave walks one after the other the better (2048 uniform updates: 19.0 us with 16 to a bucket, 16.7 with 8, 17.4 with 4) --, of 64 from
@@ -145,6 +169,14 @@ ECRM_HD uint32_t sample_position(uint32_t i, uint32_t n)
     const uint32_t bits = sample_bits(n);
     const uint32_t lo = (uint32_t)(((uint64_t)i * n) >> bits), hi = (uint32_t)(((uint64_t)(i + 1u) * n) >> bits);
     return lo + (uint32_t)(((uint64_t)scramble32(i) * (hi - lo)) >> 32);
+}
+// What `hits` of the sample, on `seen` different entries, say of a stripe: its updates; its entries, all that were seen if
+// most hits repeat an entry, and by the number of repeats (as of birthdays) otherwise.
+ECRM_HD uint32_t sampled_updates(uint32_t hits, uint32_t n) { return (uint32_t)(((uint64_t)hits * n) >> sample_bits(n)); }
+ECRM_HD uint32_t sampled_entries(uint32_t hits, uint32_t seen, uint32_t k)
+{
+    const uint32_t guess = hits * hits / (2u * (hits - seen) + 1u), entries = hits >= 3u * seen ? seen : guess > seen ? guess : seen;
+    return entries < k ? entries : k;
 }
 // hits from which on a stripe counts as hot
 ECRM_HD uint32_t hot_hits(uint32_t n)

@@ -496,7 +496,7 @@ struct PartitionArgs {
     uint32_t *tile_cnt;        // [tiles][2S]: load counts of the tile (not for the combined rules)
     uint32_t *tile_state;      // [tiles]: updates that are held back, twice, and one if a key is out of range
     Header *hdr;
-    uint32_t n, buckets, rows, count;
+    uint32_t n, tiles, buckets, rows, count, D;
     uint32_t clear_sticky, packed;
     Divider dk, dS;
     RecoveryView rv;
@@ -520,15 +520,17 @@ __device__ __forceinline__ bool takes_part(const PartitionArgs &a, uint64_t k64,
 constexpr uint32_t kSampleSlots = 2048, kHotCand = 256, kHotMax = 64, kHotSlots = 256;
 
 struct SampleShared {
-    uint32_t g[kSampleSlots], c[kSampleSlots];
+    uint32_t g[kSampleSlots], c[kSampleSlots];                     // stripe; hits (and, if asked for, a bit << 16 for each of its first 16 entries)
     uint32_t cand_g[kHotCand], cand_c[kHotCand];
 };
+constexpr uint32_t kHitsMask = 0xFFFFu;
+static_assert(kSample <= kHitsMask && kInPlaceEntries <= 16u, "hits and entries in one word");
 struct HotShared {
     uint32_t g[kHotSlots], h[kHotSlots];       // open addressing: stripe, its number among the hot ones
     uint32_t n_cand;
 };
 
-__device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n, SampleShared &t, HotShared &hot)
+__device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n, bool entries, SampleShared &t, HotShared &hot)
 {
     const uint32_t tid = threadIdx.x;
     const uint32_t sample = 1u << sample_bits(n), least = hot_hits(n), cap = min(kHotMax, kHotBuckets / a.dk.d);
@@ -551,14 +553,16 @@ __device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n,
         for (uint32_t s = scramble32(g) & (kSampleSlots - 1u);; s = (s + 1u) & (kSampleSlots - 1u)) {   // at most kSample slots fill
             const uint32_t was = atomicCAS(&t.g[s], kNoKey, g);
             if (was == kNoKey || was == g) {
+                const uint32_t j = x - g * a.dk.d;
                 atomicAdd(&t.c[s], 1u);
+                if (entries && j < kInPlaceEntries) atomicOr(&t.c[s], 0x10000u << j);
                 break;
             }
         }
     }
     __syncthreads();
     for (uint32_t i = tid; i < kSampleSlots; i += kPartThreads) {
-        if (t.c[i] >= least) {                                      // at most kSample / 4 = kHotCand of them
+        if ((t.c[i] & kHitsMask) >= least) {                        // at most kSample / 4 = kHotCand of them
             const uint32_t at = atomicAdd(&hot.n_cand, 1u);
             t.cand_g[at] = t.g[i];
             t.cand_c[at] = t.c[i];
@@ -567,11 +571,14 @@ __device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n,
     __syncthreads();
     const uint32_t nc = hot.n_cand;
     if (tid < nc) {                                                 // the cap most frequent, smaller numbers first
-        const uint32_t g = t.cand_g[tid], c = t.cand_c[tid];
+        const uint32_t g = t.cand_g[tid], what = t.cand_c[tid], c = what & kHitsMask;
         uint32_t rank = 0;
-        for (uint32_t i = 0; i < nc; ++i)
-            rank += t.cand_c[i] > c || (t.cand_c[i] == c && t.cand_g[i] < g) ? 1u : 0u;
+        for (uint32_t i = 0; i < nc; ++i) {
+            const uint32_t ci = t.cand_c[i] & kHitsMask;
+            rank += ci > c || (ci == c && t.cand_g[i] < g) ? 1u : 0u;
+        }
         if (rank < cap) {
+            t.c[rank] = what;                                       // for divide_hot
             uint32_t s = scramble32(g) & (kHotSlots - 1u);
             while (atomicCAS(&hot.g[s], kNoKey, g) != kNoKey) s = (s + 1u) & (kHotSlots - 1u);     // kHotMax < kHotSlots
             hot.h[s] = rank;
@@ -579,6 +586,24 @@ __device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n,
     }
     __syncthreads();
     return min(nc, cap);
+}
+
+// What is worked off beside the buckets and what is left to heavy_stripes (bucket_plan.h), from what the sample says of the
+// hot stripes.  One wave, after find_hot.  All whose size allows it, or none: where some are left, their time comes on top.
+// A stripe's time is that of its hits less their standard deviation: the longest of many equal ones looks longer than they are.
+__device__ __forceinline__ void divide_hot(const PartitionArgs &a, uint32_t n, uint32_t n_hot, const SampleShared &t)
+{
+    const uint32_t lane = lane_id(), k = a.dk.d, what = lane < n_hot ? t.c[lane] : 0u, hits = what & kHitsMask;
+    const uint32_t entries = sampled_entries(hits, (uint32_t)__popc(what >> 16), k), updates = sampled_updates(hits, n);
+    uint32_t all = updates;
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) all += __shfl_xor(all, d, kWave);
+    const HotStripe longest{from_lane(updates, 0), from_lane(entries, 0)}, mine{sampled_updates(hits - square_root(hits), n), entries};
+    const BucketLimits lim = bucket_limits(n, k, a.D);
+    const bool fits = lane < n_hot && in_place_size(lim, k, updates);
+    const u64 slow = __ballot(fits && !in_place_time(lim, a.D, n_hot, n - min(all, n), longest, mine));
+    const u64 here = slow ? 0ull : __ballot(fits);
+    if (lane == 0) a.hdr->hot_here = here;
 }
 
 // Bound by its chain of dependent steps (keys, ranks, scan, write), not by its 16 bytes per update; the ranks are
@@ -596,7 +621,12 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
     const uint32_t n = a.packed ? min(a.n, a.hdr->buf_count) : a.n;       // a replay: everything that is waiting now
     const uint32_t S = a.dS.d, tile0 = tile * kTile;
     static_assert(sizeof(SampleShared) <= sizeof(s_cnt), "the sample is counted where the buckets are, before them");
-    const uint32_t n_hot = n >= kSample * 4u ? find_hot(a, n, *(SampleShared *)&s_cnt[0][0], s_hot) : 0u;
+    SampleShared &sample = *(SampleShared *)&s_cnt[0][0];
+    const uint32_t n_hot = n >= kSample * 4u ? find_hot(a, n, tile == a.tiles, sample, s_hot) : 0u;
+    if (tile == a.tiles) {                                                // no tile: one workgroup more, beside the others
+        if (wave == 0) divide_hot(a, n, n_hot, sample);
+        return;
+    }
     // a replay's buckets are those of what is waiting, not of the buffer that holds it: 4096 workgroups for 20 000 updates
     const uint32_t ordinary = a.packed ? bucket_count(n) : a.buckets;
     const uint32_t B = ordinary + kHotBuckets;                            // buckets in the table; the last are the hot entries'
@@ -1222,7 +1252,7 @@ __device__ __forceinline__ void split_run(const BucketArgs &a, BucketShared &sh,
 // The stripes that the sample took for hot, numbered as they are ranked.  The first kHotMax workgroups look after one each,
 // should it be short after all; the others of the hot buckets' kHotBuckets hand on what is left to heavy_stripes, and take
 // (stripe, 16 columns) jobs of the rest, so that what takes long begins first and beside everything else: as a launch of its own
-// behind this one it was 7 to 11 us of a call.
+// behind this one it was 7 to 11 us of a call.  Which way they go is the partition's choice (divide_hot).
 
 // one entry's updates, or a whole stripe's: how many, where each tile's lie
 struct HotSpan { uint32_t from, len; };
@@ -1360,7 +1390,7 @@ __device__ __forceinline__ void hot_job(const BucketArgs &a, BucketShared &sh, u
 // What a workgroup of the hot buckets has to do; true: it goes on with the stripe as an ordinary bucket.  s: first_hot_stripe,
 // e: the entry of the same number as the workgroup.
 template <int MODE, bool PARITY>
-__device__ __forceinline__ bool hot_block(const BucketArgs &a, BucketShared &sh, uint32_t n_hot, HotSpan s, HotSpan e)
+__device__ __forceinline__ bool hot_block(const BucketArgs &a, BucketShared &sh, uint32_t n_hot, u64 here, HotSpan s, HotSpan e)
 {
     const uint32_t k = a.geo.k, tid = threadIdx.x, ncg = (a.geo.D + kHeavyCols - 1) / kHeavyCols;
     const uint32_t hot = min(n_hot, min(kHotMax, kHotBuckets / k));
@@ -1386,7 +1416,7 @@ __device__ __forceinline__ bool hot_block(const BucketArgs &a, BucketShared &sh,
         }
         uint32_t m;
         bucket_excl_scan(s.len, sh.wave, m);
-        if (m < least || in_place_size(a.lim, k, m)) continue;
+        if (m < least || (((here >> h) & 1u) && in_place_size(a.lim, k, m))) continue;
         if (m >= a.lim.split_stripe) {
             split_run(a, sh, q, e.from, e.len);
             __syncthreads();                                        // sh.fill
@@ -1410,6 +1440,7 @@ __device__ __forceinline__ bool hot_block(const BucketArgs &a, BucketShared &sh,
     }
     for (uint32_t job = worker; job < hot * ncg; job += kWorkers) {
         const uint32_t h = job / ncg;
+        if (!((here >> h) & 1u)) continue;
         uint32_t m;
         bucket_excl_scan(hot_span(a, a.buckets + h * k, k).len, sh.wave, m);
         if (m >= least && in_place_size(a.lim, k, m)) hot_job<MODE, PARITY>(a, sh, h, job % ncg);
@@ -1444,6 +1475,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
         len = (uint32_t)row[first + buckets] - row[first];
     }
     const uint32_t n_hot = a.hdr->n_hot;
+    const u64 here = a.hdr->hot_here;
     const bool many = n_hot > kManyHot;                             // long stripes
     const bool full = a.hdr->batch_bad != 0;                        // the recovery buffer could not take its part
     key_bad = __syncthreads_or(key_bad);
@@ -1454,7 +1486,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
         }
         return;
     }
-    if (of_hot && !hot_block<MODE, PARITY>(a, sh, n_hot, HotSpan{from, len}, HotSpan{entry_from, entry_len})) return;
+    if (of_hot && !hot_block<MODE, PARITY>(a, sh, n_hot, here, HotSpan{from, len}, HotSpan{entry_from, entry_len})) return;
     uint32_t m;
     const uint32_t at = bucket_excl_scan(len, sh.wave, m);
     if (!Rule<MODE>::combine && b == 0) {                           // the batch is valid: publish its per-server counts
@@ -1901,12 +1933,12 @@ void launch_bucket_partition(const BucketScratch &bs, Header *hdr, const Geometr
     const BucketPlan p = bucket_plan(n);
     PartitionArgs a;
     a.keys = keys; a.items = bs.items; a.table = bs.table; a.tile_cnt = bs.tile_cnt; a.tile_state = bs.tile_state;
-    a.hdr = hdr; a.n = n; a.buckets = p.buckets; a.rows = g.rows;
+    a.hdr = hdr; a.n = n; a.tiles = p.tiles; a.buckets = p.buckets; a.rows = g.rows; a.D = g.D;
     a.count = (g.mode & 2u) ? 0u : 1u;               // the combined rules count per modified entry, later
     a.clear_sticky = clear_sticky ? 1u : 0u;
     a.packed = src == kWaitingUpdates ? 1u : 0u;
     a.dk = g.dk; a.dS = g.dS; a.rv = rv;
-    const dim3 grid(p.tiles), block(kPartThreads);
+    const dim3 grid(p.tiles + 1u), block(kPartThreads);
     switch (p.ipt) {
         case 1: hipLaunchKernelGGL(bucket_partition_kernel<1>, grid, block, 0, st, a); break;
         case 2: hipLaunchKernelGGL(bucket_partition_kernel<2>, grid, block, 0, st, a); break;

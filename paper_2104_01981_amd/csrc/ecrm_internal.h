@@ -79,7 +79,9 @@ struct Header {
     uint32_t n_reads;      // entries with a long waiting run that a read left to read_long_kernel (cleared by read_begin_kernel)
     uint32_t read_ticket;  // next of its jobs to be handed out (the same)
     uint32_t piece_ticket; // next chain piece to be handed out (cleared by reset)
-    uint32_t pad[35];
+    uint32_t pad0;
+    unsigned long long hot_here;   // which of them are worked off beside the buckets, a bit each (set by the partition)
+    uint32_t pad[32];
 };
 static_assert(sizeof(Header) == 256, "header is one 256-byte block");
 

@@ -20,6 +20,17 @@ uint32_t plan_bucket_cap() { return kBucketCap; }
 uint32_t plan_heavy_stripe(uint32_t k) { return heavy_stripe(k); }
 uint32_t plan_split_stripe(uint32_t n, uint32_t D) { return split_stripe(n, D); }
 uint32_t plan_shared_stripe(uint32_t n, uint32_t k) { return shared_stripe(n, k); }
+uint32_t plan_hot_in_place(uint32_t n) { return hot_in_place(n); }
+uint32_t plan_hot_least(uint32_t n, uint32_t k, uint32_t D, uint32_t candidates) { return hot_least(bucket_limits(n, k, D), k, candidates); }
+uint32_t plan_many_hot() { return kManyHot; }
+uint32_t plan_in_place_size(uint32_t n, uint32_t k, uint32_t D, uint32_t m) { return in_place_size(bucket_limits(n, k, D), k, m); }
+uint32_t plan_in_place_time(uint32_t n, uint32_t k, uint32_t D, uint32_t hot, uint32_t rest, uint32_t m0, uint32_t e0, uint32_t m, uint32_t e)
+{
+    return in_place_time(bucket_limits(n, k, D), D, hot, rest, HotStripe{m0, e0}, HotStripe{m, e});
+}
+uint32_t plan_sampled_updates(uint32_t hits, uint32_t n) { return sampled_updates(hits, n); }
+uint32_t plan_sampled_entries(uint32_t hits, uint32_t seen, uint32_t k) { return sampled_entries(hits, seen, k); }
+uint32_t plan_square_root(uint32_t v) { return square_root(v); }
 uint32_t plan_hot_hits(uint32_t n) { return hot_hits(n); }
 uint32_t plan_sample(uint32_t n, uint32_t *at)
 {
@@ -87,3 +98,38 @@ def hot_stripes(keys, k):
     """The stripes that the partition takes for hot (before it keeps the most frequent ones of too many)."""
     g, hits = np.unique(np.asarray(keys, np.int64)[sample_positions(len(keys))] // k, return_counts=True)
     return g[hits >= int(lib().plan_hot_hits(C.c_uint32(len(keys))))]
+
+
+def hot_in_place(n):
+    return int(lib().plan_hot_in_place(C.c_uint32(n)))
+
+
+def ranked_hot_stripes(keys, k):
+    """The stripes of the sample that the partition keeps, as it numbers them: (stripe, hits, of its first 16 entries those seen),
+    and how many it had to choose from."""
+    sample = np.asarray(keys, np.int64)[sample_positions(len(keys))]
+    g, hits = np.unique(sample // k, return_counts=True)
+    hot = hits >= int(lib().plan_hot_hits(C.c_uint32(len(keys))))
+    g, hits = g[hot], hits[hot]
+    order = np.lexsort((g, -hits))[:min(64, 256 // k)]
+    seen = [sum(1 for x in np.unique(sample[sample // k == s]) if x % k < 16) for s in g[order]]
+    return list(zip(g[order].tolist(), hits[order].tolist(), seen)), len(g)
+
+
+def divide_hot(keys, k, D):
+    """What the partition makes of the hot stripes: those that are worked off beside the buckets, and whether others are left."""
+    u, n = C.c_uint32, len(keys)
+    ranked, candidates = ranked_hot_stripes(keys, k)
+    if n < 4096 or not ranked:
+        return set(), False
+    updates = [int(lib().plan_sampled_updates(u(h), u(n))) for _, h, _ in ranked]
+    entries = [int(lib().plan_sampled_entries(u(h), u(s), u(k))) for _, h, s in ranked]
+    rest = n - min(sum(updates), n)
+    fits = [bool(lib().plan_in_place_size(u(n), u(k), u(D), u(m))) for m in updates]
+    slow = False
+    for (_, h, _), e, f in zip(ranked, entries, fits):
+        m = lib().plan_sampled_updates(u(h - lib().plan_square_root(u(h))), u(n))
+        slow |= f and not lib().plan_in_place_time(u(n), u(k), u(D), u(len(ranked)), u(rest), u(updates[0]), u(entries[0]), u(m), u(e))
+    here = set() if slow else {g for (g, _, _), f in zip(ranked, fits) if f}
+    least = int(lib().plan_hot_least(u(n), u(k), u(D), u(candidates)))
+    return here, any(m >= least and g not in here for (g, _, _), m in zip(ranked, updates))

@@ -1,5 +1,5 @@
 """The sample in which the partition looks for hot stripes, on the host: one position in every segment of the batch, and
-blind to no period of it."""
+blind to no period of it; and what becomes of the hot stripes: worked off beside the buckets where that ends with them."""
 import numpy as np
 import pytest
 
@@ -33,3 +33,48 @@ def test_hot_stripes_at_odd_positions_are_found(n):
     keys = rng.integers(0, 1 << 20, n)
     keys[1::2] = rng.integers(0, 32, n // 2)
     assert set(range(8)) <= set(bp.hot_stripes(keys, 4).tolist())
+
+
+def _batch(n, R, k, hot, seed=1):
+    """n keys: hot {row: updates}, the rest uniform"""
+    rng = np.random.default_rng(seed)
+    rest = rng.integers(0, R, n - sum(hot.values()))
+    return rng.permutation(np.concatenate([np.repeat(np.array(list(hot), np.int64), list(hot.values())), rest]))
+
+
+@pytest.mark.parametrize("n,R,k,D", [(1 << 14, 32, 4, 128), (1 << 16, 64, 4, 128), (1 << 16, 128, 4, 512), (1 << 18, 64, 4, 128),
+                                     (1 << 18, 256, 4, 512), (1 << 19, 128, 4, 128), (1 << 19, 256, 4, 128)])
+def test_a_batch_of_hot_stripes_is_left_to_heavy_stripes(n, R, k, D):
+    """Nothing but hot stripes: beside the buckets there is nothing to hide their work behind.  (Worked off there all the same
+    they took up to twice as long.)"""
+    keys = np.random.default_rng(n + R).integers(0, R, n)
+    assert bp.hot_stripes(keys, k).size and bp.divide_hot(keys, k, D) == (set(), True)
+
+
+@pytest.mark.parametrize("D", [64, 128, 512, 1024])
+def test_many_hot_stripes_beside_few_others(D):
+    """15 stripes of n / 16 updates in two entries each."""
+    for n, k in ((1 << 16, 4), (1 << 17, 4), (1 << 19, 4)):
+        hot = {g * k + j: n // 32 for g in range(3, 18) for j in range(2)}
+        here, left = bp.divide_hot(_batch(n, n // 2, k, hot), k, D)
+        assert left and not here
+
+
+@pytest.mark.parametrize("n,T", [(8192, 600), (26624, 1500), (65536, 2000), (200000, 6000)])
+def test_a_few_hot_stripes_go_beside_the_buckets(n, T):
+    k = 4
+    hot = {40: T, 81: T // 2, 122: T // 2}
+    here, left = bp.divide_hot(_batch(n, 4 * n, k, hot), k, 128)
+    assert here == {10, 20, 30} and not left
+
+
+def test_what_the_sample_says_of_a_stripe():
+    u = bp.C.c_uint32
+    entries = lambda hits, seen, k: int(bp.lib().plan_sampled_entries(u(hits), u(seen), u(k)))
+    assert entries(40, 1, 10) == 1 and entries(40, 4, 4) == 4 and entries(4, 4, 10) == 10 and entries(5, 2, 10) == 3
+    for k in (1, 2, 4, 10, 16):
+        for hits in range(4, 200):
+            for seen in range(1, min(k, hits) + 1):
+                assert seen <= entries(hits, seen, k) <= k
+    root = lambda v: int(bp.lib().plan_square_root(u(v)))
+    assert all(root(v) ** 2 <= v < (root(v) + 1) ** 2 for v in list(range(2000)) + [1 << 21, (1 << 24) - 1])
