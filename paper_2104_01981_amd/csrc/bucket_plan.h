@@ -34,7 +34,10 @@ constexpr uint32_t kBucketChunk = 8;         // sorted positions whose stripes a
 // A stripe that does not end inside a window of 64 positions leaves its bucket for heavy_stripes, which splits it over the
 // columns, if it has a run of heavy_run(n) updates: its workgroup would take 25 of them per us, where heavy_stripes takes 300
 // but begins when the buckets are done.  With runs from 128 on heavy, n / 2048 in large batches: 8192 half Zipf 39.5, now 33.0;
-// 65 536 half Zipf 89.4, 84.9; 300 007 Zipf combined 197, 182; 2^19 Zipf 324, 293.  A
+// 65 536 half Zipf 89.4, 84.9; 300 007 Zipf combined 197, 182; 2^19 Zipf 324, 293.  Where heavy_stripes has hot stripes to
+// work off anyway, behind the buckets, that shorter run (heavy_run_beside) is the better one, up to 128 floats: 26 features of
+// 3 to 4096 rows and up, 131 072 updates 151 with heavy_run, 129 with heavy_run_beside, 262 144 with k = 10 338, 308; but
+// 65 536 Zipf on 1024 rows of 512 floats 172, 254, where each entry of a stripe is worked on by 32 workgroups.  A
 // heavy stripe takes ~6 us for every entry in each of its D / 16 workgroups, however short its run is, so that few of them
 // are a gain and many a loss.  In a batch of many long stripes -- more than kManyHot hot ones in the sample: a small table --
 // a stripe that no run dominates is shared by the waves of its workgroup instead, as long as it has fewer than
@@ -46,6 +49,7 @@ constexpr uint32_t kBucketChunk = 8;         // sorted positions whose stripes a
 constexpr uint32_t kManyHot = 32;
 constexpr uint32_t kHeavyRunMin = 128, kHeavyStripeMin = 256, kHeavyEntryMin = 16;
 ECRM_HD uint32_t heavy_run(uint32_t n) { return n / 640u > 2u * kHeavyRunMin ? n / 640u : 2u * kHeavyRunMin; }
+ECRM_HD uint32_t heavy_run_beside(uint32_t n) { return n / 2048u > kHeavyRunMin ? n / 2048u : kHeavyRunMin; }
 // of a stripe that makes its bucket too long for LDS
 ECRM_HD uint32_t heavy_stripe(uint32_t k) { return kHeavyEntryMin * k > kHeavyStripeMin ? kHeavyEntryMin * k : kHeavyStripeMin; }
 ECRM_HD uint32_t square_root(uint32_t v)     // rounded down; v below 2^24
@@ -82,10 +86,10 @@ ECRM_HD uint32_t split_segments(uint32_t n, uint32_t k)
 // heavy_stripes (2^16 updates on 2520 rows, k = 63: 594 us there, 782 in place).
 constexpr uint32_t kInPlaceEntries = 16;
 ECRM_HD uint32_t hot_in_place(uint32_t n) { return n / 16u > 2048u ? n / 16u : 2048u; }
-struct BucketLimits { uint32_t heavy_run, shared_stripe, split_stripe, hot_in_place; };
+struct BucketLimits { uint32_t shared_stripe, split_stripe, hot_in_place; };
 ECRM_HD BucketLimits bucket_limits(uint32_t n, uint32_t k, uint32_t D)
 {
-    return BucketLimits{heavy_run(n), shared_stripe(n, k), split_stripe(n, D), hot_in_place(n)};
+    return BucketLimits{shared_stripe(n, k), split_stripe(n, D), hot_in_place(n)};
 }
 // updates from which on a stripe that the sample took for hot is one; candidates: how many the sample has
 ECRM_HD uint32_t hot_least(const BucketLimits &l, uint32_t k, uint32_t candidates)

@@ -591,7 +591,7 @@ __device__ __forceinline__ uint32_t find_hot(const PartitionArgs &a, uint32_t n,
 // What is worked off beside the buckets and what is left to heavy_stripes (bucket_plan.h), from what the sample says of the
 // hot stripes.  One wave, after find_hot.  All whose size allows it, or none: where some are left, their time comes on top.
 // A stripe's time is that of its hits less their standard deviation: the longest of many equal ones looks longer than they are.
-__device__ __forceinline__ void divide_hot(const PartitionArgs &a, uint32_t n, uint32_t n_hot, const SampleShared &t)
+__device__ __forceinline__ void divide_hot(const PartitionArgs &a, uint32_t n, uint32_t n_hot, const SampleShared &t, const HotShared &found)
 {
     const uint32_t lane = lane_id(), k = a.dk.d, what = lane < n_hot ? t.c[lane] : 0u, hits = what & kHitsMask;
     const uint32_t entries = sampled_entries(hits, (uint32_t)__popc(what >> 16), k), updates = sampled_updates(hits, n);
@@ -603,7 +603,11 @@ __device__ __forceinline__ void divide_hot(const PartitionArgs &a, uint32_t n, u
     const bool fits = lane < n_hot && in_place_size(lim, k, updates);
     const u64 slow = __ballot(fits && !in_place_time(lim, a.D, n_hot, n - min(all, n), longest, mine));
     const u64 here = slow ? 0ull : __ballot(fits);
-    if (lane == 0) a.hdr->hot_here = here;
+    const u64 left = __ballot(lane < n_hot && updates >= hot_least(lim, k, found.n_cand)) & ~here;
+    if (lane == 0) {
+        a.hdr->hot_here = here;
+        a.hdr->heavy_run = left && a.D <= 128u ? heavy_run_beside(n) : heavy_run(n);
+    }
 }
 
 // Bound by its chain of dependent steps (keys, ranks, scan, write), not by its 16 bytes per update; the ranks are
@@ -624,7 +628,7 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
     SampleShared &sample = *(SampleShared *)&s_cnt[0][0];
     const uint32_t n_hot = n >= kSample * 4u ? find_hot(a, n, tile == a.tiles, sample, s_hot) : 0u;
     if (tile == a.tiles) {                                                // no tile: one workgroup more, beside the others
-        if (wave == 0) divide_hot(a, n, n_hot, sample);
+        if (wave == 0) divide_hot(a, n, n_hot, sample, s_hot);
         return;
     }
     // a replay's buckets are those of what is waiting, not of the buffer that holds it: 4096 workgroups for 20 000 updates
@@ -1474,7 +1478,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
         from = tid * a.tile + row[first];
         len = (uint32_t)row[first + buckets] - row[first];
     }
-    const uint32_t n_hot = a.hdr->n_hot;
+    const uint32_t n_hot = a.hdr->n_hot, heavy_run = a.hdr->heavy_run;
     const u64 here = a.hdr->hot_here;
     const bool many = n_hot > kManyHot;                             // long stripes
     const bool full = a.hdr->batch_bad != 0;                        // the recovery buffer could not take its part
@@ -1536,7 +1540,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
         __syncthreads();
     }
     const RowArgs rows = a;
-    const uint32_t heavy_run = a.lim.heavy_run, shared = many ? a.lim.shared_stripe : 0u, packed = a.packed;
+    const uint32_t shared = many ? a.lim.shared_stripe : 0u, packed = a.packed;
     for (;;) {
         if (oversized) list = oversized_part(args_again(), sh, m, base, walk);
         if (list) {

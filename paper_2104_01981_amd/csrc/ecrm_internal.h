@@ -79,7 +79,7 @@ struct Header {
     uint32_t n_reads;      // entries with a long waiting run that a read left to read_long_kernel (cleared by read_begin_kernel)
     uint32_t read_ticket;  // next of its jobs to be handed out (the same)
     uint32_t piece_ticket; // next chain piece to be handed out (cleared by reset)
-    uint32_t pad0;
+    uint32_t heavy_run;    // updates from which on a run makes its stripe one for heavy_stripes (set by the partition)
     unsigned long long hot_here;   // which of them are worked off beside the buckets, a bit each (set by the partition)
     uint32_t pad[32];
 };

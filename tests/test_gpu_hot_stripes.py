@@ -30,9 +30,9 @@ def _batch(n, R, k, D, hot, seed, here):
 
 
 def _header(c):
-    """The bits of the stripes that were to go beside the buckets, and what heavy_stripes was left: stripes, segments"""
+    """heavy_run, the bits of the stripes that were to go beside the buckets, and what heavy_stripes was left: stripes, segments"""
     w = c.scratch[:256].cpu().numpy().view(np.uint32)
-    return int(w[30]) | int(w[31]) << 32, int(w[22]), int(w[24])
+    return int(w[29]), int(w[30]) | int(w[31]) << 32, int(w[22]), int(w[24])
 
 
 def _twice(c, keys, seed):
@@ -59,10 +59,11 @@ def test_limits(total, D, k, S, opt, comb, prop):
     keys = _batch(n, R, k, D, hot, total, here)
     assert np.bincount(keys.astype(np.int64) // k)[7] == total
     c = Case(R, D, k, S, max_batch=n, seed=94, optimizer=opt, momentum=0.9, combine=comb, propagation=prop)
-    bits, stripes, segments = _twice(c, keys, 94)
+    heavy_run, bits, stripes, segments = _twice(c, keys, 94)
     ranked = [g for g, _, _ in bp.ranked_hot_stripes(keys, k)[0]]
     assert {g for i, g in enumerate(ranked) if bits >> i & 1} == here
     assert segments == 0 and stripes == (2 if k > 16 else 1 if total > limit else 0)
+    assert heavy_run == (128 if (total == 3000 or k > 16) and D <= 128 else 256)     # shorter where heavy_stripes has work anyway
     c.compare("hot stripes")
 
 
@@ -77,8 +78,8 @@ def test_limit_of_a_large_batch(D):
     count = np.bincount(keys.astype(np.int64) // k)
     assert all(count[g] == m for g, m in sizes.items())
     c = Case(R, D, k, S, max_batch=n, seed=95)
-    _, stripes, segments = _twice(c, keys, 95)
-    assert (stripes, segments) == (1, 0)
+    heavy_run, _, stripes, segments = _twice(c, keys, 95)
+    assert (stripes, segments) == (1, 0) and heavy_run == bp.heavy_run(n)
     stats = c.ctx.batch_stats()
     assert stats["long_rows"] == 3 and stats["long_items"] == sum(sizes.values())
     c.compare("large batch")
@@ -96,7 +97,7 @@ def test_handed_on(k, D):
     here, left = bp.divide_hot(keys, k, D)
     assert not here and left
     c = Case(R, D, k, S, max_batch=n, seed=96)
-    bits, stripes, segments = _twice(c, keys, 96)
+    heavy_run, bits, stripes, segments = _twice(c, keys, 96)
     described = int(np.bincount(keys.astype(np.int64) // k)[0] >= bp.split_stripe(n, D))
     assert bits == 0 and stripes == min(24, 256 // k) - described and (segments > 0) == bool(described)
     c.compare("handed on")
