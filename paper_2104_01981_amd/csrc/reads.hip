@@ -398,10 +398,23 @@ static ReadArgs read_args(const Scratch &s, const Geometry &g, const float *E, c
     return a;
 }
 
+// Requests that are answered by one set of launches: as many threads, which is what a launch can have.
+constexpr uint64_t kReadSlice = 1u << 30;
+
 static dim3 read_grid(const ReadArgs &a)
 {
     const uint64_t waves = (a.n + a.per - 1) / a.per;
     return dim3((uint32_t)((waves + kReadWaves - 1) / kReadWaves));
+}
+
+// the requests from the at-th of n on
+static void next_slice(ReadArgs &a, uint64_t at, uint64_t n, const uint64_t *keys, float *out_E, float *out_A, int cus)
+{
+    a.keys = keys + at;
+    a.n = n - at < kReadSlice ? n - at : kReadSlice;
+    a.out_E = out_E + at * a.geo.D;
+    a.out_A = out_A ? out_A + at * a.geo.D : nullptr;
+    a.per = requests_per_wave(a.n, cus);
 }
 
 void launch_degraded_read(const Scratch &s, const Geometry &g, const float *E, const float *A, const float *PE,
@@ -409,9 +422,10 @@ void launch_degraded_read(const Scratch &s, const Geometry &g, const float *E, c
                           float *out_A, int cus, hipStream_t st)
 {
     ReadArgs a = read_args(s, g, E, A, PE, PA, lost);
-    a.keys = keys; a.n = n; a.out_E = out_E; a.out_A = out_A;
-    a.per = requests_per_wave(n, cus);
-    hipLaunchKernelGGL((read_entries_kernel<false, kAdagradSeq>), read_grid(a), dim3(kReadThreads), 0, st, a);
+    for (uint64_t at = 0; at < n; at += kReadSlice) {
+        next_slice(a, at, n, keys, out_E, out_A, cus);
+        hipLaunchKernelGGL((read_entries_kernel<false, kAdagradSeq>), read_grid(a), dim3(kReadThreads), 0, st, a);
+    }
 }
 
 template <int MODE>

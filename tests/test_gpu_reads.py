@@ -1,6 +1,6 @@
 """Reads where the flat copy and the shared answers can go wrong: rows of any width beside the 16 bytes a lane moves, stripes of
 one member and of many, numbers of requests around what a wave takes (4 to 64), more requests than the scratch buffer serves at a
-time, and waiting runs on either side of what one wave walks (128) and of a workgroup's round (1024), requested many times."""
+time, or a launch takes, and waiting runs on either side of what one wave walks (128) and of a workgroup's round (1024), requested many times."""
 import numpy as np
 import pytest
 import torch
@@ -75,3 +75,30 @@ def test_shared_answers(D, k, S, server, opt, locked):
     for i, x in enumerate(sample.tolist()):               # requests for one entry get one answer
         first.setdefault(x, i)
     assert torch.equal(oe, oe[torch.tensor([first[x] for x in sample.tolist()], device="cuda")])
+
+
+def test_more_requests_than_a_launch_takes():
+    """2^32 requests and a few: with as many threads in one launch as requests, it was refused."""
+    n, R, D, k, S, cap = (1 << 32) + 77, 4 * 250, 4, 4, 5, 300
+    if torch.cuda.mem_get_info()[0] < n * (8 + 4 * D) + (8 << 30):
+        pytest.skip("not enough memory on the device")
+    c = Case(R, D, k, S, max_batch=cap, seed=35)
+    keys, out = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(n, D, device="cuda")
+    tables = torch.arange(R, device="cuda").repeat(1 << 18)          # whole tables, a part of the requests that torch handles
+    parts = range(0, n, len(tables))
+    for at in parts:
+        keys[at:at + len(tables)] = tables[:min(len(tables), n - at)]
+    lost = oracle.degraded_read(c.hE, c.hA, c.hPE, c.hPA, k, S, np.arange(R, dtype=np.uint64), 3)[0]
+    for read, want, atol in ((lambda: c.ctx.degraded_read(keys, 3, out), lost, 5e-7),):
+        for at in parts:
+            out[at:at + len(tables)] = float("nan")
+        read()
+        assert c.ctx.status() == 0
+        whole = torch.from_numpy(want).cuda()
+        for at in parts:
+            rows = out[at:at + len(tables)]
+            full = len(rows) // R * R
+            assert full == 0 or float((rows[:full].view(-1, R, D) - whole).abs().max()) <= atol
+            assert full == len(rows) or float((rows[full:] - whole[:len(rows) - full]).abs().max()) <= atol
+    del keys, out
+    torch.cuda.empty_cache()
