@@ -38,7 +38,7 @@ struct ReadArgs {
     const uint32_t *m_dev;   // how many there are (device word)
     const float *pool;
     uint32_t *leader;        // [m] at the head of a run: the request that answers for its entry
-    uint32_t *place;         // [n] head of the run that a request's entry has, or kNoKey
+    uint32_t *place;         // [n] head of the run that a request's entry has, or kNoKey; null: there is no room for as many
     uint32_t *longs;         // head and leader of the runs that are left to read_long_kernel
 };
 
@@ -157,6 +157,14 @@ __device__ __forceinline__ uint32_t first_not_below(const uint32_t *bk, uint32_t
     return lo;
 }
 
+// head of the run of x, an entry of the tables, among m waiting updates
+__device__ __forceinline__ uint32_t waiting_run(const ReadArgs &a, uint32_t m, uint32_t x)
+{
+    if (!m || !held_back(a.rv, x, a.geo.dk, a.geo.dS)) return kNoKey;
+    const uint32_t p = first_not_below(a.bk, m, x);
+    return p < m && a.bk[p] == x ? p : kNoKey;
+}
+
 // One entry with fewer than kReadRun waiting updates, by a wave, for request i (all wave-uniform).
 template <int MODE>
 __device__ __forceinline__ void read_run(const ReadArgs &a, uint32_t m, uint32_t pos, uint32_t x, uint64_t i)
@@ -237,20 +245,17 @@ __global__ __launch_bounds__(kReadThreads) void read_entries_kernel(ReadArgs a)
     bool claimed = false;
     const uint32_t m = WAITING ? uniform(*a.m_dev) : 0u;
     if (WAITING) {
-        if (valid && m && held_back(a.rv, x, a.geo.dk, a.geo.dS)) {
-            const uint32_t p = first_not_below(a.bk, m, x);
-            if (p < m && a.bk[p] == x) {
-                pos = p;
-                claimed = atomicCAS(&a.leader[p], kNoKey, (uint32_t)(first + lane)) == kNoKey;
-                if (claimed && p + kReadRun <= m && a.bk[p + kReadRun - 1u] == x) {
-                    const uint32_t at = atomicAdd(&a.hdr->n_reads, 1u);
-                    a.longs[2u * at] = p;                // at most m / kReadRun of them
-                    a.longs[2u * at + 1u] = (uint32_t)(first + lane);
-                    claimed = false;
-                }
+        if (valid) pos = waiting_run(a, m, x);
+        if (pos != kNoKey) {
+            claimed = atomicCAS(&a.leader[pos], kNoKey, (uint32_t)(first + lane)) == kNoKey;
+            if (claimed && pos + kReadRun <= m && a.bk[pos + kReadRun - 1u] == x) {
+                const uint32_t at = atomicAdd(&a.hdr->n_reads, 1u);
+                a.longs[2u * at] = pos;                  // at most m / kReadRun of them
+                a.longs[2u * at + 1u] = (uint32_t)(first + lane);
+                claimed = false;
             }
         }
-        if (lane < cnt) a.place[first + lane] = pos;
+        if (lane < cnt && a.place) a.place[first + lane] = pos;
     }
     const bool lost = valid && pos == kNoKey && is_lost(a, g, j);
     const uint32_t plain = collect(valid && pos == kNoKey && !lost, x, lane, list);
@@ -360,7 +365,9 @@ __global__ __launch_bounds__(kHeavyThreads) void read_long_kernel(ReadArgs a)
     }
 }
 
-// the requests whose entries were answered for another one
+// The requests whose entries were answered for another one.  Where there was no room for the places of their runs they are
+// looked up once more: 2^18 requests of a context made for batches of 2048 148 us; when such a read was cut into parts of 2048,
+// of four launches each, 2367.
 __global__ __launch_bounds__(kReadThreads) void read_shared_kernel(ReadArgs a)
 {
     __shared__ uint2 s_list[kReadWaves][kWave];
@@ -370,7 +377,13 @@ __global__ __launch_bounds__(kReadThreads) void read_shared_kernel(ReadArgs a)
     if (first >= a.n) return;
     uint32_t from = kNoKey;
     if (lane < a.per && first + lane < a.n) {
-        const uint32_t pos = a.place[first + lane];
+        uint32_t pos = kNoKey;
+        if (a.place) {
+            pos = a.place[first + lane];
+        } else {
+            const uint64_t key = a.keys[first + lane];
+            if (key < (uint64_t)a.geo.rows) pos = waiting_run(a, *a.m_dev, (uint32_t)key);
+        }
         if (pos != kNoKey) from = a.leader[pos];
     }
     const uint32_t cnt = collect(from != kNoKey && from != (uint32_t)(first + lane), from, lane, list);
@@ -438,8 +451,7 @@ static void recovery_read_slice(const ReadArgs &a, uint32_t cap, int cus, hipStr
     hipLaunchKernelGGL(read_shared_kernel, read_grid(a), dim3(kReadThreads), 0, st, a);
 }
 
-// bk, bi: the waiting updates, as launch_sort left them (of a buffer of `cap` of them); max_batch: what the scratch buffer
-// serves, and the requests that are answered at a time.
+// bk, bi: the waiting updates, as launch_sort left them (of a buffer of `cap` of them); max_batch: what the scratch buffer serves
 void launch_recovery_read(const Scratch &s, const Geometry &g, const RecoveryView &rv, const float *E, const float *A,
                           const float *PE, const float *PA, const uint64_t *keys, uint64_t n, const uint32_t *bk,
                           const uint32_t *bi, const uint32_t *m_dev, uint32_t cap, const float *pool, uint32_t max_batch,
@@ -447,15 +459,11 @@ void launch_recovery_read(const Scratch &s, const Geometry &g, const RecoveryVie
 {
     ReadArgs a = read_args(s, g, E, A, PE, PA, rv.server);
     a.rv = rv; a.bk = bk; a.bi = bi; a.m_dev = m_dev; a.pool = pool;
-    a.place = s.keys[bk == s.keys[0] ? 1 : 0];           // the sort is done with the other halves of its buffers
+    a.place = n <= max_batch ? s.keys[bk == s.keys[0] ? 1 : 0] : nullptr;   // the sort is done with the other halves of its buffers
     a.leader = s.vals[bi == s.vals[0] ? 1 : 0];
     a.longs = s.active;
-    for (uint64_t at = 0; at < n; at += max_batch) {
-        a.keys = keys + at;
-        a.n = n - at < max_batch ? n - at : max_batch;
-        a.out_E = out_E + at * g.D;
-        a.out_A = out_A ? out_A + at * g.D : nullptr;
-        a.per = requests_per_wave(a.n, cus);
+    for (uint64_t at = 0; at < n; at += kReadSlice) {
+        next_slice(a, at, n, keys, out_E, out_A, cus);
         if (g.mode == kMomentumSeq) recovery_read_slice<kMomentumSeq>(a, cap, cus, st);
         else recovery_read_slice<kAdagradSeq>(a, cap, cus, st);       // a recovery takes no combined rule
     }

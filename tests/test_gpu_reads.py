@@ -1,6 +1,8 @@
 """Reads where the flat copy and the shared answers can go wrong: rows of any width beside the 16 bytes a lane moves, stripes of
 one member and of many, numbers of requests around what a wave takes (4 to 64), more requests than the scratch buffer serves at a
 time, or a launch takes, and waiting runs on either side of what one wave walks (128) and of a workgroup's round (1024), requested many times."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -77,19 +79,75 @@ def test_shared_answers(D, k, S, server, opt, locked):
     assert torch.equal(oe, oe[torch.tensor([first[x] for x in sample.tolist()], device="cuda")])
 
 
+def _hip():
+    """The HIP runtime this process has loaded."""
+    with open("/proc/self/maps") as f:
+        return C.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+
+
+def _launches(call):
+    """How many launches a call enqueues, counted in a graph captured of it (which is not run)."""
+    hip, stream = _hip(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    handle, graph, nodes = C.c_void_p(stream.cuda_stream), C.c_void_p(), C.c_size_t(0)
+    assert hip.hipStreamBeginCapture(handle, 1) == 0         # only what this thread does
+    try:
+        call(stream)
+    finally:
+        assert hip.hipStreamEndCapture(handle, C.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, C.byref(nodes)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return nodes.value
+
+
+def _waiting(R, D, k, S, server, cap, max_batch, keys, seed=35):
+    """A recovery with the updates of `keys` to lost entries and to the first half of the stripes waiting."""
+    c = Case(R, D, k, S, max_batch=max_batch, seed=seed)
+    bk, bg = torch.empty(2 * cap, dtype=torch.int64, device="cuda"), torch.empty(2 * cap, D, device="cuda")
+    c.ctx.recovery_begin(server, 2, bk, bg, cap)
+    ses = RecoverySession(c.hE, c.hA, c.hPE, c.hPA, k, S, c.lr, c.eps, server, 2, cap, c.hld, c.hlp, threads=4)
+    c.ctx.recovery_lock()
+    ses.lock()
+    for at in range(0, len(keys), max_batch):
+        part = keys[at:at + max_batch]
+        g = grads_for(seed, at, len(part), D)
+        c.ctx.update(torch.from_numpy(part.view(np.int64)).cuda(), g)
+        assert ses.update(part, g.cpu().numpy())
+    return c, ses
+
+
+def test_a_read_of_many_requests_is_as_many_launches():
+    """A context made for small batches reads as many entries as it likes: the launches do not follow the requests."""
+    R, D, k, S, cap = 4 * 500, 16, 4, 5, 256
+    keys = np.random.default_rng(2).integers(0, R, cap).astype(np.uint64)
+    c, ses = _waiting(R, D, k, S, 1, cap, cap, keys)
+    count = []
+    for n in (cap, 8 * cap, 100 * cap + 1):
+        sample = np.random.default_rng(n).integers(0, R, n).astype(np.uint64)
+        st, oe = torch.from_numpy(sample.view(np.int64)).cuda(), torch.full((n + 1, D), -7.0, device="cuda")
+        c.ctx.recovery_read(st, oe[:n])
+        want, _ = ses.read(sample)
+        np.testing.assert_allclose(oe[:n].cpu().numpy(), want, rtol=1e-5, atol=5e-7)
+        assert bool((oe[n] == -7.0).all())
+        count.append(_launches(lambda s: c.ctx.recovery_read(st, oe[:n], stream=s)))
+    assert count[0] == count[1] == count[2] <= 10
+
+
 def test_more_requests_than_a_launch_takes():
     """2^32 requests and a few: with as many threads in one launch as requests, it was refused."""
     n, R, D, k, S, cap = (1 << 32) + 77, 4 * 250, 4, 4, 5, 300
     if torch.cuda.mem_get_info()[0] < n * (8 + 4 * D) + (8 << 30):
         pytest.skip("not enough memory on the device")
-    c = Case(R, D, k, S, max_batch=cap, seed=35)
+    c, ses = _waiting(R, D, k, S, 3, cap, cap, np.random.default_rng(4).integers(0, R, cap).astype(np.uint64))
     keys, out = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(n, D, device="cuda")
     tables = torch.arange(R, device="cuda").repeat(1 << 18)          # whole tables, a part of the requests that torch handles
     parts = range(0, n, len(tables))
     for at in parts:
         keys[at:at + len(tables)] = tables[:min(len(tables), n - at)]
+    want_waiting, _ = ses.read(np.arange(R, dtype=np.uint64))
     lost = oracle.degraded_read(c.hE, c.hA, c.hPE, c.hPA, k, S, np.arange(R, dtype=np.uint64), 3)[0]
-    for read, want, atol in ((lambda: c.ctx.degraded_read(keys, 3, out), lost, 5e-7),):
+    for read, want, atol in ((lambda: c.ctx.degraded_read(keys, 3, out), lost, 5e-7),
+                             (lambda: c.ctx.recovery_read(keys, out), want_waiting, 5e-7)):
         for at in parts:
             out[at:at + len(tables)] = float("nan")
         read()
