@@ -607,12 +607,18 @@ int ecrm_recovery_read(ecrm_ctx *c, const uint64_t *keys, uint64_t n, float *out
     }
     // The waiting updates, grouped by entry with the update path's own sort on the list's keys.  How
     // many there are is known on the device only: the launches are sized by the buffer's capacity.
-    uint32_t *bk = nullptr, *bi = nullptr;
-    RecoveryView none;
-    memset(&none, 0, sizeof(none));
-    launch_sort(c->s, c->geo, none, (const uint64_t *)c->hb.list[c->buf_cur], c->hb.cap, &c->s.hdr->buf_count, kWaitingUpdates,
-                c->key_bits, false, false, &bk, &bi, st);
-    launch_recovery_read(c->s, c->geo, c->rv, c->t.E, c->t.A, c->t.PE, c->t.PA, keys, n, bk, bi, &c->s.hdr->buf_count,
+    uint32_t *bk = nullptr, *bi = nullptr, *leader = c->s.long_slot;
+    const uint64_t *list = (const uint64_t *)c->hb.list[c->buf_cur];
+    const uint32_t *waiting = &c->s.hdr->buf_count;
+    const bool by_list = c->hb.cap <= kListSortMax;
+    if (by_list) {
+        launch_sort_list(c->s, c->geo, list, c->hb.cap, waiting, c->key_bits, leader, &bk, &bi, st);
+    } else {
+        RecoveryView none;
+        memset(&none, 0, sizeof(none));
+        launch_sort(c->s, c->geo, none, list, c->hb.cap, waiting, kWaitingUpdates, c->key_bits, false, false, &bk, &bi, st);
+    }
+    launch_recovery_read(c->s, c->geo, c->rv, c->t.E, c->t.A, c->t.PE, c->t.PA, keys, n, bk, bi, leader, by_list, waiting,
                          c->hb.cap, c->hb.rows, c->lay.max_batch, out_E, out_A, c->cus, st);
     return check_launch();
 }

@@ -230,6 +230,11 @@ void launch_reset(const Scratch &s, uint32_t S, uint32_t n, bool clear_sticky, B
 void launch_sort(const Scratch &s, const Geometry &g, const RecoveryView &rv, const uint64_t *keys, uint32_t n,
                  const uint32_t *n_dev, BatchSource src, int key_bits, bool by_stripe, bool count_servers,
                  uint32_t **sorted_keys, uint32_t **sorted_vals, hipStream_t st);
+// The same for the waiting updates of a recovery, of a buffer of cap <= kListSortMax; leader[0 .. n) and the header's fields of
+// a read are cleared on the way.
+constexpr uint32_t kListSortMax = 1u << 18;
+void launch_sort_list(const Scratch &s, const Geometry &g, const uint64_t *list, uint32_t cap, const uint32_t *n_dev, int key_bits,
+                      uint32_t *leader, uint32_t **sorted_keys, uint32_t **sorted_vals, hipStream_t st);
 // tile_count: scratch for the tiles' counts
 void launch_hold_back(Header *hdr, uint32_t *tile_count, const Geometry &g, const RecoveryView &rv, const uint64_t *keys,
                       const float *grads, uint32_t n, BatchSource src, const HoldBuffer &hb, uint32_t cur, hipStream_t st);
@@ -258,8 +263,8 @@ void launch_route(const Scratch &s, const Geometry &g, const uint64_t *keys, uin
                   uint32_t *member, uint32_t *data_srv, uint32_t *parity_srv, hipStream_t st);
 void launch_recovery_read(const Scratch &s, const Geometry &g, const RecoveryView &rv, const float *E, const float *A,
                           const float *PE, const float *PA, const uint64_t *keys, uint64_t n, const uint32_t *bk,
-                          const uint32_t *bi, const uint32_t *m_dev, uint32_t cap, const float *pool, uint32_t max_batch,
-                          float *out_E, float *out_A, int cus, hipStream_t st);
+                          const uint32_t *bi, uint32_t *leader, bool cleared, const uint32_t *m_dev, uint32_t cap,
+                          const float *pool, uint32_t max_batch, float *out_E, float *out_A, int cus, hipStream_t st);
 void launch_clear_status(const Scratch &s, hipStream_t st);
 void launch_fail_server(const Geometry &g, float *E, float *A, float *PE, float *PA, uint32_t server,
                         int grid_blocks, hipStream_t st);

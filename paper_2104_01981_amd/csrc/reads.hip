@@ -442,30 +442,34 @@ void launch_degraded_read(const Scratch &s, const Geometry &g, const float *E, c
 }
 
 template <int MODE>
-static void recovery_read_slice(const ReadArgs &a, uint32_t cap, int cus, hipStream_t st)
+static void recovery_read_slice(const ReadArgs &a, uint32_t cap, bool cleared, int cus, hipStream_t st)
 {
-    hipLaunchKernelGGL(read_begin_kernel, dim3((cap + 4u * kReadThreads - 1) / (4u * kReadThreads)), dim3(kReadThreads), 0, st,
-                       a.hdr, a.m_dev, a.leader);
+    if (!cleared)
+        hipLaunchKernelGGL(read_begin_kernel, dim3((cap + 4u * kReadThreads - 1) / (4u * kReadThreads)), dim3(kReadThreads), 0, st,
+                           a.hdr, a.m_dev, a.leader);
     hipLaunchKernelGGL((read_entries_kernel<true, MODE>), read_grid(a), dim3(kReadThreads), 0, st, a);
-    if (cap >= kReadRun) hipLaunchKernelGGL(read_long_kernel<MODE>, dim3(cus), dim3(kHeavyThreads), 0, st, a);
+    const uint32_t jobs = cap / kReadRun * ((a.geo.D + kHeavyCols - 1) / kHeavyCols);         // at most
+    if (jobs) hipLaunchKernelGGL(read_long_kernel<MODE>, dim3(min(jobs, (uint32_t)cus)), dim3(kHeavyThreads), 0, st, a);
     hipLaunchKernelGGL(read_shared_kernel, read_grid(a), dim3(kReadThreads), 0, st, a);
 }
 
-// bk, bi: the waiting updates, as launch_sort left them (of a buffer of `cap` of them); max_batch: what the scratch buffer serves
+// bk, bi: the waiting updates, as launch_sort left them (of a buffer of `cap` of them); leader: room for as many, and if it and
+// the header's fields are cleared already; max_batch: what the scratch buffer serves
 void launch_recovery_read(const Scratch &s, const Geometry &g, const RecoveryView &rv, const float *E, const float *A,
                           const float *PE, const float *PA, const uint64_t *keys, uint64_t n, const uint32_t *bk,
-                          const uint32_t *bi, const uint32_t *m_dev, uint32_t cap, const float *pool, uint32_t max_batch,
-                          float *out_E, float *out_A, int cus, hipStream_t st)
+                          const uint32_t *bi, uint32_t *leader, bool cleared, const uint32_t *m_dev, uint32_t cap,
+                          const float *pool, uint32_t max_batch, float *out_E, float *out_A, int cus, hipStream_t st)
 {
     ReadArgs a = read_args(s, g, E, A, PE, PA, rv.server);
     a.rv = rv; a.bk = bk; a.bi = bi; a.m_dev = m_dev; a.pool = pool;
     a.place = n <= max_batch ? s.keys[bk == s.keys[0] ? 1 : 0] : nullptr;   // the sort is done with the other halves of its buffers
-    a.leader = s.vals[bi == s.vals[0] ? 1 : 0];
+    a.leader = leader;
     a.longs = s.active;
     for (uint64_t at = 0; at < n; at += kReadSlice) {
         next_slice(a, at, n, keys, out_E, out_A, cus);
-        if (g.mode == kMomentumSeq) recovery_read_slice<kMomentumSeq>(a, cap, cus, st);
-        else recovery_read_slice<kAdagradSeq>(a, cap, cus, st);       // a recovery takes no combined rule
+        if (at) cleared = false;                             // the leaders of the requests before
+        if (g.mode == kMomentumSeq) recovery_read_slice<kMomentumSeq>(a, cap, cleared, cus, st);
+        else recovery_read_slice<kAdagradSeq>(a, cap, cleared, cus, st);       // a recovery takes no combined rule
     }
 }
 

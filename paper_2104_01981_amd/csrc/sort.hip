@@ -117,11 +117,12 @@ __device__ __forceinline__ uint32_t first_pass_key(uint64_t k64, uint32_t rows, 
 // ---- histogram ---------------------------------------------------------------------------------
 // FIRST: keys are the caller's u64 row ids; also range check + load accounting (count != 0).  by_stripe
 // groups by row id / k instead (for the parity half of gradient propagation).
-template <bool FIRST, int IPT>
+// LIST: for launch_sort_list, tile by tile in block_hist; the first pass prepares what a read needs next.
+template <bool FIRST, int IPT, bool LIST = false>
 __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(
     const void *keys_in, uint32_t n, const uint32_t *n_dev, uint32_t nblocks, int shift, int bits, uint32_t *block_hist,
     Header *hdr, unsigned long long *cnt, uint32_t rows, Divider dk, Divider dS, uint32_t count, RecoveryView rv,
-    uint32_t by_stripe, uint32_t packed)
+    uint32_t by_stripe, uint32_t packed, uint32_t *leader)
 {
     __shared__ uint32_t s_hist[kMaxBins];
     if (n_dev) n = min(n, *n_dev);
@@ -150,6 +151,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(
                 bool oob, held;                                   // held back: sorts behind every row, not applied
                 key = first_pass_key(k64, rows, dk, dS, rv, by_stripe != 0, packed != 0, oob, held);
                 bad |= oob;
+                if (LIST) leader[i] = kNoKey;
                 if (!oob && !held && S) {
                     const uint32_t x = (uint32_t)k64, g = dk.div(x), j = x - g * dk.d;
                     atomicAdd(&s_cnt[dS.mod(g + 1 + j)], 1u);     // server of the entry
@@ -163,7 +165,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(
     }
     if (FIRST && bad) s_bad = 1;
     __syncthreads();
-    for (uint32_t b = tid; b < bins; b += kSortThreads) block_hist[(size_t)b * nblocks + tile] = s_hist[b];
+    for (uint32_t b = tid; b < bins; b += kSortThreads)
+        block_hist[LIST ? (size_t)tile * bins + b : (size_t)b * nblocks + tile] = s_hist[b];
+    if (FIRST && LIST && tile == 0 && tid == 0) hdr->n_reads = hdr->read_ticket = 0;
     if (FIRST) {
         for (uint32_t i = tid; i < 2 * S; i += kSortThreads)
             if (s_cnt[i]) atomicAdd(&cnt[i], (unsigned long long)s_cnt[i]);
@@ -196,7 +200,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_scan_kernel(uint32_t *block
 #ifndef ECRM_SORT_WAVES
 #define ECRM_SORT_WAVES 4
 #endif
-template <bool FIRST, int IPT>
+// LIST: every workgroup adds up the counts of the tiles before its own, and of all, by itself: a launch less, and there are no
+// more tiles than are in use on the device.
+template <bool FIRST, int IPT, bool LIST = false>
 __global__ __launch_bounds__(kSortThreads, ECRM_SORT_WAVES) void sort_scatter_kernel(
     const void *keys_in, const uint32_t *vals_in, uint32_t *keys_out, uint32_t *vals_out,
     const uint32_t *block_hist, const uint32_t *bin_total, uint32_t n, const uint32_t *n_dev, uint32_t nblocks, int shift,
@@ -217,6 +223,22 @@ __global__ __launch_bounds__(kSortThreads, ECRM_SORT_WAVES) void sort_scatter_ke
     __syncthreads();
 
     const uint32_t tile = tile_of_block(blockIdx.x, nblocks), tile0 = tile * kTile;
+    if (LIST && tile0 >= n) return;
+    uint32_t before_tile = 0, in_all = 0;
+    if (LIST && tid < bins) {
+        const uint32_t used = (n + kTile - 1u) / kTile;
+        constexpr uint32_t U = 16;
+        for (uint32_t t0 = 0; t0 < used; t0 += U) {
+            uint32_t c[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) c[u] = t0 + u < used ? block_hist[(size_t)(t0 + u) * bins + tid] : 0u;
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                in_all += c[u];
+                before_tile += t0 + u < tile ? c[u] : 0u;
+            }
+        }
+    }
     uint32_t key[IPT], val[IPT], rank[IPT];
 #pragma unroll
     for (int r = 0; r < IPT; ++r) {
@@ -272,11 +294,11 @@ __global__ __launch_bounds__(kSortThreads, ECRM_SORT_WAVES) void sort_scatter_ke
     }
     uint32_t dummy;
     const uint32_t binstart = block_excl_scan(my_total, s_wave, dummy);
-    const uint32_t gtot = tid < bins ? bin_total[tid] : 0;
+    const uint32_t gtot = LIST ? in_all : tid < bins ? bin_total[tid] : 0;
     const uint32_t gstart = block_excl_scan(gtot, s_wave, dummy);
     if (tid < bins) {
         s_binstart[tid] = binstart;
-        s_gbase[tid] = gstart + block_hist[(size_t)tid * nblocks + tile] - binstart;
+        s_gbase[tid] = gstart + (LIST ? before_tile : block_hist[(size_t)tid * nblocks + tile]) - binstart;
     }
     __syncthreads();
 
@@ -318,6 +340,18 @@ void launch_clear_status(const Scratch &s, hipStream_t st)
     hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(64), 0, st, s.hdr);
 }
 
+static int sort_passes(int key_bits)
+{
+    const int passes = (key_bits + kMaxRadixBits - 1) / kMaxRadixBits;
+    return passes < 1 ? 1 : passes;
+}
+// the bits spread as evenly as possible, wider digits first
+static int digit_bits(int bits_left, int passes_left)
+{
+    const int bits = (bits_left + passes_left - 1) / passes_left;
+    return bits < 1 ? 1 : bits;
+}
+
 // One digit of the sort with tiles of kSortThreads * IPT items.
 template <int IPT>
 static void launch_sort_pass(const Scratch &s, const Geometry &g, const RecoveryView &rv, bool first, const void *keys_in,
@@ -328,10 +362,10 @@ static void launch_sort_pass(const Scratch &s, const Geometry &g, const Recovery
     const uint32_t tile = kSortThreads * IPT, nblocks = (n + tile - 1) / tile, bins = 1u << bits;
     if (first)
         hipLaunchKernelGGL((sort_hist_kernel<true, IPT>), dim3(nblocks), dim3(kSortThreads), 0, st, keys_in, n, n_dev,
-                           nblocks, shift, bits, s.block_hist, s.hdr, s.cnt, g.rows, g.dk, g.dS, count, rv, by_stripe, packed);
+                           nblocks, shift, bits, s.block_hist, s.hdr, s.cnt, g.rows, g.dk, g.dS, count, rv, by_stripe, packed, nullptr);
     else
         hipLaunchKernelGGL((sort_hist_kernel<false, IPT>), dim3(nblocks), dim3(kSortThreads), 0, st, keys_in, n, n_dev,
-                           nblocks, shift, bits, s.block_hist, s.hdr, s.cnt, g.rows, g.dk, g.dS, 0u, rv, 0u, 0u);
+                           nblocks, shift, bits, s.block_hist, s.hdr, s.cnt, g.rows, g.dk, g.dS, 0u, rv, 0u, 0u, nullptr);
     hipLaunchKernelGGL(sort_scan_kernel, dim3(bins), dim3(kSortThreads), 0, st, s.block_hist, s.bin_total, nblocks);
     if (first)
         hipLaunchKernelGGL((sort_scatter_kernel<true, IPT>), dim3(nblocks), dim3(kSortThreads), 0, st, keys_in, vals_in,
@@ -351,14 +385,10 @@ void launch_sort(const Scratch &s, const Geometry &g, const RecoveryView &rv, co
     const uint32_t packed = src == kWaitingUpdates ? 1u : 0u;
     // a small batch is cut into small tiles, so that it still spreads over the compute units
     const bool small = n <= kSmallSortBatch;
-    int passes = (key_bits + kMaxRadixBits - 1) / kMaxRadixBits;
-    if (passes < 1) passes = 1;
+    const int passes = sort_passes(key_bits);
     int shift = 0, cur = 0;
     for (int p = 0; p < passes; ++p) {
-        // spread the bits as evenly as possible, wider digits first
-        const int left = key_bits - shift;
-        int bits = (left + (passes - p) - 1) / (passes - p);
-        if (bits < 1) bits = 1;
+        const int bits = digit_bits(key_bits - shift, passes - p);
         const void *kin = p == 0 ? (const void *)keys : (const void *)s.keys[cur];
         const uint32_t *vin = p == 0 ? nullptr : s.vals[cur];
         const int out = p == 0 ? 0 : cur ^ 1;
@@ -373,6 +403,40 @@ void launch_sort(const Scratch &s, const Geometry &g, const RecoveryView &rv, co
     }
     *sorted_keys = s.keys[cur];
     *sorted_vals = s.vals[cur];
+}
+
+// The waiting updates of a recovery, for a read: two launches to a digit instead of three, and the read's leaders and its list
+// of long runs are cleared on the way.  A read of a few requests is these launches more than anything else: of 64, few updates
+// waiting of up to 1024, 4096, 16 384, 65 536, 262 144, us a call with three to a digit and
+// a launch to clear the leaders / so: 34, 36, 36, 36, 36 / 24, 24, 24, 26, 24; 65 536 requests, 65 536 of 262 144 waiting 87 / 81.
+void launch_sort_list(const Scratch &s, const Geometry &g, const uint64_t *list, uint32_t cap, const uint32_t *n_dev, int key_bits,
+                      uint32_t *leader, uint32_t **sorted_keys, uint32_t **sorted_vals, hipStream_t st)
+{
+    constexpr uint32_t tile = kSortThreads * kSmallSortIpt;
+    const uint32_t nblocks = (cap + tile - 1) / tile;
+    const dim3 grid(nblocks), block(kSortThreads);
+    const RecoveryView none{};
+    const int passes = sort_passes(key_bits);
+    int shift = 0;
+    for (int p = 0; p < passes; ++p) {
+        const int bits = digit_bits(key_bits - shift, passes - p);
+        uint32_t *const *k = s.keys, *const *v = s.vals;
+        const int in = (p + 1) & 1, out = p & 1;
+        if (p == 0) {
+            hipLaunchKernelGGL((sort_hist_kernel<true, kSmallSortIpt, true>), grid, block, 0, st, list, cap, n_dev, nblocks, shift,
+                               bits, s.block_hist, s.hdr, s.cnt, g.rows, g.dk, g.dS, 0u, none, 0u, 1u, leader);
+            hipLaunchKernelGGL((sort_scatter_kernel<true, kSmallSortIpt, true>), grid, block, 0, st, list, nullptr, k[out], v[out],
+                               s.block_hist, s.bin_total, cap, n_dev, nblocks, shift, bits, g.rows, g.dk, g.dS, none, 0u, 1u);
+        } else {
+            hipLaunchKernelGGL((sort_hist_kernel<false, kSmallSortIpt, true>), grid, block, 0, st, k[in], cap, n_dev, nblocks, shift,
+                               bits, s.block_hist, s.hdr, s.cnt, g.rows, g.dk, g.dS, 0u, none, 0u, 0u, nullptr);
+            hipLaunchKernelGGL((sort_scatter_kernel<false, kSmallSortIpt, true>), grid, block, 0, st, k[in], v[in], k[out], v[out],
+                               s.block_hist, s.bin_total, cap, n_dev, nblocks, shift, bits, g.rows, g.dk, g.dS, none, 0u, 0u);
+        }
+        shift += bits;
+    }
+    *sorted_keys = s.keys[(passes - 1) & 1];
+    *sorted_vals = s.vals[(passes - 1) & 1];
 }
 
 }  // namespace ecrm
