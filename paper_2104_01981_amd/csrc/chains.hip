@@ -487,7 +487,7 @@ __global__ __launch_bounds__(kMidWaves * kWave, 4) void mid_chain_kernel(
     }
     const uint32_t D = geo.D, lane = lane_id(), w = uniform(threadIdx.x / kWave);
     const RuleParams rp = rule_params(geo);
-    for (;;) {
+    while (total != 0) {                                     // without such runs nobody draws: 512 tickets are 8 us
         if (threadIdx.x == 0) s_ticket = atomicAdd(&hdr->mid_ticket, 1u);
         __syncthreads();
         uint32_t t = uniform(s_ticket);
