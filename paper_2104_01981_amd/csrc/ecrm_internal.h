@@ -40,9 +40,13 @@ constexpr uint32_t kPieceMaxCount = 1024;     // a chain is cut into at most thi
 // takes ~0.5 ms over 32768 updates, beside the first pass over the pieces, and that pass takes as long as the
 // batch has long rows: with kMidMinRows of them, runs of up to kMidShare updates for each are walked so.  us a
 // call without / with 12 / with 24 of them: 2^24 Zipf updates, 1066 long rows, 4050 / 3829 / 3886; 2^23, 553,
-// 1987 / 1917 / 1965; 2^24 half Zipf, 420, 8097 / 8053 / 8082; 2^22, 287, 1141 / 1169 / 1181.
+// 1987 / 1917 / 1965; 2^22, 287, 1141 / 1169 / 1181.  Where it begins to pay, in one batch size -- 2^22 updates on 2^20 rows,
+// without / with 12, so many rows of 1100 to 3000 updates; the r-th of m rows of 1100 m / r --: 200 1176 / 1227; 1281 / 1343.
+// 300 1203 / 1180; 1316 / 1344.  400 1213 / 1171; 1326 / 1301.  500 1225 / 1159; 1219 / 1165.  1000 1348 / 1133.  Of 256 floats:
+// 200 2135 / 2201; 2325 / 2341.  400 2204 / 2111; 2424 / 2299.  Of 1024, 2^21 updates: 300 3437 / 3232.
 constexpr uint32_t kMidMax = ECRM_MID_RUN;
-// Rows of at most 64 floats leave half of its waves idle (6 M Zipf updates of 64 floats: 1060 without, 1100 with).
+// Rows of at most 64 floats leave half of its waves idle (6 M Zipf updates of 64 floats: 1060 without, 1100 with; 2^22 with
+// 400 rows of 1100 to 3000 updates 808 and 782).
 constexpr uint32_t kMidMinRows = 400, kMidMinNarrowRows = 2048, kMidShare = 12;
 constexpr uint32_t kMidMinBatch = 1u << 21;
 constexpr int kMidWaves = 8;         // waves of the workgroup that walks such a run
