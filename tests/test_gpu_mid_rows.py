@@ -17,10 +17,13 @@ def test_runs_and_pieces_together(D, k, long_rows):
     lens = rng.integers(1025, 1200, long_rows)
     limit = 12 * long_rows
     lens[:6] = [limit, limit + 1, 9000, 4 * limit // 3, 1025, limit - 1]
-    keys = rng.permutation(np.concatenate([np.repeat(rows, lens), rng.integers(0, R, max((1 << 21) + 1 - int(lens.sum()), 1000))])).astype(np.uint64)
+    others = np.setdiff1d(np.arange(R), rows)                        # the lengths are exact
+    rest = rng.choice(others, max((1 << 21) + 1 - int(lens.sum()), 1000))
+    keys = rng.permutation(np.concatenate([np.repeat(rows, lens), rest])).astype(np.uint64)
     n = len(keys)
     assert n > 1 << 21
     counts = np.bincount(keys.astype(np.int64), minlength=R)
+    assert (counts[rows] == lens).all() and counts[others].max() <= 1024
     c = Case(R, D, k, S, max_batch=n, seed=101)
     for call in range(2):
         c.update(keys, grads_for(101, call * n, n, D))
