@@ -1,16 +1,19 @@
 """Stripes that a workgroup's waves share: runs around the 32 updates from which on the waves share a run's columns (eight
-updates to a group of lanes, 32 to a round), beside runs that one wave takes as a whole, rows that end inside a wave's 32 columns,
-and the smallest buckets.  No run is so long that it leaves its bucket (128)."""
+updates to a group of lanes, 32 to a round) and the length from which on one leaves its bucket for heavy_stripes, beside runs
+that one wave takes as a whole, rows that end inside a wave's 32 columns, and the smallest buckets."""
 import numpy as np
 import pytest
 import torch
 
+import bucket_plan as bp
 import synth_inputs as si
 from ecrm_case import Case, grads_for
 
 pytestmark = pytest.mark.gpu
 
-LENS = [[58, 1], [31, 32, 33, 1], [127], [65, 40, 3, 96], [8, 39, 40, 41], [5] * 12, [64, 64], [126, 2, 1, 33]]
+LEAVES = bp.heavy_run(4000)                              # of a batch of this size
+LENS = [[58, 1], [31, 32, 33, 1], [127], [65, 40, 3, 96], [8, 39, 40, 41], [5] * 12, [64, 64], [126, 2, 1, 33], [128, 129],
+        [192, 3, 1, 70], [224, 225], [LEAVES - 1], [LEAVES], [LEAVES, 3 * LEAVES // 4]]
 
 
 @pytest.mark.parametrize("D,k,S", [(4, 4, 5), (36, 12, 13), (128, 4, 5), (132, 4, 5), (260, 12, 13), (1024, 4, 5)])
@@ -22,11 +25,16 @@ def test_shared_stripes(D, k, S, opt, comb, prop):
     for g, lens in enumerate(LENS):
         lens = lens[:k] if len(lens) > k else lens
         for j, m in enumerate(lens):
-            keys += [(g * 331 + 5) * k + j] * m
-    keys = rng.permutation(np.concatenate([keys, rng.integers(0, R, 1500)])).astype(np.uint64)
+            keys += [(g * 211 + 5) * k + j] * m
+    taken = [g * 211 + 5 for g in range(len(LENS))]
+    rest = rng.choice(np.setdiff1d(np.arange(R // k), taken), 1000) * k
+    keys = rng.permutation(np.concatenate([keys, rest])).astype(np.uint64)
+    assert len(keys) < 4096 and bp.heavy_run(len(keys)) == LEAVES           # no sample is taken: nothing is known beforehand
     c = Case(R, D, k, S, max_batch=len(keys), seed=91, optimizer=opt, momentum=0.9, combine=comb, propagation=prop)
     for call in range(2):
         c.update(keys, grads_for(91, call * len(keys), len(keys), D))
+    left = int(c.scratch[:256].cpu().numpy().view(np.uint32)[22])           # stripes that heavy_stripes was left
+    assert left == 2
     c.compare("shared stripes")
 
 
