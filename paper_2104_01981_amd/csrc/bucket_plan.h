@@ -112,7 +112,7 @@ ECRM_HD bool in_place_size(const BucketLimits &l, uint32_t k, uint32_t m)
 struct HotStripe { uint32_t updates, entries; };
 ECRM_HD bool in_place_time(const BucketLimits &l, uint32_t D, uint32_t hot, uint32_t rest, const HotStripe &longest, const HotStripe &s)
 {
-    const uint32_t jobs = hot * ((D + 15u) / 16u), wide = D > 96u ? D : 96u;
+    const uint32_t jobs = hot * ((D + 15u) / 16u), wide = D > 128u ? D : 128u;
     const uint32_t here = (512u * s.entries + s.updates) * (jobs > 288u ? jobs : 288u) / 288u;
     const uint32_t behind = (512u * s.entries + s.updates / 5u) * (jobs > 256u ? jobs : 256u) / 256u;
     const bool is_left = longest.updates > l.hot_in_place || longest.updates >= l.split_stripe;
