@@ -27,10 +27,10 @@ LONG_RUN = 1024          # ECRM_LONG_RUN of include/ecrm.h: longer runs leave th
 # HBM bytes per launch of the apply kernel, from rocprofv3 FETCH_SIZE and WRITE_SIZE scaled by a plain copy of known
 # size (profiles/update_path_<workload>_hbm_traffic.txt).  Reported only while the code of the kernel's sources is
 # what the counters were taken on.
-TRAFFIC_BYTES_PER_LAUNCH = {"hbm_scale": 37958642995, "large_uniform": 77514097152, "large_skewed": 42561777562}
+TRAFFIC_BYTES_PER_LAUNCH = {"hbm_scale": 37958469222, "large_uniform": 77514271232, "large_skewed": 42561405440}
 TRAFFIC_SOURCES = ["paper_2104_01981_amd/csrc/update.hip", "paper_2104_01981_amd/csrc/rows.h",
                    "paper_2104_01981_amd/csrc/ecrm_internal.h"]
-TRAFFIC_SOURCES_SHA256 = "2cbe171c465a0fd1884bd74602a1a11e50be6f7b7f2e544d20a64f53dc8bad33"
+TRAFFIC_SOURCES_SHA256 = "bce7972aebf42fb5b1927d367454d64b60a941ca500028990901c7c7e5618d01"
 
 
 def code_digest(paths):
