@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kHeavyThreads) void read_long_kernel(ReadArgs a)
 }
 
 // The requests whose entries were answered for another one.  Where there was no room for the places of their runs they are
-// looked up once more: 2^18 requests of a context made for batches of 2048 148 us; when such a read was cut into parts of 2048,
+// looked up once more: 2^18 requests of a context made for batches of 2048 138 us; when such a read was cut into parts of 2048,
 // of four launches each, 2367.
 __global__ __launch_bounds__(kReadThreads) void read_shared_kernel(ReadArgs a)
 {

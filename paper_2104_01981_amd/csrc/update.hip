@@ -405,8 +405,9 @@ __device__ __forceinline__ void apply_window(const ApplyArgs &a, uint32_t wkey, 
 
 // The same for rows of at most 64 (P = 2) or 32 (P = 4) floats: a step takes up to P consecutive entries, one to each group of
 // 64 / P lanes, so that one instruction moves P rows; with one row to a wave half of the lanes, or more, had nothing to do, and
-// the instructions, not the memory, set the pace (1.5 M half-Zipf momentum updates, k = 2: 64 floats 533 us, now 458, at
-// 4.4 TB/s; a call of 32 floats 678 us, now 497; 3 M of 16 floats 850, now 580).  All control flow is that of the wave: the
+// the instructions, not the memory, set the pace.  Half-Zipf momentum updates, k = 2, this kernel alone in a trace, and the whole
+// call: 1.5 M of 64 floats 537 us, now 354 to 434 with the placement of the tables, the call 721, now 587; of 32 floats 492, now
+// 258, the call 680, now 410; 3 M of 16 floats 621, now 355, the call 853, now 547.  All control flow is that of the wave: the
 // entries' numbers of updates and stripes differ from group to group, and what a group has no part in is masked; every exchange
 // between groups is executed by all lanes.  Rows are read through per-lane addresses.
 template <int P>
