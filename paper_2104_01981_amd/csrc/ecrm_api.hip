@@ -605,8 +605,8 @@ int ecrm_recovery_read(ecrm_ctx *c, const uint64_t *keys, uint64_t n, float *out
                              c->cus, st);
         return check_launch();
     }
-    // The waiting updates, grouped by entry with the update path's own sort on the list's keys.  How
-    // many there are is known on the device only: the launches are sized by the buffer's capacity.
+    // The waiting updates, grouped by entry with the update path's own sort on the list's keys, or, of a smaller buffer, its
+    // variant of fewer launches.  How many there are is known on the device only: the launches are sized by the buffer's capacity.
     uint32_t *bk = nullptr, *bi = nullptr, *leader = c->s.long_slot;
     const uint64_t *list = (const uint64_t *)c->hb.list[c->buf_cur];
     const uint32_t *waiting = &c->s.hdr->buf_count;

@@ -80,7 +80,7 @@ struct Header {
     uint32_t heavy_ticket; // next of its jobs to be handed out (cleared by the partition)
     uint32_t n_segments;   // segments of runs that heavy_stripes cuts up (cleared by the partition)
     uint32_t n_hot;        // stripes that the sample took for hot (set by the partition)
-    uint32_t n_reads;      // entries with a long waiting run that a read left to read_long_kernel (cleared by read_begin_kernel)
+    uint32_t n_reads;      // entries with a long waiting run that a read left to read_long_kernel (cleared by read_begin_kernel or launch_sort_list)
     uint32_t read_ticket;  // next of its jobs to be handed out (the same)
     uint32_t piece_ticket; // next chain piece to be handed out (cleared by reset)
     uint32_t heavy_run;    // updates from which on a run makes its stripe one for heavy_stripes (set by the partition)
