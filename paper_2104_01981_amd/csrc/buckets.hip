@@ -919,6 +919,7 @@ struct BucketArgs : RowArgs {
     SplitScratch split;          // of stripes whose runs are cut up
     Header *hdr;
     u64 *load_data, *load_parity;
+    uint32_t *rejected;          // null, or where the caller wants to read whether the batch was rejected
     uint32_t n, tile, tiles, buckets, packed;
     uint32_t holding;            // a recovery is in progress: the header follows what hold_tiles did
     BucketLimits lim;
@@ -1487,6 +1488,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
     const bool many = n_hot > kManyHot;                             // long stripes
     const bool full = a.hdr->batch_bad != 0;                        // the recovery buffer could not take its part
     key_bad = __syncthreads_or(key_bad);
+    if (b == 0 && tid == 0 && a.rejected) *a.rejected = key_bad || full ? 1u : 0u;
     if (key_bad || full) {
         if (b == 0 && tid == 0 && key_bad) {
             a.hdr->batch_bad = 1;
@@ -1958,14 +1960,14 @@ void launch_bucket_partition(const BucketScratch &bs, Header *hdr, const Geometr
 
 void launch_bucket_apply(const BucketScratch &bs, Header *hdr, const Geometry &g, float *E, float *A, float *PE, float *PA,
                          unsigned long long *load_data, unsigned long long *load_parity, const uint64_t *keys,
-                         const float *grads, uint32_t n, BatchSource src, bool holding, int cus, hipStream_t st)
+                         uint32_t *rejected, const float *grads, uint32_t n, BatchSource src, bool holding, int cus, hipStream_t st)
 {
     const BucketPlan p = bucket_plan(n);
     BucketArgs a;
     a.E = E; a.A = A; a.PE = PE; a.PA = PA; a.grads = grads; a.geo = g;
     a.keys = keys; a.items = bs.items; a.tmp = bs.tmp; a.dense = bs.dense; a.table = bs.table;
     a.tile_cnt = bs.tile_cnt; a.tile_state = bs.tile_state; a.heavy = bs.heavy; a.split = bs.split; a.hdr = hdr;
-    a.load_data = load_data; a.load_parity = load_parity;
+    a.load_data = load_data; a.load_parity = load_parity; a.rejected = rejected;
     a.n = n; a.tile = p.ipt * kPartThreads; a.tiles = p.tiles; a.buckets = p.buckets;
     a.packed = src == kWaitingUpdates ? 1u : 0u;
     a.holding = holding ? 1u : 0u;
