@@ -264,25 +264,8 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
     }
     // the header of the call: no other workgroup of this launch touches it (a replay reads buf_count only)
     if (tile == 0 && tid == 0) {
-        Header *h = a.hdr;
-        if (a.clear_sticky) {
-            h->err_sticky = 0;
-            h->buf_count = 0;
-            h->free_count = 0;
-            h->bump = 0;
-        }
-        h->batch_bad = 0;
-        h->n_long = 0;
-        h->n_pieces = 0;
-        h->n_long_items = 0;
-        h->n_batch = n;
-        h->n_valid = n;
-        h->n_held = 0;
-        h->n_heavy = 0;
-        h->n_segments = 0;
-        h->heavy_ticket = 0;
-        h->n_hot = n >= kSample * 4u ? s_hot.n_cand : 0u;
-        for (uint32_t c = 0; c < kMidClasses; ++c) h->n_mid[c] = 0;
+        begin_batch(a.hdr, n, a.clear_sticky != 0);
+        a.hdr->n_hot = n >= kSample * 4u ? s_hot.n_cand : 0u;
     }
 }
 
@@ -376,7 +359,10 @@ struct BucketShared {
         struct { uint32_t tab_g[kStripeSlots], tab_c[kStripeSlots]; };     // of an oversized bucket, before it
         ExchangeOf<kBucketWaves> ex[2];                        // of a hot stripe
     };
-    ListShared<kBucketCap> list;
+    union {
+        FewRows few;                                           // before the list is walked
+        ListShared<kBucketCap> list;
+    };
     uint32_t pref[kMaxTiles + 1], start[kMaxTiles], wave[kBucketWaves];
     uint32_t hv[kHeavySlots], hv_n, fill, light, n_light, over;
     uint32_t member[kBucketWaves][64];
@@ -931,7 +917,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
     for (;;) {
         if (oversized) list = oversized_part(args_again(), sh, m, base, walk);
         if (list) {
-            sort_items(sh.item, sh.tmp, list);
+            sort_items(sh.item, sh.tmp, list, !oversized, sh.few);
             if (packed) {
                 const BucketArgs b2 = args_again();
                 for (uint32_t i = tid; i < list; i += kBucketThreads) sh.item[i] = resolved(b2, sh.item[i]);
