@@ -361,6 +361,14 @@ static int run_update(ecrm_ctx *c, const Tables &t, const Scratch &s, const Layo
         const BucketScratch bs = carve_buckets(l, s);
         const bool diff = c->cfg.propagation == ECRM_PROP_DIFFERENCE;
         if (ev) (void)hipEventRecord(ev[0], st);
+        if (n32 <= kDirectBatch && src == kCallerBatch && !rv.active) {        // nothing is held back: no list of what goes where
+            if (ev) (void)hipEventRecord(ev[1], st);
+            if (ev) (void)hipEventRecord(ev[2], st);
+            launch_direct(s.hdr, c->geo, t.E, t.A, diff ? t.PE : nullptr, diff ? t.PA : nullptr, t.load_data,
+                          diff ? t.load_parity : nullptr, keys, rejected, grads, n32, clear_sticky, st);
+            if (ev) (void)hipEventRecord(ev[3], st);
+            return check_launch();
+        }
         launch_bucket_partition(bs, s.hdr, c->geo, rv, keys, n32, src, clear_sticky, st);
         const bool holding = rv.active || src == kWaitingUpdates;
         if (holding) launch_hold_tiles(s.hdr, bs.tile_state, c->geo, rv, keys, grads, n32, src, c->hb, c->buf_cur, st);

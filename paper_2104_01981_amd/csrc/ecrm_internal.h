@@ -251,6 +251,9 @@ void launch_bucket_partition(const BucketScratch &bs, Header *hdr, const Geometr
 void launch_bucket_apply(const BucketScratch &bs, Header *hdr, const Geometry &g, float *E, float *A, float *PE, float *PA,
                          unsigned long long *load_data, unsigned long long *load_parity, const uint64_t *keys,
                          uint32_t *rejected, const float *grads, uint32_t n, BatchSource src, bool holding, int cus, hipStream_t st);
+void launch_direct(Header *hdr, const Geometry &g, float *E, float *A, float *PE, float *PA, unsigned long long *load_data,
+                   unsigned long long *load_parity, const uint64_t *keys, uint32_t *rejected, const float *grads, uint32_t n,
+                   bool clear_sticky, hipStream_t st);
 void launch_recover_range(const Geometry &g, float *E, float *A, float *PE, float *PA, uint32_t server,
                           uint32_t g_lo, uint32_t g_hi, int grid_blocks, hipStream_t st);
 void launch_clear_buffer(const Scratch &s, hipStream_t st);

@@ -1,6 +1,6 @@
 // Stripes from a sorted list of (row, position) pairs in LDS, by a workgroup of kBucketThreads: the walk over a window of the
 // list, the walk of a stripe that is longer than that, sorting, and handing the list out to the waves.  Shared by the kernels of
-// small batches.
+// small batches (buckets.hip, direct.hip).
 #pragma once
 
 #include "long_runs.h"
@@ -825,6 +825,147 @@ __device__ __forceinline__ void begin_batch(Header *h, uint32_t n, bool clear_st
     h->n_segments = 0;
     h->heavy_ticket = 0;
     for (uint32_t c = 0; c < kMidClasses; ++c) h->n_mid[c] = 0;
+}
+
+// 2 G columns of one stripe, [start, end) of a sorted list, by a workgroup: as in long_runs.h, with T updates to a group of G lanes:
+// 256 updates to a round with G = 8, 512 with G = 4.  A run of fewer than kGroupRun updates goes to one group, all of them at once
+// behind the long ones: each took a round by itself.  ex: both halves free; ends with a barrier.
+constexpr uint32_t kGroupRun = 32;
+template <int MODE, bool PARITY, int G>
+__device__ __forceinline__ void stripe_columns(const RowArgs &a, const u64 *items, uint32_t start, uint32_t end, uint32_t cg,
+                                               ExchangeOf<kBucketWaves, G> (&ex)[2])
+{
+    constexpr int T = 8;
+    constexpr uint32_t kGroups = kBucketThreads / G, kRound = kGroups * T;
+    const uint32_t D = a.geo.D, tid = threadIdx.x, lane = lane_id(), w = uniform(tid / kWave);
+    const uint32_t col_lane = lane % G, sub = tid / G, col = (cg * G + col_lane) * 2u;
+    const bool live = col < D;                                      // D is a multiple of 4: both columns or none
+    const RuleParams rp = rule_params(a.geo);
+    const uint32_t g = a.geo.dk.div(uniform(item_row(items[start])));
+    D2 pe = D2{-0.0, -0.0}, pa = D2{-0.0, -0.0};                    // a group's differences; the neutral summand
+    uint32_t buf = 0, runs = 0, own0 = start, len0 = 0, own1 = start, len1 = 0;       // the group's runs: a stripe has 64 at most
+    // the gradients of updates r0 + off .. of the run at pos, zeros past its end
+    auto rows = [&](float2 (&r)[T], uint32_t pos, uint32_t off, uint32_t L) {
+        uint32_t mine[T / G];
+#pragma unroll
+        for (int q = 0; q < T / G; ++q) mine[q] = (uint32_t)items[pos + min(off + q * G + col_lane, L - 1u)];
+#pragma unroll
+        for (int u = 0; u < T; ++u) {
+            const uint32_t i = __shfl(mine[u / G], (int)(lane - col_lane + u % G), kWave);
+            r[u] = float2{0, 0};
+            if (live && off + u < L) r[u] = *(const float2 *)(a.grads + (size_t)i * D + col);
+        }
+    };
+    auto store = [&](uint32_t x, D2 state, D2 acc, const D2 &a64, bool mine) {
+        finish2<MODE>(state, acc, a64, rp);
+        if (!mine) return;
+        float2 *e = (float2 *)(a.E + (size_t)x * D + col);
+        const D2 e64 = widen2(*e);
+        *e = narrow2(D2{e64.x - acc.x, e64.y - acc.y});
+        *(float2 *)(a.A + (size_t)x * D + col) = narrow2(state);
+        pe.x -= acc.x;
+        pe.y -= acc.y;
+        pa.x += state.x - a64.x;
+        pa.y += state.y - a64.y;
+    };
+    for (uint32_t pos = start, run_end; pos < end; pos = run_end) {
+        const uint32_t x = uniform(item_row(items[pos]));
+        run_end = run_of(items, pos, end, x);
+        const uint32_t L = run_end - pos;
+        if (L < kGroupRun) {
+            if (runs == sub) own0 = pos, len0 = L;
+            if (runs == sub + kGroups) own1 = pos, len1 = L;
+            ++runs;
+            continue;
+        }
+        float2 gr[T], nx[T];
+        rows(nx, pos, sub * T, L);
+        D2 a64 = D2{0, 0};
+        if (live) a64 = widen2(*(const float2 *)(a.A + (size_t)x * D + col));
+        D2 state = start2<MODE>(a64), acc = D2{0, 0};
+        for (uint32_t r0 = 0; r0 < L; r0 += kRound) {
+            const uint32_t off = r0 + sub * T, cnt = off < L ? min((uint32_t)T, L - off) : 0u;
+#pragma unroll
+            for (int u = 0; u < T; ++u) gr[u] = nx[u];
+            if (r0 + kRound < L) rows(nx, pos, off + kRound, L);
+            if (Rule<MODE>::combine) {                              // a sum: nothing to exchange before the run's end
+#pragma unroll
+                for (int u = 0; u < T; ++u) {                       // zeros past the end of the run
+                    acc.x += (double)gr[u].x;
+                    acc.y += (double)gr[u].y;
+                }
+                continue;
+            }
+            double ed;
+            const D2 before = heavy_sums<MODE>(gr, cnt, rp, ex[buf], w, ed);
+            __syncthreads();
+            D2 mine = heavy_fold<MODE>(state, ex[buf], w, before, ed);
+#pragma unroll
+            for (int u = 0; u < T; ++u) asm volatile("" : "+v"(gr[u].x), "+v"(gr[u].y));     // widened once more (walk_columns)
+#pragma unroll
+            for (int u = 0; u < T; ++u) {
+                if ((uint32_t)u < cnt) item2<MODE>(mine, acc, gr[u], rp);
+            }
+            buf ^= 1u;                                              // a half is written again only behind the other's barrier
+        }
+        acc = heavy_total(acc, ex[buf], w);
+        buf ^= 1u;
+        if (Rule<MODE>::combine) {
+            state = acc;
+            acc = D2{0, 0};
+        }
+        store(x, state, acc, a64, live && sub == 0);
+    }
+    for (uint32_t half = 0; half < runs; half += kGroups) {         // once or twice
+        const uint32_t pos = half ? own1 : own0, L = half ? len1 : len0, x = item_row(items[pos]);
+        uint32_t most = L;
+#pragma unroll
+        for (int by = G; by < kWave; by <<= 1) most = max(most, __shfl_xor(most, by, kWave));
+        D2 a64 = D2{0, 0};
+        if (live && L) a64 = widen2(*(const float2 *)(a.A + (size_t)x * D + col));
+        D2 state = start2<MODE>(a64), acc = D2{0, 0};
+        for (uint32_t r0 = 0; r0 < most; r0 += T) {
+            float2 gr[T];
+            rows(gr, pos, r0, max(L, 1u));
+#pragma unroll
+            for (int u = 0; u < T; ++u) {
+                if (r0 + u < L) item2<MODE>(state, acc, gr[u], rp);
+            }
+        }
+        store(x, state, acc, a64, live && L);
+    }
+    if (PARITY) {
+        __syncthreads();                                            // ex has been read
+        // over the groups, in their order; the first group's lanes add the sums up
+#pragma unroll
+        for (int by = G; by < kWave; by <<= 1) {
+            pe.x += __shfl_xor(pe.x, by, kWave);
+            pe.y += __shfl_xor(pe.y, by, kWave);
+            pa.x += __shfl_xor(pa.x, by, kWave);
+            pa.y += __shfl_xor(pa.y, by, kWave);
+        }
+        if (lane < (uint32_t)G) {
+            ex[0].sum[w][col_lane][0] = pe.x;
+            ex[0].sum[w][col_lane][1] = pe.y;
+            ex[1].sum[w][col_lane][0] = pa.x;
+            ex[1].sum[w][col_lane][1] = pa.y;
+        }
+        __syncthreads();
+        if (live && sub == 0) {
+            float2 *to = (float2 *)(a.PE + (size_t)g * D + col), *to_state = (float2 *)(a.PA + (size_t)g * D + col);
+            D2 pe64 = widen2(*to), pa64 = widen2(*to_state);
+#pragma unroll
+            for (int v = 0; v < kBucketWaves; ++v) {
+                pe64.x += ex[0].sum[v][col_lane][0];
+                pe64.y += ex[0].sum[v][col_lane][1];
+                pa64.x += ex[1].sum[v][col_lane][0];
+                pa64.y += ex[1].sum[v][col_lane][1];
+            }
+            *to = narrow2(pe64);
+            *to_state = narrow2(pa64);
+        }
+    }
+    __syncthreads();
 }
 
 }  // namespace ecrm

@@ -51,29 +51,30 @@ __device__ __forceinline__ void heavy_rows(float2 (&r)[T], const float *grads, u
     }
 }
 
-// what the waves exchange: sums (or, at the end of a run, steps) of two columns a lane, and the decay over a wave's updates
-template <int WAVES>
+// what the waves exchange: sums (or, at the end of a run, steps) of two columns a lane, and the decay over a wave's updates.  G:
+// lanes of a group.
+template <int WAVES, int G = 8>
 struct ExchangeOf {
-    double sum[WAVES][8][2], dec[WAVES];
+    double sum[WAVES][G][2], dec[WAVES];
 };
 using HeavyExchange = ExchangeOf<kHeavyWaves>;
 // Sums of a round: every wave leaves that of its updates in ex; returned is what lies before the lane's group inside its
 // wave, with its decay.
-template <int MODE, int T, int WAVES>
-__device__ __forceinline__ D2 heavy_sums(const float2 (&gr)[T], uint32_t cnt, const RuleParams &rp, ExchangeOf<WAVES> &ex,
+template <int MODE, int T, int WAVES, int G>
+__device__ __forceinline__ D2 heavy_sums(const float2 (&gr)[T], uint32_t cnt, const RuleParams &rp, ExchangeOf<WAVES, G> &ex,
                                          uint32_t w, double &before_decay)
 {
     constexpr bool kMomentum = MODE == kMomentumSeq;
-    const uint32_t lane = lane_id(), col_lane = lane & 7u;
+    const uint32_t lane = lane_id(), col_lane = lane % G;
     D2 s = D2{-0.0, -0.0};                              // the neutral summand: +0.0 would take a -0.0's sign
     double d = kMomentum ? decay_over(cnt, rp.mu) : 1.0;
 #pragma unroll
     for (int u = 0; u < T; ++u) {
         if ((uint32_t)u < cnt) summary2<MODE>(s, gr[u], rp);
     }
-    // inclusive scan over the wave's eight groups of the maps v -> d * v + s
+    // inclusive scan over the wave's groups of the maps v -> d * v + s
 #pragma unroll
-    for (int by = 8; by < kWave; by <<= 1) {
+    for (int by = G; by < kWave; by <<= 1) {
         const double ox = __shfl_up(s.x, by, kWave), oy = __shfl_up(s.y, by, kWave);
         const double od = kMomentum ? __shfl_up(d, by, kWave) : 1.0;
         if (lane >= (uint32_t)by) {
@@ -82,14 +83,14 @@ __device__ __forceinline__ D2 heavy_sums(const float2 (&gr)[T], uint32_t cnt, co
             if (kMomentum) d = decay(d * od, rp.mu);
         }
     }
-    if (lane >= 56u) {
+    if (lane >= (uint32_t)(kWave - G)) {
         ex.sum[w][col_lane][0] = s.x;
         ex.sum[w][col_lane][1] = s.y;
         if (col_lane == 0) ex.dec[w] = d;
     }
-    D2 before = D2{__shfl_up(s.x, 8, kWave), __shfl_up(s.y, 8, kWave)};
-    before_decay = kMomentum ? __shfl_up(d, 8, kWave) : 1.0;
-    if (lane < 8u) {
+    D2 before = D2{__shfl_up(s.x, G, kWave), __shfl_up(s.y, G, kWave)};
+    before_decay = kMomentum ? __shfl_up(d, G, kWave) : 1.0;
+    if (lane < (uint32_t)G) {
         before = D2{-0.0, -0.0};
         before_decay = 1.0;
     }
@@ -97,11 +98,11 @@ __device__ __forceinline__ D2 heavy_sums(const float2 (&gr)[T], uint32_t cnt, co
 }
 
 // behind a barrier after heavy_sums: takes `state` from the round's start to its end, returns it as the lane's group finds it
-template <int MODE, int WAVES>
-__device__ __forceinline__ D2 heavy_fold(D2 &state, const ExchangeOf<WAVES> &ex, uint32_t w, const D2 &before, double before_decay)
+template <int MODE, int WAVES, int G>
+__device__ __forceinline__ D2 heavy_fold(D2 &state, const ExchangeOf<WAVES, G> &ex, uint32_t w, const D2 &before, double before_decay)
 {
     constexpr bool kMomentum = MODE == kMomentumSeq;
-    const uint32_t col_lane = lane_id() & 7u;
+    const uint32_t col_lane = lane_id() % G;
     D2 mine = state;
 #pragma unroll
     for (int v = 0; v < WAVES; ++v) {
@@ -117,16 +118,16 @@ __device__ __forceinline__ D2 heavy_fold(D2 &state, const ExchangeOf<WAVES> &ex,
 }
 
 // sum of the groups' steps over the workgroup, for every lane; one barrier, after ex was written
-template <int WAVES>
-__device__ __forceinline__ D2 heavy_total(D2 acc, ExchangeOf<WAVES> &ex, uint32_t w)
+template <int WAVES, int G>
+__device__ __forceinline__ D2 heavy_total(D2 acc, ExchangeOf<WAVES, G> &ex, uint32_t w)
 {
-    const uint32_t lane = lane_id(), col_lane = lane & 7u;
+    const uint32_t lane = lane_id(), col_lane = lane % G;
 #pragma unroll
-    for (int by = 8; by < kWave; by <<= 1) {
+    for (int by = G; by < kWave; by <<= 1) {
         acc.x += __shfl_xor(acc.x, by, kWave);
         acc.y += __shfl_xor(acc.y, by, kWave);
     }
-    if (lane < 8u) {
+    if (lane < (uint32_t)G) {
         ex.sum[w][col_lane][0] = acc.x;
         ex.sum[w][col_lane][1] = acc.y;
     }

@@ -16,6 +16,8 @@ using namespace ecrm;
 extern "C" {
 uint32_t plan_buckets(uint32_t n) { return bucket_plan(n).buckets; }
 uint32_t plan_heavy_run(uint32_t n) { return heavy_run(n); }
+uint32_t plan_direct_batch() { return kDirectBatch; }
+uint32_t plan_direct_long() { return kDirectLong; }
 uint32_t plan_bucket_cap() { return kBucketCap; }
 uint32_t plan_heavy_stripe(uint32_t k) { return heavy_stripe(k); }
 uint32_t plan_split_stripe(uint32_t n, uint32_t D) { return split_stripe(n, D); }
@@ -65,6 +67,14 @@ def heavy_run(n):
 
 def bucket_cap():
     return int(lib().plan_bucket_cap())
+
+
+def direct_batch():
+    return int(lib().plan_direct_batch())
+
+
+def direct_long():
+    return int(lib().plan_direct_long())
 
 
 def heavy_stripe(k):
