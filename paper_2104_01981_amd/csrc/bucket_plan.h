@@ -142,7 +142,7 @@ static_assert(kBucketMaxBatch <= 4u * kPartThreads * kMaxTiles, "the plan's larg
 
 // Batches of up to kDirectBatch updates take one launch, in which every workgroup reads all of the keys (direct.hip).  us a call
 // through the three launches of the buckets / so, D = 128, k = 4: 512 uniform updates 15.3 / 9.5, 2048 16.2 / 10.4, 3000
-// 18.1 / 12.8; Zipf, 2048 on 2^16 rows 22.9 / 17.2, on 1024 rows 28.6 / 18.0; 2048 on one row 40.4 / 32.7, on four 51.2 / 41.6, on 64
+// 18.1 / 12.8; Zipf, 2048 on 2^16 rows 22.9 / 17.2, on 1024 rows 28.6 / 15.6; 2048 on one row 40.4 / 31, on four 51.2 / 38.3, on 64
 // 20.5 / 14.2; 2048 half Zipf of 256 floats, k = 10, 28.3 / 21.5.  4096 would gain as well (20.6 / 16.2), but not 4096 on four rows
 // (51 / 145), and what the buckets hand on is tested with batches of 3800.  A stripe of kDirectLong updates or more is left to
 // the kDirectWorkers workgroups that take such stripes by their columns: with 128, and 64 workgroups, 2048 on 64 rows took 59 us; with
