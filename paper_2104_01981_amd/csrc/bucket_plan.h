@@ -25,6 +25,8 @@ constexpr int kBucketThreads = 256;
 constexpr int kPartThreads = 512;            // of the partition: 8 waves, 1, 2 or 4 updates per thread
 constexpr uint32_t kMaxBuckets = 4096;
 constexpr uint32_t kHotBuckets = 256;        // more, for the entries of hot stripes
+// Of the workgroups of as many the first look after a hot stripe each, the others work off their columns.
+constexpr uint32_t kHotMax = 64, kHotWorkers = kHotBuckets - kHotMax;
 constexpr uint32_t kMaxTiles = 256;          // one thread per tile when a bucket is collected
 // Items of a bucket that are sorted in LDS: what leaves room for the four workgroups of a compute unit that the registers
 // allow.  2^19 updates on 2^13 rows (k = 10) take 395 us with 1024, 230 with 1536 and 289 with 2048; 2^16 Zipf 87, 88, 109.
@@ -129,6 +131,18 @@ ECRM_HD uint32_t bucket_count(uint32_t n)
 {
     const uint32_t fine = n / 8u < 1024u ? n / 8u : 1024u, most = n / 64u > fine ? n / 64u : fine;
     return most < 1u ? 1u : most > kMaxBuckets ? kMaxBuckets : most;
+}
+// Buckets of a plan that are filled where `hot` stripes may be worked off beside them: as many as are resident at once beside these
+// stripes' workgroups, which keep their places for 20 to 35 us.  The ones behind would begin when the first of the others end, and
+// the call would wait for them.  The rest of the plan's buckets stay empty, which costs nothing.  Of larger plans many begin
+// late anyway.  Not during a recovery, whose decoder takes places of its own (20 batches of 65 536 half Zipf 3383 us, with fewer
+// buckets 3407).  us a call, all buckets filled / so: 65 536 Zipf on 2^16 rows 79.2 / 72.1, half Zipf on 2^18 86.3 / 83.9, of 256
+// floats 129.8 / 126.4, of 64 floats 77.4 / 73.3; 12 000 Zipf on 2^14 43.3 / 40.9; 26 624 half Zipf on 2^20 50.6 / 49.1.
+constexpr uint32_t kResidentBuckets = 1024;
+ECRM_HD uint32_t buckets_beside(uint32_t buckets, uint32_t hot, uint32_t D)
+{
+    const uint32_t jobs = hot * ((D + 15u) / 16u), left = kResidentBuckets - (jobs < kHotWorkers ? jobs : kHotWorkers);
+    return buckets <= kResidentBuckets && buckets > left ? left : buckets;
 }
 ECRM_HD BucketPlan bucket_plan(uint32_t n)
 {

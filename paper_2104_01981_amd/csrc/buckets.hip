@@ -55,7 +55,7 @@ __device__ __forceinline__ bool takes_part(const PartitionArgs &a, uint64_t k64,
 // to have kHotRun updates or more.  Their entries get buckets of their own behind the others, so that neither the sorting
 // of a bucket nor the walk of a workgroup sees a hot run; a stripe that the sample misses is found in its bucket.  The
 // choice depends on nothing but the sample: every workgroup makes the same one.
-constexpr uint32_t kSampleSlots = 2048, kHotCand = 256, kHotMax = 64, kHotSlots = 256;
+constexpr uint32_t kSampleSlots = 2048, kHotCand = 256, kHotSlots = 256;
 
 struct SampleShared {
     uint32_t g[kSampleSlots], c[kSampleSlots];                     // stripe; hits (and, if asked for, a bit << 16 for each of its first 16 entries)
@@ -171,6 +171,8 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
     }
     // a replay's buckets are those of what is waiting, not of the buffer that holds it: 4096 workgroups for 20 000 updates
     const uint32_t ordinary = a.packed ? bucket_count(n) : a.buckets;
+    // ... and some of the plan's stay empty where hot stripes are worked off beside them
+    const uint32_t used = a.packed || a.rv.active ? ordinary : buckets_beside(ordinary, n_hot, a.D);
     const uint32_t B = ordinary + kHotBuckets;                            // buckets in the table; the last are the hot entries'
     for (uint32_t i = tid; i < B; i += kPartThreads) *(ulonglong2 *)s_cnt[i] = ulonglong2{0, 0};
     for (uint32_t i = tid; i < 2 * S; i += kPartThreads) s_srv[i] = 0;
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
             if (in[r]) {
                 const uint32_t j = x - g * a.dk.d;
                 row[r] = x;
-                dig[r] = bucket_of(g, ordinary);
+                dig[r] = bucket_of(g, used);
                 if (n_hot) {
                     for (uint32_t s = scramble32(g) & (kHotSlots - 1u); s_hot.g[s] != kNoKey; s = (s + 1u) & (kHotSlots - 1u)) {
                         if (s_hot.g[s] == g) {
@@ -779,7 +781,7 @@ __device__ __forceinline__ bool hot_block(const BucketArgs &a, BucketShared &sh,
         bucket_excl_scan(s.len, sh.wave, m);
         return m < least;
     }
-    constexpr uint32_t kWorkers = kHotBuckets - kHotMax;
+    constexpr uint32_t kWorkers = kHotWorkers;
     const uint32_t worker = blockIdx.x - kHotMax;
     // Left to heavy_stripes: the entries of the longest are described to it, the others copied, in arrival order, by all of
     // these workgroups alike (by those of the stripe's first columns, 24 of the 192 did all of it with four entries of 512

@@ -15,6 +15,7 @@ SOURCE = """
 using namespace ecrm;
 extern "C" {
 uint32_t plan_buckets(uint32_t n) { return bucket_plan(n).buckets; }
+uint32_t plan_buckets_beside(uint32_t buckets, uint32_t hot, uint32_t D) { return buckets_beside(buckets, hot, D); }
 uint32_t plan_heavy_run(uint32_t n) { return heavy_run(n); }
 uint32_t plan_direct_batch() { return kDirectBatch; }
 uint32_t plan_direct_long() { return kDirectLong; }
@@ -59,6 +60,10 @@ def lib():
 
 def buckets(n):
     return int(lib().plan_buckets(C.c_uint32(n)))
+
+
+def buckets_beside(n, hot, D):
+    return int(lib().plan_buckets_beside(C.c_uint32(buckets(n)), C.c_uint32(hot), C.c_uint32(D)))
 
 
 def heavy_run(n):

@@ -78,3 +78,14 @@ def test_what_the_sample_says_of_a_stripe():
                 assert seen <= entries(hits, seen, k) <= k
     root = lambda v: int(bp.lib().plan_square_root(u(v)))
     assert all(root(v) ** 2 <= v < (root(v) + 1) ** 2 for v in list(range(2000)) + [1 << 21, (1 << 24) - 1])
+
+
+@pytest.mark.parametrize("n", [4096, 8191, 8192, 65536, 65600, 1 << 19])
+@pytest.mark.parametrize("D", [4, 16, 20, 128, 1024])
+def test_buckets_beside_hot_stripes(n, D):
+    """Without hot stripes all of a plan's buckets are filled; with them those that are resident beside the stripes' workgroups, of
+    which there are 192 at most; a plan that leaves them room anyway, or has more buckets than are resident, stays as it is."""
+    assert bp.buckets_beside(n, 0, D) == bp.buckets(n)
+    for hot in (1, 8, 64):
+        beside = 1024 - min(hot * -(-D // 16), 192)
+        assert bp.buckets_beside(n, hot, D) == (bp.buckets(n) if bp.buckets(n) > 1024 else min(bp.buckets(n), beside))
