@@ -77,7 +77,7 @@ struct Walk {
     {
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            pe[i] = pa[i] = D2{0, 0};
+            pe[i] = pa[i] = D2{-0.0, -0.0};            // the neutral summand
             e[i] = a[i] = float2{0, 0};
         }
         clear_chain();
@@ -130,15 +130,22 @@ __device__ __forceinline__ uint32_t issue_step(StepLoads<NC, U> &l, const RowArg
     return cnt;
 }
 
-// The updates in lanes [first, end) of a window, in order: whole stripes.
-template <int NC, int MODE, bool PARITY, int Q, int U>
+// What a wave's part of a list that is cut at entries has of stripes that are not all its own.
+struct Shared {
+    bool before, goes_on;      // the first entries belong to a stripe that another wave opens; another wave goes on with the last one
+    double *part;              // for the differences of those first entries
+};
+
+// The updates in lanes [first, end) of a window, in order: whole stripes; or (SPLIT) whole entries, where the differences of a
+// stripe that another wave opens are left in from.part, and one that another wave goes on with is not stored: if this wave has
+// opened it, w has its parity rows so far.
+template <int NC, int MODE, bool PARITY, int Q, int U, bool SPLIT>
 __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uint32_t widx, u64 rowheads, u64 stripeheads,
-                                            uint32_t first, uint32_t end, uint32_t cb)
+                                            uint32_t first, uint32_t end, uint32_t cb, Walk<NC> &w, Shared from)
 {
     const uint32_t D = a.geo.D;
     const RuleParams rp = rule_params(a.geo);
     const uint32_t col0 = cb * NC * 128u;
-    Walk<NC> w;
     w.begin();
     StepLoads<NC, U> l[Q];
     uint32_t at[Q], cnt[Q], next = first;          // lane a step in flight starts in, and how many updates it takes
@@ -227,7 +234,15 @@ __device__ __forceinline__ void walk_window(const RowArgs &a, uint32_t wkey, uin
                         w.pa[i].y += w.G[i].y - a64.y;
                     }
                 }
-                if (PARITY && (last || (bool)((stripeheads >> t1) & 1ull))) {
+                const bool closed = last || (bool)((stripeheads >> t1) & 1ull);
+                if (SPLIT && PARITY && closed && from.before) {
+#pragma unroll
+                    for (int i = 0; i < NC; ++i) {
+                        *(double2 *)(from.part + i * 128u + 2u * lane_id()) = double2{w.pe[i].x, w.pe[i].y};
+                        *(double2 *)(from.part + (NC + i) * 128u + 2u * lane_id()) = double2{w.pa[i].x, w.pa[i].y};
+                    }
+                    from.before = false;
+                } else if (PARITY && closed && !(SPLIT && last && from.goes_on)) {
                     const uint32_t g = a.geo.dk.div(x);
                     const rsrc_t perow = row_f32(a.PE, g, D, col0), parow = row_f32(a.PA, g, D, col0);
 #pragma unroll
@@ -700,10 +715,131 @@ struct ListShared {
     // stripes for other workgroups, and those that the whole workgroup walks: start | end << 16
     uint32_t heavy[CAP / (kWave - kBucketChunk)], longs[CAP / (kWave - kBucketChunk)];
     uint32_t n_heavy, n_long, chunk;
+    uint32_t handed[kBucketWaves];           // of a wave's part of a list that is cut at entries (kNothing, ...)
     uint32_t srv[2 * kBucketMaxServers];
 };
 
-// Applies every stripe of a sorted list of m items (m <= CAP).  Chunks of a few positions are handed to the waves as
+// Cuts a list of m items, at most kSplitWords * 64, into a part for each wave, at entries, with equally many steps of up to U updates
+// of an entry to a part.  false: a part does not fit a window -- or, where a stripe may be too long for a window, has a run that the
+// workgroup had better share.  The same for every wave.
+constexpr uint32_t kSplitWords = 3, kSplitLeast = 16, kSplitStripes = 4 * kBucketWaves;
+template <uint32_t U>
+__device__ __forceinline__ bool split_list(const u64 *items, uint32_t m, uint32_t (&bound)[kBucketWaves + 1])
+{
+    const uint32_t lane = lane_id();
+    u64 heads[kSplitWords];
+    uint32_t before[kSplitWords], begin = 0, all = 0;        // begin: of the entry that goes on into the word
+#pragma unroll
+    for (uint32_t j = 0; j < kSplitWords; ++j) {
+        heads[j] = 0;
+        before[j] = all;
+        if (j * kWave >= m) continue;
+        const uint32_t p = j * kWave + lane, q = min(p, m - 1u);
+        heads[j] = __ballot(p < m && (p == 0 || item_row(items[q]) != item_row(items[max(q, 1u) - 1u])));
+        const u64 mine = heads[j] & bits_below(lane + 1u);
+        const uint32_t from = mine ? j * kWave + 63u - (uint32_t)__builtin_clzll(mine) : begin;
+        const u64 steps = __ballot(p < m && (p - from) % U == 0);
+        before[j] += (uint32_t)__popcll(steps & bits_below(lane));
+        all += (uint32_t)__popcll(steps);
+        if (heads[j]) begin = j * kWave + 63u - (uint32_t)__builtin_clzll(heads[j]);
+    }
+    const uint32_t most = m <= (uint32_t)kWave ? kWave - 1u : kTogether;
+    bound[0] = 0;
+    bool fits = true;
+#pragma unroll
+    for (uint32_t v = 1; v <= (uint32_t)kBucketWaves; ++v) {
+        uint32_t at = m;
+#pragma unroll
+        for (int j = kSplitWords - 1; j >= 0 && v < (uint32_t)kBucketWaves; --j) {
+            const u64 reached = heads[j] & __ballot(before[j] * kBucketWaves >= v * all);
+            if (reached) at = j * kWave + lowest_bit(reached);
+        }
+        bound[v] = at;
+        fits = fits && at - bound[v - 1u] <= most;
+    }
+    return fits;
+}
+
+// Which lists that is tried on: of few stripes, more than a wave's and fewer than kSplitStripes.
+__device__ __forceinline__ bool few_stripes(const u64 *items, uint32_t m, const Divider &dk)
+{
+    if (m <= kSplitLeast || m > kSplitWords * kWave) return false;
+    uint32_t stripes = 0;
+    for (uint32_t p0 = 0; p0 < m; p0 += kWave) {
+        const uint32_t p = p0 + lane_id(), q = min(p, m - 1u);
+        stripes += (uint32_t)__popcll(__ballot(p < m && (p == 0 || dk.div(item_row(items[q])) != dk.div(item_row(items[max(q, 1u) - 1u])))));
+    }
+    return stripes < kSplitStripes;
+}
+
+// Applies a list of few stripes in parts of equal length, a wave to each, if it can be cut into such; false: nothing has been done.
+// Where a stripe goes from one part to the next its parity rows are put together afterwards by the wave that has opened it.
+// s_part: 6 * NC * 128 doubles.  A stripe a wave, 64 updates of four stripes kept the waves busy from 1.5 to 12 us: 65 536
+// uniform updates on 2^14 rows 40.5 us a call, so 36.5, of 256 floats 66.4, now 59.1; on 1024 rows 46.8, 46.1.  Lists of many
+// stripes, whose waves come out even by themselves, would lose (8192 half Zipf on 2^16 rows 34.9, all lists cut 36.3), and what the
+// kernel takes for it costs the others up to 1 % (65 536 Zipf on 2^16 rows 72.2, 73.0; 12 000 on 2^14 40.9, 41.6).
+// What a part begins with: a stripe of its own, the end of an earlier part's, or one that takes all of it.
+enum { kNothing, kSome, kAll, kEmpty };
+template <int NC, int MODE, bool PARITY, int Q, int U>
+__device__ __forceinline__ bool apply_split(const RowArgs &a, const u64 *items, uint32_t m, uint32_t *handed, double *s_part)
+{
+    const uint32_t lane = lane_id(), w = uniform(threadIdx.x / kWave);
+    const Divider dk = a.geo.dk;
+    if (!few_stripes(items, m, dk)) return false;
+    uint32_t bound[kBucketWaves + 1];
+    if (!split_list<U>(items, m, bound)) return false;
+    uint32_t p0 = bound[0], out = bound[1];
+#pragma unroll
+    for (uint32_t v = 1; v < (uint32_t)kBucketWaves; ++v)
+        if (w == v) p0 = bound[v], out = bound[v + 1u];
+    const uint32_t end = out - p0;
+    const u64 it = p0 + lane < m ? items[p0 + lane] : ~0ull;
+    const uint32_t wkey = item_row(it), widx = (uint32_t)it;
+    uint32_t leftk = __shfl_up(wkey, 1, kWave);
+    if (lane == 0) leftk = p0 ? item_row(items[p0 - 1]) : kNoKey;
+    const bool valid = wkey != kNoKey;
+    const u64 rowheads = __ballot(!valid || leftk == kNoKey || leftk != wkey);
+    const u64 stripeheads = __ballot(valid && (leftk == kNoKey || dk.div(leftk) != dk.div(wkey)));
+    const u64 opened = stripeheads & bits_below(end);
+    const bool before = end && !(stripeheads & 1ull), goes_on = out < m && !((stripeheads >> end) & 1ull);
+    if (lane == 0) handed[w] = end == 0 ? kEmpty : !before ? kNothing : opened ? kSome : kAll;
+    for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
+        Walk<NC> walk;
+        if (end)                                             // the first wave begins with a stripe
+            walk_window<NC, MODE, PARITY, Q, U, true>(a, wkey, widx, rowheads, stripeheads, 0, end, cb, walk,
+                                                      Shared{before, goes_on, s_part + (w - 1u) * 2u * NC * 128u});
+        __syncthreads();
+        if (PARITY && goes_on && opened) {
+            for (uint32_t v = w + 1u; v < (uint32_t)kBucketWaves; ++v) {
+                const uint32_t what = uniform(handed[v]);
+                if (what == kEmpty) continue;
+                if (what == kNothing) break;
+                const double *from = s_part + (v - 1u) * 2u * NC * 128u;
+#pragma unroll
+                for (int i = 0; i < NC; ++i) {
+                    const double2 pe = *(const double2 *)(from + i * 128u + 2u * lane), pa = *(const double2 *)(from + (NC + i) * 128u + 2u * lane);
+                    walk.pe[i].x += pe.x;
+                    walk.pe[i].y += pe.y;
+                    walk.pa[i].x += pa.x;
+                    walk.pa[i].y += pa.y;
+                }
+                if (what == kSome) break;
+            }
+            const uint32_t g = dk.div(from_lane(wkey, end - 1u)), col0 = cb * NC * 128u;
+            const rsrc_t perow = row_f32(a.PE, g, a.geo.D, col0), parow = row_f32(a.PA, g, a.geo.D, col0);
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+                st2(perow, i, narrow2(walk.pe[i]));
+                st2(parow, i, narrow2(walk.pa[i]));
+            }
+        }
+        if (cb + 1u < a.geo.ncb) __syncthreads();            // the parts have been read
+    }
+    return true;
+}
+
+// Applies every stripe of a sorted list of m items (m <= CAP).  A list of few stripes is cut at entries (apply_split).  Of others
+// chunks of a few positions are handed to the waves as
 // they come free; a wave owns the stripes that open in its chunk.  A stripe that does not end inside the wave's
 // 64-position window
 //   - is only listed in sh.heavy if it has a run of heavy_run updates and that makes up more than half of it, or it has
@@ -722,6 +858,7 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
         sh.chunk = kBucketWaves;
     }
     __syncthreads();
+    if (RUNS && apply_split<NC, MODE, PARITY, kQ, kU>(a, items, m, sh.handed, s_part)) return;
     // a chunk for each wave of a short list
     const uint32_t CH = min(kBucketChunk, max(1u, (m + kBucketWaves - 1u) / kBucketWaves));
     for (uint32_t c = uniform(threadIdx.x / kWave); c * CH < m;) {
@@ -771,8 +908,10 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
             }
         }
         if (first < end)
-            for (uint32_t cb = 0; cb < a.geo.ncb; ++cb)
-                walk_window<NC, MODE, PARITY, kQ, kU>(a, wkey, widx, rowheads, stripeheads, first, end, cb);
+            for (uint32_t cb = 0; cb < a.geo.ncb; ++cb) {
+                Walk<NC> walk;
+                walk_window<NC, MODE, PARITY, kQ, kU, false>(a, wkey, widx, rowheads, stripeheads, first, end, cb, walk, Shared{});
+            }
     }
     __syncthreads();
     const uint32_t n_long = uniform(sh.n_long);

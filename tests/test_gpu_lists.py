@@ -1,7 +1,9 @@
 """A bucket's list in LDS around the lengths where its sorting changes: 64 items that a wave counts, 128 that the workgroup counts,
 512 that are looked up in one go, the lists of 512 that are merged, and the longest that LDS takes; and around the 64 rows up to
 which a list is sorted by counting.  Entries get several updates each, so that a place that is off by one shows in their arrival
-order."""
+order.  And lists of few stripes, which are cut into a part for each wave at entries: around the 16 items from which on and the 192
+up to which they are, the 16 stripes from which on they are not, runs that fill a step, a part or a window, and stripes that go on
+over two to four parts."""
 import numpy as np
 import pytest
 
@@ -27,3 +29,38 @@ def test_list_lengths(m, n_rows):
     for call in range(2):
         c.update(keys, grads_for(61, call * n, n, D))
     c.compare(f"list of {m}")
+
+
+def _few_stripes(k):
+    """Lists as runs of (stripe, entry): lengths."""
+    rng = np.random.default_rng(k)
+    lists = [[[m]] for m in (16, 17, 31, 33, 64)]                                       # one entry
+    lists += [[[m // k + (j < m % k) for j in range(k)]] for m in (16, 17, 40, 64, 65, 100, 128, 191, 192, 193)]      # one stripe
+    lists += [[[32] * min(k, 4), [1]], [[33] + [1] * (k - 1), [32], [31]], [[1], [62], [1]], [[4] * k] * 4, [[5] * k] * 3, [[1], [30], [30], [30]]]
+    for stripes in (2, 3, 4, 5, 14, 15, 16, 17):
+        for top in (2, 5, 9, 24):
+            runs = [[int(v) for v in rng.integers(1, top, rng.integers(1, k + 1))] for _ in range(stripes)]
+            lists.append(runs)
+    return [r for r in lists if sum(map(sum, r)) <= 200]
+
+
+@pytest.mark.parametrize("opt,comb,prop", [(0, 0, 0), (1, 0, 0), (0, 1, 0), (1, 1, 0), (0, 0, 2)])
+@pytest.mark.parametrize("D,k", [(12, 4), (128, 5), (132, 4), (516, 3)])
+def test_lists_of_few_stripes(D, k, opt, comb, prop):
+    n, S, stripes = 8000, 7, 1 << 16
+    g = np.arange(stripes, dtype=np.uint32)
+    bucket = bp.bucket_of(g, n)
+    rng = np.random.default_rng(D)
+    keys, lists = [], _few_stripes(k)
+    for i, runs in enumerate(lists):
+        for s, entries in zip(np.sort(rng.choice(g[bucket == 7 + i], len(runs), replace=False)), runs):
+            for j, m in zip(np.sort(rng.choice(k, len(entries), replace=False)), entries):
+                keys.append(np.full(m, s * k + j))
+    keys = np.concatenate(keys)
+    others = g[(bucket < 7) | (bucket >= 7 + len(lists))]
+    keys = np.concatenate([keys, rng.choice(others, n - len(keys)) * k + rng.integers(0, k, n - len(keys))])
+    keys = next(p for p in (rng.permutation(keys).astype(np.uint64) for _ in range(99)) if not len(bp.hot_stripes(p, k)))
+    c = Case(k * stripes, D, k, S, max_batch=n, seed=62, optimizer=opt, momentum=0.9, combine=comb, propagation=prop)
+    for call in range(2):
+        c.update(keys, grads_for(62, call * n, n, D))
+    c.compare(f"few stripes {(D, k, opt, comb, prop)}")
