@@ -13,8 +13,8 @@
 //                     split over the columns; of very long ones the runs are cut up as well.
 //
 // The results are those of the general path: fp64 chains in arrival order, every touched element rounded once.
-// Measured against the general path (us a call, D = 128): 2048 updates 54 -> 17; 26 624 half Zipf 173 -> 54 (49 to 58 from one
-// draw of the keys to the next); 65 536 uniform on 2^14 rows 60 -> 44; 300 007 Zipf, combined rule 325 -> 187.
+// Measured against the general path (us a call, D = 128): 26 624 half Zipf 173 -> 49 (to 57 from one
+// draw of the keys to the next); 65 536 uniform on 2^14 rows 60 -> 38; 300 007 Zipf, combined rule 325 -> 173.
 #include <type_traits>
 
 #include "lists.h"

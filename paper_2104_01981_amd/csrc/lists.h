@@ -838,10 +838,9 @@ __device__ __forceinline__ bool apply_split(const RowArgs &a, const u64 *items, 
     return true;
 }
 
-// Applies every stripe of a sorted list of m items (m <= CAP).  A list of few stripes is cut at entries (apply_split).  Of others
-// chunks of a few positions are handed to the waves as
-// they come free; a wave owns the stripes that open in its chunk.  A stripe that does not end inside the wave's
-// 64-position window
+// Applies every stripe of a sorted list of m items (m <= CAP).  A list of few stripes is cut at entries (apply_split;
+// RUNS).  Of others chunks of a few positions are handed to the waves as they come free; a wave owns the stripes that open in its
+// chunk.  A stripe that does not end inside the wave's 64-position window
 //   - is only listed in sh.heavy if it has a run of heavy_run updates and that makes up more than half of it, or it has
 //     shared_stripe updates (RUNS; otherwise: if it has shared_stripe updates);
 //   - is walked by the whole workgroup afterwards otherwise (s_part: room for walk_long_stripe).
