@@ -833,7 +833,7 @@ __device__ __forceinline__ bool apply_split(const RowArgs &a, const u64 *items, 
                 st2(parow, i, narrow2(walk.pa[i]));
             }
         }
-        if (cb + 1u < a.geo.ncb) __syncthreads();            // the parts have been read
+        __syncthreads();                                     // the parts have been read: the caller may have other uses for them
     }
     return true;
 }

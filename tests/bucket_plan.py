@@ -41,6 +41,7 @@ uint32_t plan_sample(uint32_t n, uint32_t *at)
     return 1u << sample_bits(n);
 }
 void plan_mix(uint32_t *g, uint32_t m) { for (uint32_t i = 0; i < m; ++i) g[i] = mix32(g[i]); }
+void plan_scramble(uint32_t *g, uint32_t m) { for (uint32_t i = 0; i < m; ++i) g[i] = scramble32(g[i]); }
 }
 """
 _lib = None
@@ -98,6 +99,31 @@ def mix(stripes):
     g = np.ascontiguousarray(stripes, np.uint32).copy()
     lib().plan_mix(g.ctypes.data_as(C.POINTER(C.c_uint32)), C.c_uint32(len(g)))
     return g
+
+
+def scramble(stripes):
+    g = np.ascontiguousarray(stripes, np.uint32).copy()
+    lib().plan_scramble(g.ctypes.data_as(C.POINTER(C.c_uint32)), C.c_uint32(len(g)))
+    return g
+
+
+def oversized_parts(stripes, updates, k):
+    """A bucket of more items than LDS takes, as bucket_apply works it off: one list after the other, each as the numbers of its
+    stripes of fewer than heavy_stripe(k) updates.  For buckets of few stripes, which overflow no table."""
+    bits, updates, lists = scramble(stripes), np.asarray(updates), []
+    assert len(stripes) < 640 and updates.sum() > bucket_cap()
+
+    def walk(part, depth):
+        mine = np.nonzero(bits & np.uint32((1 << depth) - 1) == part)[0]
+        light = mine[updates[mine] < heavy_stripe(k)]
+        if updates[light].sum() > bucket_cap() or len(mine) - len(light) > 16:
+            walk(part, depth + 1)
+            walk(part | 1 << depth, depth + 1)
+        else:
+            lists.append(light)
+
+    walk(0, 0)
+    return lists
 
 
 def bucket_of(stripes, n):

@@ -64,3 +64,30 @@ def test_lists_of_few_stripes(D, k, opt, comb, prop):
     for call in range(2):
         c.update(keys, grads_for(62, call * n, n, D))
     c.compare(f"few stripes {(D, k, opt, comb, prop)}")
+
+
+@pytest.mark.parametrize("opt,comb", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("D,k", [(12, 4), (128, 4), (260, 4), (128, 10)])
+def test_a_short_list_before_another_one_of_its_bucket(D, k, opt, comb):
+    """Buckets of more items than LDS takes, which are worked off in parts: a list that is cut at entries comes first, and what it
+    leaves in LDS has to be there until all waves are done with it, though the workgroup goes on to the next list."""
+    n, stripes, shape = 40000, 1 << 16, [15] * 4 + [200] * 8
+    g = np.arange(stripes, dtype=np.uint32)
+    bucket, low = bp.bucket_of(g, n), bp.scramble(g) & 3
+    rng = np.random.default_rng(D + k)
+    keys = []
+    for b in range(7, 27):
+        mine = g[bucket == b]
+        chosen = np.concatenate([mine[low[bucket == b] == v][:m] for v, m in ((0, 4), (1, 4), (3, 4))])
+        assert [len(l) for l in bp.oversized_parts(chosen, shape, k)] == [4, 4, 4]
+        keys.append(np.repeat(chosen, shape) * k + rng.integers(0, k, sum(shape)))
+    keys = np.concatenate(keys)
+    others = g[(bucket < 7) | (bucket >= 27)]
+    at = rng.permutation(np.setdiff1d(np.arange(n), bp.sample_positions(n)))[:len(keys)]        # none of them is seen to be hot
+    batch = rng.choice(others, n) * k + rng.integers(0, k, n)
+    batch[at] = keys
+    assert not len(bp.hot_stripes(batch, k))
+    c = Case(k * stripes, D, k, 11, max_batch=n, seed=63, optimizer=opt, momentum=0.9, combine=comb)
+    for call in range(2):
+        c.update(batch.astype(np.uint64), grads_for(63, call * n, n, D))
+    c.compare(f"short list before another {(D, k, opt, comb)}")
