@@ -155,14 +155,46 @@ ECRM_HD BucketPlan bucket_plan(uint32_t n)
 static_assert(kBucketMaxBatch <= 4u * kPartThreads * kMaxTiles, "the plan's largest tile covers the largest batch");
 
 // Batches of up to kDirectBatch updates take one launch, in which every workgroup reads all of the keys (direct.hip).  us a call
-// through the three launches of the buckets / so, D = 128, k = 4: 512 uniform updates 15.3 / 9.5, 2048 16.2 / 10.4, 3000
-// 18.1 / 12.8; Zipf, 2048 on 2^16 rows 22.9 / 17.2, on 1024 rows 28.6 / 15.6; 2048 on one row 40.4 / 31, on four 51.2 / 38.3, on 64
-// 20.5 / 14.2; 2048 half Zipf of 256 floats, k = 10, 28.3 / 21.5.  4096 would gain as well (20.6 / 16.2), but not 4096 on four rows
-// (51 / 145), and what the buckets hand on is tested with batches of 3800.  A stripe of kDirectLong updates or more is left to
-// the kDirectWorkers workgroups that take such stripes by their columns: with 128, and 64 workgroups, 2048 on 64 rows took 59 us; with
-// 256 2048 Zipf on 1024 rows 22.3.
+// through the three launches of the buckets / so, D = 128, k = 4: 512 uniform updates 15.3 / 9.5, 2048 16.2 / 10.4, 3072
+// 19.2 / 14.0; Zipf, 2048 on 2^16 rows 24.4 / 18.1, on 256 rows 27.7 / 17.7; on one row, on four, on 64: 2048 40.8 / 31.1, 51.4 / 40.1,
+// 21.9 / 16.0, 3072 52.9 / 42.6, 63.8 / 51.8, 25.4 / 21.6; D = 1024, 2048 44.2 / 33.4, 54.8 / 46.8, 81.5 / 73.2, 3072
+// 55.5 / 45.1, 66.9 / 58.7, 89.6 / 86.9; 650 batches of 1 to 3072 updates, rows of 4 to 1024 floats, k of 1 to 63 and all rules take
+// 0.70 times as long, the slowest one 0.99.  4096 would gain as well (20.6 / 16.2), but not 4096 on four rows (51 / 145).
 constexpr uint32_t kDirectBatch = 3072, kDirectLong = 192, kDirectWorkers = 128;
 ECRM_HD uint32_t direct_buckets(uint32_t n) { return n / 8u > 1u ? n / 8u : 1u; }
+ECRM_HD uint32_t direct_groups(uint32_t D) { return (D + 7u) / 8u; }
+ECRM_HD uint32_t direct_workers(uint32_t jobs, uint32_t empty) { return jobs <= kDirectWorkers ? kDirectWorkers : kDirectWorkers + empty; }
+// A bucket of kDirectLong updates or more may have a stripe that kDirectWorkers workgroups take instead of its own, eight columns each
+// (and those whose bucket is empty, if that makes more jobs than these take at once).  By columns a run of kDirectRun updates or more
+// is a trip to memory and an exchange, whatever its length, and the shorter runs go all at once; its own workgroup takes ~22 updates
+// per us, so that it is the better one for a few hundred updates of several entries alike.  Both in eighths of a us, fitted to
+// batches of 3000 updates on equally many stripes; D > 128 costs its own workgroup so much more.  How many other such stripes there
+// are no workgroup but those of the columns knows: in a table of few stripes as many as there is room for, otherwise as a power law has
+// them.  us a call through the buckets' launches / every long stripe by columns, 128 workgroups / so: 3000 on 56 rows, k = 4, D = 128
+// 25.9 / 44.0 / 22.6, D = 1024 97 / 343 / 92; on 100, k = 10, D = 256 48.6 / 143.5 / 45.1; on 882, k = 63, D = 256 48.6 / 98.1 / 42.3; on
+// ten, k = 1, D = 1024 61.8 / 123.0 / 42.7; but 2048 Zipf on 1020 rows, k = 10, 65.8 / 45.6 / 53.8: there it finds too few.
+constexpr uint32_t kDirectRun = 32;
+// a bucket's list: updates, entries, entries with kDirectRun updates or more, the other entries' updates; a run that is a third of it?
+struct DirectList { uint32_t updates, entries, longer, others; bool third; };
+ECRM_HD bool direct_by_columns(const DirectList &s, uint32_t n, uint32_t stripes, uint32_t D, bool combine)
+{
+    const uint32_t like = stripes < n / 128u ? n / s.updates : s.updates / kDirectLong;
+    const uint32_t jobs = like * direct_groups(D), workers = kDirectWorkers + direct_buckets(n), turns = (jobs + workers - 1u) / workers;
+    const uint32_t here = 16u + s.updates * 4u / 11u + 3u * s.entries + (s.third && s.entries > 1u ? 24u : 0u);
+    const uint32_t run = (jobs <= kDirectWorkers ? 29u : turns == 1u ? 40u : 52u) >> (combine ? 1 : 0);
+    const uint32_t rest = s.entries > s.longer ? 24u + 4u * s.others / (s.entries - s.longer) : 0u;
+    return 8u + turns * (8u + s.entries + run * s.longer + rest) <= (D > 170u ? here * 3u * D / 512u : here);
+}
+// updates from which on a list's stripes go by columns whatever its runs are, so that nobody has to count them (0.5 us)
+ECRM_HD uint32_t direct_sure(uint32_t n, uint32_t stripes, uint32_t k, uint32_t D, bool combine)
+{
+    uint32_t lo = kDirectLong - 1u, hi = n + 1u;
+    while (hi > lo + 1u) {
+        const uint32_t m = (lo + hi) / 2u, longer = k < m / kDirectRun ? k : m / kDirectRun;
+        if (direct_by_columns(DirectList{m, k, longer, m, false}, n, stripes, D, combine)) hi = m; else lo = m;
+    }
+    return hi;
+}
 
 // Bijective mix of a stripe number: its low bits split a bucket further, and number the slots of tables in LDS.
 ECRM_HD uint32_t scramble32(uint32_t g)

@@ -1,9 +1,9 @@
 // The smallest batches (up to kDirectBatch updates) in one launch.  What bounds them is the number of dependent steps and
 // nothing else: through the three launches of buckets.hip 2048 uniform updates, 9 MB, took 16.2 us, now 10.4.  Here every workgroup
-// reads all keys of the batch -- 16 KB that come out of the L2 --, picks its bucket's and goes on as bucket_apply does with a list
-// in LDS.  Since all workgroups see all keys, they agree on what is long without a word: a stripe of kDirectLong updates is left to
-// workgroups that look at the long buckets only, eight columns of such a stripe at a time.  One more workgroup does what concerns
-// the batch as a whole: the load counts and the header.  Nothing of the scratch buffer but the header is used.
+// reads all keys of the batch -- up to 24 KB that come out of the L2 --, picks its bucket's and goes on as bucket_apply does with a list
+// in LDS.  Since all workgroups see all keys, they agree on what is long without a word: a stripe of kDirectLong updates may be left
+// to workgroups that look at the long buckets only, eight columns of such a stripe at a time (direct_by_columns).  One more workgroup
+// does what concerns the batch as a whole: the load counts and the header.  Nothing of the scratch buffer but the header is used.
 #include "lists.h"
 
 namespace ecrm {
@@ -20,6 +20,7 @@ struct DirectArgs : RowArgs {
     u64 *load_data, *load_parity;
     uint32_t *rejected;
     uint32_t n, buckets, clear_sticky;
+    uint32_t stripes, sure;      // of the table; direct_sure
 };
 
 template <uint32_t K>
@@ -36,7 +37,7 @@ struct DirectShared {
     };
     uint32_t in_bucket[kItems / 8u];                              // items of each bucket
     uint32_t found[kLongs], longs[kLongs], n_found, count[K * kBucketWaves];
-    uint32_t n_long, n_long_items;
+    uint32_t n_long, n_long_items, n_empty;
 };
 
 // the thread's keys of the batch: positions threadIdx.x, + kBucketThreads, ...
@@ -95,12 +96,13 @@ __device__ __forceinline__ uint32_t collect(const DirectArgs &a, const Keys<K> &
     return m;
 }
 
-// Which buckets have `least` items or more (at least kDirectLong): their numbers, ascending, in sh.longs; returns how many.
+// The buckets of `least` items or more (at least kDirectLong), their numbers, ascending, in sh.longs; and those that have none.
+struct Buckets { uint32_t found, empty; };
 template <uint32_t K>
-__device__ __forceinline__ uint32_t find_long(const DirectArgs &a, const Keys<K> &k, DirectShared<K> &sh, uint32_t least)
+__device__ __forceinline__ Buckets find_long(const DirectArgs &a, const Keys<K> &k, DirectShared<K> &sh, uint32_t least)
 {
     for (uint32_t b = threadIdx.x; b < a.buckets; b += kBucketThreads) sh.in_bucket[b] = 0;
-    if (threadIdx.x == 0) sh.n_found = 0;
+    if (threadIdx.x == 0) sh.n_found = sh.n_empty = 0;
     __syncthreads();
 #pragma unroll
     for (uint32_t r = 0; r < K; ++r) {
@@ -108,8 +110,12 @@ __device__ __forceinline__ uint32_t find_long(const DirectArgs &a, const Keys<K>
         if (i < a.n) atomicAdd(&sh.in_bucket[bucket_of(a.geo.dk.div(k.row[r]), a.buckets)], 1u);
     }
     __syncthreads();
-    for (uint32_t b = threadIdx.x; b < a.buckets; b += kBucketThreads)
-        if (sh.in_bucket[b] >= least) sh.found[atomicAdd(&sh.n_found, 1u)] = b;
+    for (uint32_t b = threadIdx.x; b < a.buckets; b += kBucketThreads) {
+        const uint32_t m = sh.in_bucket[b];
+        const u64 none = __ballot(m == 0);
+        if (lane_id() == 0 && none) atomicAdd(&sh.n_empty, (uint32_t)__popcll(none));
+        if (m >= least) sh.found[atomicAdd(&sh.n_found, 1u)] = b;
+    }
     __syncthreads();
     const uint32_t nb = uniform(sh.n_found);
     if (threadIdx.x < nb) {
@@ -118,7 +124,18 @@ __device__ __forceinline__ uint32_t find_long(const DirectArgs &a, const Keys<K>
         sh.longs[rank] = sh.found[threadIdx.x];
     }
     __syncthreads();
-    return nb;
+    return Buckets{nb, uniform(sh.n_empty)};
+}
+
+// Whether the long stripes of a bucket, whose list of m items this is, are left to the workgroups that take them by columns: the
+// same for all that look at it.  By a whole workgroup.
+template <int MODE, uint32_t K>
+__device__ __forceinline__ bool by_columns(const DirectArgs &a, DirectShared<K> &sh, uint32_t m)
+{
+    if (m >= a.sure) return true;
+    const uint32_t x = item_row(sh.item[m / 2u]);                       // a row that has nearly all of them
+    if (x == item_row(sh.item[m / 8u]) || x == item_row(sh.item[m - 1u - m / 8u])) return true;
+    return direct_by_columns(count_runs(sh.item, m, sh.count), a.n, a.stripes, a.geo.D, Rule<MODE>::combine);
 }
 
 // What concerns the batch as a whole: one workgroup.
@@ -155,7 +172,7 @@ __device__ __forceinline__ void direct_batch(const DirectArgs &a, const Keys<K> 
     }
     if (a.n <= kLongRun) return;
     if (tid == 0) sh.n_long = sh.n_long_items = 0;                      // rows that ecrm_batch_stats reports
-    const uint32_t nb = find_long(a, k, sh, kLongRun + 1u);
+    const uint32_t nb = find_long(a, k, sh, kLongRun + 1u).found;
     for (uint32_t i = 0; i < nb; ++i) {
         const uint32_t m = collect(a, k, sh, uniform(sh.longs[i]));
         for (uint32_t p = tid; p + kLongRun < m; p += kBucketThreads) {
@@ -177,21 +194,32 @@ __device__ __forceinline__ void direct_batch(const DirectArgs &a, const Keys<K> 
     }
 }
 
-// The long stripes, 16 columns at a time.
+// The long stripes, eight columns at a time: a workgroup takes consecutive jobs -- a bucket, eight columns --, mostly of one
+// bucket, whose list it makes once.  own: of a workgroup whose bucket is empty the bucket, otherwise kNoKey.
 template <int MODE, bool PARITY, uint32_t K>
-__device__ __forceinline__ void direct_columns(const DirectArgs &a, const Keys<K> &k, DirectShared<K> &sh, uint32_t worker)
+__device__ __forceinline__ void direct_columns(const DirectArgs &a, const Keys<K> &k, DirectShared<K> &sh, uint32_t own)
 {
-    const uint32_t ncg = (a.geo.D + 2u * kDirectLanes - 1u) / (2u * kDirectLanes);
     const Divider dk = a.geo.dk;
-    const uint32_t nb = find_long(a, k, sh, kDirectLong);
+    const Buckets longs = find_long(a, k, sh, kDirectLong);
+    const uint32_t groups = direct_groups(a.geo.D), jobs = longs.found * groups, workers = direct_workers(jobs, longs.empty);
+    const uint32_t turns = (jobs + workers - 1u) / workers;
+    uint32_t worker = blockIdx.x - 1u;
+    if (own != kNoKey) {                                                // these come behind the others, in their order
+        worker = kDirectWorkers;
+        for (uint32_t b = lane_id(); b - lane_id() < own; b += kWave)
+            worker += (uint32_t)__popcll(__ballot(b < own && sh.in_bucket[b] == 0));
+    }
     uint32_t have = kNoKey, m = 0;
-    for (uint32_t job = worker; job < nb * ncg; job += kDirectWorkers) {
-        const uint32_t b = uniform(sh.longs[job / ncg]);
+    const uint32_t end_job = min((worker + 1u) * turns, jobs);
+    bool mine = false;
+    for (uint32_t job = worker * turns; job < end_job; ++job) {
+        const uint32_t b = uniform(sh.longs[job / groups]);
         if (b != have) {
             m = collect(a, k, sh, b);
             have = b;
+            mine = by_columns<MODE>(a, sh, m);
         }
-        for (uint32_t p = 0; p + kDirectLong <= m;) {
+        for (uint32_t p = 0; mine && p + kDirectLong <= m;) {
             const uint32_t g = dk.div(uniform(item_row(sh.item[p])));
             uint32_t end = p;
             for (;;) {
@@ -203,7 +231,7 @@ __device__ __forceinline__ void direct_columns(const DirectArgs &a, const Keys<K
                 }
                 end += kWave;
             }
-            if (end - p >= kDirectLong) stripe_columns<MODE, PARITY>(a, sh.item, p, end, job % ncg, sh.ex);
+            if (end - p >= kDirectLong) stripe_columns<MODE, PARITY>(a, sh.item, p, end, job % groups, sh.ex);
             p = end;
         }
     }
@@ -223,14 +251,23 @@ __global__ __launch_bounds__(kBucketThreads, 2) void direct_kernel(DirectArgs a)
         return;
     }
     if (bad) return;
-    if (blockIdx.x <= kDirectWorkers) {
-        direct_columns<MODE, PARITY>(a, k, sh, blockIdx.x - 1u);
-        return;
+    const uint32_t b = blockIdx.x > kDirectWorkers ? blockIdx.x - 1u - kDirectWorkers : kNoKey;
+    if (b != kNoKey) {
+        const uint32_t m = collect(a, k, sh, b);
+        if (m) {
+            if (Rule<MODE>::combine) count_list(a.geo, sh.item, m, sh.list.srv, a.load_data, a.load_parity);
+            uint32_t least = ~0u;
+            if (__builtin_expect(m >= kDirectLong, 0) && by_columns<MODE>(a, sh, m)) {
+                if (a.geo.dk.div(item_row(sh.item[0])) == a.geo.dk.div(item_row(sh.item[m - 1u]))) return;      // nothing else
+                least = kDirectLong;
+            }
+            apply_list<NC, MODE, PARITY, false>(a, sh.item, m, 0u, least, sh.list, (double *)sh.tmp);
+            return;
+        }
+        // an empty bucket's workgroup helps where there may be more jobs than the others take at once
+        if (min(a.n / kDirectLong, a.stripes) * direct_groups(a.geo.D) <= kDirectWorkers) return;
     }
-    const uint32_t m = collect(a, k, sh, blockIdx.x - 1u - kDirectWorkers);
-    if (m == 0) return;
-    if (Rule<MODE>::combine) count_list(a.geo, sh.item, m, sh.list.srv, a.load_data, a.load_parity);
-    apply_list<NC, MODE, PARITY, false>(a, sh.item, m, 0u, kDirectLong, sh.list, (double *)sh.tmp);
+    direct_columns<MODE, PARITY>(a, k, sh, b);
 }
 
 // ================================================================================================
@@ -258,6 +295,8 @@ void launch_direct(Header *hdr, const Geometry &g, float *E, float *A, float *PE
     a.E = E; a.A = A; a.PE = PE; a.PA = PA; a.grads = grads; a.geo = g;
     a.keys = keys; a.hdr = hdr; a.load_data = load_data; a.load_parity = load_parity; a.rejected = rejected;
     a.n = n; a.buckets = direct_buckets(n); a.clear_sticky = clear_sticky ? 1u : 0u;
+    a.stripes = g.dk.div(g.rows);
+    a.sure = direct_sure(n, a.stripes, g.k, g.D, (g.mode & 2u) != 0);
     ECRM_DISPATCH(direct_for, a, PE != nullptr, st);
 }
 

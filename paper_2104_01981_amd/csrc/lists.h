@@ -965,10 +965,41 @@ __device__ __forceinline__ void begin_batch(Header *h, uint32_t n, bool clear_st
     for (uint32_t c = 0; c < kMidClasses; ++c) h->n_mid[c] = 0;
 }
 
+// the runs of a sorted list, by the workgroup: every wave its part (s_sum: kBucketWaves * 4); ends with a barrier
+__device__ __forceinline__ DirectList count_runs(const u64 *items, uint32_t m, uint32_t *s_sum)
+{
+    const uint32_t w = uniform(threadIdx.x / kWave), third = m / 3u;
+    uint32_t sum[4] = {0, 0, 0, 0};
+    for (uint32_t q = w * kWave; q < m; q += kBucketThreads) {
+        const uint32_t p = min(q + lane_id(), m - 1u), x = item_row(items[p]);
+        const bool in = q + lane_id() < m, head = in && (p == 0 || item_row(items[p - 1u]) != x);
+        auto goes_on = [&](uint32_t updates) { return in && p + updates <= m && item_row(items[min(p + updates, m) - 1u]) == x; };
+        const u64 heads = __ballot(head), longer = __ballot(goes_on(kDirectRun));
+        sum[0] += (uint32_t)__popcll(heads);
+        sum[1] += (uint32_t)__popcll(heads & longer);
+        sum[2] += (uint32_t)__popcll(longer);
+        sum[3] |= __ballot(goes_on(third)) ? 1u : 0u;
+    }
+    if (lane_id() == 0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s_sum[w * 4 + i] = sum[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        sum[i] = 0;
+#pragma unroll
+        for (int v = 0; v < kBucketWaves; ++v) sum[i] += s_sum[v * 4 + i];
+        sum[i] = uniform(sum[i]);
+    }
+    __syncthreads();
+    // a run of r updates goes on for kDirectRun from r - kDirectRun + 1 of its positions
+    return DirectList{m, sum[0], sum[1], m - (sum[2] + sum[1] * (kDirectRun - 1u)), sum[3] != 0};
+}
+
 // 2 G columns of one stripe, [start, end) of a sorted list, by a workgroup: as in long_runs.h, with T updates to a group of G lanes:
 // 256 updates to a round with G = 8, 512 with G = 4.  A run of fewer than kGroupRun updates goes to one group, all of them at once
 // behind the long ones: each took a round by itself.  ex: both halves free; ends with a barrier.
-constexpr uint32_t kGroupRun = 32;
+constexpr uint32_t kGroupRun = kDirectRun;
 template <int MODE, bool PARITY, int G>
 __device__ __forceinline__ void stripe_columns(const RowArgs &a, const u64 *items, uint32_t start, uint32_t end, uint32_t cg,
                                                ExchangeOf<kBucketWaves, G> (&ex)[2])

@@ -19,6 +19,10 @@ uint32_t plan_buckets_beside(uint32_t buckets, uint32_t hot, uint32_t D) { retur
 uint32_t plan_heavy_run(uint32_t n) { return heavy_run(n); }
 uint32_t plan_direct_batch() { return kDirectBatch; }
 uint32_t plan_direct_long() { return kDirectLong; }
+uint32_t plan_direct_by_columns(uint32_t updates, uint32_t entries, uint32_t longer, uint32_t others, uint32_t third, uint32_t n, uint32_t stripes, uint32_t D)
+{
+    return direct_by_columns(DirectList{updates, entries, longer, others, third != 0}, n, stripes, D, false);
+}
 uint32_t plan_bucket_cap() { return kBucketCap; }
 uint32_t plan_heavy_stripe(uint32_t k) { return heavy_stripe(k); }
 uint32_t plan_split_stripe(uint32_t n, uint32_t D) { return split_stripe(n, D); }
@@ -81,6 +85,13 @@ def direct_batch():
 
 def direct_long():
     return int(lib().plan_direct_long())
+
+
+def direct_by_columns(runs, n, stripes, D):
+    """Whether the one-launch path has a stripe with these runs worked off by columns (Adagrad)."""
+    u, longer = C.c_uint32, [r for r in runs if r >= 32]
+    third = max(runs) >= sum(runs) // 3
+    return bool(lib().plan_direct_by_columns(u(sum(runs)), u(len(runs)), u(len(longer)), u(sum(runs) - sum(longer)), u(third), u(n), u(stripes), u(D)))
 
 
 def heavy_stripe(k):

@@ -1,7 +1,8 @@
 """Batches of up to 3072 updates, which take one launch, against the oracle: sizes around the two variants' 2048 and 3072 keys and
 around a workgroup's 256, stripes around the 192 updates from which on they are taken by columns, runs of it around the 32 up to
-which a group of lanes takes them, more such stripes than there are workgroups for, rows of more than 1024 updates, every rule; and a
-batch with a bad key, at each place a workgroup reads."""
+which a group of lanes takes them, more such stripes than there are workgroups for, rows of more than 1024 updates, every rule; batches of
+nothing but stripes of a few hundred updates, which stay in their buckets or make more jobs than the workgroups for them take at once; and
+a batch with a bad key, at each place a workgroup reads."""
 import numpy as np
 import pytest
 import torch
@@ -58,6 +59,19 @@ def test_nothing_but_long_stripes(R, k, n):
     D, S = 260, k + 1                                                         # 15 stripes of 33 groups of columns; one row of 3072 updates
     c = Case(R, D, k, S, max_batch=n, seed=73)
     _check(c, si.uniform_keys(73, 0, n, R), 73, f"direct few rows {(R, n)}")
+
+
+@pytest.mark.parametrize("opt,comb", RULES)
+@pytest.mark.parametrize("R,k,D,every", [(56, 4, 128, False), (100, 10, 260, False), (140, 10, 32, False), (10, 1, 260, True), (40, 4, 1024, True),
+                                         (882, 63, 132, True), (60, 10, 4, False), (12, 4, 1024, True)])
+def test_stripes_of_a_few_hundred_updates(R, k, D, every, opt, comb):
+    n, S = 3000, k + 1
+    keys = si.uniform_keys(75, 0, n, R)
+    runs = [np.unique(keys[keys // k == g], return_counts=True)[1].tolist() for g in range(R // k)]
+    columns = [bp.direct_by_columns(r, n, R // k, D) for r in runs if sum(r) >= bp.direct_long()]
+    assert all(columns) if every else not all(columns)
+    c = Case(R, D, k, S, max_batch=n, seed=75, optimizer=opt, momentum=0.9, combine=comb)
+    _check(c, keys, 75, f"direct, a few hundred {(R, k, D, opt, comb)}")
 
 
 @pytest.mark.parametrize("n,at", [(1, 0), (600, 599), (2048, 2047), (3072, 1300)])
