@@ -721,8 +721,9 @@ struct ListShared {
 
 // Cuts a list of m items, at most kSplitWords * 64, into a part for each wave, at entries, with equally many steps of up to U updates
 // of an entry to a part.  false: a part does not fit a window -- or, where a stripe may be too long for a window, has a run that the
-// workgroup had better share.  The same for every wave.
-constexpr uint32_t kSplitWords = 3, kSplitLeast = 16, kSplitStripes = 4 * kBucketWaves;
+// workgroup had better share, which is what limits such a list to a part of kTogether for each wave.  The same for every wave.
+constexpr uint32_t kSplitWords = 2, kSplitLeast = 16, kSplitStripes = 4 * kBucketWaves;
+static_assert(kSplitWords * kWave == kBucketWaves * kTogether, "longer lists are never cut");
 template <uint32_t U>
 __device__ __forceinline__ bool split_list(const u64 *items, uint32_t m, uint32_t (&bound)[kBucketWaves + 1])
 {

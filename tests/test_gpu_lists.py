@@ -1,7 +1,7 @@
 """A bucket's list in LDS around the lengths where its sorting changes: 64 items that a wave counts, 128 that the workgroup counts,
 512 that are looked up in one go, the lists of 512 that are merged, and the longest that LDS takes; and around the 64 rows up to
 which a list is sorted by counting.  Entries get several updates each, so that a place that is off by one shows in their arrival
-order.  And lists of few stripes, which are cut into a part for each wave at entries: around the 16 items from which on and the 192
+order.  And lists of few stripes, which are cut into a part for each wave at entries: around the 16 items from which on and the 128
 up to which they are, the 16 stripes from which on they are not, runs that fill a step, a part or a window, and stripes that go on
 over two to four parts."""
 import numpy as np
@@ -35,7 +35,7 @@ def _few_stripes(k):
     """Lists as runs of (stripe, entry): lengths."""
     rng = np.random.default_rng(k)
     lists = [[[m]] for m in (16, 17, 31, 33, 64)]                                       # one entry
-    lists += [[[m // k + (j < m % k) for j in range(k)]] for m in (16, 17, 40, 64, 65, 100, 128, 191, 192, 193)]      # one stripe
+    lists += [[[m // k + (j < m % k) for j in range(k)]] for m in (16, 17, 40, 64, 65, 100, 127, 128, 129, 191, 192, 193)]      # one stripe
     lists += [[[32] * min(k, 4), [1]], [[33] + [1] * (k - 1), [32], [31]], [[1], [62], [1]], [[4] * k] * 4, [[5] * k] * 3, [[1], [30], [30], [30]]]
     for stripes in (2, 3, 4, 5, 14, 15, 16, 17):
         for top in (2, 5, 9, 24):
