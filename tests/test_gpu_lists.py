@@ -2,8 +2,8 @@
 512 that are looked up in one go, the lists of 512 that are merged, and the longest that LDS takes; and around the 64 rows up to
 which a list is sorted by counting.  Entries get several updates each, so that a place that is off by one shows in their arrival
 order.  And lists of few stripes, which are cut into a part for each wave at entries: around the 16 items from which on and the 128
-up to which they are, the 16 stripes from which on they are not, runs that fill a step, a part or a window, and stripes that go on
-over two to four parts."""
+up to which they are, the 16 stripes from which on they are not, runs that fill a step, a part or a window, stripes that go on
+over two to four parts, and stripes longer than a window, of few entries, which are not cut, and of many."""
 import numpy as np
 import pytest
 
@@ -45,9 +45,9 @@ def _few_stripes(k):
 
 
 @pytest.mark.parametrize("opt,comb,prop", [(0, 0, 0), (1, 0, 0), (0, 1, 0), (1, 1, 0), (0, 0, 2)])
-@pytest.mark.parametrize("D,k", [(12, 4), (128, 5), (132, 4), (516, 3)])
+@pytest.mark.parametrize("D,k", [(12, 4), (128, 5), (132, 4), (516, 3), (36, 63)])
 def test_lists_of_few_stripes(D, k, opt, comb, prop):
-    n, S, stripes = 8000, 7, 1 << 16
+    n, S, stripes = 8000, max(7, k + 1), 1 << 15
     g = np.arange(stripes, dtype=np.uint32)
     bucket = bp.bucket_of(g, n)
     rng = np.random.default_rng(D)
