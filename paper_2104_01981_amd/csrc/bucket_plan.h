@@ -136,8 +136,14 @@ ECRM_HD uint32_t bucket_count(uint32_t n)
 // stripes' workgroups, which keep their places for 20 to 35 us.  The ones behind would begin when the first of the others end, and
 // the call would wait for them.  The rest of the plan's buckets stay empty, which costs nothing.  Of larger plans many begin
 // late anyway.  Not during a recovery, whose decoder takes places of its own (20 batches of 65 536 half Zipf 3383 us, with fewer
-// buckets 3407).  us a call, all buckets filled / so: 65 536 Zipf on 2^16 rows 79.2 / 72.1, half Zipf on 2^18 86.3 / 83.9, of 256
-// floats 129.8 / 126.4, of 64 floats 77.4 / 73.3; 12 000 Zipf on 2^14 43.3 / 40.9; 26 624 half Zipf on 2^20 50.6 / 49.1.
+// buckets 3407).  us a call, all buckets filled / so: 65 536 Zipf on 2^16 rows 81.7 / 77.7, half Zipf on 2^18 90.4 / 85.9, combined
+// 87.9 / 83.4; 12 000 Zipf on 2^14 44.5 / 42.3; 63 207 half Zipf, combined, on 27 920 rows of 64 floats 71.8 / 65.2; but 52 947 Zipf, momentum, k = 1,
+// on 25 934 rows of 64 floats 64.9 / 69.5, 26 624 half Zipf on 2^20 54.3 / 54.7: 92 batches with rows of up to 128 floats 0.989 times as long,
+// 25 with rows of up to 256 0.994, though fewer than 1024 of those are resident.  Where a batch's hot stripes are left to heavy_stripes all
+// the same, which only one workgroup finds out, it makes no difference (18 batches, 1.000).
+// Not with longer rows, nor where stripes have too many entries to be worked off beside the buckets: 29 batches with rows of more than
+// 256 floats took 1.011 times as long (33 549 half Zipf on 3432 rows of 512 floats 111, 120).
+ECRM_HD bool beside_pays(uint32_t k, uint32_t D) { return k <= kInPlaceEntries && D <= 256u; }
 constexpr uint32_t kResidentBuckets = 1024;
 ECRM_HD uint32_t buckets_beside(uint32_t buckets, uint32_t hot, uint32_t D)
 {

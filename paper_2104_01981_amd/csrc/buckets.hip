@@ -172,7 +172,8 @@ __global__ __launch_bounds__(kPartThreads) void bucket_partition_kernel(Partitio
     // a replay's buckets are those of what is waiting, not of the buffer that holds it: 4096 workgroups for 20 000 updates
     const uint32_t ordinary = a.packed ? bucket_count(n) : a.buckets;
     // ... and some of the plan's stay empty where hot stripes are worked off beside them
-    const uint32_t used = a.packed || a.rv.active ? ordinary : buckets_beside(ordinary, n_hot, a.D);
+    const bool beside = !a.packed && !a.rv.active && beside_pays(a.dk.d, a.D);
+    const uint32_t used = beside ? buckets_beside(ordinary, n_hot, a.D) : ordinary;
     const uint32_t B = ordinary + kHotBuckets;                            // buckets in the table; the last are the hot entries'
     for (uint32_t i = tid; i < B; i += kPartThreads) *(ulonglong2 *)s_cnt[i] = ulonglong2{0, 0};
     for (uint32_t i = tid; i < 2 * S; i += kPartThreads) s_srv[i] = 0;

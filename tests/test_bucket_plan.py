@@ -92,6 +92,15 @@ def test_buckets_beside_hot_stripes(n, D):
         assert bp.buckets_beside(n, hot, D) == (bp.buckets(n) if bp.buckets(n) > 1024 else min(bp.buckets(n), beside))
 
 
+def test_no_buckets_stay_empty_for_stripes_that_are_not_beside_them():
+    """No stripe of more than 16 entries is worked off beside the buckets, whatever the sample says; and long rows keep all buckets."""
+    pays = lambda k, D: bool(bp.lib().plan_beside_pays(bp.C.c_uint32(k), bp.C.c_uint32(D)))
+    for k in (1, 4, 16, 17, 63):
+        for D in (4, 128, 256, 260, 1024):
+            in_place = bool(bp.lib().plan_in_place_size(bp.C.c_uint32(1 << 16), bp.C.c_uint32(k), bp.C.c_uint32(D), bp.C.c_uint32(600)))
+            assert in_place == (k <= 16) and pays(k, D) == (in_place and D <= 256)
+
+
 @pytest.mark.parametrize("D", [32, 128, 256, 512, 1024])
 def test_long_stripes_of_a_batch_in_one_launch(D):
     """A stripe with one run goes by columns, and so does any of a thousand updates.  A few hundred updates of several entries alike
