@@ -160,6 +160,12 @@ ECRM_HD BucketPlan bucket_plan(uint32_t n)
 }
 static_assert(kBucketMaxBatch <= 4u * kPartThreads * kMaxTiles, "the plan's largest tile covers the largest batch");
 
+// A bucket's list of fewer than kSplitStripes stripes is cut at entries (apply_split in lists.h), by a kernel of its own where the table
+// has fewer stripes than that for each bucket.  On larger ones such a list is an exception, and what the kernel takes for it --
+// scalar registers, instructions -- costs all other lists: 81 batches on such tables 0.991 times as long without.
+constexpr uint32_t kSplitStripes = 16;
+ECRM_HD bool lists_are_cut(uint32_t stripes, uint32_t buckets) { return stripes < kSplitStripes * buckets; }
+
 // Batches of up to kDirectBatch updates take one launch, in which every workgroup reads all of the keys (direct.hip).  us a call
 // through the three launches of the buckets / so, D = 128, k = 4: 512 uniform updates 15.3 / 9.5, 2048 16.2 / 10.4, 3072
 // 19.2 / 14.0; Zipf, 2048 on 2^16 rows 24.4 / 18.1, on 256 rows 27.7 / 17.7; on one row, on four, on 64: 2048 40.8 / 31.1, 51.4 / 40.1,

@@ -829,7 +829,7 @@ __device__ __forceinline__ bool hot_block(const BucketArgs &a, BucketShared &sh,
 
 static_assert(sizeof(BucketShared::tmp) >= (kBucketWaves + 2) * 2 * 128 * sizeof(double), "walk_long_stripe's sums for NC = 2");
 
-template <int NC, int MODE, bool PARITY>
+template <int NC, int MODE, bool PARITY, bool CUT>
 __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_kernel(BucketArgs a)
 {
     __shared__ BucketShared sh;
@@ -930,7 +930,7 @@ __global__ __launch_bounds__(kBucketThreads, NC == 1 ? 4 : 3) void bucket_apply_
                 const BucketArgs b2 = args_again();
                 count_list(b2.geo, sh.item, list, sh.list.srv, b2.load_data, b2.load_parity);
             }
-            apply_list<NC, MODE, PARITY, true>(rows, sh.item, list, heavy_run, shared, sh.list, (double *)sh.tmp);
+            apply_list<NC, MODE, PARITY, true, CUT>(rows, sh.item, list, heavy_run, shared, sh.list, (double *)sh.tmp);
             const uint32_t nh = uniform(sh.list.n_heavy);
             if (nh) {
                 const BucketArgs b2 = args_again();
@@ -1292,20 +1292,27 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_stripes_kernel(BucketArgs
 // host side
 // ================================================================================================
 
-template <int NC, int MODE>
-static void bucket_apply_for(const BucketArgs &a, bool parity, bool heavy, int cus, hipStream_t st)
+template <int NC, int MODE, bool PARITY, bool CUT>
+static void bucket_apply_as(const BucketArgs &a, bool heavy, int cus, hipStream_t st)
 {
-    static_assert(std::is_same_v<decltype(&bucket_apply_kernel<NC, MODE, true>), void (*)(BucketArgs)> &&
-                  std::is_same_v<decltype(&bucket_apply_kernel<NC, MODE, false>), void (*)(BucketArgs)>, "args_again reads one argument");
+    static_assert(std::is_same_v<decltype(&bucket_apply_kernel<NC, MODE, PARITY, CUT>), void (*)(BucketArgs)>, "args_again reads one argument");
     const dim3 grid(a.buckets + kHotBuckets), block(kBucketThreads);
     const uint32_t most = a.n / kHeavyRunMin * ((a.geo.D + kHeavyCols - 1) / kHeavyCols);
     const dim3 hgrid(most < (uint32_t)cus ? most : (uint32_t)cus), hblock(kHeavyThreads);
+    hipLaunchKernelGGL((bucket_apply_kernel<NC, MODE, PARITY, CUT>), grid, block, 0, st, a);
+    if (heavy) hipLaunchKernelGGL((heavy_stripes_kernel<MODE, PARITY>), hgrid, hblock, 0, st, a);
+}
+
+template <int NC, int MODE>
+static void bucket_apply_for(const BucketArgs &a, bool parity, bool heavy, int cus, hipStream_t st)
+{
+    const bool cut = lists_are_cut(a.geo.dk.div(a.geo.rows), a.buckets);
     if (parity) {
-        hipLaunchKernelGGL((bucket_apply_kernel<NC, MODE, true>), grid, block, 0, st, a);
-        if (heavy) hipLaunchKernelGGL((heavy_stripes_kernel<MODE, true>), hgrid, hblock, 0, st, a);
+        if (cut) bucket_apply_as<NC, MODE, true, true>(a, heavy, cus, st);
+        else bucket_apply_as<NC, MODE, true, false>(a, heavy, cus, st);
     } else {
-        hipLaunchKernelGGL((bucket_apply_kernel<NC, MODE, false>), grid, block, 0, st, a);
-        if (heavy) hipLaunchKernelGGL((heavy_stripes_kernel<MODE, false>), hgrid, hblock, 0, st, a);
+        if (cut) bucket_apply_as<NC, MODE, false, true>(a, heavy, cus, st);
+        else bucket_apply_as<NC, MODE, false, false>(a, heavy, cus, st);
     }
 }
 

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(kBucketThreads, 2) void direct_kernel(DirectArgs a)
                 if (a.geo.dk.div(item_row(sh.item[0])) == a.geo.dk.div(item_row(sh.item[m - 1u]))) return;      // nothing else
                 least = kDirectLong;
             }
-            apply_list<NC, MODE, PARITY, false>(a, sh.item, m, 0u, least, sh.list, (double *)sh.tmp);
+            apply_list<NC, MODE, PARITY, false, false>(a, sh.item, m, 0u, least, sh.list, (double *)sh.tmp);
             return;
         }
         // an empty bucket's workgroup helps where there may be more jobs than the others take at once

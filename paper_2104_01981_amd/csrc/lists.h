@@ -722,7 +722,7 @@ struct ListShared {
 // Cuts a list of m items, at most kSplitWords * 64, into a part for each wave, at entries, with equally many steps of up to U updates
 // of an entry to a part.  false: a part does not fit a window -- or, where a stripe may be too long for a window, has a run that the
 // workgroup had better share, which is what limits such a list to a part of kTogether for each wave.  The same for every wave.
-constexpr uint32_t kSplitWords = 2, kSplitLeast = 16, kSplitStripes = 4 * kBucketWaves;
+constexpr uint32_t kSplitWords = 2, kSplitLeast = 16;
 static_assert(kSplitWords * kWave == kBucketWaves * kTogether, "longer lists are never cut");
 template <uint32_t U>
 __device__ __forceinline__ bool split_list(const u64 *items, uint32_t m, uint32_t (&bound)[kBucketWaves + 1])
@@ -846,13 +846,13 @@ __device__ __forceinline__ bool apply_split(const RowArgs &a, const u64 *items, 
 }
 
 // Applies every stripe of a sorted list of m items (m <= CAP).  A list of few stripes is cut at entries (apply_split;
-// RUNS).  Of others chunks of a few positions are handed to the waves as they come free; a wave owns the stripes that open in its
+// CUT).  Of others chunks of a few positions are handed to the waves as they come free; a wave owns the stripes that open in its
 // chunk.  A stripe that does not end inside the wave's 64-position window
 //   - is only listed in sh.heavy if it has a run of heavy_run updates and that makes up more than half of it, or it has
 //     shared_stripe updates (RUNS; otherwise: if it has shared_stripe updates);
 //   - is walked by the whole workgroup afterwards otherwise (s_part: room for walk_long_stripe).
 // A barrier has to lie between the last write of the list and this call; the call ends with one.
-template <int NC, int MODE, bool PARITY, bool RUNS, uint32_t CAP>
+template <int NC, int MODE, bool PARITY, bool RUNS, bool CUT, uint32_t CAP>
 __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, uint32_t m, uint32_t heavy_run,
                                            uint32_t shared_stripe, ListShared<CAP> &sh, double *s_part)
 {
@@ -864,7 +864,7 @@ __device__ __forceinline__ void apply_list(const RowArgs &a, const u64 *items, u
         sh.chunk = kBucketWaves;
     }
     __syncthreads();
-    if (RUNS && apply_split<NC, MODE, PARITY, kQ, kU>(a, items, m, sh.handed, s_part)) return;
+    if (CUT && apply_split<NC, MODE, PARITY, kQ, kU>(a, items, m, sh.handed, s_part)) return;
     // a chunk for each wave of a short list
     const uint32_t CH = min(kBucketChunk, max(1u, (m + kBucketWaves - 1u) / kBucketWaves));
     for (uint32_t c = uniform(threadIdx.x / kWave); c * CH < m;) {

@@ -16,6 +16,7 @@ using namespace ecrm;
 extern "C" {
 uint32_t plan_buckets(uint32_t n) { return bucket_plan(n).buckets; }
 uint32_t plan_buckets_beside(uint32_t buckets, uint32_t hot, uint32_t D) { return buckets_beside(buckets, hot, D); }
+uint32_t plan_lists_are_cut(uint32_t stripes, uint32_t n) { return lists_are_cut(stripes, bucket_plan(n).buckets); }
 uint32_t plan_beside_pays(uint32_t k, uint32_t D) { return beside_pays(k, D); }
 uint32_t plan_heavy_run(uint32_t n) { return heavy_run(n); }
 uint32_t plan_direct_batch() { return kDirectBatch; }
@@ -117,6 +118,10 @@ def scramble(stripes):
     g = np.ascontiguousarray(stripes, np.uint32).copy()
     lib().plan_scramble(g.ctypes.data_as(C.POINTER(C.c_uint32)), C.c_uint32(len(g)))
     return g
+
+
+def lists_are_cut(stripes, n):
+    return bool(lib().plan_lists_are_cut(C.c_uint32(stripes), C.c_uint32(n)))
 
 
 def oversized_parts(stripes, updates, k):

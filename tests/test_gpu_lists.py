@@ -3,7 +3,8 @@
 which a list is sorted by counting.  Entries get several updates each, so that a place that is off by one shows in their arrival
 order.  And lists of few stripes, which are cut into a part for each wave at entries: around the 16 items from which on and the 128
 up to which they are, the 16 stripes from which on they are not, runs that fill a step, a part or a window, stripes that go on
-over two to four parts, and stripes longer than a window, of few entries, which are not cut, and of many."""
+over two to four parts, and stripes longer than a window, of few entries, which are not cut, and of many; on tables of up
+to 16 stripes for a bucket, and on one of more, whose lists are not cut."""
 import numpy as np
 import pytest
 
@@ -45,19 +46,21 @@ def _few_stripes(k):
 
 
 @pytest.mark.parametrize("opt,comb,prop", [(0, 0, 0), (1, 0, 0), (0, 1, 0), (1, 1, 0), (0, 0, 2)])
-@pytest.mark.parametrize("D,k", [(12, 4), (128, 5), (132, 4), (516, 3), (36, 63)])
-def test_lists_of_few_stripes(D, k, opt, comb, prop):
-    n, S, stripes = 8000, max(7, k + 1), 1 << 15
+@pytest.mark.parametrize("D,k,stripes", [(12, 4, 15999), (12, 4, 16000), (128, 5, 15999), (132, 4, 15999), (516, 3, 15999), (36, 63, 15999)])
+def test_lists_of_few_stripes(D, k, stripes, opt, comb, prop):
+    n, S = 8000, max(7, k + 1)
+    assert bp.lists_are_cut(stripes, n) == (stripes < 16000)
     g = np.arange(stripes, dtype=np.uint32)
     bucket = bp.bucket_of(g, n)
     rng = np.random.default_rng(D)
     keys, lists = [], _few_stripes(k)
-    for i, runs in enumerate(lists):
-        for s, entries in zip(np.sort(rng.choice(g[bucket == 7 + i], len(runs), replace=False)), runs):
+    chosen = np.argsort(-np.bincount(bucket.astype(np.int64)), kind="stable")[:len(lists)]      # buckets of 17 stripes at least
+    for b, runs in zip(chosen, lists):
+        for s, entries in zip(np.sort(rng.choice(g[bucket == b], len(runs), replace=False)), runs):
             for j, m in zip(np.sort(rng.choice(k, len(entries), replace=False)), entries):
                 keys.append(np.full(m, s * k + j))
     keys = np.concatenate(keys)
-    others = g[(bucket < 7) | (bucket >= 7 + len(lists))]
+    others = g[~np.isin(bucket, chosen)]
     keys = np.concatenate([keys, rng.choice(others, n - len(keys)) * k + rng.integers(0, k, n - len(keys))])
     keys = next(p for p in (rng.permutation(keys).astype(np.uint64) for _ in range(99)) if not len(bp.hot_stripes(p, k)))
     c = Case(k * stripes, D, k, S, max_batch=n, seed=62, optimizer=opt, momentum=0.9, combine=comb, propagation=prop)
@@ -71,18 +74,21 @@ def test_lists_of_few_stripes(D, k, opt, comb, prop):
 def test_a_short_list_before_another_one_of_its_bucket(D, k, opt, comb):
     """Buckets of more items than LDS takes, which are worked off in parts: a list that is cut at entries comes first, and what it
     leaves in LDS has to be there until all waves are done with it, though the workgroup goes on to the next list."""
-    n, stripes, shape = 40000, 1 << 16, [15] * 4 + [200] * 8
+    n, stripes, shape = 40000, 16383, [15] * 4 + [200] * 8
+    assert bp.lists_are_cut(stripes, n)
     g = np.arange(stripes, dtype=np.uint32)
-    bucket, low = bp.bucket_of(g, n), bp.scramble(g) & 3
+    bucket, low = bp.bucket_of(g, n).astype(np.int64), bp.scramble(g) & 3
     rng = np.random.default_rng(D + k)
     keys = []
-    for b in range(7, 27):
+    buckets = np.nonzero(np.min([np.bincount(bucket[low == v], minlength=bp.buckets(n)) for v in (0, 1, 3)], axis=0) >= 4)[0][:20]
+    assert len(buckets) == 20
+    for b in buckets:
         mine = g[bucket == b]
-        chosen = np.concatenate([mine[low[bucket == b] == v][:m] for v, m in ((0, 4), (1, 4), (3, 4))])
+        chosen = np.concatenate([mine[low[bucket == b] == v][:4] for v in (0, 1, 3)])
         assert [len(l) for l in bp.oversized_parts(chosen, shape, k)] == [4, 4, 4]
         keys.append(np.repeat(chosen, shape) * k + rng.integers(0, k, sum(shape)))
     keys = np.concatenate(keys)
-    others = g[(bucket < 7) | (bucket >= 27)]
+    others = g[~np.isin(bucket, buckets)]
     at = rng.permutation(np.setdiff1d(np.arange(n), bp.sample_positions(n)))[:len(keys)]        # none of them is seen to be hot
     batch = rng.choice(others, n) * k + rng.integers(0, k, n)
     batch[at] = keys
