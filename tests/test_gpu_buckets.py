@@ -51,7 +51,7 @@ def test_runs_and_stripes_around_the_thresholds(D, k, S, opt, comb):
 
 @pytest.mark.parametrize("prop", [0, 2])
 @pytest.mark.parametrize("R,D,k,S,n", [
-    (4 * 5000, 128, 4, 5, 2049), (4 * 5000, 128, 4, 5, 32 * 512 + 1), (4 * 100000, 8, 4, 5, (1 << 17) + 1),
+    (4 * 5000, 128, 4, 5, 2049), (4 * 5000, 128, 4, 5, 7 * 512 + 1), (4 * 5000, 128, 4, 5, 32 * 512 + 1), (4 * 100000, 8, 4, 5, (1 << 17) + 1),
     (4 * 60000, 8, 4, 5, 1 << 18), (4 * 60000, 4, 4, 5, (1 << 18) + 1), (2 * 60000, 12, 2, 3, (1 << 19) - 1),
     (2 * 60000, 12, 2, 3, 1 << 19), (2 * 60000, 12, 2, 3, (1 << 19) + 1), (4 * 31, 12, 4, 5, 1 << 18), (4 * 31, 12, 4, 5, (1 << 18) + 1),
     (4 * 32, 12, 4, 5, (1 << 18) + 1),

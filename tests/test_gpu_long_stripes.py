@@ -8,6 +8,7 @@ import torch
 import bucket_plan as bp
 import synth_inputs as si
 from ecrm_case import Case, grads_for
+from test_gpu_hold_tiles import _both, _start
 
 pytestmark = pytest.mark.gpu
 
@@ -47,10 +48,29 @@ def test_smallest_buckets(n):
     c.compare("smallest buckets")
 
 
-def test_infinities_in_a_shared_run():
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 16, 17, 33, 65, 1023, 3072])
+def test_smallest_buckets_during_a_recovery(n):
+    """Without one so few updates take a single launch."""
+    R, D, k, S, server = 4 * 64, 64, 4, 5, 3
+    c, ses = _start(n, R, D, k, S, server, 6 * n)
+    for call in range(4):
+        if call % 2:
+            c.ctx.recovery_lock(); ses.lock()
+        assert _both(c, ses, si.uniform_keys(94, call * n, n, R), grads_for(94, call * n, n, D))
+        if call % 2:
+            c.ctx.recovery_decode(); ses.decode()
+            c.ctx.recovery_unlock(); ses.unlock()
+        assert c.ctx.recovery_state()["buffered"] == len(ses.buf_keys)
+    assert not c.ctx.recovery_state()["active"]
+    c.compare("smallest buckets during a recovery")
+
+
+@pytest.mark.parametrize("others", [0, 3400])               # in one launch, through the buckets
+def test_infinities_in_a_shared_run(others):
     """What an infinity or a NaN among the gradients of a long run makes of its column, and of no other."""
     R, D, k, S, n = 4 * 100, 36, 4, 5, 100
-    keys = np.concatenate([np.full(n, 41), np.full(60, 42)]).astype(np.uint64)
+    rest = np.random.default_rng(93).integers(4 * 20, R, others)
+    keys = np.concatenate([np.full(n, 41), np.full(60, 42), rest]).astype(np.uint64)
     for opt in (0, 1):
         c = Case(R, D, k, S, max_batch=len(keys), seed=93, optimizer=opt, momentum=0.9)
         g = grads_for(93, 0, len(keys), D)

@@ -1,17 +1,20 @@
 """Infinities, NaN and signed zeros in entries, state, parities and gradients: every path through the update has to give
 what the rule gives when it is applied update by update in 64 bits, with the differences added to the parities once per
-call.  Runs from one update to more than the 128 above which a workgroup walks a stripe.  Through the buckets and through
-the sort (the tuning knob sends a batch there)."""
+call.  Runs from one update to more than the 128 above which a workgroup walks a stripe.  In one launch, through the buckets -- without
+a sample for hot stripes, with some worked off beside the buckets, with a run that is cut into segments -- and through the sort (the
+tuning knob sends a batch there)."""
 import numpy as np
 import pytest
 import torch
 
+import bucket_plan as bp
 import synth_inputs as si
 from ecrm_case import RTOL, Case, grads_for
 
 pytestmark = pytest.mark.gpu
 
 LENS = [1, 2, 3, 4, 5, 7, 8, 9, 31, 63, 64, 65, 127, 128, 129, 300, 600]
+PATHS = {"direct": 0, "sort": 0, "buckets": 2000, "hot": 8000, "segments": 2500}       # path: updates on other rows
 RULES = [(0, 0, 0.0), (0, 1, 0.0), (1, 0, 0.9), (1, 1, 0.9), (1, 0, 0.001), (1, 0, 0.0)]
 
 
@@ -38,14 +41,21 @@ def reference(tables, keys, grads, k, lr, eps, opt, comb, mu):
     return E, A, PE, PA
 
 
-def run(D, opt, comb, mu, general, spoil):
+def run(D, opt, comb, mu, path, spoil):
     """One call on tables and gradients that spoil(tables, keys, grads) has put its values into; compares all tables."""
-    k, S, R = 4, 5, 4 * 64
+    k, S, R = 4, 5, 4 * 64 if PATHS[path] == 0 else 4 * 2000
     keys = np.concatenate([np.full(m, 4 * i + i % 4) for i, m in enumerate(LENS)] + [[4 * 40 + 1, 4 * 40 + 2, 4 * 40 + 2]])
-    keys = np.random.default_rng(13).permutation(keys).astype(np.uint64)
+    rng = np.random.default_rng(13)
+    keys = np.concatenate([keys, rng.integers(4 * 64, R, PATHS[path]) if PATHS[path] else [], np.full(8300 if path == "segments" else 0, 4 * 50)])
+    keys = rng.permutation(keys).astype(np.uint64)
     n = len(keys)
+    assert (n <= bp.direct_batch()) == (path in ("direct", "sort")) and (bp.buckets(n) * 16 > R // k) and (path != "buckets" or n < 4096)
+    if path == "hot":
+        assert bp.divide_hot(keys, k, D)[0]
+    if path == "segments":
+        assert np.bincount(keys.astype(np.int64) // k).max() >= bp.split_stripe(n, D)
     c = Case(R, D, k, S, max_batch=n, seed=83, optimizer=opt, momentum=mu, combine=comb)
-    if general:
+    if path == "sort":
         c.ctx.tune(1, 0xFFFFFFFF)                   # ECRM_TUNE_MID_MIN_ROWS: not through buckets
     tables = [t.cpu().numpy().copy() for t in (c.E, c.A, c.PE, c.PA)]
     grads = grads_for(83, 0, n, D).cpu().numpy().copy()
@@ -70,10 +80,10 @@ def middle(keys):
     return np.array([np.nonzero(keys == x)[0][(keys == x).sum() // 2] for x in np.unique(keys)])
 
 
-@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("path", PATHS)
 @pytest.mark.parametrize("D", [8, 260])
 @pytest.mark.parametrize("opt,comb,mu", RULES[:4])
-def test_infinities(opt, comb, mu, D, general):
+def test_infinities(opt, comb, mu, D, path):
     def spoil(tables, keys, grads):
         E, A, PE, PA = tables
         grads[middle(keys), 0] = np.inf
@@ -85,14 +95,14 @@ def test_infinities(opt, comb, mu, D, general):
         PA[:, 3] = np.inf
         if opt == 1:
             A[:, 5] = -np.inf                       # an Adagrad accumulator is a sum of squares: never infinite before NaN
-    for name, got, w in run(D, opt, comb, mu, general, spoil):
+    for name, got, w in run(D, opt, comb, mu, path, spoil):
         assert np.isinf(w).any()
 
 
-@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("path", PATHS)
 @pytest.mark.parametrize("D", [8, 260])
 @pytest.mark.parametrize("opt,comb,mu", RULES)
-def test_signed_zeros(opt, comb, mu, D, general):
+def test_signed_zeros(opt, comb, mu, D, path):
     def spoil(tables, keys, grads):
         E, A, PE, PA = tables
         E[:, :4] = -0.0
@@ -102,19 +112,20 @@ def test_signed_zeros(opt, comb, mu, D, general):
         grads[:, 1:3] = -0.0
         if opt == 1:
             A[:, :3] = -0.0
-    for name, got, w in run(D, opt, comb, mu, general, spoil):
+    for name, got, w in run(D, opt, comb, mu, path, spoil):
         zero = w == 0
         assert zero.any() or (name == "A" and opt == 0)       # Adagrad's accumulators start above zero
         np.testing.assert_array_equal(got[zero], 0.0, err_msg=name)
         np.testing.assert_array_equal(np.signbit(got[zero]), np.signbit(w[zero]), err_msg=name)
 
 
+@pytest.mark.parametrize("path", [p for p in PATHS if p != "sort"])
 @pytest.mark.parametrize("mu", [0.001, 1e-20, 0.0])
-def test_infinite_velocity_under_a_strong_decay(mu):
+def test_infinite_velocity_under_a_strong_decay(mu, path):
     """Heavy stripes: the decay over 128 updates underflows in 64 bits, but the rule keeps an infinite velocity infinite
     (with mu = 0 it makes NaN of it at the next update)."""
     def spoil(tables, keys, grads):
         tables[1][:, 0] = -np.inf
         grads[middle(keys), 1] = np.inf
-    for name, got, w in run(16, 1, 0, mu, False, spoil):
+    for name, got, w in run(16, 1, 0, mu, path, spoil):
         assert np.isinf(w).any() or mu == 0
