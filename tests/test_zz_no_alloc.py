@@ -1,7 +1,7 @@
 """ecrm_update_static (the entry point for callers that cannot allocate: its scratch buffer is a fixed
-array inside the library) against ecrm_update on the same inputs, through the C ABI: two calls in a row,
-the second with a smaller batch, so that what the first call left in the shared array is there when the
-second one runs."""
+array inside the library) against ecrm_update on the same inputs, through the C ABI: several calls in a row, through the
+buckets and in one launch by turns, so that what a call left in the shared array is there when the next one runs; through the sort
+(gradient propagation, more servers than the buckets count for); and inside a captured graph."""
 import numpy as np
 import pytest
 import torch
@@ -35,9 +35,10 @@ def _batches(R, D, seed, sizes):
 
 
 @pytest.mark.parametrize("R,D,k,S,opt,prop", [(4 * 4096, 128, 4, 5, 0, 0), (2 * 3000, 256, 2, 5, 1, 0),
-                                              (10 * 500, 36, 10, 11, 0, 0), (4 * 2048, 128, 4, 5, 0, 2)])
+                                              (10 * 500, 36, 10, 11, 0, 0), (4 * 2048, 128, 4, 5, 0, 2),
+                                              (4 * 2048, 36, 4, 5, 0, 1), (4 * 2048, 36, 4, 65, 0, 0)])
 def test_static_scratch_matches_bound_scratch(R, D, k, S, opt, prop):
-    seed, sizes = 41, [1 << 16, 20011]       # the largest batch the array serves, then a smaller one
+    seed, sizes = 41, [1 << 16, 20011, 3072, 3073, 1, 2048, 5000]      # the largest batch the array serves first
     ref = _tables(R, D, k, S, seed)
     got = _tables(R, D, k, S, seed)
     ctx = Ecrm(R, D, k, S, si.DEFAULT_LR, si.DEFAULT_EPS, max(sizes), optimizer=opt, momentum=0.9, propagation=prop)
@@ -49,6 +50,7 @@ def test_static_scratch_matches_bound_scratch(R, D, k, S, opt, prop):
     rejected = torch.full((1,), 7, dtype=torch.int32, device=DEV)
     for keys, g in _batches(R, D, seed, sizes):
         ctx.update(keys, g)
+        rejected.fill_(7)
         ctx.update_static(*got, keys, g, rejected=rejected)
         assert int(rejected.item()) == 0
         for name, a, b, atol in (("E", got[0], ref[0], ATOL_E), ("A", got[1], ref[1], ATOL_A),
@@ -58,17 +60,20 @@ def test_static_scratch_matches_bound_scratch(R, D, k, S, opt, prop):
             log(f"  n={keys.numel()} {name}: {int((a != b).sum())} of {a.numel()} elements differ")
         assert torch.equal(got[4], ref[4]) and torch.equal(got[5], ref[5])
     assert ctx.status() == 0
-    # a bad key: nothing applied, reported through `rejected`, and the next call starts clean
-    keys, g = _batches(R, D, seed, [4096])[0]
-    before = [t.clone() for t in got]
-    bad = keys.clone()
-    bad[100] = R
-    ctx.update_static(*got, bad, g, rejected=rejected)
-    assert int(rejected.item()) == 1
-    for t, b in zip(got, before):
-        assert torch.equal(t, b)
-    ctx.update_static(*got, keys, g, rejected=rejected)
-    assert int(rejected.item()) == 0 and not torch.equal(got[0], before[0])
+    # a bad key: nothing applied, reported through `rejected`, and the next call starts clean, whichever way it goes
+    batches = _batches(R, D, seed, [4096, 600])
+    for (keys, g), (others, og) in zip(batches, batches[::-1]):
+        before = [t.clone() for t in got]
+        bad = keys.clone()
+        bad[100] = R
+        rejected.fill_(7)
+        ctx.update_static(*got, bad, g, rejected=rejected)
+        assert int(rejected.item()) == 1
+        for t, b in zip(got, before):
+            assert torch.equal(t, b)
+        rejected.fill_(7)
+        ctx.update_static(*got, others, og, rejected=rejected)
+        assert int(rejected.item()) == 0 and not torch.equal(got[0], before[0])
     # limits
     big = torch.zeros((1 << 16) + 1, dtype=torch.int64, device=DEV)
     assert ctx.update_static(*got, big, g, check=False) == -4            # more than the array serves
@@ -82,4 +87,30 @@ def test_static_scratch_refuses_what_does_not_fit():
     keys = torch.zeros(16, dtype=torch.int64, device=DEV)
     g = torch.zeros(16, D, device=DEV)
     assert ctx.update_static(*t, keys, g, check=False) == -3
+    ctx.destroy()
+
+
+def test_static_call_in_one_launch_inside_a_graph():
+    """Replays of a captured call against eager ones on a twin, with larger eager calls on the same array in between."""
+    R, D, k, S, n = 4 * 1000, 36, 4, 5, 2048
+    ctx = Ecrm(R, D, k, S, si.DEFAULT_LR, si.DEFAULT_EPS, 1 << 14)
+    a, b = _tables(R, D, k, S, 43), _tables(R, D, k, S, 43)
+    (keys, g), (more, mg) = _batches(R, D, 43, [n, 1 << 14])
+    rejected = torch.full((1,), 7, dtype=torch.int32, device=DEV)
+    ctx.update_static(*a, keys, g, rejected=rejected)
+    ctx.update_static(*b, keys, g)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        ctx.update_static(*a, keys, g, rejected=rejected, stream=side)
+    for rep in range(4):
+        rejected.fill_(7)
+        graph.replay()
+        ctx.update_static(*b, keys, g)
+        ctx.update_static(*a, more, mg)
+        ctx.update_static(*b, more, mg)
+        torch.cuda.synchronize()
+        assert int(rejected.item()) == 0
+        for x, y in zip(a, b):
+            assert torch.equal(x, y), f"replay {rep}"
     ctx.destroy()
