@@ -495,7 +495,11 @@ __device__ __forceinline__ void walk_long_stripe(const RowArgs &a, const u64 *it
 // their order, and the items, which come in arrival order (`ordered`), go to the places behind those of smaller rows and of
 // earlier updates of their own.  false: there are more rows, and nothing has moved.  By pieces and merging 2048 items of four
 // rows take 25 us, so 5; 300 007 Zipf updates, combined, 184 -> 171 us a call.
-constexpr uint32_t kFewLimit = 64, kFewSlots = 256;
+// Lists of more than kFewLeast items: shorter ones mostly have more rows and were numbered in vain.  us a call, tried from 129 items
+// on / from 193 / from 257 / from 513: 26 624 half Zipf on 2^20 rows 51.4, 51.0, 50.7, 51.0; 2^19 uniform on 2^22 rows of 16
+// floats 310.2, 303.5, 303.0, 304.3; 8192 half Zipf 34.75, 34.4, 34.15, 34.45; 2^18 on 4096 rows 82.7, -, 82.2, 84.3; but 300 007 Zipf,
+// combined, 174.7, 175.5, 175.4, 176.8, and 2^14 on 2520 rows, k = 63, 69.8, -, 73.0, 75.0.
+constexpr uint32_t kFewLimit = 64, kFewSlots = 256, kFewLeast = 256;
 struct FewRows {
     uint32_t slot[kFewSlots], number[kFewSlots];             // open addressing: row, its number
     uint32_t row[kFewLimit], at[kFewLimit], count[kBucketWaves][kFewLimit], rows;
@@ -636,7 +640,7 @@ __device__ __forceinline__ void sort_items(u64 *s_item, u64 *s_tmp, uint32_t m, 
         __syncthreads();
         return;
     }
-    if (ordered && sort_few(s_item, s_tmp, m, few)) return;
+    if (__builtin_expect(ordered && m > kFewLeast, 0) && sort_few(s_item, s_tmp, m, few)) return;
     if (tid < pieces * kWave - m) s_item[m + tid] = ~0ull;       // fewer than 64: what is read behind the list counts as larger
     __syncthreads();
     for (uint32_t i = tid; i - lane < m; i += kBucketThreads) {

@@ -1,6 +1,6 @@
 """A bucket's list in LDS around the lengths where its sorting changes: 64 items that a wave counts, 128 that the workgroup counts,
 512 that are looked up in one go, the lists of 512 that are merged, and the longest that LDS takes; and around the 64 rows up to
-which a list is sorted by counting.  Entries get several updates each, so that a place that is off by one shows in their arrival
+which a list of more than 256 items is sorted by counting.  Entries get several updates each, so that a place that is off by one shows in their arrival
 order.  And lists of few stripes, which are cut into a part for each wave at entries: around the 16 items from which on and the 128
 up to which they are, the 16 stripes from which on they are not, runs that fill a step, a part or a window, stripes that go on
 over two to four parts, and stripes longer than a window, of few entries, which are not cut, and of many; on tables of up
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("m,n_rows", [(m, max(m // 3, 1)) for m in (1, 2, 63, 64, 65, 127, 128, 129, 192, 511, 512, 513, 576, 1024, 1025,
                                                                    1087, 1535, bp.bucket_cap())] +
-                         [(129, 1), (150, 2), (150, 63), (500, 64), (501, 65), (bp.bucket_cap(), 64), (bp.bucket_cap(), 65)])
+                         [(129, 1), (150, 2), (150, 63), (256, 1), (256, 64), (257, 1), (257, 64), (257, 65), (500, 64), (501, 65), (bp.bucket_cap(), 64), (bp.bucket_cap(), 65)])
 def test_list_lengths(m, n_rows):
     n, k, S, D, stripes = 6000, 4, 5, 12, 1 << 18
     g = np.arange(stripes, dtype=np.uint32)
