@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("m,n_rows", [(m, max(m // 3, 1)) for m in (1, 2, 63, 64, 65, 127, 128, 129, 192, 511, 512, 513, 576, 1024, 1025,
                                                                    1087, 1535, bp.bucket_cap())] +
-                         [(129, 1), (150, 2), (150, 63), (256, 1), (256, 64), (257, 1), (257, 64), (257, 65), (500, 64), (501, 65), (bp.bucket_cap(), 64), (bp.bucket_cap(), 65)])
+                         [(129, 1), (150, 2), (150, 63), (256, 12), (256, 64), (257, 12), (257, 64), (257, 65), (500, 64), (501, 65), (bp.bucket_cap(), 64), (bp.bucket_cap(), 65)])
 def test_list_lengths(m, n_rows):
     n, k, S, D, stripes = 6000, 4, 5, 12, 1 << 18
     g = np.arange(stripes, dtype=np.uint32)
