@@ -163,8 +163,12 @@ static_assert(kBucketMaxBatch <= 4u * kPartThreads * kMaxTiles, "the plan's larg
 // A bucket's list of fewer than kSplitStripes stripes is cut at entries (apply_split in lists.h), by a kernel of its own where the table
 // has fewer stripes than that for each bucket.  On larger ones such a list is an exception, and what the kernel takes for it --
 // scalar registers, instructions -- costs all other lists: 81 batches on such tables 0.991 times as long without.
-constexpr uint32_t kSplitStripes = 16;
-ECRM_HD bool lists_are_cut(uint32_t stripes, uint32_t buckets) { return stripes < kSplitStripes * buckets; }
+// Nor where the batch has kSplitUpdates updates for each stripe of the table: then few lists are short enough.  us a call, cut / not: 2^19
+// uniform updates on 16 384 rows (128 to a stripe) 126.4 / 124.1, on 22 000 (95) 135.4 / 132.8, 2^18 on 11 200 (94) 86.0 / 84.1, 2^17 on
+// 14 000, k = 10 (94) 62.9 / 61.7; but 8192 on 1000, k = 10 (82) 26.1 / 27.0, 466 158 on 407 862, k = 63, combined (72) 288 / 298, 2^17 on
+// 20 000, k = 10 (66) 68.0 / 69.4, 2^18 on 16 384 (64) 101.1 / 104.0.
+constexpr uint32_t kSplitStripes = 16, kSplitUpdates = 88;
+ECRM_HD bool lists_are_cut(uint32_t stripes, uint32_t buckets, uint32_t n) { return stripes < kSplitStripes * buckets && n / kSplitUpdates < stripes; }
 
 // Batches of up to kDirectBatch updates take one launch, in which every workgroup reads all of the keys (direct.hip).  us a call
 // through the three launches of the buckets / so, D = 128, k = 4: 512 uniform updates 15.3 / 9.5, 2048 16.2 / 10.4, 3072

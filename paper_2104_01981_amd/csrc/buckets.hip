@@ -1306,7 +1306,7 @@ static void bucket_apply_as(const BucketArgs &a, bool heavy, int cus, hipStream_
 template <int NC, int MODE>
 static void bucket_apply_for(const BucketArgs &a, bool parity, bool heavy, int cus, hipStream_t st)
 {
-    const bool cut = lists_are_cut(a.geo.dk.div(a.geo.rows), a.buckets);
+    const bool cut = lists_are_cut(a.geo.dk.div(a.geo.rows), a.buckets, a.n);
     if (parity) {
         if (cut) bucket_apply_as<NC, MODE, true, true>(a, heavy, cus, st);
         else bucket_apply_as<NC, MODE, true, false>(a, heavy, cus, st);

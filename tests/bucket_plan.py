@@ -16,7 +16,7 @@ using namespace ecrm;
 extern "C" {
 uint32_t plan_buckets(uint32_t n) { return bucket_plan(n).buckets; }
 uint32_t plan_buckets_beside(uint32_t buckets, uint32_t hot, uint32_t D) { return buckets_beside(buckets, hot, D); }
-uint32_t plan_lists_are_cut(uint32_t stripes, uint32_t n) { return lists_are_cut(stripes, bucket_plan(n).buckets); }
+uint32_t plan_lists_are_cut(uint32_t stripes, uint32_t n) { return lists_are_cut(stripes, bucket_plan(n).buckets, n); }
 uint32_t plan_beside_pays(uint32_t k, uint32_t D) { return beside_pays(k, D); }
 uint32_t plan_heavy_run(uint32_t n) { return heavy_run(n); }
 uint32_t plan_direct_batch() { return kDirectBatch; }

@@ -110,3 +110,11 @@ def test_long_stripes_of_a_batch_in_one_launch(D):
     assert by([214], n, 14, D) and by([300], n, 10, D) and by([200, 3, 2, 1], n, 1 << 14, D)
     assert by([750] * 4, n, 1, D) and by([250] * 4, n, 3, D) and by([100] * 10, n, 3, D) and by([16] * 63, n, 3, D)
     assert not by([54, 53, 53, 54], n, 14, D) and not by([30] * 6 + [35] * 4, n, 10, D)
+
+
+@pytest.mark.parametrize("n", [3073, 8192, 65536, 300007, 1 << 19])
+def test_lists_are_cut_on_tables_of_some_stripes(n):
+    """Neither where most lists have many stripes, nor where the stripes are too long for a list that can be cut."""
+    most, least = 16 * bp.buckets(n), n // 88
+    assert bp.lists_are_cut(most - 1, n) and not bp.lists_are_cut(most, n)
+    assert bp.lists_are_cut(least + 1, n) and not bp.lists_are_cut(least, n) and not bp.lists_are_cut(1, n)
