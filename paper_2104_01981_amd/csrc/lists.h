@@ -618,7 +618,7 @@ __device__ __forceinline__ bool sort_few(u64 *s_item, u64 *s_tmp, uint32_t m, Fe
 // in all other pieces, and only 64 were counted by one wave / so: 2048 uniform updates 16.9 / 16.2, 26 624 half Zipf 48.2 / 47.6,
 // 300 007 Zipf, combined, where 1250 items took 30 us, 187.5 / 184.8; merged from 64 on, 65 536 half Zipf 84.9, so 82.9.  Short
 // loops: code that only a few long lists run through costs more in instruction fetches than it saves.
-__device__ __forceinline__ void sort_items(u64 *s_item, u64 *s_tmp, uint32_t m, bool ordered, FewRows &few)
+__device__ __forceinline__ void sort_items(u64 *s_item, u64 *s_tmp, uint32_t m, bool ordered, FewRows &few, uint32_t few_least = kFewLeast)
 {
     const uint32_t tid = threadIdx.x, lane = lane_id(), w = uniform(tid / kWave);
     const uint32_t pieces = (m + kWave - 1) / kWave;
@@ -640,7 +640,7 @@ __device__ __forceinline__ void sort_items(u64 *s_item, u64 *s_tmp, uint32_t m, 
         __syncthreads();
         return;
     }
-    if (__builtin_expect(ordered && m > kFewLeast, 0) && sort_few(s_item, s_tmp, m, few)) return;
+    if (__builtin_expect(ordered && m > few_least, 0) && sort_few(s_item, s_tmp, m, few)) return;
     if (tid < pieces * kWave - m) s_item[m + tid] = ~0ull;       // fewer than 64: what is read behind the list counts as larger
     __syncthreads();
     for (uint32_t i = tid; i - lane < m; i += kBucketThreads) {
