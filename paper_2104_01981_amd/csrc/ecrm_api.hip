@@ -334,8 +334,8 @@ __global__ void publish_rejected_kernel(const Header *h, uint32_t *rejected)
     if (threadIdx.x == 0) *rejected = h ? h->batch_bad : 0u;
 }
 
-// Which way a batch goes.  Up to kBucketMaxBatch updates the buckets' three launches beat the sort's and the chains'
-// thirteen to twenty, but for large batches on a handful of rows (bucket_plan.h); gradient propagation groups the batch
+// Which way a batch goes.  Up to kBucketMaxBatch updates the buckets' three launches, or one (kDirectBatch), beat the sort's and the
+// chains' thirteen to twenty, but for large batches on a handful of rows (bucket_plan.h); gradient propagation groups the batch
 // twice, and a caller that has set the chain tiers' knob wants those tiers: both take the general path, as do more servers
 // than the per-tile counts are kept for.
 static bool takes_buckets(const ecrm_ctx *c, uint32_t n)
@@ -497,8 +497,8 @@ int ecrm_update_static(ecrm_ctx *c, float *E, float *A, float *PE, float *PA, ui
     RecoveryView none;
     memset(&none, 0, sizeof(none));
     // The array keeps the last call's contents.  A batch through buckets has the status word (clear_sticky) and the fields of
-    // the header that its kernels and ecrm_batch_stats read set by the partition, and reads none of the others; a batch
-    // through the sort has all of the header and the per-server counts cleared by the reset kernel.  Everything else is
+    // the header that its kernels and ecrm_batch_stats read set by the partition, or by the one launch of a small batch, and reads
+    // none of the others; a batch through the sort has all of the header and the per-server counts cleared by the reset kernel.  Everything else is
     // written before it is read.
     return run_update(c, t, s, c->slay, none, true, kCallerBatch, keys, grads, (uint32_t)n, rejected, st);
 }
